@@ -7,16 +7,12 @@
 //                                     LDS (swizzled, see gram_swizzle) so that both operands of
 //                                     v_mfma_f32_16x16x32_bf16 (eight consecutive rows of one
 //                                     column per lane) are one 16-byte LDS read; bf16 keys are exact, fp32 keys enter as two bf16 terms
-//   cov_reduce_kernel  (head)         chunk partials added in a fixed order in fp64; sample
+//   cov_reduce_kernel  (tiles, head)  chunk partials added in a fixed order in fp64; sample
 //                                     covariance C = (G - s s^T / N) / (N - 1)
-//   jacobi_sweep_kernel, jacobi_apply_kernel, jacobi_finish_kernel
-//                                     cyclic Jacobi eigensolver in fp64 (see there): C resident in
-//                                     LDS (129 KiB), 64 disjoint rotations per round in a
-//                                     round-robin order, the eigenvector accumulation spread over
-//                                     8 blocks per head; eigenpairs sorted by decreasing
-//                                     eigenvalue, every component's largest entry made positive
+//   eigensolver.hip                   eigenpairs of C, sorted by decreasing eigenvalue, every
+//                                     component's largest entry made positive
 //   rank_at_kernel, layer_width_kernel, jaccard_kernel    small reductions
-#include "common.h"
+#include "eigensolver.h"
 
 namespace loki {
 
@@ -151,216 +147,47 @@ __global__ __launch_bounds__(kGramThreads) void gram_kernel(const void* __restri
   }
 }
 
-// C = (G - s s^T / N) / (N - 1), chunk partials added in order in fp64.
-__global__ __launch_bounds__(1024) void cov_reduce_kernel(const float* __restrict__ gram_part,
-                                                          const float* __restrict__ sum_part,
-                                                          double* __restrict__ cov, long long N,
-                                                          int nchunks) {
-  const int head = blockIdx.x, e = blockIdx.y * 1024 + threadIdx.x;  // entry (row, col)
-  const int row = e / kD, col = e % kD;
+// C = (G - s s^T / N) / (N - 1), chunk partials added in order in fp64, and exactly symmetric: G's two
+// halves are averaged (with fp32 keys they differ in the last place, value x remainder and
+// remainder x value being added in the opposite order; a skew part, however small, never leaves a
+// Jacobi iteration, which then took all of its 30 sweeps: 9.9 ms for 4 heads).  Block (tile pair,
+// head): a 32 x 32 tile on or above the diagonal and its mirror image, exchanged through LDS.
+constexpr int kCovTile = 32;
+constexpr int kCovTiles = kD / kCovTile;
+constexpr int kCovPairs = kCovTiles * (kCovTiles + 1) / 2;
+__global__ __launch_bounds__(kCovTile * kCovTile) void cov_reduce_kernel(const float* __restrict__ gram_part,
+                                                                         const float* __restrict__ sum_part,
+                                                                         double* __restrict__ cov, long long N,
+                                                                         int nchunks) {
+  __shared__ double s_mirror[kCovTile][kCovTile + 1];
+  const int head = blockIdx.y;
+  int ti = 0, tj = blockIdx.x;
+  while (tj >= kCovTiles - ti) {
+    tj -= kCovTiles - ti;
+    ++ti;
+  }
+  tj += ti;
+  const int r = threadIdx.x / kCovTile, c = threadIdx.x % kCovTile;
+  const int row = ti * kCovTile + r, col = tj * kCovTile + c;            // this thread's entry of the tile
+  const int mrow = tj * kCovTile + r, mcol = ti * kCovTile + c;          // and of its mirror image
   const float* gp = gram_part + (size_t)head * nchunks * kD * kD;
   const float* sp = sum_part + (size_t)head * nchunks * kD;
-  double g = 0.0, sr = 0.0, sc = 0.0;
+  double g = 0.0, gm = 0.0, sr = 0.0, sc = 0.0;
   for (int cc = 0; cc < nchunks; ++cc) {
-    g += (double)gp[(size_t)cc * kD * kD + e];
+    g += (double)gp[(size_t)cc * kD * kD + (size_t)row * kD + col];
+    gm += (double)gp[(size_t)cc * kD * kD + (size_t)mrow * kD + mcol];
     sr += (double)sp[cc * kD + row];
     sc += (double)sp[cc * kD + col];
   }
+  s_mirror[r][c] = gm;
+  __syncthreads();
   const double n = (double)N;
-  cov[(size_t)head * kD * kD + e] = (g - sr * sc / n) / (n > 1.0 ? n - 1.0 : 1.0);
-}
-
-// ---- eigensolver ------------------------------------------------------------------------------
-// Cyclic Jacobi in fp64, one sweep (127 rounds of 64 disjoint rotations, round-robin pairing)
-// per launch pair:
-//   jacobi_sweep_kernel (head)            C resident in LDS (129 KiB); checks convergence, then
-//                                         rotates C round by round and logs every rotation's
-//                                         (cos, sin); C goes back to global memory for the next sweep
-//   jacobi_apply_kernel (column slice, head)  the eigenvector accumulator Vt is only ever rotated,
-//                                         row pair by row pair, and columns do not mix: each block
-//                                         keeps 16 columns of Vt in LDS and replays the sweep's log
-// so that the accumulation, which used to cost the solver block 256 KiB of L2 traffic per round,
-// is spread over 8 blocks per head.  The host enqueues kJacMaxSweeps pairs; a converged head's
-// blocks leave at once.  jacobi_finish_kernel sorts the eigenpairs and writes P.
-constexpr int kJacThreads = 1024;
-constexpr int kJacPitch = kD + 1;  // doubles per row of the LDS-resident matrix
-constexpr int kJacMaxSweeps = 30;
-constexpr int kJacRounds = kD - 1;
-constexpr int kJacSliceCols = 16;                  // columns of Vt one apply block owns
-constexpr int kJacSlices = kD / kJacSliceCols;
-constexpr int kJacApplyThreads = 256;
-
-// round-robin pairing of 128 indices: slot 0 pairs (round, 127), slot t pairs
-// ((round + t) % 127, (round - t) % 127); returned with p < q
-__device__ __forceinline__ void jacobi_pair(int round, int slot, int& p, int& q) {
-  if (slot == 0) {
-    p = round;
-    q = kD - 1;
-  } else {
-    p = (round + slot) % (kD - 1);
-    q = (round - slot + (kD - 1)) % (kD - 1);
-  }
-  if (p > q) {
-    const int t = p;
-    p = q;
-    q = t;
-  }
-}
-
-// state[head]: 0 while the head still rotates, 1 once it has converged (set here, read by later
-// launches); log[head][round][slot] = (cos, sin) of this sweep; n_logged[head] = rounds logged
-// by this launch (0 or kJacRounds).
-__global__ __launch_bounds__(kJacThreads) void jacobi_sweep_kernel(double* __restrict__ a_all,
-                                                                   double2* __restrict__ log_all,
-                                                                   int* __restrict__ state,
-                                                                   int* __restrict__ n_logged, int sweep) {
-  extern __shared__ __align__(16) unsigned char jac_smem[];
-  double* A = reinterpret_cast<double*>(jac_smem);  // [128][kJacPitch]
-  __shared__ double s_c[kD / 2], s_s[kD / 2];
-  __shared__ int s_p[kD / 2], s_q[kD / 2];
-  __shared__ double s_red[kJacThreads / 64];
-
-  const int tid = threadIdx.x, head = blockIdx.x;
-  if (sweep == 0 && tid == 0) state[head] = 0;
-  if (sweep > 0 && state[head] != 0) {  // (uniform; written by an earlier launch)
-    if (tid == 0) n_logged[head] = 0;
-    return;
-  }
-  double* Ag = a_all + (size_t)head * kD * kD;
-  double2* log = log_all + (size_t)head * kJacRounds * (kD / 2);
-  for (int e = tid; e < kD * kD; e += kJacThreads) A[(e / kD) * kJacPitch + e % kD] = Ag[e];
+  const double x = (0.5 * (g + s_mirror[c][r]) - sr * sc / n) / (n > 1.0 ? n - 1.0 : 1.0);
+  cov[(size_t)head * kD * kD + (size_t)row * kD + col] = x;
   __syncthreads();
-
-  auto block_sum = [&](double x) -> double {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off);
-    __syncthreads();
-    if ((tid & 63) == 0) s_red[tid >> 6] = x;
-    __syncthreads();
-    double t = 0.0;
-#pragma unroll
-    for (int w = 0; w < kJacThreads / 64; ++w) t += s_red[w];
-    return t;
-  };
-
-  // converged when the off-diagonal mass is at rounding level of the diagonal's
-  double off = 0.0, dg = 0.0;
-  for (int e = tid; e < kD * kD; e += kJacThreads) {
-    const double x = A[(e / kD) * kJacPitch + e % kD];
-    if (e / kD == e % kD) dg += x * x; else off += x * x;
-  }
-  off = block_sum(off);
-  dg = block_sum(dg);
-  if (off <= 1e-28 * dg || dg == 0.0) {  // uniform: every thread holds the same sums
-    if (tid == 0) {
-      state[head] = 1;
-      n_logged[head] = 0;
-    }
-    return;
-  }
-
-  for (int round = 0; round < kJacRounds; ++round) {
-    if (tid < kD / 2) {
-      int p, q;
-      jacobi_pair(round, tid, p, q);
-      const double app = A[p * kJacPitch + p], aqq = A[q * kJacPitch + q], apq = A[p * kJacPitch + q];
-      double cs = 1.0, sn = 0.0;
-      if (fabs(apq) > 1e-300) {
-        const double theta = (aqq - app) / (2.0 * apq);
-        const double t = (theta >= 0.0 ? 1.0 : -1.0) / (fabs(theta) + sqrt(theta * theta + 1.0));
-        cs = 1.0 / sqrt(t * t + 1.0);
-        sn = t * cs;
-      }
-      s_p[tid] = p; s_q[tid] = q; s_c[tid] = cs; s_s[tid] = sn;
-      log[round * (kD / 2) + tid] = make_double2(cs, sn);
-    }
-    __syncthreads();
-    // A <- J^T A J, one 2 x 2 block (row pair, column pair) at a time: the rows are rotated
-    // first and the columns after, element by element the same operations as two whole-matrix
-    // passes, with every element read and written once
-    for (int it = tid; it < (kD / 2) * (kD / 2); it += kJacThreads) {
-      const int pr = it / (kD / 2), pc = it % (kD / 2);
-      const int p = s_p[pr], q = s_q[pr], p2 = s_p[pc], q2 = s_q[pc];
-      const double cs = s_c[pr], sn = s_s[pr], cs2 = s_c[pc], sn2 = s_s[pc];
-      const double xpp = A[p * kJacPitch + p2], xpq = A[p * kJacPitch + q2];
-      const double xqp = A[q * kJacPitch + p2], xqq = A[q * kJacPitch + q2];
-      const double tpp = cs * xpp - sn * xqp, tqp = sn * xpp + cs * xqp;  // rows p, q at column p2
-      const double tpq = cs * xpq - sn * xqq, tqq = sn * xpq + cs * xqq;  // rows p, q at column q2
-      A[p * kJacPitch + p2] = cs2 * tpp - sn2 * tpq;
-      A[p * kJacPitch + q2] = sn2 * tpp + cs2 * tpq;
-      A[q * kJacPitch + p2] = cs2 * tqp - sn2 * tqq;
-      A[q * kJacPitch + q2] = sn2 * tqp + cs2 * tqq;
-    }
-    __syncthreads();
-  }
-  for (int e = tid; e < kD * kD; e += kJacThreads) Ag[e] = A[(e / kD) * kJacPitch + e % kD];
-  if (tid == 0) n_logged[head] = kJacRounds;
-}
-
-// Vt[j][i] = component j, entry i.  Block (slice, head) owns entries i in [16 slice, 16 slice + 16)
-// of every component; the rotation of components p and q is the same on every entry.  The first
-// sweep starts from the identity.
-__global__ __launch_bounds__(kJacApplyThreads) void jacobi_apply_kernel(double* __restrict__ vt_all,
-                                                                        const double2* __restrict__ log_all,
-                                                                        const int* __restrict__ n_logged,
-                                                                        int sweep) {
-  __shared__ double s_v[kD][kJacSliceCols + 1];
-  const int tid = threadIdx.x, slice = blockIdx.x, head = blockIdx.y;
-  const int n_rounds = n_logged[head];
-  if (n_rounds == 0 && sweep > 0) return;  // (uniform) nothing to replay: Vt stays as it is
-  double* Vt = vt_all + (size_t)head * kD * kD;
-  const double2* log = log_all + (size_t)head * kJacRounds * (kD / 2);
-  const int i0 = slice * kJacSliceCols;
-  for (int e = tid; e < kD * kJacSliceCols; e += kJacApplyThreads) {
-    const int j = e / kJacSliceCols, c = e % kJacSliceCols;
-    s_v[j][c] = sweep == 0 ? (j == i0 + c ? 1.0 : 0.0) : Vt[(size_t)j * kD + i0 + c];
-  }
+  s_mirror[c][r] = x;
   __syncthreads();
-  // thread t: pair slot t / 4, columns 4 (t % 4) .. + 3 of the slice
-  const int slot = tid >> 2, c0 = 4 * (tid & 3);
-  for (int round = 0; round < n_rounds; ++round) {
-    int p, q;
-    jacobi_pair(round, slot, p, q);
-    const double2 r = log[round * (kD / 2) + slot];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const double vx = s_v[p][c0 + c], vy = s_v[q][c0 + c];
-      s_v[p][c0 + c] = r.x * vx - r.y * vy;
-      s_v[q][c0 + c] = r.y * vx + r.x * vy;
-    }
-    __syncthreads();
-  }
-  for (int e = tid; e < kD * kJacSliceCols; e += kJacApplyThreads) {
-    const int j = e / kJacSliceCols, c = e % kJacSliceCols;
-    Vt[(size_t)j * kD + i0 + c] = s_v[j][c];
-  }
-}
-
-// decreasing eigenvalue order (ties: lower index first); largest entry of a component positive
-__global__ __launch_bounds__(kD) void jacobi_finish_kernel(const double* __restrict__ a_all,
-                                                           const double* __restrict__ vt_all,
-                                                           float* __restrict__ P,
-                                                           float* __restrict__ eigenvalues) {
-  __shared__ double s_diag[kD];
-  const int tid = threadIdx.x, head = blockIdx.x;
-  const double* Ag = a_all + (size_t)head * kD * kD;
-  const double* Vt = vt_all + (size_t)head * kD * kD;
-  s_diag[tid] = Ag[(size_t)tid * kD + tid];
-  __syncthreads();
-  const double mine = s_diag[tid];
-  int rank = 0;
-  for (int j = 0; j < kD; ++j) {
-    const double other = s_diag[j];
-    rank += (other > mine || (other == mine && j < tid)) ? 1 : 0;
-  }
-  eigenvalues[(size_t)head * kD + rank] = (float)mine;
-  const double* vrow = Vt + (size_t)tid * kD;
-  double best = 0.0;
-  for (int i = 0; i < kD; ++i)
-    if (fabs(vrow[i]) > fabs(best)) best = vrow[i];
-  const double sgn = best < 0.0 ? -1.0 : 1.0;
-  float* Pc = P + (size_t)head * kD * kD + rank;  // column = component
-  for (int i = 0; i < kD; ++i) Pc[(size_t)i * kD] = (float)(sgn * vrow[i]);
+  cov[(size_t)head * kD * kD + (size_t)mrow * kD + mcol] = s_mirror[r][c];
 }
 
 // Eq. 2: the smallest d whose leading normalised eigenvalues sum to at least v percent.
@@ -457,9 +284,9 @@ size_t pca_workspace_bytes(int Hkv, long long N) {
   b += (size_t)Hkv * nc * kD * sizeof(float);       // partial column sums
   b = (b + 255) / 256 * 256;
   b += (size_t)Hkv * kD * kD * sizeof(double);      // covariance
-  b += (size_t)Hkv * kD * kD * sizeof(double);      // eigenvector accumulator
-  b += (size_t)Hkv * kJacRounds * (kD / 2) * sizeof(double2);  // one sweep's rotations
-  b += (size_t)2 * Hkv * sizeof(int);               // converged flags, rounds logged
+  b += (size_t)Hkv * kD * kD * sizeof(double);      // eigensolver: the vectors, later the projected matrix
+  b += (size_t)Hkv * kEigReflBytes;                 // eigensolver: reflectors, later half of the vectors
+  b += (size_t)2 * Hkv * sizeof(int);               // eigensolver: a state word per head
   return b;
 }
 
@@ -474,7 +301,7 @@ hipError_t launch_pca_stage(int stage, int Hkv, int dtype, const void* keys, lon
   size_t off = ((size_t)Hkv * nc * kD * kD + (size_t)Hkv * nc * kD) * sizeof(float);
   off = (off + 255) / 256 * 256;
   double* cov = reinterpret_cast<double*>(w + off);
-  double* vt = cov + (size_t)Hkv * kD * kD;
+  double* mat = cov + (size_t)Hkv * kD * kD;
   if (stage == 0) {
     if (dtype == 0)
       hipLaunchKernelGGL(gram_kernel<2>, dim3(nc, Hkv), dim3(kGramThreads), 0, st, keys, gram_part,
@@ -483,25 +310,17 @@ hipError_t launch_pca_stage(int stage, int Hkv, int dtype, const void* keys, lon
       hipLaunchKernelGGL(gram_kernel<1>, dim3(nc, Hkv), dim3(kGramThreads), 0, st, keys, gram_part,
                          sum_part, N, rpc);
   } else if (stage == 1) {
-    hipLaunchKernelGGL(cov_reduce_kernel, dim3(Hkv, kD * kD / 1024), dim3(1024), 0, st, gram_part,
+    hipLaunchKernelGGL(cov_reduce_kernel, dim3(kCovPairs, Hkv), dim3(kCovTile * kCovTile), 0, st, gram_part,
                        sum_part, cov, N, nc);
   } else {
-    double2* log = reinterpret_cast<double2*>(vt + (size_t)Hkv * kD * kD);
-    int* state = reinterpret_cast<int*>(log + (size_t)Hkv * kJacRounds * (kD / 2));
-    int* n_logged = state + Hkv;
-    const size_t lds = (size_t)kD * kJacPitch * sizeof(double);
-    static std::atomic<unsigned long long> lds_allowed{0};  // devices already set up
-    const hipError_t ea =
-        allow_dynamic_lds(reinterpret_cast<const void*>(jacobi_sweep_kernel), (int)lds, lds_allowed);
-    if (ea != hipSuccess) return ea;
-    // the covariance array is rotated in place, sweep by sweep
-    for (int sweep = 0; sweep < kJacMaxSweeps; ++sweep) {
-      hipLaunchKernelGGL(jacobi_sweep_kernel, dim3(Hkv), dim3(kJacThreads), lds, st, cov, log, state,
-                         n_logged, sweep);
-      hipLaunchKernelGGL(jacobi_apply_kernel, dim3(kJacSlices, Hkv), dim3(kJacApplyThreads), 0, st, vt, log,
-                         n_logged, sweep);
-    }
-    hipLaunchKernelGGL(jacobi_finish_kernel, dim3(Hkv), dim3(kD), 0, st, cov, vt, P, eigenvalues);
+    EigRegions r;
+    r.cov = cov;
+    r.mat = mat;
+    r.refl = reinterpret_cast<char*>(mat + (size_t)Hkv * kD * kD);
+    r.state = reinterpret_cast<int*>(r.refl + (size_t)Hkv * kEigReflBytes);
+    r.spare = w;  // the partial Gram matrices (64 KiB each) have been added up
+    r.spare_halves = nc;
+    return launch_eigensolver(Hkv, r, P, eigenvalues, st);
   }
   return hipGetLastError();
 }

@@ -187,3 +187,31 @@ def test_loki_selection_agrees_with_exact_topk_more_as_d_grows():
                                                lists[128].view(8, 256)[i].cpu().numpy())) < 1e-6
     say(f"mean Jaccard vs exact top-k: {j}")
     assert j[16] < j[64] < j[128] == 1.0
+
+
+@pytest.mark.parametrize("dtype,N", [("bf16", 3), ("f32", 127), ("bf16", 1025), ("f32", 9000)])
+def test_pca_fit_mixes_regular_and_degenerate_heads(dtype, N):
+    """Heads solved by the tridiagonal route next to heads whose equal eigenvalues send them to
+    the Jacobi iteration: dead columns, every column twice, a steep spectrum without noise, one
+    direction only; few rows (all heads rank-deficient) and many."""
+    keys = calibration_keys(900 + N, 5, N, dtype)
+    keys[1, :, 100:] = 0.0
+    keys[2, :, 64:] = keys[2, :, :64]
+    rng = np.random.default_rng(N)
+    keys[3] = synth.round_storage((rng.standard_normal((N, 128)) * np.exp(-np.arange(128) / 3.0)[None, :]).astype(np.float32), dtype)
+    keys[4] = synth.round_storage((rng.standard_normal((N, 1)) * np.ones((1, 128))).astype(np.float32), dtype)
+    say(f"case dtype {dtype} N {N}")
+    P, lam, _ = fit(keys, dtype)
+    for h in range(5):
+        lam_o, _ = O.pca_basis(keys[h])
+        cov_o = np.cov(keys[h].astype(np.float64), rowvar=False)
+        err = np.max(np.abs(lam[h] - lam_o)) / lam_o[0]
+        orth = np.max(np.abs(P[h].T @ P[h] - np.eye(128)))
+        rec = np.linalg.norm(P[h] @ np.diag(lam[h]) @ P[h].T - cov_o) / np.linalg.norm(cov_o)
+        say(f"   head {h}: eigenvalue err {err:.2e}, orthonormality {orth:.2e}, reconstruction {rec:.2e}")
+        # fp32 output of an orthonormal basis: 128 products of entries rounded to 2^-25 each
+        assert orth < 1e-6
+        # the bounds of test_pca_fit_matches_oracle (the Gram matrix is accumulated in fp32)
+        assert np.all(np.diff(lam[h]) <= 0) and err < 5e-6 and rec < 2e-5
+        # the largest entry is positive; entries of opposite sign that fp32 rounds to the same size tie
+        assert np.all(P[h].max(axis=0) >= np.abs(P[h]).max(axis=0))
