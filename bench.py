@@ -65,6 +65,7 @@ def algorithmic_bytes(w, select_mode):
     gather = sel_heads * w.k * 2 * w.D * e
     dense = units * w.S * 2 * w.D * e
     return {"score": score, "gather_attend": gather, "step": score + gather,
+            "rotate_score": score, "select_attend": gather,
             "fused_decode": score + gather, "dense_attend": dense}
 
 

@@ -44,10 +44,7 @@ hipError_t allow_dynamic_lds(const void* kernel, int bytes, std::atomic<unsigned
 
 int score_rows_per_block(const Shape& s) {
   const int units = s.B * s.Hkv;
-#ifndef LOKI_SCORE_BLOCKS_PER_CU
-#define LOKI_SCORE_BLOCKS_PER_CU 8
-#endif
-  int nchunks = div_up(LOKI_SCORE_BLOCKS_PER_CU * device_cus(), units);
+  int nchunks = div_up(kScoreBlocksPerCU * device_cus(), units);
   const int max_chunks = div_up(s.S, 2 * kScoreRowsPerStep);
   if (nchunks > max_chunks) nchunks = max_chunks;
   if (nchunks < 1) nchunks = 1;
@@ -422,16 +419,30 @@ static int decode_impl(const loki_layout* layout, const void* q, const float* P,
   const int hist_chunks = w.sel_scratch ? select_hist_chunks(s, select_mode) : 0;
   uint32_t* hist_part = hist_chunks ? w.sel_scratch : nullptr;
   if (hist_chunks) idx = w.sel_idx;
-  tm.begin("rotate_query");
-  // (the tickets lie directly before the select scratch, whose first words the histograms are)
-  e = launch_qrot(s, q, P, w.qhat, klo, khi, v, reinterpret_cast<uint32_t*>(w.tickets),
-                  w.ticket_words + (size_t)heads_sel * hist_chunks * 2048, st);
-  tm.end();
-  if (e != hipSuccess) return LOKI_ERR_HIP;
-  tm.begin("score");
-  e = launch_score(s, select_mode, q, P, klo, w.scores, w.qhat, hist_part, hist_chunks, st);
-  tm.end();
-  if (e != hipSuccess) return LOKI_ERR_HIP;
+  if (rotate_score_applies(s) && hist_chunks == 0) {  // (histograms have to be clear before the scoring begins)
+    tm.begin("rotate_score");
+    e = launch_rotate_score(s, select_mode, q, P, klo, khi, v, w.scores, w.qhat, reinterpret_cast<uint32_t*>(w.tickets),
+                            w.ticket_words, st);
+    tm.end();
+    if (e != hipSuccess) return LOKI_ERR_HIP;
+  } else {
+    tm.begin("rotate_query");
+    // (the tickets lie directly before the select scratch, whose first words the histograms are)
+    e = launch_qrot(s, q, P, w.qhat, klo, khi, v, reinterpret_cast<uint32_t*>(w.tickets),
+                    w.ticket_words + (size_t)heads_sel * hist_chunks * 2048, st);
+    tm.end();
+    if (e != hipSuccess) return LOKI_ERR_HIP;
+    tm.begin("score");
+    e = launch_score(s, select_mode, klo, w.scores, w.qhat, hist_part, hist_chunks, st);
+    tm.end();
+    if (e != hipSuccess) return LOKI_ERR_HIP;
+  }
+  if (select_attend_applies(s)) {
+    tm.begin("select_attend");
+    e = launch_select_attend(s, select_mode, nsplit, w.scores, out_idx, w.qhat, klo, khi, v, w.partial, w.tickets, out, st);
+    tm.end();
+    return e == hipSuccess ? LOKI_OK : LOKI_ERR_HIP;
+  }
   tm.begin("select");
   e = launch_select(s, heads_sel, w.scores, idx, w.sel_score, w.sel_scratch, hist_chunks != 0,
                     hist_chunks ? out_idx : nullptr, st);

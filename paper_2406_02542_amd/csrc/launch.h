@@ -59,6 +59,7 @@ int device_cus();
 // attribute belongs to the function on one device; `done` is a bit mask of devices, one static
 // per kernel instantiation, so that the launch path makes no attribute call afterwards).
 hipError_t allow_dynamic_lds(const void* kernel, int bytes, std::atomic<unsigned long long>& done);
+constexpr int kScoreBlocksPerCU = 8;     // score blocks a launch aims at
 constexpr int kScoreRowsPerStep = 256;   // rows one 256-thread block scores per step
 constexpr int kMaxGatherChunk = 2048;    // selected rows one attend block may own (LDS index list)
 constexpr int kFusedMaxS = 8192;         // fused single-kernel path: scores of a unit live in LDS
@@ -95,9 +96,12 @@ Workspace plan_workspace(const Shape& s, int select_mode, int nsplit, void* base
 hipError_t launch_qrot(const Shape& s, const void* q, const float* P, float* qhat, void* klo,
                        void* khi, void* v, uint32_t* zero_words, size_t n_zero, hipStream_t st);
 // hist_part [selecting heads][hist_chunks][2048] (zeroed) or null: see select_hist_chunks.
-hipError_t launch_score(const Shape& s, int select_mode, const void* q, const float* P,
-                        const void* klo, float* scores, float* qhat, uint32_t* hist_part,
-                        int hist_chunks, hipStream_t st);
+hipError_t launch_score(const Shape& s, int select_mode, const void* klo, float* scores, const float* qhat,
+                        uint32_t* hist_part, int hist_chunks, hipStream_t st);
+// launch_qrot and launch_score in one launch (no chunk histograms).
+bool rotate_score_applies(const Shape& s);
+hipError_t launch_rotate_score(const Shape& s, int select_mode, const void* q, const float* P, void* klo, void* khi, void* v,
+                               float* scores, float* qhat, uint32_t* zero_words, size_t n_zero, hipStream_t st);
 size_t select_scratch_words(int S, int n_sel_heads);
 // Long sequences, one token per sequence: the number of 16384-row chunks whose leading-digit
 // histograms the score kernel fills for the selection (they are the first words of the select
@@ -116,6 +120,12 @@ hipError_t launch_gather(const Shape& s, int select_mode, int nsplit, const floa
                          const void* klo, const void* khi, const void* v, const int32_t* sel_idx,
                          const float* sel_score, float* partial, int32_t* tickets, void* out,
                          hipStream_t st);
+// Selection and attention in one launch (select_attend.hip; S <= 16384), behind launch_score: user_idx
+// (nullable) receives the caller's lists; tickets as above, always given.
+bool select_attend_applies(const Shape& s);
+hipError_t launch_select_attend(const Shape& s, int select_mode, int nsplit, const float* scores, int32_t* user_idx,
+                                const float* qhat, const void* klo, const void* khi, const void* v, float* partial,
+                                int32_t* tickets, void* out, hipStream_t st);
 hipError_t launch_dense(const Shape& s, int nsplit, const void* q, const void* k_full,
                         const void* v, float* partial, void* out, hipStream_t st);
 // Matrix-core attention for 8 query heads per block on bf16 caches (attend_mfma.hip).

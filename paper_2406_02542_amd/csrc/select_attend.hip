@@ -1,0 +1,275 @@
+// Top-k selection and exact attention over the selected rows in one launch (Algorithm 1 lines 6-9
+// of arXiv 2406.02542), for score rows short enough to be selected by one block (S <= 16384): the
+// last kernel of the split path, behind the query rotation and the scoring.
+//
+// Block (split, head): the block makes the whole selection of its head for itself, from the scores
+// the launch before left in L2, and attends over its share of the list, which never leaves LDS.
+// With several splits per head the selection is repeated by each of their blocks: it is a chain of
+// barriers and LDS round trips that costs a head the same few microseconds whoever runs it, while
+// a launch of its own costs those and a launch, and the list written and read back.  Against the two
+// launches, us per step: one sequence of 32 heads, S = 4096, k = 1024, 23.1 -> 20.4; of 32/8 heads,
+// S = 8192, k = 1024, 26.7 -> 25.0; 16 of 32/8 heads, S = 12345, per-head selection 123.8 -> 118.3 (there
+// a block's selection also runs beside its neighbour's row loads).
+#include "attend_mfma_impl.h"
+#include "select_impl.h"
+
+namespace loki {
+
+constexpr int kSaThreads = 512;
+constexpr int kSaWaves = kSaThreads / 64;
+
+// What both kernels are given beside their operands.
+struct SelectAttendArgs {
+  const float* scores;   // [selecting heads][S_max]
+  int32_t* user_idx;     // [selecting heads][k_max] or null: the caller's copy of the lists
+  float* partial;        // [B*Hq][nsplit][130] when nsplit > 1
+  int32_t* tickets;      // [selecting heads], zeroed
+  int Hkv, G, S_max, S_cap, d, k_max, nsplit, per_thread;
+  int xcd_group_blocks, xcd_sets;  // see attend.hip (0: launch order as is)
+  Ragged rg;
+  Paging pg;
+};
+
+// The selection of score row `sel` for batch entry b, entries [r0, r1) of it into s_idx (as rows of
+// the cache unit, or of the pool when the cache is paged) and, with s_a, their scores.  Ends with a
+// barrier.
+template <int KPT>
+__device__ __forceinline__ void select_share(const SelectAttendArgs& a, int sel, int b, int hkv, int S, int k, int r0,
+                                             int r1, bool write_user, ResidentSelectSmem<kSaThreads>& sm,
+                                             int32_t* s_idx, float* s_a) {
+  int32_t* user = write_user && a.user_idx != nullptr ? a.user_idx + (size_t)sel * a.k_max : nullptr;
+  if (user)
+    for (int i = k + (int)threadIdx.x; i < a.k_max; i += kSaThreads) user[i] = -1;  // a sequence keeping fewer rows
+  const bool paged = a.pg.table != nullptr;
+  const int cache_b = b / max(a.rg.queries, 1);
+  resident_select_clear<kSaThreads>(sm);
+  __syncthreads();
+  block_select_topk_resident<kSaThreads, KPT>(
+      a.scores + (size_t)sel * a.S_max, S, k, a.per_thread, sm, [&](int rank, int pos, float score) {
+        if (user) user[rank] = pos;
+        if (rank >= r0 && rank < r1) {
+          s_idx[rank - r0] = paged ? (int32_t)cache_row(a.pg, cache_b, hkv, a.Hkv, a.S_cap, pos) : pos;
+          if (s_a) s_a[rank - r0] = score;
+        }
+      });
+  __syncthreads();
+}
+
+// The block's merged (max, sum, output) of NH heads: the result, or its part of it, merged by the
+// block of the head group that finishes last (see splits_all_done).
+template <typename T, int NH>
+__device__ __forceinline__ void finish_share(const SelectAttendArgs& a, const MergeSmem<kSaWaves, NH>& sm, size_t head0,
+                                             int sel, int split, typename T::store_t* out) {
+  for (int i = threadIdx.x; i < NH * kD; i += kSaThreads) {
+    const int g = i / kD, col = i % kD;
+    float mn, ls, os;
+    attend_merged<kSaWaves, NH>(sm, g, col, mn, ls, os);
+    if (a.nsplit == 1) {
+      T::store1(out + (head0 + g) * kD + col, os / ls);
+    } else {
+      float* pr = a.partial + ((head0 + g) * a.nsplit + split) * kPartialStride;
+      store_shared_f32(pr + col, os, true);
+      if (col == 0) {
+        store_shared_f32(pr + kD, mn, true);
+        store_shared_f32(pr + kD + 1, ls, true);
+      }
+    }
+  }
+  if (a.nsplit > 1 && splits_all_done(a.tickets + sel, a.nsplit))
+    for (int i = threadIdx.x; i < NH * kD; i += kSaThreads) {
+      const size_t head = head0 + i / kD;
+      T::store1(out + head * kD + i % kD,
+                combine_splits<true>(a.partial + head * a.nsplit * kPartialStride, a.nsplit, i % kD));
+    }
+}
+
+// List entries of a block: equal shares of what the sequence keeps.
+__device__ __forceinline__ void share_of(int k, int nsplit, int split, int& r0, int& r1) {
+  const int n = (k + nsplit - 1) / nsplit;
+  r0 = min(k, split * n);
+  r1 = min(k, r0 + n);
+}
+
+// Vector form.  NH = query heads that share a selection; with one, the ranking score is the
+// low-rank part of the logit and the slab is not read again (REUSE_LO).
+template <typename T, int NH, int KPT>
+__global__ __launch_bounds__(kSaThreads, NH == 1 ? 4 : 2) void select_attend_kernel(
+    const void* __restrict__ klo, const void* __restrict__ khi, const void* __restrict__ v,
+    const float* __restrict__ qhat, typename T::store_t* __restrict__ out, SelectAttendArgs a) {
+  constexpr bool REUSE_LO = NH == 1;
+  constexpr int EPC = T::EPC;
+  constexpr int LPRV = kD / EPC;
+  constexpr int RPW = 64 / LPRV;
+  __shared__ ResidentSelectSmem<kSaThreads> s_sel;
+  __shared__ int32_t s_idx[kMaxGatherChunk];
+  __shared__ float s_a[REUSE_LO ? kMaxGatherChunk : 1];
+  __shared__ MergeSmem<kSaWaves, NH> s_merge;
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int c = lane % LPRV, rg = lane / LPRV;
+  // query heads that read the same cached KV head stay on one XCD, next to each other (attend.hip)
+  int split = blockIdx.x, sel = blockIdx.y;
+  if (a.xcd_group_blocks > 0) {
+    const int n = sel * a.nsplit + split;
+    const int j = n >> 3, set = (j / a.xcd_group_blocks) * 8 + (n & 7), m = j % a.xcd_group_blocks;
+    if (set >= a.xcd_sets) return;  // uniform for the block, before any barrier
+    const int member = m / a.nsplit;  // (token, head of the group)
+    const int seq = set / a.Hkv, tokens = max(a.rg.queries, 1);
+    sel = ((seq * tokens + member / a.G) * a.Hkv + set % a.Hkv) * a.G + member % a.G;
+    split = m % a.nsplit;
+  }
+  const size_t head0 = (size_t)sel * NH;
+  const int Hq = a.Hkv * a.G;
+  const int b = (int)(head0 / Hq), hkv = (int)(head0 % Hq) / a.G;
+  const int S = seq_rows(a.rg, b, a.S_max), k = seq_keep(a.rg, b, a.k_max, S);
+  int r0, r1;
+  share_of(k, a.nsplit, split, r0, r1);
+
+  float qr[NH][EPC];  // this lane's slice of the query vectors, on its way during the selection
+#pragma unroll
+  for (int g = 0; g < NH; ++g)
+#pragma unroll
+    for (int e = 0; e < EPC; ++e) qr[g][e] = qhat[(head0 + g) * kD + c * EPC + e];
+  select_share<KPT>(a, sel, b, hkv, S, k, r0, r1, split == 0, s_sel, s_idx, REUSE_LO ? s_a : nullptr);
+
+  const size_t unit = a.pg.table != nullptr ? (size_t)0 : (size_t)cache_unit(a.rg, b * a.Hkv + hkv, a.Hkv);
+  const RowAddr ra = make_row_addr<T, REUSE_LO>(klo, khi, v, unit, a.S_cap, a.d, c);
+  AttendAcc<T, NH> acc;
+  acc.init();
+  attend_rows<T, NH, kSaWaves * RPW, true, REUSE_LO>(acc, qr, ra, s_idx, s_a, wave * RPW + rg, r0, r1);
+  attend_publish<T, NH, kSaWaves>(acc, s_merge);
+  finish_share<T, NH>(a, s_merge, head0, sel, split, out);
+}
+
+// Matrix-core form for 4 or 8 query heads that share a selection (bf16 caches, attend_mfma_impl.h).
+template <int NH, int KPT>
+__global__ __launch_bounds__(kSaThreads, 2) void select_attend_mfma_kernel(
+    const void* __restrict__ klo, const void* __restrict__ khi, const void* __restrict__ v,
+    const float* __restrict__ qhat, uint16_t* __restrict__ out, SelectAttendArgs a) {
+  __shared__ ResidentSelectSmem<kSaThreads> s_sel;
+  __shared__ int32_t s_idx[kMaxGatherChunk];
+  __shared__ __align__(16) unsigned char s_v[kSaWaves][kAmStageBytes];
+  MergeSmem<kSaWaves, NH>& s_merge = *reinterpret_cast<MergeSmem<kSaWaves, NH>*>(s_v);  // the tiles are dead by then
+  static_assert(sizeof(s_merge) <= sizeof(s_v), "the merge fits the value tiles");
+
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int r16 = lane & 15;
+  const int split = blockIdx.x, unit = blockIdx.y;
+  const size_t head0 = (size_t)unit * NH;
+  const bool head_ok = r16 < NH;
+  const int b = unit / a.Hkv;
+  const int S = seq_rows(a.rg, b, a.S_max), k = seq_keep(a.rg, b, a.k_max, S);
+  int r0, r1;
+  share_of(k, a.nsplit, split, r0, r1);
+
+  select_share<KPT>(a, unit, b, unit % a.Hkv, S, k, r0, r1, split == 0, s_sel, s_idx, nullptr);
+
+  am_bf16x8_t bq[4][2];
+  am_query_operands<4, 2>(qhat + (head0 + (head_ok ? r16 : 0)) * kD, head_ok, kD, bq);
+  const size_t addr_unit = a.pg.table != nullptr ? (size_t)0 : (size_t)cache_unit(a.rg, unit, a.Hkv);
+  const AmAddr<4> ad = am_make_addr<4, false>(klo, khi, v, addr_unit, a.S_cap, a.d);
+  AmState st;
+  st.init();
+  am_attend_rows<true, 4, 2, kSaWaves>(ad, bq, s_idx, r0, r1, s_v[wave], st);
+  __syncthreads();  // every wave is done with its tiles: the space turns into the merge
+  am_publish<NH, kSaWaves>(st, s_merge);
+  finish_share<BF16, NH>(a, s_merge, head0, unit, split, out);
+}
+
+// ---- launchers ------------------------------------------------------------------------------------
+static inline int div_up(int a, int b) { return (a + b - 1) / b; }
+
+bool select_attend_applies(const Shape& s) { return s.S <= kSaThreads * 32; }
+
+template <typename T, int NH>
+static hipError_t launch_sa(const SelectAttendArgs& a, dim3 grid, const void* klo, const void* khi, const void* v,
+                            const float* qhat, void* out, hipStream_t st) {
+  auto* o = static_cast<typename T::store_t*>(out);
+  if (a.per_thread <= 8)
+    hipLaunchKernelGGL((select_attend_kernel<T, NH, 8>), grid, dim3(kSaThreads), 0, st, klo, khi, v, qhat, o, a);
+  else if (a.per_thread <= 16)
+    hipLaunchKernelGGL((select_attend_kernel<T, NH, 16>), grid, dim3(kSaThreads), 0, st, klo, khi, v, qhat, o, a);
+  else
+    hipLaunchKernelGGL((select_attend_kernel<T, NH, 32>), grid, dim3(kSaThreads), 0, st, klo, khi, v, qhat, o, a);
+  return hipGetLastError();
+}
+
+template <int NH>
+static hipError_t launch_sa_mfma(const SelectAttendArgs& a, dim3 grid, const void* klo, const void* khi, const void* v,
+                                 const float* qhat, void* out, hipStream_t st) {
+  auto* o = static_cast<uint16_t*>(out);
+  if (a.per_thread <= 8)
+    hipLaunchKernelGGL((select_attend_mfma_kernel<NH, 8>), grid, dim3(kSaThreads), 0, st, klo, khi, v, qhat, o, a);
+  else if (a.per_thread <= 16)
+    hipLaunchKernelGGL((select_attend_mfma_kernel<NH, 16>), grid, dim3(kSaThreads), 0, st, klo, khi, v, qhat, o, a);
+  else
+    hipLaunchKernelGGL((select_attend_mfma_kernel<NH, 32>), grid, dim3(kSaThreads), 0, st, klo, khi, v, qhat, o, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_select_attend(const Shape& s, int select_mode, int nsplit, const float* scores, int32_t* user_idx,
+                                const float* qhat, const void* klo, const void* khi, const void* v, float* partial,
+                                int32_t* tickets, void* out, hipStream_t st) {
+  if (!select_attend_applies(s) || div_up(s.k, nsplit) > kMaxGatherChunk) return hipErrorInvalidValue;
+  const int NH = select_mode == 1 ? s.G : 1;
+  const bool mfma = attend_mfma_applies(s, NH);
+  // Row splits: a block per CU, no more (a second one repeats the selection on a CU that is busy with
+  // it already: 4 tokens of 2 sequences, 32/8 heads, k = 1329 45.6 -> 30.2 us), each with two trips of its row
+  // loop (vector: 256 rows in bf16, 128 in fp32; against half as many, one sequence of 2 KV groups at
+  // k = 1341: 26.1 -> 23.6 us), on the matrix cores half a trip (128 rows; against 256, Llama-3 shape at
+  // batch 1: 24.3 -> 22.4 us).  Never more than the workspace has partials for.
+  const int min_rows = mfma || s.dtype == 0 ? 128 : 256;
+  int n = device_cus() / (s.B * s.Hq / NH);
+  if (n > s.k / min_rows) n = s.k / min_rows;
+  if (n < div_up(s.k, kMaxGatherChunk)) n = div_up(s.k, kMaxGatherChunk);
+  if (n < nsplit) nsplit = n > 1 ? n : 1;
+  SelectAttendArgs a;
+  a.scores = scores;
+  a.user_idx = user_idx;
+  a.partial = partial;
+  a.tickets = tickets;
+  a.Hkv = s.Hkv;
+  a.G = s.G;
+  a.S_max = s.S;
+  a.S_cap = s.S_cap;
+  a.d = s.d;
+  a.k_max = s.k;
+  a.nsplit = nsplit;
+  a.per_thread = ((s.S + kSaThreads - 1) / kSaThreads + 3) & ~3;
+  a.xcd_group_blocks = a.xcd_sets = 0;
+  a.rg = s.rg;
+  a.pg = s.pg;
+  int blocks_y = s.B * s.Hq / NH;
+  if (mfma) {
+    const dim3 grid(nsplit, blocks_y);
+    return NH == 8 ? launch_sa_mfma<8>(a, grid, klo, khi, v, qhat, out, st)
+                   : launch_sa_mfma<4>(a, grid, klo, khi, v, qhat, out, st);
+  }
+  const int tokens = s.rg.queries > 1 ? s.rg.queries : 1;
+  const int sharers = tokens * s.G, sets = s.B / tokens * s.Hkv, rounds = (sets + 7) / 8;
+  if (NH == 1 && sharers > 1 && (long long)rounds * 8 * sharers <= 65535) {
+    a.xcd_group_blocks = sharers * nsplit;
+    a.xcd_sets = sets;
+    blocks_y = rounds * 8 * sharers;
+  }
+  const dim3 grid(nsplit, blocks_y);
+#define LOKI_SA(T, NHV) return launch_sa<T, NHV>(a, grid, klo, khi, v, qhat, out, st)
+  if (s.dtype == 0) {
+    switch (NH) {
+      case 1: LOKI_SA(F32, 1);
+      case 2: LOKI_SA(F32, 2);
+      case 4: LOKI_SA(F32, 4);
+      case 8: LOKI_SA(F32, 8);
+      default: return hipErrorInvalidValue;
+    }
+  }
+  switch (NH) {  // (4 and 8 heads: the matrix-core form above)
+    case 1: LOKI_SA(BF16, 1);
+    case 2: LOKI_SA(BF16, 2);
+    default: return hipErrorInvalidValue;
+  }
+#undef LOKI_SA
+}
+
+}  // namespace loki

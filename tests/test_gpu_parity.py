@@ -583,3 +583,21 @@ def test_stream_read_probe_runs():
     api.loki_stream_read(buf, buf.numel() * 4)
     api.loki_stream_read(buf, 16 * 1237)
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("dtype,G,mode,S,d,k", [
+    ("bf16", 1, 0, 1, 32, 1), ("bf16", 1, 0, 255, 8, 200), ("f32", 1, 0, 513, 20, 129), ("bf16", 2, 1, 4097, 64, 257),
+    ("bf16", 4, 1, 8192, 40, 128), ("bf16", 8, 1, 8193, 128, 2048), ("f32", 4, 1, 1025, 128, 513), ("bf16", 4, 0, 16384, 48, 4097),
+    ("bf16", 8, 0, 12345, 96, 511), ("f32", 8, 0, 4099, 64, 300)])
+def test_selection_inside_the_attention_launch(dtype, G, mode, S, d, k):
+    """The split path up to 16384 rows: every row count at which the keys a thread holds or the
+    selection's tiles change, list lengths around a whole number of splits, widths of one to four
+    rotated 32-column groups, both forms of the attention; the appended row is scored by the block
+    that writes its low-rank part."""
+    from tests.test_gpu_step import run_step_case
+    w = synth.Workload("sel_att", 2, 2 * G, 2, 128, S, dtype, d, k, seed=77 + S)
+    say(f"case {dtype} G {G} mode {mode} S {S} d {d} k {k}")
+    case = DeviceCase(w, synth.make_inputs(w))
+    say(f"   batch {check_loki(case, mode, path=api.PATH_SPLIT)}")
+    run_step_case(w, mode, False, True, path=api.PATH_SPLIT)
+    run_step_case(w, mode, S > 4, True, path=api.PATH_SPLIT, page_rows=256)
