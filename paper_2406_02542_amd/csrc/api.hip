@@ -390,15 +390,22 @@ static int decode_impl(const loki_layout* layout, const void* q, const float* P,
   hipError_t e;
   if (path == LOKI_PATH_CLUSTER && (s.G == 1 || !fused_gqa_cluster_eligible(s, select_mode)))
     return LOKI_ERR_UNSUPPORTED;
-  if (s.G == 1) {
-    if (path == LOKI_PATH_FUSED && !fused_eligible(s)) return LOKI_ERR_UNSUPPORTED;
-    if (path == LOKI_PATH_FUSED || (path == 0 && fused_preferred(s))) {
-      tm.begin("fused_decode");
-      e = launch_fused(s, q, P, klo, khi, v, out, out_idx, st);
+  if (s.G == 1 && path == LOKI_PATH_FUSED && !fused_pinnable(s)) return LOKI_ERR_UNSUPPORTED;
+  if (select_mode == LOKI_SELECT_PER_QUERY_HEAD &&
+      ((s.G == 1 && path == LOKI_PATH_FUSED) || (path == 0 && fused_preferred(s)))) {
+    if (s.G > 1 && s.ap.k_new != nullptr) {
+      tm.begin("append");
+      e = launch_qrot(s, q, P, w.qhat, klo, khi, v, nullptr, 0, st);
       tm.end();
-      return e == hipSuccess ? LOKI_OK : LOKI_ERR_HIP;
+      if (e != hipSuccess) return LOKI_ERR_HIP;
+      s.ap = Append{};
     }
-  } else {
+    tm.begin("fused_decode");
+    e = launch_fused(s, q, P, klo, khi, v, out, out_idx, st);
+    tm.end();
+    return e == hipSuccess ? LOKI_OK : LOKI_ERR_HIP;
+  }
+  if (s.G > 1) {
     if (path == LOKI_PATH_CLUSTER || (path == 0 && w.cluster != nullptr && fused_gqa_cluster_preferred(s, select_mode))) {
       tm.begin("fused_decode");
       e = launch_fused_gqa_cluster(s, q, P, klo, khi, v, out, out_idx, w.cluster_ctl, ws_zeroed, w.cluster, st);

@@ -15,6 +15,12 @@ constexpr int kFusedThreads = 512;
 constexpr int kFusedWaves = kFusedThreads / 64;
 constexpr int kFusedKPT = kFusedMaxS / kFusedThreads;  // keys a thread may hold in the select stage
 
+// bytes of the region that holds the rotation's partial sums (query, new key) and then the scores
+__host__ __device__ inline size_t fused_region_bytes(int S) {
+  const size_t scores = ((size_t)S * 4 + 15) & ~(size_t)15, rot = 2 * kRotParts * kD * sizeof(float);
+  return scores > rot ? scores : rot;
+}
+
 // positions per thread in the select stage: ceil(S / threads) rounded up to a multiple of 4
 __host__ __device__ inline int fused_keys_per_thread(int S) {
   const int c = (S + kFusedThreads - 1) / kFusedThreads;
@@ -54,37 +60,51 @@ __device__ __forceinline__ int fused_unit_of_block(const Ragged& rag, int B, int
 constexpr int kFusedMaxPages = kFusedMaxS / 256;  // pages are at least 256 rows
 
 // PAGED: the three slabs are pools addressed through the sequence's page list (see Paging).
-template <typename T, int LPR, bool REUSE_LO, int KPT, bool APPEND, bool PAGED>
+// GROUPED: G query heads to a KV head, every one selecting for itself.
+template <typename T, int LPR, bool REUSE_LO, int KPT, bool APPEND, bool PAGED, bool GROUPED>
 __global__ __launch_bounds__(kFusedThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) void
 fused_decode_kernel(
     const typename T::store_t* klo, const typename T::store_t* khi, const typename T::store_t* v,
     const typename T::store_t* __restrict__ q, const float* __restrict__ P,
-    typename T::store_t* __restrict__ out, int32_t* __restrict__ out_idx, int Hkv, int S_max,
+    typename T::store_t* __restrict__ out, int32_t* __restrict__ out_idx, int n_seq, int Hkv, int G, int S_max,
     int S_cap, int d, int k_max, Ragged rag, Append ap, Paging pg) {
   using ST = typename T::store_t;
   constexpr int EPC = T::EPC;
   constexpr int LPRV = kD / EPC;
   constexpr int RPW = 64 / LPRV;
 
+  // The rotation's partial sums and then the scores, the index list, and the scores of its entries;
+  // long sequences (KPT = 32) leave those out, so that two blocks still share a CU's LDS, and look a
+  // row's score up by its position (a paged cache's entries are pool rows and need the copy).
+  constexpr bool kScoreByRow = KPT > 16 && !PAGED;
   extern __shared__ __align__(16) unsigned char dyn_smem[];
-  const int per_thread = fused_keys_per_thread(S_max);           // multiple of 4, <= kFusedKPT
-  float* s_score = reinterpret_cast<float*>(dyn_smem);           // [kFusedThreads * per_thread]
-  int32_t* s_idx = reinterpret_cast<int32_t*>(s_score + kFusedThreads * per_thread);  // [k_max]
-  float* s_a = reinterpret_cast<float*>(s_idx + k_max);          // [k_max]
+  const int per_thread = fused_keys_per_thread(S_max);           // multiple of 4, <= KPT
+  float* s_score = reinterpret_cast<float*>(dyn_smem);           // [S_max]
+  float(*s_part)[kD] = reinterpret_cast<float(*)[kD]>(dyn_smem);   // [kRotParts][kD]: the query's; then the new key's
+  int32_t* s_idx = reinterpret_cast<int32_t*>(dyn_smem + fused_region_bytes(S_max));  // [k_max]
+  float* s_a = kScoreByRow ? s_score : reinterpret_cast<float*>(s_idx + k_max);
 
   __shared__ __align__(16) float s_q[kD];
-  __shared__ __align__(8) float s_part[kRotParts][kD];
   __shared__ float s_qhat[1][kD];
   __shared__ __align__(16) float s_kn[APPEND ? kD : 4];                       // the new key
-  __shared__ __align__(8) float s_partk[APPEND ? kRotParts : 1][APPEND ? kD : 2];
   static_assert(kFusedWaves == kRotParts, "one wave per part of the rotation");
   __shared__ ResidentSelectSmem<kFusedThreads> s_sel;
   __shared__ MergeSmem<kFusedWaves, 1> s_merge;
   __shared__ int32_t s_pages[PAGED ? kFusedMaxPages : 1];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  // = b * H + h; one query head per KV head here
-  const int unit = fused_unit_of_block(rag, (int)gridDim.x / Hkv, Hkv, (int)blockIdx.x);
+  // head = b * Hq + query head; unit = b * Hkv + KV head, whose cache it reads
+  int head, unit;
+  if constexpr (!GROUPED) {
+    head = unit = fused_unit_of_block(rag, (int)gridDim.x / Hkv, Hkv, (int)blockIdx.x);
+  } else {
+    // The G heads of a unit read the same slab and largely the same rows: blocks go to the 8 XCDs in
+    // turn, so a unit's heads are blocks 8 apart, on one XCD and next to each other in time.
+    const int j = (int)blockIdx.x >> 3;
+    unit = fused_unit_of_block(rag, n_seq, Hkv, (j / G) * 8 + ((int)blockIdx.x & 7));
+    if (unit >= n_seq * Hkv) return;  // (padding of the launch; uniform for the block)
+    head = unit * G + j % G;
+  }
   const int h = unit % Hkv;
   const int S = seq_rows(rag, unit / Hkv, S_max);
   const int k = seq_keep(rag, unit / Hkv, k_max, S);
@@ -119,7 +139,7 @@ fused_decode_kernel(
   // Issue order = the order the results are needed in (loads return in order): q, then this
   // thread's 16 x 2 entries of P_h, then the first slab loads, which do not need qhat and stay
   // in flight during the rotation.
-  const float q_mine = T::load1(q + (size_t)unit * kD + (tid & (kD - 1)));  // no branch: no early wait
+  const float q_mine = T::load1(q + (size_t)head * kD + (tid & (kD - 1)));  // no branch: no early wait
   float kn_mine = 0.f, vn_mine = 0.f;
   if constexpr (APPEND) {
     kn_mine = T::load1(static_cast<const ST*>(ap.k_new) + (size_t)unit * kD + (tid & (kD - 1)));
@@ -167,7 +187,7 @@ fused_decode_kernel(
     *reinterpret_cast<float2*>(&part_row[2 * lane]) = make_float2(a0, a1);
   };
   rotate_part(s_q, s_part[wave]);
-  if constexpr (APPEND) rotate_part(s_kn, s_partk[wave]);
+  if constexpr (APPEND) rotate_part(s_kn, s_part[kRotParts + wave]);
   __syncthreads();
   if (tid < kD) {
     float sum = 0.f;
@@ -185,7 +205,7 @@ fused_decode_kernel(
       const int j = tid - kD;
       float sum = 0.f;
 #pragma unroll
-      for (int pp = 0; pp < kRotParts; ++pp) sum += s_partk[pp][j];
+      for (int pp = 0; pp < kRotParts; ++pp) sum += s_part[kRotParts + pp][j];
       ST* dst = j < d ? const_cast<ST*>(klo) + row * d + j : const_cast<ST*>(khi) + row * (kD - d) + (j - d);
       T::store1(dst, sum);
     } else if (tid >= 2 * kD && tid < 3 * kD) {
@@ -216,14 +236,14 @@ fused_decode_kernel(
   LOKI_STAMP(2);
 
   // ---- top-k in LDS ------------------------------------------------------------------------
-  int32_t* gidx = out_idx ? out_idx + (size_t)unit * k_max : nullptr;
+  int32_t* gidx = out_idx ? out_idx + (size_t)head * k_max : nullptr;
   if (gidx)
     for (int i = k + tid; i < k_max; i += kFusedThreads) gidx[i] = -1;  // a sequence keeping fewer rows
   block_select_topk_resident<kFusedThreads, KPT>(s_score, S, k, per_thread, s_sel,
                                                        [&](int rank, int pos, float score) {
     if constexpr (PAGED) s_idx[rank] = (int32_t)slab.pool_row(pos);  // the attention stage reads pool rows
     else s_idx[rank] = pos;
-    s_a[rank] = score;
+    if constexpr (!kScoreByRow) s_a[rank] = score;
     if (gidx) gidx[rank] = pos;
   });
   __syncthreads();
@@ -237,14 +257,13 @@ fused_decode_kernel(
   const RowAddr ra = make_row_addr<T, REUSE_LO>(klo, khi, v, PAGED ? (size_t)0 : (size_t)unit, S_cap, d, c);
   AttendAcc<T, 1> acc;
   acc.init();
-  attend_rows<T, 1, kFusedWaves * RPW, true, REUSE_LO>(acc, qr, ra, s_idx, s_a, wave * RPW + rg, 0,
-                                                       k);
+  attend_rows<T, 1, kFusedWaves * RPW, true, REUSE_LO, kScoreByRow>(acc, qr, ra, s_idx, s_a, wave * RPW + rg, 0, k);
   LOKI_STAMP(7);
   attend_publish<T, 1, kFusedWaves>(acc, s_merge);
   if (tid < kD) {
     float mn, ls, os;
     attend_merged<kFusedWaves, 1>(s_merge, 0, tid, mn, ls, os);
-    T::store1(out + (size_t)unit * kD + tid, os / ls);
+    T::store1(out + (size_t)head * kD + tid, os / ls);
   }
   LOKI_STAMP(8);
 }
@@ -256,39 +275,61 @@ extern "C" int loki_debug_read_phase_ts(unsigned long long* host_dst, size_t cou
 #endif
 
 size_t fused_dynamic_lds(const Shape& s) {
-  return (size_t)kFusedThreads * fused_keys_per_thread(s.S) * 4 + (size_t)s.k * 8;
+  const bool score_by_row = fused_keys_per_thread(s.S) > 16 && s.pg.table == nullptr;
+  return fused_region_bytes(s.S) + (size_t)s.k * (score_by_row ? 4 : 8);
 }
 
 bool fused_eligible(const Shape& s) {
   // several new tokens per sequence: a block would read rows appended by other blocks of the launch
   if (s.rg.queries > 1) return false;
-  if (s.pg.table != nullptr && s.pg.pages_per_seq > kFusedMaxS / 256) return false;  // page list in LDS
-  return s.G == 1 && s.S <= kFusedMaxS && s.k <= kFusedMaxK;
+  if (s.pg.table != nullptr && s.pg.pages_per_seq > kFusedMaxPages) return false;  // page list in LDS
+  return s.S <= kFusedMaxS && s.k <= kFusedMaxK;
 }
 
+bool fused_pinnable(const Shape& s) {
+  return fused_eligible(s) && s.G == 1 && s.S <= 8192 && (s.pg.table == nullptr || s.pg.pages_per_seq <= 32);
+}
+
+// One block per query head, or the heads' rows spread over the chip by the split path's two launches?
+// A block's time grows with what its head has to read, the split path's hardly as long as the chip is
+// not full.  Measured at 8 to 1024 heads, S = 512 to 16384, both types, us (one launch / split):
+//   one query head per KV head: 0.36 MB a head (S = 2048, k = 512) 8 heads 13.8 / 15.0; 0.72 MB 32 heads
+//   21.5 / 19.2, 64 21.8 / 22.1; 1.4 MB 64 heads 45.5 / 36.0, 96 48.7 / 47.5, 128 50.8 / 56.8
+//   groups: 0.49 MB 32 heads 16.6 / 16.8; 0.74 MB 64 heads 22.2 / 22.7; 0.98 MB 64 heads 26.9 / 24.0, 128
+//   29.5 / 29.5; 1.5 MB 128 heads 49.2 / 48.1, 256 59.1 / 70.6, 512 88.8 / 115.6
+// With groups every head's block rotates its query from P_h again: 1024 heads of 0.12 MB 29.4 / 25.0, of 0.25 MB
+// 38.8 / 39.3.  Past the length at which two blocks share a CU's LDS a second round of blocks costs more than the
+// split path: S = 16384, k = 2048, groups of 4, 256 heads 71.6 / 76.4, 512 139 / 132.  A group's appended row
+// needs a launch of its own in front (about 4 us): groups of 4, 0.49 MB, 512 heads 38.6 / 42.2, 0.98 MB 256 heads
+// 43.8 / 44.2; groups of 8, 0.49 MB 512 heads 35.5 / 32.2, 0.98 MB 256 heads 38.6 / 37.3, 512 56.7 / 60.3.
 bool fused_preferred(const Shape& s) {
   if (!fused_eligible(s)) return false;
-  const int units = s.B * s.Hkv;
-  // measured on the Llama-2-shaped layer (S = 4096 and 8192): equal at 32 units, the single
-  // launch ahead from 64 units on (25 vs 27 us) and by a third at 128 and more; below that only
-  // when there is so little work per unit that the launch count dominates
-  return units >= 48 || s.S <= 2048;
+  const long long heads = (long long)s.B * s.Hq, cus = device_cus();
+  const double mb = ((double)s.S * s.d + (double)s.k * (2 * kD - s.d)) * s.elem_bytes * 1e-6;
+  if (s.G == 1) return mb <= 0.5 || 2 * heads >= cus || (4 * heads >= cus && mb <= 0.8);
+  if (heads > cus && s.G > 2 && fused_dynamic_lds(s) > 58 * 1024) return false;
+  if (s.ap.k_new != nullptr) {
+    if (s.G == 8) return (heads >= 2 * cus && mb >= 0.9) || (heads >= cus && mb >= 1.2);
+    return (heads >= 2 * cus && mb >= 0.2) || (heads >= cus && mb >= 0.9);
+  }
+  if (heads >= 2 * cus) return mb >= 0.2;
+  return mb <= 0.5 || heads >= cus || (2 * heads >= cus && mb <= 1.15) || (4 * heads >= cus && mb <= 0.75);
 }
 
-template <typename T, int LPR, bool REUSE_LO, int KPT, bool APPEND, bool PAGED>
+template <typename T, int LPR, bool REUSE_LO, int KPT, bool APPEND, bool PAGED, bool GROUPED>
 static hipError_t launch_fused_k(const Shape& s, const void* q, const float* P, void* klo, void* khi,
                                  void* v, void* out, int32_t* out_idx, hipStream_t st) {
   using ST = typename T::store_t;
-  auto kern = fused_decode_kernel<T, LPR, REUSE_LO, KPT, APPEND, PAGED>;
+  auto kern = fused_decode_kernel<T, LPR, REUSE_LO, KPT, APPEND, PAGED, GROUPED>;
   const size_t lds = fused_dynamic_lds(s);
   static std::atomic<unsigned long long> lds_allowed{0};  // per instantiation: devices already set up
   const hipError_t ea = allow_dynamic_lds(reinterpret_cast<const void*>(kern),
                                           (int)(kFusedMaxS * 4 + kFusedMaxK * 8), lds_allowed);
   if (ea != hipSuccess) return ea;
-  hipLaunchKernelGGL(kern, dim3(s.B * s.Hkv), dim3(kFusedThreads), lds, st,
+  hipLaunchKernelGGL(kern, dim3(GROUPED ? (s.B * s.Hkv + 7) / 8 * 8 * s.G : s.B * s.Hkv), dim3(kFusedThreads), lds, st,
                      static_cast<const ST*>(klo), static_cast<const ST*>(khi),
                      static_cast<const ST*>(v), static_cast<const ST*>(q), P, static_cast<ST*>(out),
-                     out_idx, s.Hkv, s.S, s.S_cap, s.d, s.k, s.rg, s.ap, s.pg);
+                     out_idx, s.B, s.Hkv, s.G, s.S, s.S_cap, s.d, s.k, s.rg, s.ap, s.pg);
   return hipGetLastError();
 }
 
@@ -296,12 +337,17 @@ template <typename T, int LPR, bool REUSE_LO, int KPT>
 static hipError_t launch_fused_a(const Shape& s, const void* q, const float* P, void* klo, void* khi,
                                  void* v, void* out, int32_t* out_idx, hipStream_t st) {
   const bool paged = s.pg.table != nullptr;
-  if (s.ap.k_new != nullptr) {
-    if (paged) return launch_fused_k<T, LPR, REUSE_LO, KPT, true, true>(s, q, P, klo, khi, v, out, out_idx, st);
-    return launch_fused_k<T, LPR, REUSE_LO, KPT, true, false>(s, q, P, klo, khi, v, out, out_idx, st);
+  if (s.G > 1) {
+    if (s.ap.k_new != nullptr) return hipErrorInvalidValue;  // (G blocks read the row: it is appended by a launch before)
+    if (paged) return launch_fused_k<T, LPR, REUSE_LO, KPT, false, true, true>(s, q, P, klo, khi, v, out, out_idx, st);
+    return launch_fused_k<T, LPR, REUSE_LO, KPT, false, false, true>(s, q, P, klo, khi, v, out, out_idx, st);
   }
-  if (paged) return launch_fused_k<T, LPR, REUSE_LO, KPT, false, true>(s, q, P, klo, khi, v, out, out_idx, st);
-  return launch_fused_k<T, LPR, REUSE_LO, KPT, false, false>(s, q, P, klo, khi, v, out, out_idx, st);
+  if (s.ap.k_new != nullptr) {
+    if (paged) return launch_fused_k<T, LPR, REUSE_LO, KPT, true, true, false>(s, q, P, klo, khi, v, out, out_idx, st);
+    return launch_fused_k<T, LPR, REUSE_LO, KPT, true, false, false>(s, q, P, klo, khi, v, out, out_idx, st);
+  }
+  if (paged) return launch_fused_k<T, LPR, REUSE_LO, KPT, false, true, false>(s, q, P, klo, khi, v, out, out_idx, st);
+  return launch_fused_k<T, LPR, REUSE_LO, KPT, false, false, false>(s, q, P, klo, khi, v, out, out_idx, st);
 }
 
 template <typename T, int LPR, bool REUSE_LO>
@@ -309,6 +355,8 @@ static hipError_t launch_fused_r(const Shape& s, const void* q, const float* P, 
                                  void* v, void* out, int32_t* out_idx, hipStream_t st) {
   if (fused_keys_per_thread(s.S) <= 8)
     return launch_fused_a<T, LPR, REUSE_LO, 8>(s, q, P, klo, khi, v, out, out_idx, st);
+  if (fused_keys_per_thread(s.S) <= 16)
+    return launch_fused_a<T, LPR, REUSE_LO, 16>(s, q, P, klo, khi, v, out, out_idx, st);
   return launch_fused_a<T, LPR, REUSE_LO, kFusedKPT>(s, q, P, klo, khi, v, out, out_idx, st);
 }
 

@@ -31,11 +31,13 @@ bool fused_gqa_eligible(const Shape& s, int select_mode) {
 
 bool fused_gqa_preferred(const Shape& s, int select_mode) {
   if (!fused_gqa_eligible(s, select_mode)) return false;
-  // one block per unit: worth it from a quarter of the CUs on (three eighths for sequences
-  // beyond 8192 rows); below that the split path's many blocks per unit win (measured at 16 to
-  // 192 units, S = 4096 / 8192 / 16384, 4 and 8 query heads per KV head)
+  // one block per unit: worth it from three eighths of the CUs on (half with 2 query heads per KV head);
+  // below that the split path's many blocks per unit win.  Measured at 8 to 192 units, S = 1024 to
+  // 16384, us (one launch / split): 2 heads, 96 units S = 8192 39.8 / 36.6, 128 units 42.5 / 42.8; 4 heads,
+  // 64 units S = 4096 25.0 / 22.2, 96 units 26.1 / 25.9, 128 units 28.4 / 29.6; 8 heads, 64 units S = 2048
+  // 21.8 / 22.7, S = 4096 26.5 / 25.6, 96 units 27.4 / 29.5
   const long long units = (long long)s.B * s.Hkv, cus = device_cus();
-  return s.S <= 8192 ? 4 * units >= cus : 8 * units >= 3 * cus;
+  return 8 * units >= (s.G == 2 ? 4 : 3) * cus || (s.G == 8 && 4 * units >= cus && s.S <= 3072);
 }
 
 template <int THREADS, int NCH, int G, int KPT, bool PAGED = false>

@@ -62,7 +62,7 @@ hipError_t allow_dynamic_lds(const void* kernel, int bytes, std::atomic<unsigned
 constexpr int kScoreBlocksPerCU = 8;     // score blocks a launch aims at
 constexpr int kScoreRowsPerStep = 256;   // rows one 256-thread block scores per step
 constexpr int kMaxGatherChunk = 2048;    // selected rows one attend block may own (LDS index list)
-constexpr int kFusedMaxS = 8192;         // fused single-kernel path: scores of a unit live in LDS
+constexpr int kFusedMaxS = 16384;        // fused single-kernel path: scores of a unit live in LDS
 constexpr int kFusedMaxK = 2048;
 
 int score_rows_per_block(const Shape& s);
@@ -142,9 +142,11 @@ hipError_t launch_pca_attend(const Shape& s, int nsplit, const float* qhat, cons
                              const void* v, float* partial, void* out, hipStream_t st);
 hipError_t launch_combine(const Shape& s, int nsplit, const float* partial, void* out,
                           hipStream_t st);
-// Fused single-kernel decode step (one query head per KV head only).
-bool fused_eligible(const Shape& s);
+// Fused single-kernel decode step: one block per query head, every head selecting for itself.
+// fused_pinnable: the shapes LOKI_PATH_FUSED takes.  Several query heads per KV head: the appended row
+// (launch_qrot) goes first, and s.ap is empty.
 bool fused_preferred(const Shape& s);
+bool fused_pinnable(const Shape& s);
 hipError_t launch_fused(const Shape& s, const void* q, const float* P, void* klo, void* khi,
                         void* v, void* out, int32_t* out_idx, hipStream_t st);
 // Single-launch step for grouped query heads sharing one selection per KV head (fused_gqa.hip;

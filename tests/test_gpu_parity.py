@@ -601,3 +601,32 @@ def test_selection_inside_the_attention_launch(dtype, G, mode, S, d, k):
     say(f"   batch {check_loki(case, mode, path=api.PATH_SPLIT)}")
     run_step_case(w, mode, False, True, path=api.PATH_SPLIT)
     run_step_case(w, mode, S > 4, True, path=api.PATH_SPLIT, page_rows=256)
+
+
+@pytest.mark.parametrize("dtype,B,G,S,d,k", [
+    ("bf16", 2, 4, 1, 32, 1), ("bf16", 3, 2, 4096, 16, 129), ("bf16", 2, 4, 4097, 8, 600), ("bf16", 1, 8, 8193, 8, 64),
+    ("bf16", 5, 4, 16384, 8, 200), ("f32", 2, 8, 1025, 20, 100), ("f32", 1, 2, 8193, 4, 31), ("bf16", 1, 1, 8193, 8, 300),
+    ("bf16", 3, 1, 16384, 8, 111)])
+def test_one_block_per_head(dtype, B, G, S, d, k):
+    """The library's own choice at little work per head: one block per query head, also with
+    several query heads per KV head and from 8193 to 16384 rows (keys a thread holds: 4 to 32); unit
+    counts that are not a multiple of 8; contiguous, ragged and paged caches, against the oracle and,
+    for the lists, against the split path."""
+    from tests.test_gpu_step import run_step_case
+    w = synth.Workload("per_head", B, G * 2, 2, 128, S, dtype, d, k, seed=900 + S + G)
+    say(f"case {dtype} B {B} G {G} S {S} d {d} k {k}")
+    case = DeviceCase(w, synth.make_inputs(w))
+    say(f"   batch {check_loki(case, 0)}")
+    _, a = case.run_loki(0)
+    _, b = case.run_loki(0, path=api.PATH_SPLIT)
+    assert torch.equal(torch.as_tensor(a), torch.as_tensor(b))
+    for page_rows in (0, 256):
+        run_step_case(w, 0, S > 4, False, page_rows=page_rows)
+
+
+def test_one_block_per_head_appending_group():
+    """512 heads in groups: the appended row goes in by a launch of its own before the heads' blocks."""
+    from tests.test_gpu_step import run_step_case
+    w = synth.Workload("per_head_app", 16, 32, 8, 128, 1100, "bf16", 32, 400, seed=17)
+    for page_rows in (0, 256):
+        run_step_case(w, 0, True, True, page_rows=page_rows)
