@@ -40,15 +40,21 @@ __device__ __forceinline__ void select_share(const SelectAttendArgs& a, int sel,
   int32_t* user = write_user && a.user_idx != nullptr ? a.user_idx + (size_t)sel * a.k_max : nullptr;
   if (user)
     for (int i = k + (int)threadIdx.x; i < a.k_max; i += kSaThreads) user[i] = -1;  // a sequence keeping fewer rows
+  // a paged cache: the pages of the sequence's rows, clamped into the pool
+  __shared__ int32_t s_pages[kSaThreads * KPT / 256];
   const bool paged = a.pg.table != nullptr;
-  const int cache_b = b / max(a.rg.queries, 1);
+  if (paged && (int)threadIdx.x <= (S - 1) >> a.pg.lg_rows) {
+    const int32_t* table = a.pg.table + (size_t)(b / max(a.rg.queries, 1)) * a.pg.pages_per_seq;
+    s_pages[threadIdx.x] = min(max(table[threadIdx.x], 0), a.pg.n_pages - 1);
+  }
   resident_select_clear<kSaThreads>(sm);
   __syncthreads();
   block_select_topk_resident<kSaThreads, KPT>(
       a.scores + (size_t)sel * a.S_max, S, k, a.per_thread, sm, [&](int rank, int pos, float score) {
         if (user) user[rank] = pos;
         if (rank >= r0 && rank < r1) {
-          s_idx[rank - r0] = paged ? (int32_t)cache_row(a.pg, cache_b, hkv, a.Hkv, a.S_cap, pos) : pos;
+          const int lg = a.pg.lg_rows;
+          s_idx[rank - r0] = paged ? ((s_pages[pos >> lg] * a.Hkv + hkv) << lg) | (pos & ((1 << lg) - 1)) : pos;
           if (s_a) s_a[rank - r0] = score;
         }
       });
