@@ -78,12 +78,32 @@ int gather_splits(const Shape& s, int select_mode) {
   return n;
 }
 
-int dense_splits(const Shape& s) {
-  const int units = s.B * s.Hkv;
-  int n = div_up(8 * device_cus(), units);
+// Row splits of dense attention and of Algorithm 2, of at least 256 rows.  As many as make two blocks per
+// CU in bf16 and four in fp32, where that fills nine tenths of those places: a block's set-up and merge,
+// and the parts the combine launch reads, cost more than a smoother last round gains, and a few blocks
+// over a full round cost most.  Against eight per CU, us: 16 sequences of 32/8 heads at S = 16384 191 -> 181
+// (three per CU 183, four 186), 7 of them at S = 12000 73 -> 66 (rounded up to 2.2 per CU: 80), 32/32 heads at
+// S = 4096 188 -> 178, 64/8 heads at S = 8192 105 -> 97; Algorithm 2 121 -> 114, 129 -> 120, 136 -> 125; fp32, 9
+// sequences of 32/16 heads at S = 5790 154 -> 149.  Otherwise eight per CU (10 sequences of 32 heads, S = 4000:
+// 116, unsplit 120), and also where that makes one full round of three small blocks per CU (48 units,
+// S = 4186: 25.2, two larger per CU 26.0).
+// Sequences of unequal length, where the blocks are dealt out by length (dense_runs): three per CU, as many
+// as are resident, for one full round (16 of 32/8 heads, S = 16384: two 133, three 130, four 131).
+int dense_splits(const Shape& s, bool ragged) {
+  const int units = s.B * s.Hkv, cus = device_cus();
   const int max_n = s.S / 256 > 0 ? s.S / 256 : 1;
-  if (n > max_n) n = max_n;
-  return n < 1 ? 1 : n;
+  int many = div_up(8 * cus, units);
+  if (many > max_n) many = max_n;
+  auto full = [&](int n, int per_cu) { return 10LL * units * n >= 9LL * per_cu * cus; };
+  if (ragged && s.dtype == 1 && s.B <= kDenseMaxRagged) {
+    const int n = 3 * cus / units;
+    if (n > 1 && n <= max_n && full(n, 3) && s.S >= kDenseBalanceRows * n) return n;
+  }
+  const int per_cu = s.dtype == 1 ? 2 : 4;
+  const int n = per_cu * cus / units;
+  if (n < 1 || n > max_n || !full(n, per_cu)) return many;
+  if (s.S < 512 * n && full(many, 3) && many * units <= 3 * cus) return many;
+  return n;
 }
 
 Workspace plan_workspace(const Shape& s, int select_mode, int nsplit, void* base, bool with_cluster) {
@@ -269,7 +289,8 @@ int loki_workspace_bytes(const loki_layout* layout, int S, int d, int k, int sel
   if (S < 1 || S > s.S_cap) return LOKI_ERR_INVALID_ARG;
   s.S = S;
   if (select_mode == -1 || select_mode == -2) {  // dense baseline; PCAAttn (rotated queries too)
-    *bytes = plan_workspace(s, select_mode, dense_splits(s), nullptr).total_bytes;
+    const int n = dense_splits(s, false), n_ragged = select_mode == -1 ? dense_splits(s, true) : n;
+    *bytes = plan_workspace(s, select_mode, n > n_ragged ? n : n_ragged, nullptr).total_bytes;
     return LOKI_OK;
   }
   if (select_mode < 0) return LOKI_ERR_INVALID_ARG;
@@ -531,7 +552,7 @@ static int dense_impl(const loki_layout* layout, const void* q, const void* k_fu
   if (reinterpret_cast<uintptr_t>(seq_lens) & 3u) return LOKI_ERR_ALIGNMENT;
   s.S = S;
   s.rg.seq_lens = seq_lens;
-  const int nsplit = dense_splits(s);
+  const int nsplit = dense_splits(s, seq_lens != nullptr);
   const Workspace w = plan_workspace(s, -1, nsplit, workspace);
   if (nsplit > 1) {
     if (!workspace) return LOKI_ERR_INVALID_ARG;
@@ -578,7 +599,7 @@ int loki_pca_attn(const loki_layout* layout, const void* q, const float* P, cons
     return LOKI_ERR_ALIGNMENT;
   if (!aligned256(workspace)) return LOKI_ERR_ALIGNMENT;
   s.S = S;
-  const int nsplit = dense_splits(s);
+  const int nsplit = dense_splits(s, false);
   const Workspace w = plan_workspace(s, -2, nsplit, workspace);
   if (w.total_bytes > workspace_bytes) return LOKI_ERR_WORKSPACE;
   hipStream_t st = static_cast<hipStream_t>(stream);

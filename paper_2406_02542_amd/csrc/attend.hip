@@ -16,8 +16,9 @@ constexpr int kAttThreads = 256;
 constexpr int kAttWaves = kAttThreads / 64;
 
 // LO_ONLY (with GATHER = false): every row, rotated query, logits from the low-rank slab alone
-// (Appendix E, Algorithm 2).
-template <typename T, int NH, bool GATHER, bool REUSE_LO, bool LO_ONLY = false>
+// (Appendix E, Algorithm 2).  BALANCED (dense): the blocks of a KV head are dealt out over its sequences by
+// length (dense_runs).
+template <typename T, int NH, bool GATHER, bool REUSE_LO, bool LO_ONLY = false, bool BALANCED = false>
 __global__ __launch_bounds__(kAttThreads) void attend_kernel(
     const void* __restrict__ k_a,   // GATHER: klo [units, S_cap, d]; dense: K [units, S_cap, 128]
     const void* __restrict__ k_b,   // GATHER: khi [units, S_cap, 128-d]; dense: unused
@@ -60,17 +61,38 @@ __global__ __launch_bounds__(kAttThreads) void attend_kernel(
     by = ((seq * tokens + member / Gq) * Hkv + hkv) * Gq + member % Gq;
     bx = m % nsplit;
   }
+  int run_rows = rows_per_block;
+  size_t part0 = 0, part_stride = 0;  // this block's first partial result, and from one head's to the next's
+  if constexpr (BALANCED) {
+    const int Hkv = Hq / Gq, B = (int)gridDim.y / Hkv;
+    const int X = nsplit * B, id = by * nsplit + bx, x = id % X;
+    int runs, incl;
+    dense_runs(rag, B, S_max, nsplit, runs, incl);
+    const unsigned long long behind = __ballot(incl > x);
+    if (behind == 0ull) return;  // uniform for the block: no run is left for it
+    const int b = __ffsll((long long)behind) - 1;
+    const int n_b = __builtin_amdgcn_readlane(runs, b), base = __builtin_amdgcn_readlane(incl, b) - n_b;
+    by = b * Hkv + id / X;
+    bx = x - base;
+    run_rows = (seq_rows(rag, b, S_max) + n_b - 1) / n_b;
+    part_stride = (size_t)X;
+    part0 = (size_t)(id / X) * Gq * X + x;
+  }
   const int head0 = by * NH;              // first query head, flattened over batch
   const int bidx = head0 / Hq;
   const int kv_unit = bidx * (Hq / Gq) + (head0 % Hq) / Gq;
+  if constexpr (!BALANCED) {
+    part_stride = (size_t)nsplit;
+    part0 = (size_t)head0 * nsplit + bx;
+  }
 
   // list length of this sequence: the rows it keeps (gather: exactly what the select stage
   // computed) or the rows it holds (dense).  A block whose run starts past the end publishes
   // the neutral partial (max -big, sum 0).
   const int n = GATHER ? seq_keep(rag, bidx, n_max, seq_rows(rag, bidx, S_max))
                        : seq_rows(rag, bidx, n_max);
-  const int r0 = bx * rows_per_block;
-  const int r1 = min(n, r0 + rows_per_block);
+  const int r0 = bx * run_rows;
+  const int r1 = min(n, r0 + run_rows);
 
   // a paged cache: the list in LDS holds rows of the pool and the slabs are addressed from their start
   const bool paged = GATHER && pg.table != nullptr;
@@ -119,7 +141,7 @@ __global__ __launch_bounds__(kAttThreads) void attend_kernel(
     if (nsplit == 1) {
       T::store1(static_cast<ST*>(out) + head * kD + col, os / ls);
     } else {
-      float* pr = partial + (head * nsplit + bx) * kPartialStride;
+      float* pr = partial + (part0 + g * part_stride) * kPartialStride;
       const bool shared = tickets != nullptr;  // another block of this launch reads them
       store_shared_f32(pr + col, os, shared);
       if (col == 0) {
@@ -139,13 +161,22 @@ __global__ __launch_bounds__(kAttThreads) void attend_kernel(
 
 // Merges the nsplit partial results of each query head (launches that have no ticket array:
 // the dense baseline and Algorithm 2 of Appendix E).
-template <typename T>
+template <typename T, bool BALANCED>
 __global__ __launch_bounds__(kD) void combine_kernel(const float* __restrict__ partial,
                                                      typename T::store_t* __restrict__ out,
-                                                     int nsplit) {
+                                                     int nsplit, int B, int Hq, int S_max, Ragged rg) {
   const size_t head = blockIdx.x;
   const int col = threadIdx.x;
-  T::store1(out + head * kD + col, combine_splits<false>(partial + head * nsplit * kPartialStride, nsplit, col));
+  size_t first = head * nsplit;
+  int n = nsplit;
+  if constexpr (BALANCED) {
+    int runs, incl;
+    dense_runs(rg, B, S_max, nsplit, runs, incl);
+    const int b = (int)(head / Hq);
+    n = __builtin_amdgcn_readlane(runs, b);
+    first = (head % Hq) * (size_t)nsplit * B + (__builtin_amdgcn_readlane(incl, b) - n);
+  }
+  T::store1(out + head * kD + col, combine_splits<false>(partial + first * kPartialStride, n, col));
 }
 
 // ---- launchers ------------------------------------------------------------------------
@@ -221,9 +252,33 @@ hipError_t launch_gather(const Shape& s, int select_mode, int nsplit, const floa
                                      sel_score, partial, tickets, out, s.Hq, s.G, s.S_cap, s.d, s.k, s.S, s.rg, s.pg, xcd, sets, st);
 }
 
+template <typename T, int NH>
+static hipError_t launch_dense_balanced_nh(const Shape& s, int nsplit, const void* q, const void* k_full, const void* v,
+                                           float* partial, void* out, hipStream_t st) {
+  hipLaunchKernelGGL((attend_kernel<T, NH, false, false, false, true>), dim3(nsplit, s.B * s.Hkv), dim3(kAttThreads), 0, st,
+                     k_full, nullptr, v, q, nullptr, nullptr, partial, nullptr, out, s.Hq, s.G, s.S_cap, kD, s.S,
+                     div_up(s.S, nsplit), nsplit, s.S, s.rg, Paging{}, 0, 0);
+  return hipGetLastError();
+}
+
+template <typename T>
+static hipError_t launch_dense_balanced(const Shape& s, int nsplit, const void* q, const void* k_full, const void* v,
+                                        float* partial, void* out, hipStream_t st) {
+  switch (s.G) {
+    case 1: return launch_dense_balanced_nh<T, 1>(s, nsplit, q, k_full, v, partial, out, st);
+    case 2: return launch_dense_balanced_nh<T, 2>(s, nsplit, q, k_full, v, partial, out, st);
+    case 4: return launch_dense_balanced_nh<T, 4>(s, nsplit, q, k_full, v, partial, out, st);
+    case 8: return launch_dense_balanced_nh<T, 8>(s, nsplit, q, k_full, v, partial, out, st);
+    default: return hipErrorInvalidValue;
+  }
+}
+
 hipError_t launch_dense(const Shape& s, int nsplit, const void* q, const void* k_full,
                         const void* v, float* partial, void* out, hipStream_t st) {
   if (attend_mfma_applies(s, s.G)) return launch_dense_mfma(s, nsplit, q, k_full, v, partial, out, st);
+  if (dense_balanced(s, nsplit))
+    return s.dtype == 0 ? launch_dense_balanced<F32>(s, nsplit, q, k_full, v, partial, out, st)
+                        : launch_dense_balanced<BF16>(s, nsplit, q, k_full, v, partial, out, st);
   const int blocks_y = s.B * s.Hkv;
   const int rpb = div_up(s.S, nsplit);
   if (s.dtype == 0)
@@ -262,15 +317,19 @@ hipError_t launch_pca_attend(const Shape& s, int nsplit, const float* qhat, cons
                       : launch_pca_t<BF16>(s, nsplit, rpb, qhat, klo, v, partial, out, st);
 }
 
+template <typename T>
+static hipError_t launch_combine_t(const Shape& s, int nsplit, const float* partial, void* out, hipStream_t st) {
+  auto* o = static_cast<typename T::store_t*>(out);
+  if (dense_balanced(s, nsplit))
+    hipLaunchKernelGGL((combine_kernel<T, true>), dim3(s.B * s.Hq), dim3(kD), 0, st, partial, o, nsplit, s.B, s.Hq, s.S, s.rg);
+  else
+    hipLaunchKernelGGL((combine_kernel<T, false>), dim3(s.B * s.Hq), dim3(kD), 0, st, partial, o, nsplit, s.B, s.Hq, s.S, s.rg);
+  return hipGetLastError();
+}
+
 hipError_t launch_combine(const Shape& s, int nsplit, const float* partial, void* out,
                           hipStream_t st) {
-  if (s.dtype == 0)
-    hipLaunchKernelGGL(combine_kernel<F32>, dim3(s.B * s.Hq), dim3(kD), 0, st, partial,
-                       static_cast<float*>(out), nsplit);
-  else
-    hipLaunchKernelGGL(combine_kernel<BF16>, dim3(s.B * s.Hq), dim3(kD), 0, st, partial,
-                       static_cast<uint16_t*>(out), nsplit);
-  return hipGetLastError();
+  return s.dtype == 0 ? launch_combine_t<F32>(s, nsplit, partial, out, st) : launch_combine_t<BF16>(s, nsplit, partial, out, st);
 }
 
 }  // namespace loki

@@ -33,7 +33,8 @@ constexpr int kAmWaves = kAmThreads / 64;
 // with row pitch d (Appendix E, Algorithm 2): KSTEPS = ceil(d / 32) of the four 32-column
 // steps of the first product are issued, and columns past d (a partial last step) meet a zero
 // in the B operand, so whatever valid chunk their lanes load does not count.
-template <int NH, bool GATHER, int KSTEPS = 4, bool LO_ONLY = false>
+// BALANCED (dense): the blocks of a KV head are dealt out over its sequences by length (dense_runs).
+template <int NH, bool GATHER, int KSTEPS = 4, bool LO_ONLY = false, bool BALANCED = false>
 __global__ __launch_bounds__(kAmThreads, 2) void attend_mfma_kernel(
     const void* __restrict__ k_a,   // GATHER: klo [units, S_cap, d]; dense: K [units, S_cap, 128]
     const void* __restrict__ k_b,   // GATHER: khi [units, S_cap, 128-d]; dense: unused
@@ -54,22 +55,41 @@ __global__ __launch_bounds__(kAmThreads, 2) void attend_mfma_kernel(
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r16 = lane & 15, kgrp = lane >> 4;
-  const int kv_unit = blockIdx.y;          // one block row per KV unit: its NH heads share the rows
-  const size_t head0 = (size_t)kv_unit * NH;
+  int kv_unit = blockIdx.y, split = blockIdx.x;  // one block row per KV unit: its NH heads share the rows
   const bool head_ok = r16 < NH;
+  int run_rows = rows_per_block;
+  size_t part0 = 0, part_stride = (size_t)nsplit;  // this block's first partial result, and from one head's to the next's
+  if constexpr (BALANCED) {
+    const int B = (int)gridDim.y / Hkv;
+    const int X = nsplit * B, id = kv_unit * nsplit + split, x = id % X;
+    int runs, incl;
+    dense_runs(rg, B, S_max, nsplit, runs, incl);
+    const unsigned long long behind = __ballot(incl > x);
+    if (behind == 0ull) return;  // uniform for the block: no run is left for it
+    const int b = __ffsll((long long)behind) - 1;
+    const int n_b = __builtin_amdgcn_readlane(runs, b), base = __builtin_amdgcn_readlane(incl, b) - n_b;
+    kv_unit = b * Hkv + id / X;
+    split = x - base;
+    run_rows = (seq_rows(rg, b, S_max) + n_b - 1) / n_b;
+    part_stride = (size_t)X;
+    part0 = (size_t)(id / X) * NH * X + x;
+  } else {
+    part0 = (size_t)kv_unit * NH * nsplit + split;
+  }
+  const size_t head0 = (size_t)kv_unit * NH;
 
   // list length of this sequence: the rows it keeps (gather) or holds (dense); a block whose
   // run starts past the end publishes the neutral partial
   const int bidx = kv_unit / Hkv;
   const int n = GATHER ? seq_keep(rg, bidx, n_max, seq_rows(rg, bidx, S_max))
                        : seq_rows(rg, bidx, n_max);
-  const int r0 = blockIdx.x * rows_per_block;
-  const int r1 = min(n, r0 + rows_per_block);
+  const int r0 = split * run_rows;
+  const int r1 = min(n, r0 + run_rows);
 
   // a paged cache: the list in LDS holds rows of the pool and the slabs are addressed from their start
   const bool paged = GATHER && pg.table != nullptr;
   if constexpr (GATHER) {
-    const int32_t* idx = sel_idx + (size_t)blockIdx.y * n_max;
+    const int32_t* idx = sel_idx + (size_t)kv_unit * n_max;
     const int cache_b = bidx / max(rg.queries, 1);
     const int S_b = seq_rows(rg, bidx, S_max);
     for (int i = tid; i < r1 - r0; i += kAmThreads) {
@@ -110,7 +130,7 @@ __global__ __launch_bounds__(kAmThreads, 2) void attend_mfma_kernel(
     if (nsplit == 1) {
       out[head * kD + col] = BF16::round(os / ls);
     } else {
-      float* pr = partial + (head * nsplit + blockIdx.x) * kPartialStride;
+      float* pr = partial + (part0 + g * part_stride) * kPartialStride;
       const bool shared = tickets != nullptr;  // another block of this launch reads them
       store_shared_f32(pr + col, os, shared);
       if (col == 0) {
@@ -188,6 +208,17 @@ bool attend_mfma_applies(const Shape& s, int heads_per_block) {
 hipError_t launch_dense_mfma(const Shape& s, int nsplit, const void* q, const void* k_full,
                              const void* v, float* partial, void* out, hipStream_t st) {
   const int rpb = (s.S + nsplit - 1) / nsplit;
+  if (dense_balanced(s, nsplit)) {
+    const dim3 grid(nsplit, s.B * s.Hkv), block(kAmThreads);
+    uint16_t* o16 = static_cast<uint16_t*>(out);
+    if (s.G == 8)
+      hipLaunchKernelGGL((attend_mfma_kernel<8, false, 4, false, true>), grid, block, 0, st, k_full, nullptr, v, q, nullptr,
+                         partial, nullptr, o16, s.S_cap, kD, s.S, rpb, nsplit, s.Hkv, s.S, s.rg, Paging{});
+    else
+      hipLaunchKernelGGL((attend_mfma_kernel<4, false, 4, false, true>), grid, block, 0, st, k_full, nullptr, v, q, nullptr,
+                         partial, nullptr, o16, s.S_cap, kD, s.S, rpb, nsplit, s.Hkv, s.S, s.rg, Paging{});
+    return hipGetLastError();
+  }
   return launch_attend_mfma_nh<false>(s.G, s.B * s.Hkv, nsplit, rpb, k_full, nullptr, v, q, nullptr,
                                       partial, nullptr, out, s.S_cap, kD, s.S, s.Hkv, s.S, s.rg, Paging{}, st);
 }

@@ -24,23 +24,6 @@ struct SelectSmem {
   uint32_t cnt[2][kWaves][2];
 };
 
-template <int CTRL, int ROW_MASK, bool BOUND_CTRL>
-__device__ __forceinline__ uint32_t dpp_u32(uint32_t x) {
-  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROW_MASK, 0xf, BOUND_CTRL);
-}
-
-// Inclusive prefix sum over the 64 lanes of a wave, all in DPP: a shift-and-add scan inside
-// each row of 16 lanes, then the row totals are carried into the following rows.
-__device__ __forceinline__ uint32_t wave_inclusive_scan_u32(uint32_t x) {
-  x += dpp_u32<0x111, 0xf, true>(x);   // row_shr:1, zero shifted in
-  x += dpp_u32<0x112, 0xf, true>(x);   // row_shr:2
-  x += dpp_u32<0x114, 0xf, true>(x);   // row_shr:4
-  x += dpp_u32<0x118, 0xf, true>(x);   // row_shr:8
-  x += dpp_u32<0x142, 0xa, false>(x);  // row_bcast:15 into rows 1 and 3
-  x += dpp_u32<0x143, 0xc, false>(x);  // row_bcast:31 into rows 2 and 3
-  return x;
-}
-
 // Scanning bins from the highest down, finds the bin holding the rem-th largest key and how
 // many keys are still needed from inside it: sm.out[0] = bin, sm.out[1] = remainder.
 // Thread t owns the BPT consecutive bins ending at nbins-1-BPT*t.  Ends with a barrier.

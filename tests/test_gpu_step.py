@@ -737,3 +737,33 @@ def test_paged_key_rotation_equals_contiguous(dtype):
     assert not torch.all(klo == 5.0)
     unused = torch.from_numpy(np.setdiff1d(np.arange(n_pages), perm)).cuda().long()
     assert torch.all(pklo[unused] == 5.0) and torch.all(pkhi[unused] == 5.0)
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,S,dtype,lens", [
+    (3, 8, 2, 4096, "bf16", (4096, 1, 1030)), (5, 4, 4, 3000, "bf16", (1, 2, 3000, 3, 129)),
+    (2, 8, 1, 16384, "bf16", (16383, 9000)), (4, 4, 2, 2500, "f32", (2500, 2499, 128, 127)),
+    (64, 8, 2, 2048, "bf16", None), (65, 2, 2, 1024, "bf16", None), (7, 32, 32, 2777, "bf16", None)])
+def test_dense_unequal_lengths_dealt_out(B, Hq, Hkv, S, dtype, lens):
+    """Dense attention over sequences of very unequal length: the blocks are dealt out by length (or, with
+    more than 64 sequences or short ones, cut at the longest sequence's run length)."""
+    rng = np.random.default_rng(B * 1000 + S)
+    lens = np.asarray(lens if lens is not None else rng.integers(1, S + 1, size=B), np.int32)
+    lay = api.make_layout(B, Hq, Hkv, 128, 128, S, TORCH_DT[dtype])
+    g = torch.Generator(device="cuda").manual_seed(S)
+    q, k, v = (torch.randn(*sh, generator=g, device="cuda").to(TORCH_DT[dtype])
+               for sh in ((B, Hq, 128), (B, Hkv, S, 128), (B, Hkv, S, 128)))
+    say(f"case B {B} {Hq}/{Hkv} S {S} {dtype} lens {lens.min()}..{lens.max()}")
+    ws = api.alloc_workspace(lay, S, 0, 0, -1)
+    ws.fill_(0xFF)  # nothing in it may be taken as a result that is not one
+    out = torch.empty_like(q)
+    api.dense_decode_step(lay, q, k, v, S, torch.from_numpy(lens).cuda(), ws, out)
+    torch.cuda.synchronize()
+    for b in range(B):
+        kk = k[b, :, :lens[b]].double().repeat_interleave(Hq // Hkv, 0)
+        vv = v[b, :, :lens[b]].double().repeat_interleave(Hq // Hkv, 0)
+        w = torch.softmax((q[b].double()[:, None, :] * kk).sum(-1) / 128 ** 0.5, -1)
+        ref = (w[..., None] * vv).sum(1)
+        err = (out[b].double() - ref).abs()
+        # one rounding to storage and fp32 sums: the bound of tests/parity.py
+        bound = (2.0 ** -8 if dtype == "bf16" else 2.0 ** -23) * ref.abs() + (1e-3 if dtype == "bf16" else 1e-5) * ref.abs().amax(-1, keepdim=True)
+        assert bool((err <= bound).all()), (b, lens[b], float((err / bound).max()))
