@@ -78,6 +78,14 @@ int gather_splits(const Shape& s, int select_mode) {
   return n;
 }
 
+// Eight blocks per CU of at least 256 rows: at least dense_splits at any length up to S, which a workspace is
+// sized for (one sized at the longest length serves all shorter ones).
+static int max_dense_splits(const Shape& s) {
+  const int n = div_up(8 * device_cus(), s.B * s.Hkv);
+  const int max_n = s.S / 256 > 0 ? s.S / 256 : 1;
+  return n > max_n ? max_n : n;
+}
+
 // Row splits of dense attention and of Algorithm 2, of at least 256 rows.  As many as make two blocks per
 // CU in bf16 and four in fp32, where that fills nine tenths of those places: a block's set-up and merge,
 // and the parts the combine launch reads, cost more than a smoother last round gains, and a few blocks
@@ -92,8 +100,7 @@ int gather_splits(const Shape& s, int select_mode) {
 int dense_splits(const Shape& s, bool ragged) {
   const int units = s.B * s.Hkv, cus = device_cus();
   const int max_n = s.S / 256 > 0 ? s.S / 256 : 1;
-  int many = div_up(8 * cus, units);
-  if (many > max_n) many = max_n;
+  const int many = max_dense_splits(s);
   auto full = [&](int n, int per_cu) { return 10LL * units * n >= 9LL * per_cu * cus; };
   if (ragged && s.dtype == 1 && s.B <= kDenseMaxRagged) {
     const int n = 3 * cus / units;
@@ -289,8 +296,7 @@ int loki_workspace_bytes(const loki_layout* layout, int S, int d, int k, int sel
   if (S < 1 || S > s.S_cap) return LOKI_ERR_INVALID_ARG;
   s.S = S;
   if (select_mode == -1 || select_mode == -2) {  // dense baseline; PCAAttn (rotated queries too)
-    const int n = dense_splits(s, false), n_ragged = select_mode == -1 ? dense_splits(s, true) : n;
-    *bytes = plan_workspace(s, select_mode, n > n_ragged ? n : n_ragged, nullptr).total_bytes;
+    *bytes = plan_workspace(s, select_mode, max_dense_splits(s), nullptr).total_bytes;
     return LOKI_OK;
   }
   if (select_mode < 0) return LOKI_ERR_INVALID_ARG;

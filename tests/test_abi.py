@@ -117,3 +117,13 @@ def test_binding_refuses_cpu_tensors():
     t = torch.zeros(128)
     with pytest.raises(ValueError):
         api.dense_decode_attn(lay, t, torch.zeros(64 * 128), torch.zeros(64 * 128), 64, None, t)
+
+
+@pytest.mark.parametrize("mode", [-1, -2])
+def test_dense_workspace_of_the_longest_length_serves_shorter_ones(mode):
+    """A serving loop sizes the dense workspace once, at the cache's length."""
+    for dtype in (torch.bfloat16, torch.float32):
+        for B, Hq, Hkv in ((1, 8, 8), (6, 32, 8), (10, 32, 32), (16, 64, 8), (48, 32, 32)):
+            lay = api.make_layout(B, Hq, Hkv, 128, 128, 16384, dtype)
+            sizes = [api.loki_workspace_bytes(lay, S, 128, 0, mode) for S in (1, 255, 511, 700, 3000, 4186, 8192, 10000, 16384)]
+            assert sizes == sorted(sizes)
