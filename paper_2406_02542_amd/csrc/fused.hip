@@ -302,12 +302,16 @@ bool fused_pinnable(const Shape& s) {
 // split path: S = 16384, k = 2048, groups of 4, 256 heads 71.6 / 76.4, 512 139 / 132.  A group's appended row
 // needs a launch of its own in front (about 4 us): groups of 4, 0.49 MB, 512 heads 38.6 / 42.2, 0.98 MB 256 heads
 // 43.8 / 44.2; groups of 8, 0.49 MB 512 heads 35.5 / 32.2, 0.98 MB 256 heads 38.6 / 37.3, 512 56.7 / 60.3.
+// Eight heads that each stream slab rows of a whole 128-byte line pay for it in L2 once the chip is full several
+// times over: d = 64, S = 8192, k = 1024, 512 heads 66.6 / 71, 1024 heads 125 / 110; 4096 heads, k = 2048
+// 603 / 546, k = 512 377 / 378 (d = 32, k = 1024 383 / 398, d = 16, k = 512 252 / 295).
 bool fused_preferred(const Shape& s) {
   if (!fused_eligible(s)) return false;
   const long long heads = (long long)s.B * s.Hq, cus = device_cus();
   const double mb = ((double)s.S * s.d + (double)s.k * (2 * kD - s.d)) * s.elem_bytes * 1e-6;
   if (s.G == 1) return mb <= 0.5 || 2 * heads >= cus || (4 * heads >= cus && mb <= 0.8);
   if (heads > cus && s.G > 2 && fused_dynamic_lds(s) > 58 * 1024) return false;
+  if (heads > 2 * cus && s.G == 8 && s.d * s.elem_bytes > 64) return false;
   if (s.ap.k_new != nullptr) {
     if (s.G == 8) return (heads >= 2 * cus && mb >= 0.9) || (heads >= cus && mb >= 1.2);
     return (heads >= 2 * cus && mb >= 0.2) || (heads >= cus && mb >= 0.9);
