@@ -453,7 +453,7 @@ static int decode_impl(const loki_layout* layout, const void* q, const float* P,
   const int hist_chunks = w.sel_scratch ? select_hist_chunks(s, select_mode) : 0;
   uint32_t* hist_part = hist_chunks ? w.sel_scratch : nullptr;
   if (hist_chunks) idx = w.sel_idx;
-  if (rotate_score_applies(s) && hist_chunks == 0) {  // (histograms have to be clear before the scoring begins)
+  if (rotate_score_applies(s, select_mode) && hist_chunks == 0) {  // (histograms have to be clear before the scoring begins)
     tm.begin("rotate_score");
     e = launch_rotate_score(s, select_mode, q, P, klo, khi, v, w.scores, w.qhat, reinterpret_cast<uint32_t*>(w.tickets),
                             w.ticket_words, st);

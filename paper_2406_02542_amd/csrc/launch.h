@@ -103,7 +103,7 @@ hipError_t launch_qrot(const Shape& s, const void* q, const float* P, float* qha
 hipError_t launch_score(const Shape& s, int select_mode, const void* klo, float* scores, const float* qhat,
                         uint32_t* hist_part, int hist_chunks, hipStream_t st);
 // launch_qrot and launch_score in one launch (no chunk histograms).
-bool rotate_score_applies(const Shape& s);
+bool rotate_score_applies(const Shape& s, int select_mode);
 hipError_t launch_rotate_score(const Shape& s, int select_mode, const void* q, const float* P, void* klo, void* khi, void* v,
                                float* scores, float* qhat, uint32_t* zero_words, size_t n_zero, hipStream_t st);
 size_t select_scratch_words(int S, int n_sel_heads);

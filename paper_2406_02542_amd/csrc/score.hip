@@ -10,7 +10,8 @@
 //                      appended row.  Against a rotation launch in front of it, us per step: one
 //                      sequence of 32 heads, S = 4096, 20.4 -> 19.4; of 32/8 heads, S = 8192,
 //                      25.0 -> 22.3; 16 of 32/8 heads, S = 12345, per-head selection 118.3 -> 115.0
-//   qrot_kernel first  everything else: with several tokens per sequence a block reads rows that
+//   qrot_kernel first  everything else: with many blocks their own rotations cost more than the launch
+//                      (rotate_score_applies), with several tokens per sequence a block reads rows that
 //                      another one appends, and the histograms of a long sequence's selection
 //                      have to be clear before the scoring begins.  A score block then needs no LDS and no barrier: its
 //                      slice of qhat goes straight to registers while the first slab loads are
@@ -179,12 +180,6 @@ __device__ __forceinline__ bool score_block_rotate(RotSmem<T, G>& sm, float (&s_
   return append;
 }
 
-// Long sequences (hist_part != nullptr): the first counting pass of the selection rides along.
-// The block counts the leading 11 bits of the key of every score it writes in LDS (16-bit
-// counters, two bins per word: a block scores at most kHistChunk rows) and adds the counts into
-// the histogram of the select chunk its rows belong to, hist_part[selecting head][chunk][2048];
-// the host keeps a block inside one chunk.  The dynamic LDS holds kHistWords words per
-// selecting head of the block (none without hist_part).
 // Tickets of the attention stage, cleared by the rotating blocks of a ROT launch.
 __device__ __forceinline__ void zero_tickets(const RotArgs& ra) {
   const size_t nthreads = (size_t)kQrotBlocks * gridDim.y * 256;
@@ -192,6 +187,12 @@ __device__ __forceinline__ void zero_tickets(const RotArgs& ra) {
     ra.zero_words[i] = 0u;
 }
 
+// Long sequences (hist_part != nullptr): the first counting pass of the selection rides along.
+// The block counts the leading 11 bits of the key of every score it writes in LDS (16-bit
+// counters, two bins per word: a block scores at most kHistChunk rows) and adds the counts into
+// the histogram of the select chunk its rows belong to, hist_part[selecting head][chunk][2048];
+// the host keeps a block inside one chunk.  The dynamic LDS holds kHistWords words per
+// selecting head of the block (none without hist_part).
 constexpr int kHistChunk = 16384;  // rows per select chunk (select.hip: kMbChunk)
 constexpr int kHistWords = 1024;
 
@@ -555,8 +556,11 @@ static hipError_t launch_score_r(const Shape& s, const void* klo, float* scores,
   const int rpb = score_rows_per_block(s);
   const int chunks = (s.S + rpb - 1) / rpb, units = s.B * s.Hkv;
   if (rot != nullptr) {
-    hipLaunchKernelGGL((score_kernel<T, LPR, G, GM, true>), dim3(chunks + kQrotBlocks, units), dim3(256), 0, st,
-                       static_cast<const ST*>(klo), qhat, scores, s.Hkv, s.S, s.S_cap, s.d, rpb, s.rg, s.pg, nullptr, 0, *rot);
+    if constexpr (LPR <= 16)  // (rotate_score_applies)
+      hipLaunchKernelGGL((score_kernel<T, LPR, G, GM, true>), dim3(chunks + kQrotBlocks, units), dim3(256), 0, st,
+                         static_cast<const ST*>(klo), qhat, scores, s.Hkv, s.S, s.S_cap, s.d, rpb, s.rg, s.pg, nullptr, 0, *rot);
+    else
+      return hipErrorInvalidValue;
   } else {
     if (s.rg.queries > 1) hist_part = nullptr;  // (several tokens per sequence keep the separate counting pass)
     hipLaunchKernelGGL((score_kernel<T, LPR, G, GM, false>), dim3(chunks, units), dim3(256),
@@ -644,20 +648,35 @@ hipError_t launch_score(const Shape& s, int select_mode, const void* klo, float*
   return launch_score_any(s, select_mode, klo, scores, qhat, hist_part, hist_chunks, nullptr, st);
 }
 
-// One token per sequence, and not so many blocks that their rotations outweigh the launch they save
-// (a paged cache cuts a sequence into blocks of one page): at most 16 per CU, counted once for every 32
-// columns a block rotates.  Measured with / without: 4 sequences x 8 KV heads on 256-row pages, S = 26463,
-// d = 16 (3328 blocks) 111.6 / 114.6 us; 16 units, S = 70873, d = 64 (4432 blocks, twice) 106.1 / 104.1;
-// 96 units, S = 20967, d = 64 (7872, twice) 163.4 / 156.8.
-bool rotate_score_applies(const Shape& s) {
+// Rotation inside the scoring, or a launch in front of it?  It saves that launch, about 3 us, and costs every
+// score block a rotation of its own, of all G heads of the group, and the score kernel the registers
+// that hold a pass's P_h across the first slab loads (matrix cores, waves per SIMD without / with: d = 32 7 / 4,
+// d = 64 6 / 3, d = 128 4 / 2).  So it is taken while all blocks are soon resident: at most 18 per CU, where a
+// unit's four rotating blocks count as eight (each reads a quarter of P_h and stores qhat), and everything
+// counts twice at 64 columns (two passes) and eight times beyond; on the vector units twice again
+// with several heads per KV head, but no more than twice for bf16 rows of over 64 columns, which hold no slab loads in
+// flight.  fp32 rows of over 64 columns spill in this form: never.
+// One launch / two, us per step, both with the same stages behind them (1287 shapes, 8 to 4096 heads, S = 500 to 131072):
+// 32 units, S = 4096, k = 512, d = 32 18.4 / 20.2 (fp32, contiguous), 19.6 / 20.5 (bf16, paged); 4 sequences of 32/8 heads, S =
+// 131072, d = 16 206.9 / 210.0; 512 units, S = 12000, d = 32 271 / 247; 64 sequences of 64/8 heads, S = 8192, d = 64, every
+// head selecting for itself, k = 512 377 / 317, k = 1024 438 / 380, k = 2048 545 / 488 (the scoring alone 209 / 142); of 32/8
+// heads, S = 4096, d = 48, one selection per group 149 / 115; 16 of 32/8, S = 4096, fp32, d = 128 99 / 87.
+bool rotate_score_applies(const Shape& s, int select_mode) {
   if (s.rg.queries > 1) return false;
   const int rpb = score_rows_per_block(s), passes = (s.d + kQrotCols - 1) / kQrotCols;
-  return (long long)((s.S + rpb - 1) / rpb) * s.B * s.Hkv * passes <= 16LL * device_cus();
+  const long long units = (long long)s.B * s.Hkv, blocks = (long long)((s.S + rpb - 1) / rpb) * units;
+  int weight = passes > 2 ? 8 : passes;
+  if (!score_mfma_applies(s, select_mode)) {
+    if (s.d * s.elem_bytes > 256) return false;
+    if (s.dtype == 1 && passes > 2) weight = 2;
+    else if (s.G > 1) weight *= 2;
+  }
+  return (blocks + 8 * units) * weight <= 18LL * device_cus();
 }
 
 hipError_t launch_rotate_score(const Shape& s, int select_mode, const void* q, const float* P, void* klo, void* khi, void* v,
                                float* scores, float* qhat, uint32_t* zero_words, size_t n_zero, hipStream_t st) {
-  if (!rotate_score_applies(s)) return hipErrorInvalidValue;
+  if (!rotate_score_applies(s, select_mode)) return hipErrorInvalidValue;
   const RotArgs ra{q, P, qhat, klo, khi, v, s.ap, zero_words, n_zero};
   return launch_score_any(s, select_mode, klo, scores, qhat, nullptr, 0, &ra, st);
 }
