@@ -471,9 +471,9 @@ static int decode_impl(const loki_layout* layout, const void* q, const float* P,
     tm.end();
     if (e != hipSuccess) return LOKI_ERR_HIP;
   }
-  if (select_attend_applies(s)) {
+  if (select_attend_applies(s, select_mode)) {
     tm.begin("select_attend");
-    e = launch_select_attend(s, select_mode, nsplit, w.scores, out_idx, w.qhat, klo, khi, v, w.partial, w.tickets, out, st);
+    e = launch_select_attend(s, select_mode, w.scores, out_idx, w.qhat, klo, khi, v, w.partial, w.tickets, out, st);
     tm.end();
     return e == hipSuccess ? LOKI_OK : LOKI_ERR_HIP;
   }

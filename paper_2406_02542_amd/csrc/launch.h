@@ -126,8 +126,8 @@ hipError_t launch_gather(const Shape& s, int select_mode, int nsplit, const floa
                          hipStream_t st);
 // Selection and attention in one launch (select_attend.hip; S <= 16384), behind launch_score: user_idx
 // (nullable) receives the caller's lists; tickets as above, always given.
-bool select_attend_applies(const Shape& s);
-hipError_t launch_select_attend(const Shape& s, int select_mode, int nsplit, const float* scores, int32_t* user_idx,
+bool select_attend_applies(const Shape& s, int select_mode);
+hipError_t launch_select_attend(const Shape& s, int select_mode, const float* scores, int32_t* user_idx,
                                 const float* qhat, const void* klo, const void* khi, const void* v, float* partial,
                                 int32_t* tickets, void* out, hipStream_t st);
 hipError_t launch_dense(const Shape& s, int nsplit, const void* q, const void* k_full,

@@ -3,17 +3,44 @@
 // positions (ascending) together with their scores, which the attention stage reuses as the
 // low-rank part of the exact logits.
 //
-// Shorter score rows (S <= 16384) are selected inside the launch that attends over them
-// (select_attend.hip).  Here: several blocks per head (mb_*_kernel below); beyond 64 chunks of
-// 16384, select_stream_kernel — the scores are streamed four times by one block (histogram of the
-// leading 11 bits; collect the keys of the threshold bin into LDS and resolve the exact threshold
-// among them; count; ordered write), each wave owning a contiguous range so that the ordered
-// write needs no barrier.
+//   S <= 16384: select_resident_kernel — every thread keeps its keys in registers
+//               (select_impl.h), one read of the scores.  Launches with few blocks select inside the
+//               attention instead (select_attend.hip).
+//   larger S:   several blocks per head (mb_*_kernel below); beyond 64 chunks of 16384,
+//               select_stream_kernel — the scores are streamed four times by one block
+//               (histogram of the leading 11 bits; collect the keys of the threshold bin into
+//               LDS and resolve the exact threshold among them; count; ordered write), each
+//               wave owning a contiguous range so that the ordered write needs no barrier.
 #include "select_impl.h"
 
 namespace loki {
 
 constexpr int kSelKPT = 16;
+
+// Second launch bound: 8 waves per SIMD, i.e. at most 64 VGPRs, so that two 1024-thread blocks
+// (or four 512-thread blocks) share a CU and overlap each other's barrier and LDS latencies.
+template <int THREADS>
+__global__ __launch_bounds__(THREADS, 8) void select_resident_kernel(const float* __restrict__ scores,
+                                                                  int32_t* __restrict__ sel_idx,
+                                                                  float* __restrict__ sel_score,
+                                                                  int S_max, int k_max, int per_thread,
+                                                                  int heads_per_seq, Ragged rg) {
+  __shared__ ResidentSelectSmem<THREADS> sm;
+  const int b = (int)blockIdx.x / heads_per_seq;
+  const int S = seq_rows(rg, b, S_max), k = seq_keep(rg, b, k_max, S);
+  const float* a = scores + (size_t)blockIdx.x * S_max;
+  int32_t* out = sel_idx + (size_t)blockIdx.x * k_max;
+  float* outs = sel_score + (size_t)blockIdx.x * k_max;
+  for (int i = k + (int)threadIdx.x; i < k_max; i += THREADS) out[i] = -1;  // a sequence keeping fewer rows
+  LOKI_STAMP(0);
+  resident_select_clear<THREADS>(sm);
+  __syncthreads();
+  block_select_topk_resident<THREADS, kSelKPT>(a, S, k, per_thread, sm,
+                                               [&](int rank, int pos, float score) {
+                                                 out[rank] = pos;
+                                                 outs[rank] = score;
+                                               });
+}
 
 constexpr int kStreamThreads = 1024;
 constexpr int kStreamWaves = kStreamThreads / 64;
@@ -798,7 +825,15 @@ hipError_t launch_select(const Shape& s, int n_sel_heads, const float* scores, i
   if (scratch != nullptr && select_scratch_words(s.S, n_sel_heads) != 0)
     return launch_select_multiblock(s, n_sel_heads, scores, sel_idx, sel_score, scratch, st);
   const int hps = n_sel_heads / s.B;  // selecting heads per sequence
-  if (s.S % 4 == 0) {
+  if (s.S <= 512 * kSelKPT) {
+    const int per_thread = (((s.S + 511) / 512) + 3) & ~3;
+    hipLaunchKernelGGL(select_resident_kernel<512>, dim3(n_sel_heads), dim3(512), 0, st, scores,
+                       sel_idx, sel_score, s.S, s.k, per_thread, hps, s.rg);
+  } else if (s.S <= 1024 * kSelKPT) {
+    const int per_thread = (((s.S + 1023) / 1024) + 3) & ~3;
+    hipLaunchKernelGGL(select_resident_kernel<1024>, dim3(n_sel_heads), dim3(1024), 0, st, scores,
+                       sel_idx, sel_score, s.S, s.k, per_thread, hps, s.rg);
+  } else if (s.S % 4 == 0) {
     hipLaunchKernelGGL(select_stream_kernel<true>, dim3(n_sel_heads), dim3(kStreamThreads), 0, st,
                        scores, sel_idx, sel_score, s.S, s.k, hps, s.rg);
   } else {

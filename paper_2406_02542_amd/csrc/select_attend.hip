@@ -1,6 +1,7 @@
 // Top-k selection and exact attention over the selected rows in one launch (Algorithm 1 lines 6-9
 // of arXiv 2406.02542), for score rows short enough to be selected by one block (S <= 16384): the
-// last kernel of the split path, behind the query rotation and the scoring.
+// last kernel of the split path, behind the query rotation and the scoring, where its blocks are not too
+// many (select_attend_applies); else select.hip and attend.hip follow each other.
 //
 // Block (split, head): the block makes the whole selection of its head for itself, from the scores
 // the launch before left in L2, and attends over its share of the list, which never leaves LDS.
@@ -186,7 +187,43 @@ __global__ __launch_bounds__(kSaThreads, 2) void select_attend_mfma_kernel(
 // ---- launchers ------------------------------------------------------------------------------------
 static inline int div_up(int a, int b) { return (a + b - 1) / b; }
 
-bool select_attend_applies(const Shape& s) { return s.S <= kSaThreads * 32; }
+// Row splits: a block per CU, no more (a second one repeats the selection on a CU that is busy with
+// it already: 4 tokens of 2 sequences, 32/8 heads, k = 1329 45.6 -> 30.2 us), each with two trips of its row
+// loop (vector: 256 rows in bf16, 128 in fp32; against half as many, one sequence of 2 KV groups at
+// k = 1341: 26.1 -> 23.6 us), on the matrix cores half a trip (128 rows; against 256, Llama-3 shape at
+// batch 1: 24.3 -> 22.4 us).  Never more than the workspace has partials for (gather_splits).
+static int select_attend_splits(const Shape& s, int select_mode) {
+  const int NH = select_mode == 1 ? s.G : 1;
+  const int min_rows = attend_mfma_applies(s, NH) || s.dtype == 0 ? 128 : 256, nsplit = gather_splits(s, select_mode);
+  int n = device_cus() / (s.B * s.Hq / NH);
+  if (n > s.k / min_rows) n = s.k / min_rows;
+  if (n < div_up(s.k, kMaxGatherChunk)) n = div_up(s.k, kMaxGatherChunk);
+  if (n >= nsplit) return nsplit;
+  return n > 1 ? n : 1;
+}
+
+// One launch, or selection and attention in two?  Every block here selects for itself, on 512 threads, so what
+// counts is how often a CU has to do that.  Both ways timed behind the same scoring on 1239 shapes, us per
+// step, one launch / two:
+//   matrix cores, and eight heads on the vector units (one block per CU fits): one round of blocks and no
+//     more.  128 units of 4 heads, S = 12000, k = 3000 (2 splits: one round) 75.4 / 76.6, 256 units (two rounds) 154 / 141,
+//     512 units 325 / 291; 256 units of 8 heads, fp32, S = 8192, k = 1024 136 / 143, 512 units, S = 4096 203 / 199
+//   vector units, S <= 8192: one split per head always (4096 heads, S = 8192, k = 2048 488 / 529; 512 heads, S = 600 19.7 /
+//     22.8), several in one round, and two of them in any number of rounds (k up to 4096; 1024 heads, k = 2500 353 / 373) but
+//     for several tokens per sequence, whose heads share their rows (768 heads, k = 2139 91 / 84)
+//   vector units, S > 8192, where a thread holds 20 to 32 keys and the selection alone has twice the threads:
+//     one split per head in more than one round (512 heads, S = 16384, k = 2048 227 / 236; 2048 heads 494 / 517); in one
+//     round the two are level (256 heads, S = 9000 43.4 / 44.1; 48 heads, 5 splits 42.8 / 38.0) and with forced
+//     splits every block selects again (4096 heads, S = 16384, k = 4096, 4 tokens 983 / 847; 320 heads, S = 14745, k = 7372
+//     219 / 180).
+bool select_attend_applies(const Shape& s, int select_mode) {
+  if (s.S > kSaThreads * 32) return false;
+  const int NH = select_mode == 1 ? s.G : 1, n = select_attend_splits(s, select_mode);
+  const bool one_round = (long long)n * s.B * s.Hq / NH <= device_cus();
+  if (attend_mfma_applies(s, NH) || NH == 8) return one_round;
+  if (s.S > 8192) return n == 1 && !one_round;
+  return n == 1 || one_round || (n == 2 && s.rg.queries <= 1);
+}
 
 template <typename T, int NH>
 static hipError_t launch_sa(const SelectAttendArgs& a, dim3 grid, const void* klo, const void* khi, const void* v,
@@ -214,22 +251,13 @@ static hipError_t launch_sa_mfma(const SelectAttendArgs& a, dim3 grid, const voi
   return hipGetLastError();
 }
 
-hipError_t launch_select_attend(const Shape& s, int select_mode, int nsplit, const float* scores, int32_t* user_idx,
+hipError_t launch_select_attend(const Shape& s, int select_mode, const float* scores, int32_t* user_idx,
                                 const float* qhat, const void* klo, const void* khi, const void* v, float* partial,
                                 int32_t* tickets, void* out, hipStream_t st) {
-  if (!select_attend_applies(s) || div_up(s.k, nsplit) > kMaxGatherChunk) return hipErrorInvalidValue;
-  const int NH = select_mode == 1 ? s.G : 1;
+  if (!select_attend_applies(s, select_mode)) return hipErrorInvalidValue;
+  const int NH = select_mode == 1 ? s.G : 1, nsplit = select_attend_splits(s, select_mode);
+  if (div_up(s.k, nsplit) > kMaxGatherChunk) return hipErrorInvalidValue;
   const bool mfma = attend_mfma_applies(s, NH);
-  // Row splits: a block per CU, no more (a second one repeats the selection on a CU that is busy with
-  // it already: 4 tokens of 2 sequences, 32/8 heads, k = 1329 45.6 -> 30.2 us), each with two trips of its row
-  // loop (vector: 256 rows in bf16, 128 in fp32; against half as many, one sequence of 2 KV groups at
-  // k = 1341: 26.1 -> 23.6 us), on the matrix cores half a trip (128 rows; against 256, Llama-3 shape at
-  // batch 1: 24.3 -> 22.4 us).  Never more than the workspace has partials for.
-  const int min_rows = mfma || s.dtype == 0 ? 128 : 256;
-  int n = device_cus() / (s.B * s.Hq / NH);
-  if (n > s.k / min_rows) n = s.k / min_rows;
-  if (n < div_up(s.k, kMaxGatherChunk)) n = div_up(s.k, kMaxGatherChunk);
-  if (n < nsplit) nsplit = n > 1 ? n : 1;
   SelectAttendArgs a;
   a.scores = scores;
   a.user_idx = user_idx;

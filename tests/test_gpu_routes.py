@@ -49,3 +49,36 @@ def test_rotation_inside_the_scoring(one_launch, dtype, B, Hq, Hkv, S, d, k, mod
     names = stages(dtype, B, Hq, Hkv, S, d, k, mode | api.PATH_SPLIT)
     assert (names[0] == "rotate_score") == one_launch
     assert one_launch or names[:2] == ["rotate_query", "score"]
+
+
+@pytest.mark.parametrize("one_launch,dtype,B,Hq,Hkv,S,d,k,mode,paged", [
+    (True, "bf16", 1, 32, 8, 2048, 32, 512, 1, False), (True, "bf16", 32, 32, 8, 700, 32, 127, 1, False),   # matrix cores: one round
+    (False, "bf16", 33, 32, 8, 700, 32, 127, 1, False), (False, "bf16", 16, 64, 8, 4500, 32, 4200, 1, False),
+    (True, "f32", 32, 64, 8, 300, 32, 100, 1, False), (False, "f32", 33, 64, 8, 300, 32, 100, 1, False),     # eight fp32 heads
+    (True, "bf16", 64, 64, 8, 300, 32, 100, 0, False), (True, "f32", 64, 32, 8, 300, 16, 100, 1, True),      # vector: one split
+    (True, "bf16", 40, 8, 8, 4096, 32, 2049, 0, True), (False, "bf16", 40, 8, 8, 4500, 16, 4097, 0, False),  # two; three
+    (False, "bf16", 4, 8, 8, 8193, 32, 300, 0, False), (True, "bf16", 33, 8, 8, 8193, 16, 300, 0, True),     # long score rows
+    (False, "bf16", 33, 8, 8, 8193, 16, 2049, 0, False)])
+def test_selection_inside_the_attention(one_launch, dtype, B, Hq, Hkv, S, d, k, mode, paged):
+    names = stages(dtype, B, Hq, Hkv, S, d, k, mode | api.PATH_SPLIT, paged=paged)
+    assert (names[-1] == "select_attend") == one_launch
+    assert one_launch or names[-2:] == ["select", "gather_attend"]
+
+
+@pytest.mark.parametrize("dtype,B,Hkv,G,mode,S,d,k", [
+    ("bf16", 33, 8, 4, 1, 700, 32, 333), ("bf16", 33, 8, 8, 1, 1100, 16, 1100), ("f32", 33, 8, 8, 1, 301, 32, 1),
+    ("bf16", 11, 8, 1, 0, 4500, 8, 4097), ("bf16", 4, 8, 1, 0, 8193, 32, 1), ("f32", 3, 2, 2, 0, 16384, 32, 2500),
+    ("bf16", 3, 2, 4, 0, 9001, 16, 8200)])
+def test_selection_in_a_launch_of_its_own(dtype, B, Hkv, G, mode, S, d, k):
+    """Score rows that one block selects (512 threads up to 8192 rows, 1024 beyond) where a second launch
+    attends: lists and outputs against the oracle on a few units, and ragged with an appended row on pages."""
+    from paper_2406_02542_amd import synth
+    from tests.parity import DeviceCase, check_loki
+    from tests.test_gpu_step import run_step_case
+    w = synth.Workload("sel_own", B, G * Hkv, Hkv, 128, S, dtype, d, k, seed=5 + S)
+    print(f"case {dtype} B {B} {G * Hkv}/{Hkv} mode {mode} S {S} d {d} k {k}", flush=True)
+    assert stages(dtype, B, G * Hkv, Hkv, S, d, k, mode | api.PATH_SPLIT)[-2:] == ["select", "gather_attend"]
+    case = DeviceCase(w, synth.make_inputs(w))
+    print(f"   {check_loki(case, mode, units=[(0, 0), (B // 2, Hkv - 1), (B - 1, 1)], path=api.PATH_SPLIT)}", flush=True)
+    if S > 8192:
+        run_step_case(w.replace(B=2, Hkv=2, Hq=2 * G), mode, True, True, path=api.PATH_SPLIT, page_rows=256)
