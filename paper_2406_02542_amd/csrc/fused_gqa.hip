@@ -29,15 +29,27 @@ bool fused_gqa_eligible(const Shape& s, int select_mode) {
   return s.S <= 16384 && s.k <= kGqaMaxK;
 }
 
+// One block per unit: worth it from a quarter of the CUs on (three eighths beyond 8192 rows); below that the
+// split path's many blocks per unit win.  Up to half the CUs with 2 query heads per KV head, three eighths with 4
+// and five sixteenths with 8 they still win where a row costs a unit much, 140 bytes or more of slab and list
+// (2 (d + (256 - d) k / S)): a block's time grows with that, the split path's selection with the rows alone.  Below 2048 rows,
+// where every kernel is short, that is so with the 64-byte slab rows that it rotates and scores fastest.
+// Measured at 64 to 176 units, S = 1024 to 12000, contiguous, paged, appended, us (one launch / split):
+//   2 heads: 96 units S = 5125, k = 320, d = 32 23.4 / 28.4, 120 units S = 8192, k = 512 27.9 / 33.2, 104 units S = 12000,
+//     k = 750, d = 16 31.7 / 50.5; 64 units S = 4096, k = 512, d = 64 33.1 / 25.8, 120 units k = 1024 39.4 / 35.3, 64
+//     units S = 1024, k = 256, d = 32 18.2 / 15.8, 128 units S = 8192 42.5 / 42.8
+//   4 heads: 64 units S = 8192, k = 1024, d = 16 32.2 / 37.9, 80 units S = 4096, k = 256 20.0 / 25.3; 72 units S = 4096,
+//     k = 1024, d = 64 41.1 / 32.8; 96 units S = 4096 26.1 / 25.9
+//   8 heads: 80 units S = 8192, k = 512, d = 32 29.5 / 35.1, 64 units S = 4096, k = 256, d = 16 21.2 / 28.1, k = 512, d = 64
+//     36.1 / 28.6
 bool fused_gqa_preferred(const Shape& s, int select_mode) {
   if (!fused_gqa_eligible(s, select_mode)) return false;
-  // one block per unit: worth it from three eighths of the CUs on (half with 2 query heads per KV head);
-  // below that the split path's many blocks per unit win.  Measured at 8 to 192 units, S = 1024 to
-  // 16384, us (one launch / split): 2 heads, 96 units S = 8192 39.8 / 36.6, 128 units 42.5 / 42.8; 4 heads,
-  // 64 units S = 4096 25.0 / 22.2, 96 units 26.1 / 25.9, 128 units 28.4 / 29.6; 8 heads, 64 units S = 2048
-  // 21.8 / 22.7, S = 4096 26.5 / 25.6, 96 units 27.4 / 29.5
   const long long units = (long long)s.B * s.Hkv, cus = device_cus();
-  return 8 * units >= (s.G == 2 ? 4 : 3) * cus || (s.G == 8 && 4 * units >= cus && s.S <= 3072);
+  if (s.S > 8192) return 8 * units >= 3 * cus;
+  if (4 * units < cus) return false;
+  if (16 * units >= (s.G == 2 ? 8 : s.G == 4 ? 6 : 5) * cus) return true;
+  if (s.S < 2048) return s.G == 8 || s.d != 32;
+  return 2 * ((long long)s.S * s.d + (long long)s.k * (2 * kD - s.d)) < 140LL * s.S;
 }
 
 template <int THREADS, int NCH, int G, int KPT, bool PAGED = false>

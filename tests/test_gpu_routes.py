@@ -82,3 +82,14 @@ def test_selection_in_a_launch_of_its_own(dtype, B, Hkv, G, mode, S, d, k):
     print(f"   {check_loki(case, mode, units=[(0, 0), (B // 2, Hkv - 1), (B - 1, 1)], path=api.PATH_SPLIT)}", flush=True)
     if S > 8192:
         run_step_case(w.replace(B=2, Hkv=2, Hq=2 * G), mode, True, True, path=api.PATH_SPLIT, page_rows=256)
+
+
+@pytest.mark.parametrize("one_launch,B,Hkv,G,S,d,k,append,paged", [
+    (True, 12, 8, 2, 5125, 32, 320, True, True), (True, 13, 8, 2, 9000, 16, 600, False, True),
+    (True, 8, 8, 4, 4096, 16, 256, False, True), (True, 10, 8, 8, 8192, 32, 512, True, False),
+    (False, 8, 8, 2, 4096, 64, 512, True, False), (False, 9, 8, 4, 4096, 64, 1024, False, False),
+    (False, 8, 8, 8, 4096, 64, 512, False, True), (False, 8, 8, 2, 1024, 32, 256, False, False),
+    (True, 8, 8, 8, 1024, 32, 256, False, False), (True, 16, 8, 2, 2048, 64, 1024, False, False)])
+def test_one_block_per_group(one_launch, B, Hkv, G, S, d, k, append, paged):
+    names = stages("bf16", B, G * Hkv, Hkv, S, d, k, 1, append=append, paged=paged)
+    assert (names == ["fused_decode"]) == one_launch
