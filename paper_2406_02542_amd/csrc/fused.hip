@@ -294,7 +294,11 @@ bool fused_pinnable(const Shape& s) {
 // A block's time grows with what its head has to read, the split path's hardly as long as the chip is
 // not full.  Measured at 8 to 1024 heads, S = 512 to 16384, both types, us (one launch / split):
 //   one query head per KV head: 0.36 MB a head (S = 2048, k = 512) 8 heads 13.8 / 15.0; 0.72 MB 32 heads
-//   21.5 / 19.2, 64 21.8 / 22.1; 1.4 MB 64 heads 45.5 / 36.0, 96 48.7 / 47.5, 128 50.8 / 56.8
+//   21.5 / 19.2, 64 21.8 / 22.1; 1.4 MB 64 heads 45.5 / 36.0, 96 48.7 / 47.5, 128 50.8 / 56.8.  Below half the CUs the
+//   MB at which the two meet grow with the heads and, up to 8192 rows, with S (a long row's selection costs the
+//   split path more than its bytes): 56 heads, S = 8192, k = 512, d = 16 on pages 20.9 / 31.0, 56 fp32, S = 2500, k = 625
+//   22.5 / 17.4, 48 fp32, S = 4096, k = 1024, d = 64 42.7 / 28.1; 112 heads, S = 8192, k = 1024, d = 32 29.2 / 37.2, 96 fp32, S =
+//   8192, k = 512, d = 32 34.5 / 41.5, k = 2048 61.6 / 47.5
 //   groups: 0.49 MB 32 heads 16.6 / 16.8; 0.74 MB 64 heads 22.2 / 22.7; 0.98 MB 64 heads 26.9 / 24.0, 128
 //   29.5 / 29.5; 1.5 MB 128 heads 49.2 / 48.1, 256 59.1 / 70.6, 512 88.8 / 115.6
 // With groups every head's block rotates its query from P_h again: 1024 heads of 0.12 MB 29.4 / 25.0, of 0.25 MB
@@ -309,7 +313,10 @@ bool fused_preferred(const Shape& s) {
   if (!fused_eligible(s)) return false;
   const long long heads = (long long)s.B * s.Hq, cus = device_cus();
   const double mb = ((double)s.S * s.d + (double)s.k * (2 * kD - s.d)) * s.elem_bytes * 1e-6;
-  if (s.G == 1) return mb <= 0.5 || 2 * heads >= cus || (4 * heads >= cus && mb <= 0.8);
+  if (s.G == 1) {
+    const double spare = heads > cus / 8 ? 6.4 * (double)(heads - cus / 8) / (double)cus : 0.0;
+    return 2 * heads >= cus || mb <= 0.5 + spare * (s.S < 8192 ? s.S / 8192.0 : 1.0);
+  }
   if (heads > cus && s.G > 2 && fused_dynamic_lds(s) > 58 * 1024) return false;
   if (heads > 2 * cus && s.G == 8 && s.d * s.elem_bytes > 64) return false;
   if (s.ap.k_new != nullptr) {

@@ -93,3 +93,13 @@ def test_selection_in_a_launch_of_its_own(dtype, B, Hkv, G, mode, S, d, k):
 def test_one_block_per_group(one_launch, B, Hkv, G, S, d, k, append, paged):
     names = stages("bf16", B, G * Hkv, Hkv, S, d, k, 1, append=append, paged=paged)
     assert (names == ["fused_decode"]) == one_launch
+
+
+@pytest.mark.parametrize("one_launch,dtype,B,S,d,k,append,paged", [
+    (True, "bf16", 7, 8192, 16, 512, True, True), (True, "bf16", 14, 8192, 32, 1024, True, False), (True, "f32", 12, 8192, 32, 512, False, True),
+    (True, "bf16", 16, 4096, 32, 1024, False, False), (True, "bf16", 1, 2000, 32, 500, False, False),
+    (False, "bf16", 4, 8192, 32, 2048, False, False), (False, "f32", 7, 2500, 32, 625, True, False),
+    (False, "f32", 6, 4096, 64, 1024, False, True), (False, "f32", 12, 8192, 32, 2048, True, False)])
+def test_one_block_per_head_of_its_own_kv_head(one_launch, dtype, B, S, d, k, append, paged):
+    names = stages(dtype, B, 8, 8, S, d, k, 0, append=append, paged=paged)
+    assert (names == ["fused_decode"]) == one_launch
