@@ -306,9 +306,18 @@ bool fused_pinnable(const Shape& s) {
 // split path: S = 16384, k = 2048, groups of 4, 256 heads 71.6 / 76.4, 512 139 / 132.  A group's appended row
 // needs a launch of its own in front (about 4 us): groups of 4, 0.49 MB, 512 heads 38.6 / 42.2, 0.98 MB 256 heads
 // 43.8 / 44.2; groups of 8, 0.49 MB 512 heads 35.5 / 32.2, 0.98 MB 256 heads 38.6 / 37.3, 512 56.7 / 60.3.
-// Eight heads that each stream slab rows of a whole 128-byte line pay for it in L2 once the chip is full several
-// times over: d = 64, S = 8192, k = 1024, 512 heads 66.6 / 71, 1024 heads 125 / 110; 4096 heads, k = 2048
-// 603 / 546, k = 512 377 / 378 (d = 32, k = 1024 383 / 398, d = 16, k = 512 252 / 295).
+// The G heads of a unit each stream the slab, which the scoring of the split path reads once, and pay for it in L2
+// once the chip is full several times over, the more the wider the rows.  Every figure one launch / split as it is now /
+// as the step was in four launches, a rotation of its own, selection and attention apart:
+//   rows of over 256 bytes (fp32, d > 64; the kernel spills too), more heads than CUs: groups of 4, S = 4096, k = 512, d =
+//     128, 512 heads 206 / 87 / 95, 2048 heads 763 / 315 / 325; groups of 2, d = 96, S = 1740, 2560 heads 512 / 298 / 325
+//   groups of 8, rows of over 64 bytes, more than two heads per CU: S = 8192, d = 64, 4096 heads k = 512 391 / 317 / 328, k =
+//     1024 469 / 380 / 407, k = 2048 605 / 488 / 528; 1024 heads k = 512 100 / 85 / 87, 512 heads k = 1024 66.6 / 71 / 71;
+//     64-byte rows stay: k = 512 300 / 296 / 306, k = 2048 521 / 487 / 539, d = 16, k = 512 252 / 295 / 295
+//   groups of 4, rows of over 192 bytes, more than two heads per CU: S = 4096, k = 512, d = 128, 1024 heads 106 / 99 / 101, 2048
+//     heads 202 / 178 / 190; rows of over 64 bytes, more than six: S = 4096, k = 256, d = 64, 2048 heads 117 / 103 / 105
+// Many heads of little work pay more for their own rotations: from six per CU on 0.3 MB a head and not 0.2 (2048
+// heads, groups of 4, S = 1000, d = 64, 0.22 MB 64.6 / 56.1 / 62.3; 4032, groups of 8, S = 2383, 0.22 MB 146 / 129 / 131).
 bool fused_preferred(const Shape& s) {
   if (!fused_eligible(s)) return false;
   const long long heads = (long long)s.B * s.Hq, cus = device_cus();
@@ -318,12 +327,16 @@ bool fused_preferred(const Shape& s) {
     return 2 * heads >= cus || mb <= 0.5 + spare * (s.S < 8192 ? s.S / 8192.0 : 1.0);
   }
   if (heads > cus && s.G > 2 && fused_dynamic_lds(s) > 58 * 1024) return false;
-  if (heads > 2 * cus && s.G == 8 && s.d * s.elem_bytes > 64) return false;
+  const int row_bytes = s.d * s.elem_bytes;
+  if (heads > cus && row_bytes > 256) return false;
+  if (heads > 2 * cus && (s.G == 8 ? row_bytes > 64 : s.G == 4 && row_bytes > 192)) return false;
+  if (heads > 6 * cus && s.G == 4 && row_bytes > 64) return false;
+  const double least = heads > 6 * cus ? 0.3 : 0.2;
   if (s.ap.k_new != nullptr) {
     if (s.G == 8) return (heads >= 2 * cus && mb >= 0.9) || (heads >= cus && mb >= 1.2);
-    return (heads >= 2 * cus && mb >= 0.2) || (heads >= cus && mb >= 0.9);
+    return (heads >= 2 * cus && mb >= least) || (heads >= cus && mb >= 0.9);
   }
-  if (heads >= 2 * cus) return mb >= 0.2;
+  if (heads >= 2 * cus) return mb >= least;
   return mb <= 0.5 || heads >= cus || (2 * heads >= cus && mb <= 1.15) || (4 * heads >= cus && mb <= 0.75);
 }
 

@@ -103,3 +103,13 @@ def test_one_block_per_group(one_launch, B, Hkv, G, S, d, k, append, paged):
 def test_one_block_per_head_of_its_own_kv_head(one_launch, dtype, B, S, d, k, append, paged):
     names = stages(dtype, B, 8, 8, S, d, k, 0, append=append, paged=paged)
     assert (names == ["fused_decode"]) == one_launch
+
+
+@pytest.mark.parametrize("one_launch,dtype,B,G,S,d,k,append", [
+    (True, "bf16", 16, 4, 1100, 32, 400, False), (True, "f32", 4, 4, 1000, 128, 250, False), (False, "f32", 16, 4, 1000, 128, 250, False),
+    (False, "f32", 33, 2, 1000, 96, 250, False), (False, "bf16", 64, 4, 1000, 128, 250, False), (True, "bf16", 64, 2, 1000, 128, 250, False),
+    (True, "bf16", 32, 4, 1500, 64, 375, False), (False, "bf16", 50, 4, 1500, 64, 375, False), (False, "bf16", 16, 8, 1500, 64, 375, False),
+    (True, "bf16", 16, 8, 1500, 32, 375, False), (False, "bf16", 32, 8, 1200, 32, 400, False), (False, "bf16", 64, 4, 1000, 64, 250, True)])
+def test_one_block_per_head_of_a_group(one_launch, dtype, B, G, S, d, k, append):
+    names = stages(dtype, B, 8 * G, 8, S, d, k, 0, append=append)
+    assert (names == (["append", "fused_decode"] if append else ["fused_decode"])) == one_launch
