@@ -6,6 +6,7 @@
 #include <type_traits>
 
 #include "attend_impl.h"
+#include "block_order.h"
 #include "score_impl.h"
 #include "select_impl.h"
 
@@ -29,7 +30,7 @@ __host__ __device__ inline int fused_keys_per_thread(int S) {
 
 // Two blocks share a CU (4 waves per SIMD): the register budget is 128 VGPRs and the compiler
 // is told not to trade load-level parallelism for a higher occupancy that cannot happen.
-// KPT = keys a thread holds in the select stage (8 for S <= 4096, else 16).
+// KPT = keys a thread holds in the select stage (8 for S <= 4096, 16 for S <= 8192, else 32).
 // Which (sequence, head) unit a block works on.  Uniform batches: unit = block.  Ragged batches
 // (up to 64 sequences): the sequences are ranked by length and handed out so that the two
 // blocks that share a CU (block i and block i + half the grid, when the whole grid is resident)
@@ -45,8 +46,7 @@ __device__ __forceinline__ int fused_unit_of_block(const Ragged& rag, int B, int
     const int other = rag.seq_lens[j];
     rank += (other > mine || (other == mine && j < lane)) ? 1 : 0;
   }
-  const int pos = block / Hkv, half = (B + 1) / 2;
-  const int want = pos < half ? pos : B - 1 - (pos - half);
+  const int want = paired_rank(block / Hkv, B);
   const unsigned long long hit = __ballot(lane < B && rank == want);
   if (hit == 0ull) return block;              // cannot happen: the ranks are a permutation of 0..B-1
   const int b = __ffsll((long long)hit) - 1;  // exactly one lane holds each rank
@@ -100,10 +100,10 @@ fused_decode_kernel(
   } else {
     // The G heads of a unit read the same slab and largely the same rows: blocks go to the 8 XCDs in
     // turn, so a unit's heads are blocks 8 apart, on one XCD and next to each other in time.
-    const int j = (int)blockIdx.x >> 3;
-    unit = fused_unit_of_block(rag, n_seq, Hkv, (j / G) * 8 + ((int)blockIdx.x & 7));
-    if (unit >= n_seq * Hkv) return;  // (padding of the launch; uniform for the block)
-    head = unit * G + j % G;
+    const int slot = grouped_slot((int)blockIdx.x, G, n_seq * Hkv);
+    if (slot < 0) return;  // (padding of the launch; uniform for the block)
+    unit = fused_unit_of_block(rag, n_seq, Hkv, slot);
+    head = unit * G + grouped_head((int)blockIdx.x, G);
   }
   const int h = unit % Hkv;
   const int S = seq_rows(rag, unit / Hkv, S_max);
