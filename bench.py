@@ -143,8 +143,32 @@ def kernel_times(api, step_fn, steps):
     return {n: float(np.mean(acc[n])) * 1e3 for n in order}
 
 
+# what an entry of bench_configs leaves in the printed line, a row each (stderr has the kernels' times, --configs-out all)
+CONFIG_COLUMNS = ("workload", "B", "Hq", "Hkv", "S", "d", "k", "select_mode", "us_per_step", "us_p10", "us_p90",
+                  "dense_us_per_step", "frac_of_peak", "step_with_append_us")
+
+
+def compact(x, digits=5):
+    """x with its floating-point numbers cut to `digits` significant digits: a line of some kilobytes is
+    kept whole by what records the output, the 25 KB of every number in full were cut in the middle."""
+    if isinstance(x, dict):
+        return {k: compact(v, digits) for k, v in x.items()}
+    if isinstance(x, (list, tuple)):
+        return [compact(v, digits) for v in x]
+    return float(f"{x:.{digits}g}") if isinstance(x, float) else x
+
+
+def result_line(result, entries):
+    """The one printed line: `result`, its measured value in full, and `entries` (or None) as rows."""
+    line = compact(result)
+    line.update({k: result[k] for k in ("value", "ms_per_step")})
+    line["configs"] = None if entries is None else {
+        "columns": list(CONFIG_COLUMNS), "rows": [compact([e.get(c) for c in CONFIG_COLUMNS], 4) for e in entries]}
+    return json.dumps(line)
+
+
 def bench_configs(args, torch, api, synth):
-    """The `configs` array: every other workload of the benchmark list, both select modes where
+    """The `configs` entries: every other workload of the benchmark list, both select modes where
     query heads are grouped, the nine (d, k) points of the large-model sweep, and the benchmark
     workload at batch 1 and 2.  Inputs come
     from the same seeded generator as the parity tests; a workload's cache is generated once and
@@ -284,7 +308,8 @@ def main():
                          "the large-model sweep) in the `configs` array of the JSON line; default: "
                          "all when --workload is the benchmark workload, none otherwise")
     ap.add_argument("--config-steps", type=int, default=200,
-                    help="event-timed steps per entry of the `configs` array")
+                    help="event-timed steps per entry of `configs`")
+    ap.add_argument("--configs-out", help="file that receives the `configs` entries with all their numbers (JSON)")
     ap.add_argument("--calibrate-copy", action="store_true",
                     help="also run a plain 1 GiB device copy 5 times (reference point for "
                          "rocprofv3 FETCH_SIZE / WRITE_SIZE counters)")
@@ -714,10 +739,13 @@ def main():
         # free the benchmark workload's tensors first: the other workloads hold up to 2 GiB caches
         del caches, x
         torch.cuda.empty_cache()
-        result["configs"] = bench_configs(args, torch, api, synth)
+        entries = bench_configs(args, torch, api, synth)
+        if args.configs_out:
+            with open(args.configs_out, "w") as f:
+                json.dump(entries, f)
     else:
-        result["configs"] = None
-    print(json.dumps(result), flush=True)
+        entries = None
+    print(result_line(result, entries), flush=True)
 
 
 if __name__ == "__main__":
