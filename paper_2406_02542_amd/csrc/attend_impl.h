@@ -145,18 +145,20 @@ __device__ __forceinline__ void attend_rows(AttendAcc<T, NH>& acc, const float (
 // the others with a last round that is half empty: 16 sequences of 32/8 heads,
 // S = 16384, 144 us with two blocks per CU, 134 dealt out.)  Every wave works it out for itself, lane b
 // for sequence b; the parts of the result lie at [query head][base_b + run].
-// Up to 64 sequences, and only where a block has at least 512 rows of the longest: working it out takes
-// about 1 us, which shorter blocks do not win back (16 units, S = 3000: 14.1 -> 15.0 us).
 constexpr int kDenseMinRun = 128;
-inline bool dense_balanced(const Shape& s, int nsplit) {  // (a kernel variant of its own)
-  return s.rg.seq_lens != nullptr && nsplit > 1 && s.B <= kDenseMaxRagged && s.S >= kDenseBalanceRows * nsplit;
-}
 // This lane's sequence: its runs, and the runs of it and the sequences before it.
 __device__ __forceinline__ void dense_runs(const Ragged& rg, int B, int S_max, int nsplit, int& runs, int& incl) {
   const int lane = threadIdx.x & 63;
   const int len = lane < B ? seq_rows(rg, lane, S_max) : 0;
   const int total = __builtin_amdgcn_readlane((int)wave_inclusive_scan_u32((uint32_t)len), 63);
   const int X = nsplit * B;
+  // equal lengths: nothing to deal out (440 units of 8 heads, S = 3440, eight blocks per CU: 161 us with the search below)
+  const int first = __builtin_amdgcn_readlane(len, 0);
+  if (first >= nsplit * kDenseMinRun && __ballot(lane < B && len != first) == 0ull) {
+    runs = lane < B ? nsplit : 0;
+    incl = nsplit * min(lane + 1, B);
+    return;
+  }
   // R lies between total / X and total / (X - B); each lane tries one length of that range
   const int lo = max((total + X - 1) / X, kDenseMinRun), hi = max((total + X - B - 1) / (X - B), lo);
   const float inv = 1.0f / (float)(lo + ((hi - lo) * lane + 62) / 63);

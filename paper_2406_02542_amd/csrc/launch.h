@@ -67,11 +67,11 @@ constexpr int kFusedMaxK = 2048;
 
 int score_rows_per_block(const Shape& s);
 int gather_splits(const Shape& s, int select_mode);
-int dense_splits(const Shape& s, bool ragged);  // ragged: with per-sequence lengths
-// dense attention over sequences of unequal length deals its blocks out by length (attend_impl.h) up to
-// this many sequences and from this many rows of the longest per split on
+// dense attention: ragged: with per-sequence lengths, whose blocks may be dealt out by length
+// (dense_balanced, attend_impl.h) up to kDenseMaxRagged sequences
 constexpr int kDenseMaxRagged = 64;
-constexpr int kDenseBalanceRows = 512;
+int dense_splits(const Shape& s, bool ragged);
+bool dense_balanced(const Shape& s, int nsplit);
 
 struct Workspace {
   float* qhat;       // [B*Hq, 128]

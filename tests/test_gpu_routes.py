@@ -113,3 +113,34 @@ def test_one_block_per_head_of_its_own_kv_head(one_launch, dtype, B, S, d, k, ap
 def test_one_block_per_head_of_a_group(one_launch, dtype, B, G, S, d, k, append):
     names = stages(dtype, B, 8 * G, 8, S, d, k, 0, append=append)
     assert (names == (["append", "fused_decode"] if append else ["fused_decode"])) == one_launch
+
+
+@pytest.mark.parametrize("split,dtype,B,Hq,Hkv,S,ragged", [
+    (True, "f32", 25, 40, 40, 600, True), (False, "f32", 25, 40, 40, 600, False),   # few long blocks end with the longest sequence
+    (False, "bf16", 60, 8, 8, 1000, False), (True, "bf16", 60, 8, 8, 1000, True)])
+def test_dense_sequences_of_unequal_length_are_cut(split, dtype, B, Hq, Hkv, S, ragged):
+    dt = DT[dtype]
+    lay = api.make_layout(B, Hq, Hkv, 128, 128, S, dt)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    q, k, v = (torch.randn(sh, generator=g, device="cuda").to(dt) for sh in ((B, Hq, 128), (B, Hkv, S, 128), (B, Hkv, S, 128)))
+    lens = torch.randint(1, S // 4, (B,), generator=torch.Generator().manual_seed(4), dtype=torch.int32)
+    lens[B // 2] = S
+    ws, out = api.alloc_workspace(lay, S, 0, 0, -1), torch.empty_like(q)
+    prof = api.Profile()
+    prof.attach()
+    try:
+        api.dense_decode_step(lay, q, k, v, S, lens.cuda() if ragged else None, ws, out)
+    finally:
+        prof.detach()
+    torch.cuda.synchronize()
+    names = [n for n, _ in prof.read()]
+    print(dtype, B, Hq, Hkv, S, ragged, names, flush=True)
+    assert names == (["dense_attend", "combine"] if split else ["dense_attend"])
+    for b in (0, B // 2):
+        n = int(lens[b]) if ragged else S
+        kk, vv = (t[b, :, :n].double().repeat_interleave(Hq // Hkv, 0) for t in (k, v))
+        w = torch.softmax((q[b].double()[:, None] * kk).sum(-1) / 128 ** 0.5, -1)
+        ref = (w[..., None] * vv).sum(1)
+        # one rounding to storage and fp32 sums: the bound of tests/parity.py
+        bound = (2.0 ** -8 if dtype == "bf16" else 2.0 ** -23) * ref.abs() + (1e-3 if dtype == "bf16" else 1e-5) * ref.abs().amax(-1, keepdim=True)
+        assert bool(((out[b].double() - ref).abs() <= bound).all()), b
