@@ -144,3 +144,26 @@ def test_dense_sequences_of_unequal_length_are_cut(split, dtype, B, Hq, Hkv, S, 
         # one rounding to storage and fp32 sums: the bound of tests/parity.py
         bound = (2.0 ** -8 if dtype == "bf16" else 2.0 ** -23) * ref.abs() + (1e-3 if dtype == "bf16" else 1e-5) * ref.abs().amax(-1, keepdim=True)
         assert bool(((out[b].double() - ref).abs() <= bound).all()), b
+
+
+@pytest.mark.parametrize("dtype,B,G,S,n", [("bf16", 24, 4, 4096, 4096), ("bf16", 24, 4, 4096, 3001), ("bf16", 24, 4, 4096, 300),
+                                           ("f32", 16, 2, 3000, 3000), ("bf16", 64, 1, 2048, 2047)])
+def test_dense_sequences_of_equal_length_given_as_lengths(dtype, B, G, S, n):
+    """Blocks dealt out by length where there is nothing to deal out, and where the runs would be too short."""
+    dt, Hkv = DT[dtype], 8
+    lay = api.make_layout(B, G * Hkv, Hkv, 128, 128, S, dt)
+    g = torch.Generator(device="cuda").manual_seed(n)
+    q, k, v = (torch.randn(sh, generator=g, device="cuda").to(dt) for sh in ((B, G * Hkv, 128), (B, Hkv, S, 128), (B, Hkv, S, 128)))
+    k[:, :, n:], v[:, :, n:] = 30.0, 1e4  # any use of them would show
+    ws, out = api.alloc_workspace(lay, S, 0, 0, -1), torch.empty_like(q)
+    ws.fill_(0xFF)
+    api.dense_decode_step(lay, q, k, v, S, torch.full((B,), n, dtype=torch.int32, device="cuda"), ws, out)
+    torch.cuda.synchronize()
+    print(dtype, B, G, S, n, flush=True)
+    for b in (0, 1, B - 1):
+        kk, vv = (t[b, :, :n].double().repeat_interleave(G, 0) for t in (k, v))
+        w = torch.softmax((q[b].double()[:, None] * kk).sum(-1) / 128 ** 0.5, -1)
+        ref = (w[..., None] * vv).sum(1)
+        # one rounding to storage and fp32 sums: the bound of tests/parity.py
+        bound = (2.0 ** -8 if dtype == "bf16" else 2.0 ** -23) * ref.abs() + (1e-3 if dtype == "bf16" else 1e-5) * ref.abs().amax(-1, keepdim=True)
+        assert bool(((out[b].double() - ref).abs() <= bound).all()), b
