@@ -307,7 +307,9 @@ int loki_pca_attn(const loki_layout* layout, const void* q, const float* P, cons
  *   eigenvalues [Hkv, D] fp32 out, decreasing
  *   workspace   >= loki_pca_workspace_bytes(layout, n_rows), 256-B aligned
  * Covariance: matrix cores with fp32 accumulation per run of rows, runs added in fp64;
- * eigensolver: cyclic Jacobi in fp64.  2 <= n_rows.
+ * eigensolver, fp64: Householder tridiagonal form, eigenvalues by multisection on Sturm counts, vectors by the
+ * twisted factorisation; cyclic Jacobi for a head whose vectors come out far from orthonormal (equal
+ * eigenvalues).  2 <= n_rows.
  */
 int loki_pca_workspace_bytes(const loki_layout* layout, long long n_rows, size_t* bytes);
 int loki_pca_fit(const loki_layout* layout, const void* keys, long long n_rows, float* P,

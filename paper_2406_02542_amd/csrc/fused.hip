@@ -28,9 +28,6 @@ __host__ __device__ inline int fused_keys_per_thread(int S) {
   return (c + 3) & ~3;
 }
 
-// Two blocks share a CU (4 waves per SIMD): the register budget is 128 VGPRs and the compiler
-// is told not to trade load-level parallelism for a higher occupancy that cannot happen.
-// KPT = keys a thread holds in the select stage (8 for S <= 4096, 16 for S <= 8192, else 32).
 // Which (sequence, head) unit a block works on.  Uniform batches: unit = block.  Ragged batches
 // (up to 64 sequences): the sequences are ranked by length and handed out so that the two
 // blocks that share a CU (block i and block i + half the grid, when the whole grid is resident)
@@ -60,6 +57,11 @@ __device__ __forceinline__ int fused_unit_of_block(const Ragged& rag, int B, int
 constexpr int kFusedMaxPages = kFusedMaxS / 256;  // pages are at least 256 rows
 
 // PAGED: the three slabs are pools addressed through the sequence's page list (see Paging).
+// Two blocks share a CU (4 waves per SIMD) as far as LDS allows: the register budget is 128 VGPRs and the compiler
+// is told not to trade load-level parallelism for a higher occupancy that cannot happen.  LDS allows it while the
+// dynamic part, 4 (S + k) bytes (4 S + 8 k up to 8192 rows or on a paged cache), leaves room for 22 KB of static arrays in
+// half of 160 KB: S = 12345, k = 1543 fits, S = 16384 does not, and a block has its CU to itself at the same budget.
+// KPT = keys a thread holds in the select stage (8 for S <= 4096, 16 for S <= 8192, else 32).
 // GROUPED: G query heads to a KV head, every one selecting for itself.
 template <typename T, int LPR, bool REUSE_LO, int KPT, bool APPEND, bool PAGED, bool GROUPED>
 __global__ __launch_bounds__(kFusedThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) void
@@ -74,8 +76,8 @@ fused_decode_kernel(
   constexpr int RPW = 64 / LPRV;
 
   // The rotation's partial sums and then the scores, the index list, and the scores of its entries;
-  // long sequences (KPT = 32) leave those out, so that two blocks still share a CU's LDS, and look a
-  // row's score up by its position (a paged cache's entries are pool rows and need the copy).
+  // long sequences (KPT = 32) leave those out, so that two blocks share a CU's LDS up to S + k = 14800,
+  // and look a row's score up by its position (a paged cache's entries are pool rows and need the copy).
   constexpr bool kScoreByRow = KPT > 16 && !PAGED;
   extern __shared__ __align__(16) unsigned char dyn_smem[];
   const int per_thread = fused_keys_per_thread(S_max);           // multiple of 4, <= KPT
