@@ -30,16 +30,18 @@ bool fused_gqa_eligible(const Shape& s, int select_mode) {
 }
 
 // One block per unit: worth it from a quarter of the CUs on (three eighths beyond 8192 rows); below that the
-// split path's many blocks per unit win.  Up to half the CUs with 2 query heads per KV head, three eighths with 4
-// and five sixteenths with 8 they still win where a row costs a unit much, 140 bytes or more of slab and list
-// (2 (d + (256 - d) k / S)): a block's time grows with that, the split path's selection with the rows alone.  Below 2048 rows,
-// where every kernel is short, that is so with the 64-byte slab rows that it rotates and scores fastest.
-// Measured at 64 to 176 units, S = 1024 to 12000, contiguous, paged, appended, us (one launch / split):
+// split path's many blocks per unit win.  From half the CUs on with 2 query heads per KV head, three eighths with 4
+// and five sixteenths with 8 it is so whatever a row costs.  Below that line a block's time grows with the bytes
+// of slab and list a row costs its unit, 2 (d + (256 - d) k / S), the split path's selection with the rows alone: it is
+// so under 150 bytes at the line, less in proportion with fewer units, and never from 140 bytes on.  Below 2048 rows,
+// where every kernel is short, all but the 64-byte slab rows that the split path rotates and scores fastest.
+// Measured at 64 to 176 units, S = 1024 to 12000, contiguous, paged, appended, ragged, us (one launch / split):
 //   2 heads: 96 units S = 5125, k = 320, d = 32 23.4 / 28.4, 120 units S = 8192, k = 512 27.9 / 33.2, 104 units S = 12000,
-//     k = 750, d = 16 31.7 / 50.5; 64 units S = 4096, k = 512, d = 64 33.1 / 25.8, 120 units k = 1024 39.4 / 35.3, 64
-//     units S = 1024, k = 256, d = 32 18.2 / 15.8, 128 units S = 8192 42.5 / 42.8
-//   4 heads: 64 units S = 8192, k = 1024, d = 16 32.2 / 37.9, 80 units S = 4096, k = 256 20.0 / 25.3; 72 units S = 4096,
-//     k = 1024, d = 64 41.1 / 32.8; 96 units S = 4096 26.1 / 25.9
+//     k = 750, d = 16 31.7 / 50.5, 80 units S = 4096, k = 512, d = 16 22.4 / 25.3; 64 units S = 4096, k = 512, d = 32, ragged
+//     23.0 / 19.1, S = 3000, k = 375 21.0 / 17.9, 80 units S = 8192, k = 1024, ragged 32.8 / 27.9; 64 units S = 4096, k = 512, d = 64
+//     33.1 / 25.8, 120 units k = 1024 39.4 / 35.3, 64 units S = 1024, k = 256, d = 32 18.2 / 15.8, 128 units S = 8192 42.5 / 42.8
+//   4 heads: 64 units S = 8192, k = 1024, d = 16 32.2 / 37.9, 80 units S = 4096, k = 256 20.0 / 25.3; 64 units S = 4096,
+//     k = 512, d = 32 24.7 / 21.8; 72 units S = 4096, k = 1024, d = 64 41.1 / 32.8; 96 units S = 4096 26.1 / 25.9
 //   8 heads: 80 units S = 8192, k = 512, d = 32 29.5 / 35.1, 64 units S = 4096, k = 256, d = 16 21.2 / 28.1, k = 512, d = 64
 //     36.1 / 28.6
 bool fused_gqa_preferred(const Shape& s, int select_mode) {
@@ -47,9 +49,11 @@ bool fused_gqa_preferred(const Shape& s, int select_mode) {
   const long long units = (long long)s.B * s.Hkv, cus = device_cus();
   if (s.S > 8192) return 8 * units >= 3 * cus;
   if (4 * units < cus) return false;
-  if (16 * units >= (s.G == 2 ? 8 : s.G == 4 ? 6 : 5) * cus) return true;
+  const long long line = s.G == 2 ? 8 : s.G == 4 ? 6 : 5;  // sixteenths of the CUs
+  if (16 * units >= line * cus) return true;
   if (s.S < 2048) return s.G == 8 || s.d != 32;
-  return 2 * ((long long)s.S * s.d + (long long)s.k * (2 * kD - s.d)) < 140LL * s.S;
+  const long long bytes = 2 * ((long long)s.S * s.d + (long long)s.k * (2 * kD - s.d));
+  return bytes < 140LL * s.S && bytes * line * cus < 150LL * 16 * units * s.S;
 }
 
 template <int THREADS, int NCH, int G, int KPT, bool PAGED = false>

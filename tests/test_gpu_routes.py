@@ -89,7 +89,10 @@ def test_selection_in_a_launch_of_its_own(dtype, B, Hkv, G, mode, S, d, k):
     (True, 8, 8, 4, 4096, 16, 256, False, True), (True, 10, 8, 8, 8192, 32, 512, True, False),
     (False, 8, 8, 2, 4096, 64, 512, True, False), (False, 9, 8, 4, 4096, 64, 1024, False, False),
     (False, 8, 8, 8, 4096, 64, 512, False, True), (False, 8, 8, 2, 1024, 32, 256, False, False),
-    (True, 8, 8, 8, 1024, 32, 256, False, False), (True, 16, 8, 2, 2048, 64, 1024, False, False)])
+    (True, 8, 8, 8, 1024, 32, 256, False, False), (True, 16, 8, 2, 2048, 64, 1024, False, False),
+    # fewer units, fewer bytes a row: 2 heads 92 bytes at 80 units, 4 heads 120 bytes at 64 and 80 units
+    (True, 10, 8, 2, 4096, 16, 512, True, False), (False, 10, 8, 2, 4096, 32, 512, False, True),
+    (False, 8, 8, 4, 4096, 32, 512, True, False), (True, 5, 16, 4, 4096, 32, 512, False, False)])
 def test_one_block_per_group(one_launch, B, Hkv, G, S, d, k, append, paged):
     names = stages("bf16", B, G * Hkv, Hkv, S, d, k, 1, append=append, paged=paged)
     assert (names == ["fused_decode"]) == one_launch
