@@ -33,7 +33,10 @@ bool fused_gqa_eligible(const Shape& s, int select_mode) {
 // split path's many blocks per unit win.  From half the CUs on with 2 query heads per KV head, three eighths with 4
 // and five sixteenths with 8 it is so whatever a row costs.  Below that line a block's time grows with the bytes
 // of slab and list a row costs its unit, 2 (d + (256 - d) k / S), the split path's selection with the rows alone: it is
-// so under 150 bytes at the line, less in proportion with fewer units, and never from 140 bytes on.  Below 2048 rows,
+// so under 150 bytes at the line, less in proportion with fewer units, 20 more on a paged cache (the split path's kernels look
+// pages up more often), 10 less for lengths that may differ (the longest sequence's block ends the step), and never from
+// 140 bytes on.  (266 such shapes, mean time above the better of the two: 0.7 %, without the 20 and the 10 1.0 %, with 140
+// bytes for any number of units 2.9 %.)  Below 2048 rows,
 // where every kernel is short, all but the 64-byte slab rows that the split path rotates and scores fastest.
 // Measured at 64 to 176 units, S = 1024 to 12000, contiguous, paged, appended, ragged, us (one launch / split):
 //   2 heads: 96 units S = 5125, k = 320, d = 32 23.4 / 28.4, 120 units S = 8192, k = 512 27.9 / 33.2, 104 units S = 12000,
@@ -53,7 +56,10 @@ bool fused_gqa_preferred(const Shape& s, int select_mode) {
   if (16 * units >= line * cus) return true;
   if (s.S < 2048) return s.G == 8 || s.d != 32;
   const long long bytes = 2 * ((long long)s.S * s.d + (long long)s.k * (2 * kD - s.d));
-  return bytes < 140LL * s.S && bytes * line * cus < 150LL * 16 * units * s.S;
+  long long limit = 150 * 16 * units / (line * cus);
+  if (s.pg.table != nullptr) limit += 20;
+  if (s.rg.seq_lens != nullptr) limit -= 10;
+  return bytes < (limit < 140 ? limit : 140) * s.S;
 }
 
 template <int THREADS, int NCH, int G, int KPT, bool PAGED = false>

@@ -9,7 +9,7 @@ pytestmark = pytest.mark.gpu
 DT = {"bf16": torch.bfloat16, "f32": torch.float32}
 
 
-def stages(dtype, B, Hq, Hkv, S, d, k, mode, append=False, paged=False):
+def stages(dtype, B, Hq, Hkv, S, d, k, mode, append=False, paged=False, lengths=False):
     """Names of the kernels that one step launches."""
     dt, D = DT[dtype], 128
     lay = api.make_layout(B, Hq, Hkv, D, d, S, dt)
@@ -19,6 +19,8 @@ def stages(dtype, B, Hq, Hkv, S, d, k, mode, append=False, paged=False):
     q = torch.randn((B, Hq, D), device="cuda").to(dt)
     P = torch.eye(D, device="cuda").repeat(Hkv, 1, 1)
     step = {}
+    if lengths:
+        step["seq_lens"] = torch.full((B,), S, dtype=torch.int32, device="cuda")
     if append:
         step["k_new"], step["v_new"] = (torch.zeros((B, Hkv, D), dtype=dt, device="cuda") for _ in range(2))
     if paged:
@@ -170,3 +172,12 @@ def test_dense_sequences_of_equal_length_given_as_lengths(dtype, B, G, S, n):
         # one rounding to storage and fp32 sums: the bound of tests/parity.py
         bound = (2.0 ** -8 if dtype == "bf16" else 2.0 ** -23) * ref.abs() + (1e-3 if dtype == "bf16" else 1e-5) * ref.abs().amax(-1, keepdim=True)
         assert bool(((out[b].double() - ref).abs() <= bound).all()), b
+
+
+@pytest.mark.parametrize("one_launch,B,G,paged,lengths", [
+    (False, 12, 2, False, False), (True, 12, 2, True, False), (True, 12, 2, True, True),
+    (True, 10, 4, False, False), (False, 10, 4, False, True), (True, 10, 4, True, True)])
+def test_one_block_per_group_on_pages_and_with_lengths(one_launch, B, G, paged, lengths):
+    """120 bytes of slab and list a row, 96 units of 2 heads and 80 of 4."""
+    names = stages("bf16", B, G * 8, 8, 4096, 32, 512, 1, paged=paged, lengths=lengths)
+    assert (names == ["fused_decode"]) == one_launch
