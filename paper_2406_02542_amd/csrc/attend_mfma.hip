@@ -12,9 +12,8 @@
 //                                              step maximum is shared with two cross-row moves
 //   O[head, col] += P[head, row] V[row, col]   A = P straight from the accumulator layout of the
 //                                              first product (two bf16 terms), B = V^T, which
-//                                              needs rows contiguous per lane: V tiles pass
-//                                              through LDS (row pitch 264 B, conflict-free
-//                                              2-byte column reads)
+//                                              needs rows contiguous per lane: whole rows are
+//                                              loaded and paired up in registers
 // q is bf16 for the dense baseline (exact).  The rotated query of the gather is fp32 and enters
 // as two bf16 terms (16 significant bits): unlike the ranking scores, these logits decide no
 // index, and a relative error of 2^-17 in them is far below the bf16 rounding of the output;
@@ -48,12 +47,10 @@ __global__ __launch_bounds__(kAmThreads, 2) void attend_mfma_kernel(
     Paging pg) {
   constexpr bool kRotated = GATHER || LO_ONLY;  // the query is the fp32 rotated one
   constexpr int QT = kRotated ? 2 : 1;
-  __shared__ __align__(16) unsigned char s_v[kAmWaves][kAmStageBytes];  // 8448 B per wave
-  __shared__ int32_t s_idx[GATHER ? kMaxGatherChunk : 1];
-  __shared__ MergeSmem<kAmWaves, NH> s_merge;
+  __shared__ __align__(16) int32_t s_idx[GATHER ? kMaxGatherChunk : 1];
+  __shared__ __align__(16) MergeSmem<kAmWaves, NH> s_merge;
 
   const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r16 = lane & 15, kgrp = lane >> 4;
   int kv_unit = blockIdx.y, split = blockIdx.x;  // one block row per KV unit: its NH heads share the rows
   const bool head_ok = r16 < NH;
@@ -119,7 +116,7 @@ __global__ __launch_bounds__(kAmThreads, 2) void attend_mfma_kernel(
   const AmAddr<KSTEPS> ad = am_make_addr<KSTEPS, LO_ONLY>(k_a, k_b, v, addr_unit, S_cap, kRotated ? d : kD);
   AmState st;
   st.init();
-  am_attend_rows<GATHER, KSTEPS, QT, kAmWaves>(ad, bq, s_idx, r0, r1, s_v[wave], st);
+  am_attend_rows<GATHER, KSTEPS, QT, kAmWaves>(ad, bq, s_idx, r0, r1, st);
   am_publish<NH, kAmWaves>(st, s_merge);
 
   for (int i = tid; i < NH * kD; i += kAmThreads) {

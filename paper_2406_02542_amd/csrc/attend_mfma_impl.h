@@ -11,12 +11,17 @@
 //                                              step maximum is shared with two cross-row moves
 //   O[head, col] += P[head, row] V[row, col]   A = P straight from the accumulator layout of the
 //                                              first product (two bf16 terms), B = V^T, which
-//                                              needs rows contiguous per lane: V tiles pass
-//                                              through LDS (row pitch 264 B, conflict-free
-//                                              2-byte column reads)
-// The loads of the next step are issued as soon as the current step's keys have gone into the
-// first product and its values into LDS, so they are in flight during the softmax and the
-// second product.
+//                                              needs rows contiguous per lane: lane (m, k-group)
+//                                              loads 16 bytes, columns 8 m .. 8 m + 7, of each of
+//                                              its k-group's 8 rows (a load instruction covers four
+//                                              whole rows) and pairs the rows up with v_perm_b32, one
+//                                              instruction per operand register; the second product's
+//                                              column m of tile c is then column 8 m + c of V
+// The next step's keys are loaded as soon as the first product has read the current ones, its values as soon as
+// the second product has, so loads are in flight all the time.  What bounds it is memory once the chip is full, the chain
+// of a step's instructions when it is not.  Against V tiles transposed through LDS (16 writes and 64 two-byte reads a step,
+// 67 KB a block, 60 registers more): one sequence of 32/8 heads, S = 8192, k = 1024, 22.4 -> 20.9 us per step; 16 of them,
+// S = 16384, k = 2048, 67.6 -> 66.8; dense attention over 16 sequences of 4096 to 16384 rows 117.7 -> 114.6 (6.0 TB/s).
 #pragma once
 
 #include "attend_impl.h"
@@ -26,9 +31,9 @@ namespace loki {
 typedef __bf16 am_bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float am_f32x4_t __attribute__((ext_vector_type(4)));
 
-constexpr int kAmRows = 32;        // rows per wave step
-constexpr int kAmPitch = 264;      // bytes per V row in LDS: 256 + 8 keeps column reads conflict-free
-constexpr int kAmStageBytes = kAmRows * kAmPitch;  // per wave
+constexpr int kAmRows = 32;  // rows per wave step
+
+__device__ __forceinline__ uint32_t am_word(const uint4& x, int i) { return i == 0 ? x.x : i == 1 ? x.y : i == 2 ? x.z : x.w; }
 
 // B operand of the first product from an fp32 (rotated) query: head r16's values at `qh`
 // (global or LDS), columns 32*step + 8*kgrp .. +7, as QT bf16 terms.  Columns at or past
@@ -60,8 +65,8 @@ __device__ __forceinline__ void am_query_operands(const float* qh, bool head_ok,
 }
 
 // Where this lane's 16-byte chunks of a K row and of a V row live: chunk 4*step + kgrp of the
-// logical key row (k_a holds the first d_a columns with row pitch d_a, k_b the rest), chunks
-// kgrp + 4*step of the value row.
+// logical key row (k_a holds the first d_a columns with row pitch d_a, k_b the rest), chunk
+// r16 of the value row.
 template <int KSTEPS>
 struct AmAddr {
   const char* kptr[KSTEPS];
@@ -73,7 +78,7 @@ struct AmAddr {
 template <int KSTEPS, bool LO_ONLY>
 __device__ __forceinline__ AmAddr<KSTEPS> am_make_addr(const void* k_a, const void* k_b, const void* v,
                                                        size_t addr_unit, int S_cap, int d_a) {
-  const int kgrp = (threadIdx.x & 63) >> 4;
+  const int r16 = threadIdx.x & 15, kgrp = (threadIdx.x & 63) >> 4;
   const int nlo = d_a / 8;  // chunks held by k_a
   AmAddr<KSTEPS> ad;
 #pragma unroll
@@ -85,12 +90,12 @@ __device__ __forceinline__ AmAddr<KSTEPS> am_make_addr(const void* k_a, const vo
                                           : static_cast<const char*>(k_b) + (size_t)(c - nlo) * 16;
     ad.kptr[step] = base + addr_unit * S_cap * ad.kpitch[step];
   }
-  ad.vptr = static_cast<const char*>(v) + addr_unit * S_cap * (kD * 2) + (size_t)kgrp * 16;
+  ad.vptr = static_cast<const char*>(v) + addr_unit * S_cap * (kD * 2) + (size_t)r16 * 16;
   return ad;
 }
 
 // Running state of one wave: head r16's maximum and sum over this lane's share of the rows,
-// and the output accumulators o[cb][i] = column 16*cb + r16 of head 4*kgrp + i.
+// and the output accumulators o[c][i] = column 8*r16 + c of head 4*kgrp + i.
 struct AmState {
   float m_run, l_run;
   am_f32x4_t o[8];
@@ -98,38 +103,57 @@ struct AmState {
     m_run = kNegBig;
     l_run = 0.f;
 #pragma unroll
-    for (int cb = 0; cb < 8; ++cb) o[cb] = am_f32x4_t{0.f, 0.f, 0.f, 0.f};
+    for (int c = 0; c < 8; ++c) o[c] = am_f32x4_t{0.f, 0.f, 0.f, 0.f};
   }
 };
 
 // List entries r in [r0, r1): cache row = GATHER ? s_idx[r - r0] : r; the block's WAVES waves
-// take steps of 32 entries round-robin.  my_v: this wave's kAmStageBytes of LDS.
+// take steps of 32 entries round-robin.  s_idx: 16-byte aligned.
 template <bool GATHER, int KSTEPS, int QT, int WAVES>
 __device__ __forceinline__ void am_attend_rows(const AmAddr<KSTEPS>& ad,
                                                const am_bf16x8_t (&bq)[KSTEPS][QT],
-                                               const int32_t* s_idx, int r0, int r1,
-                                               unsigned char* my_v, AmState& st) {
+                                               const int32_t* s_idx, int r0, int r1, AmState& st) {
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int r16 = lane & 15, kgrp = lane >> 4;
   int base = r0 + wave * kAmRows;
   if (base >= r1) return;
 
-  uint4 kraw[2][KSTEPS], vraw[2][4];
-  // two 16-row tiles of K (A operands) and of V (to LDS); rows past the end re-read the last one
-  auto issue = [&](int b) {
+  uint4 kraw[2][KSTEPS], vraw[8];
+  // two 16-row tiles of K (A operands); rows past the end re-read the last one
+  auto issue_k = [&](int b) {
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
       const int r = min(b + 16 * t + r16, r1 - 1);
       const int row = GATHER ? s_idx[r - r0] : r;
 #pragma unroll
-      for (int step = 0; step < 4; ++step) {
-        if (step < KSTEPS) kraw[t][step] = load16(ad.kptr[step] + (size_t)row * ad.kpitch[step]);
-        vraw[t][step] = load16(ad.vptr + (size_t)row * (kD * 2) + step * 64);
-      }
+      for (int step = 0; step < KSTEPS; ++step) kraw[t][step] = load16(ad.kptr[step] + (size_t)row * ad.kpitch[step]);
     }
   };
-  issue(base);
+  // this k-group's rows of V: e = 4 t + i is row 16 t + 4 kgrp + i of the step
+  auto issue_v = [&](int b) {
+    int row[8];
+    if (GATHER && b + kAmRows <= r1) {  // (uniform)
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        const int4 x = *reinterpret_cast<const int4*>(s_idx + (b - r0 + 16 * t + 4 * kgrp));
+        row[4 * t] = x.x;
+        row[4 * t + 1] = x.y;
+        row[4 * t + 2] = x.z;
+        row[4 * t + 3] = x.w;
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const int r = min(b + 16 * (e / 4) + 4 * kgrp + e % 4, r1 - 1);
+        row[e] = GATHER ? s_idx[r - r0] : r;
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) vraw[e] = load16(ad.vptr + (size_t)row[e] * (kD * 2));
+  };
+  issue_k(base);
+  issue_v(base);
   for (; base < r1; base += WAVES * kAmRows) {
     // ---- S = K q^T: acc[t][i] = logit of row base + 16 t + 4 kgrp + i for head r16 -----------
     am_f32x4_t s_acc[2];
@@ -143,19 +167,7 @@ __device__ __forceinline__ void am_attend_rows(const AmAddr<KSTEPS>& ad,
           s_acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
               __builtin_bit_cast(am_bf16x8_t, kraw[t][step]), bq[step][qt], s_acc[t], 0, 0, 0);
     }
-    // ---- V tiles to LDS, row-major with padded pitch ------------------------------------------
-    __builtin_amdgcn_wave_barrier();  // the previous step's column reads are done
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-      for (int step = 0; step < 4; ++step)
-      {  // the pitch keeps rows 8-byte aligned only: two 8-byte stores per chunk
-        unsigned char* dst = my_v + (16 * t + r16) * kAmPitch + (4 * step + kgrp) * 16;
-        *reinterpret_cast<uint2*>(dst) = make_uint2(vraw[t][step].x, vraw[t][step].y);
-        *reinterpret_cast<uint2*>(dst + 8) = make_uint2(vraw[t][step].z, vraw[t][step].w);
-      }
-    // ---- the next step's loads, in flight during the softmax and the second product ----------
-    issue(base + WAVES * kAmRows);
+    issue_k(base + WAVES * kAmRows);
     // ---- softmax scalars of head r16 -----------------------------------------------------------
     float logit[2][4];
     float smax = kNegBig;
@@ -198,27 +210,23 @@ __device__ __forceinline__ void am_attend_rows(const AmAddr<KSTEPS>& ad,
 #pragma unroll
       for (int i = 0; i < 4; ++i) c4[i] = __shfl(corr, 4 * kgrp + i);  // lane of head 4 kgrp + i
 #pragma unroll
-      for (int cb = 0; cb < 8; ++cb)
+      for (int c = 0; c < 8; ++c)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) st.o[cb][i] *= c4[i];
+        for (int i = 0; i < 4; ++i) st.o[c][i] *= c4[i];
     }
-    // ---- O += P V: B operand = V^T, rows (k index 8 kgrp + e) -> tile e/4, row 4 kgrp + e%4 ----
-    __builtin_amdgcn_wave_barrier();  // the V tiles above are written
+    // ---- O += P V: B operand c = column 8 r16 + c of this k-group's rows, two to a register ----
 #pragma unroll
-    for (int cb = 0; cb < 8; ++cb) {
+    for (int c = 0; c < 8; ++c) {
       uint32_t w[4];
 #pragma unroll
-      for (int e2 = 0; e2 < 4; ++e2) {
-        const int e = 2 * e2;
-        const int rl0 = 16 * (e / 4) + 4 * kgrp + (e % 4);
-        const uint32_t x0 = *reinterpret_cast<const uint16_t*>(my_v + rl0 * kAmPitch + (16 * cb + r16) * 2);
-        const uint32_t x1 = *reinterpret_cast<const uint16_t*>(my_v + (rl0 + 1) * kAmPitch + (16 * cb + r16) * 2);
-        w[e2] = x0 | (x1 << 16);
-      }
+      for (int e2 = 0; e2 < 4; ++e2)
+        w[e2] = __builtin_amdgcn_perm(am_word(vraw[2 * e2 + 1], c / 2), am_word(vraw[2 * e2], c / 2),
+                                      c % 2 ? 0x07060302u : 0x05040100u);
       const am_bf16x8_t bv = __builtin_bit_cast(am_bf16x8_t, make_uint4(w[0], w[1], w[2], w[3]));
-      st.o[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a_lo, bv, st.o[cb], 0, 0, 0);
-      st.o[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a_hi, bv, st.o[cb], 0, 0, 0);
+      st.o[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a_lo, bv, st.o[c], 0, 0, 0);
+      st.o[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a_hi, bv, st.o[c], 0, 0, 0);
     }
+    issue_v(base + WAVES * kAmRows);
   }
 }
 
@@ -235,12 +243,14 @@ __device__ __forceinline__ void am_publish(AmState& st, MergeSmem<WAVES, NH>& sm
     sm.l[wave][r16] = st.l_run;
   }
 #pragma unroll
-  for (int cb = 0; cb < 8; ++cb)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int head = 4 * kgrp + i;
-      if (head < NH) sm.o[wave][head][16 * cb + r16] = st.o[cb][i];
+  for (int i = 0; i < 4; ++i) {
+    const int head = 4 * kgrp + i;
+    if (head < NH) {
+      float4* dst = reinterpret_cast<float4*>(&sm.o[wave][head][8 * r16]);
+      dst[0] = make_float4(st.o[0][i], st.o[1][i], st.o[2][i], st.o[3][i]);
+      dst[1] = make_float4(st.o[4][i], st.o[5][i], st.o[6][i], st.o[7][i]);
     }
+  }
   __syncthreads();
 }
 

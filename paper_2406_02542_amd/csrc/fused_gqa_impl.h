@@ -29,8 +29,7 @@ __host__ __device__ inline int gqa_keys_per_thread(int S, int threads) {
 
 // LDS of one block beyond the static part: one region that the stages use in turn — the
 // rotation's partial sums; then the score keys (padded, select_impl.h) followed by the list of
-// threshold-bin candidates; then the value tiles of the attention stage; then the merge of the
-// waves — and behind it the index list.
+// threshold-bin candidates; then the merge of the waves — and behind it the index list.
 // CLUSTER (several blocks per unit, each on a slice of the rows): S is the longest slice, k
 // the longest list a block can end up with; the candidates' keys live in device memory, only
 // their positions in LDS.
@@ -38,7 +37,6 @@ template <int THREADS, int G, bool CLUSTER = false>
 struct GqaLds {
   static constexpr int kWaves = THREADS / 64;
   static constexpr size_t kRotBytes = (size_t)(G + 1) * (kRotParts + 1) * kD * sizeof(float);  // partial sums + vectors (G queries, the new key)
-  static constexpr size_t kStageBytes = (size_t)kWaves * kAmStageBytes;
   static constexpr size_t kMergeBytes = sizeof(MergeSmem<kWaves, G>);
   static constexpr int kCandPerThread = 8;
   static constexpr int kCandCap = kCandPerThread * THREADS;  // threshold-bin candidates kept as a compact list
@@ -50,7 +48,6 @@ struct GqaLds {
   __host__ __device__ static size_t region_bytes(int S) {
     size_t b = cand_offset(S) + kCandBytes;
     b = b > kRotBytes ? b : kRotBytes;
-    b = b > kStageBytes ? b : kStageBytes;
     b = b > kMergeBytes ? b : kMergeBytes;
     return (b + 15) & ~(size_t)15;
   }
@@ -84,7 +81,6 @@ __global__ __launch_bounds__(THREADS, THREADS == 256 ? 2 : 1) void fused_gqa_ker
   uint32_t* s_key = reinterpret_cast<uint32_t*>(dyn_smem);                 // scoring, select: keys of the scores
   float* s_q = reinterpret_cast<float*>(dyn_smem);                          // rotation: [G + 1][128]
   float* s_part = s_q + (G + 1) * kD;                                       // rotation: [G + 1][8][128]
-  unsigned char* s_stage = dyn_smem;                                        // attention: value tiles
   MergeSmem<kWaves, G>& s_merge = *reinterpret_cast<MergeSmem<kWaves, G>*>(dyn_smem);  // merge
   // rows of the longest slice (CLUSTER) / of the longest sequence: what the score region is laid out for
   const int L_max = CLUSTER ? gqa_slice_rows(S_max, cl.C) : S_max;
@@ -462,7 +458,7 @@ __global__ __launch_bounds__(THREADS, THREADS == 256 ? 2 : 1) void fused_gqa_ker
         });
   }
   }
-  __syncthreads();  // the index list is complete; the scores are dead, the region turns into value tiles
+  __syncthreads();  // the index list is complete; the scores are dead, the region turns into the merge
   LOKI_STAMP(6);
   if (gidx) {
     // the list holds the certain rows (ascending) followed by the chosen candidates (ascending);
@@ -497,8 +493,7 @@ __global__ __launch_bounds__(THREADS, THREADS == 256 ? 2 : 1) void fused_gqa_ker
     const AmAddr<4> ad = am_make_addr<4, false>(klo, khi, v, PAGED ? (size_t)0 : (size_t)unit, S_cap, d);
     AmState st;
     st.init();
-    am_attend_rows<true, 4, 2, kWaves>(ad, bq, s_idx, 0, n_list, s_stage + (size_t)wave * kAmStageBytes, st);
-    __syncthreads();  // every wave is done with its value tiles: the region turns into the merge
+    am_attend_rows<true, 4, 2, kWaves>(ad, bq, s_idx, 0, n_list, st);
     LOKI_STAMP(7);
     am_publish<G, kWaves>(st, s_merge);
   }

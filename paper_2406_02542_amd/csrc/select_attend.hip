@@ -154,13 +154,10 @@ __global__ __launch_bounds__(kSaThreads, 2) void select_attend_mfma_kernel(
     const void* __restrict__ klo, const void* __restrict__ khi, const void* __restrict__ v,
     const float* __restrict__ qhat, uint16_t* __restrict__ out, SelectAttendArgs a) {
   __shared__ ResidentSelectSmem<kSaThreads> s_sel;
-  __shared__ int32_t s_idx[kMaxGatherChunk];
-  __shared__ __align__(16) unsigned char s_v[kSaWaves][kAmStageBytes];
-  MergeSmem<kSaWaves, NH>& s_merge = *reinterpret_cast<MergeSmem<kSaWaves, NH>*>(s_v);  // the tiles are dead by then
-  static_assert(sizeof(s_merge) <= sizeof(s_v), "the merge fits the value tiles");
+  __shared__ __align__(16) int32_t s_idx[kMaxGatherChunk];
+  __shared__ __align__(16) MergeSmem<kSaWaves, NH> s_merge;
 
   const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int r16 = lane & 15;
   const int split = blockIdx.x, unit = blockIdx.y;
   const size_t head0 = (size_t)unit * NH;
@@ -178,8 +175,7 @@ __global__ __launch_bounds__(kSaThreads, 2) void select_attend_mfma_kernel(
   const AmAddr<4> ad = am_make_addr<4, false>(klo, khi, v, addr_unit, a.S_cap, a.d);
   AmState st;
   st.init();
-  am_attend_rows<true, 4, 2, kSaWaves>(ad, bq, s_idx, r0, r1, s_v[wave], st);
-  __syncthreads();  // every wave is done with its tiles: the space turns into the merge
+  am_attend_rows<true, 4, 2, kSaWaves>(ad, bq, s_idx, r0, r1, st);
   am_publish<NH, kSaWaves>(st, s_merge);
   finish_share<BF16, NH>(a, s_merge, head0, unit, split, out);
 }
