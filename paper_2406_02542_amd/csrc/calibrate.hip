@@ -2,16 +2,16 @@
 // of a set of calibration keys that produces the per-head basis P, Rank@v of its spectrum
 // (Eq. 2), and the Jaccard agreement of two index lists (the quantity of Figure 6, left).
 //
-//   gram_kernel        (chunk, head)  G = sum_s k_s^T k_s and column sums over a run of rows, on
-//                                     the matrix cores: a 32-row tile is written transposed into
-//                                     LDS (swizzled, see gram_swizzle) so that both operands of
-//                                     v_mfma_f32_16x16x32_bf16 (eight consecutive rows of one
-//                                     column per lane) are one 16-byte LDS read; bf16 keys are exact, fp32 keys enter as two bf16 terms
+//   gram_kernel        (chunk, head)  the upper half of G = sum_s k_s^T k_s and column sums over a run of rows,
+//                                     on the matrix cores, operands made in registers; bf16 keys are
+//                                     exact, fp32 keys enter as two bf16 terms
 //   cov_reduce_kernel  (tiles, head)  chunk partials added in a fixed order in fp64; sample
 //                                     covariance C = (G - s s^T / N) / (N - 1)
 //   eigensolver.hip                   eigenpairs of C, sorted by decreasing eigenvalue, every
 //                                     component's largest entry made positive
 //   rank_at_kernel, layer_width_kernel, jaccard_kernel    small reductions
+#include <algorithm>
+
 #include "eigensolver.h"
 
 namespace loki {
@@ -20,174 +20,202 @@ typedef __bf16 cal_bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float cal_f32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr int kGramThreads = 256;
-constexpr int kGramTile = 32;    // rows per tile = the k dimension of one MFMA
-constexpr int kGramPitch = 144;  // bytes per column of the transposed tile: 8 slots of 16 bytes + 16
-// A column's four 16-byte granules (rows 8 g .. 8 g + 7) sit in slots g ^ gram_swizzle(column).
-// Columns one 16-byte chunk of a key row apart (8 columns) are written by neighbouring lanes in
-// the same instruction and lie a multiple of 128 bytes apart whatever the pitch, i.e. in the same
-// bank; the swizzle spreads the 16 chunks of a row over 8 bank groups (2-way instead of 16-way
-// conflicts of the 2-byte transposing writes).
-__device__ __forceinline__ int gram_swizzle(int col) { return (col >> 3) & 7; }
+constexpr int kGramWaves = kGramThreads / 64;
+constexpr int kGramStep = 32;    // rows a wave multiplies at a time = the k dimension of one MFMA
+constexpr int kGramSets = 8;     // column set c: columns c, c + 8, .., c + 120
+constexpr int kGramTiles = kGramSets * (kGramSets + 1) / 2;  // 16 x 16 tiles of G: pairs of sets c1 <= c2
+constexpr int kGramPartWords = kGramTiles * 64 * 4;          // a partial: [tile][lane][4] as the accumulators lie
+__host__ __device__ constexpr int gram_tile(int c1, int c2) { return c1 * kGramSets - c1 * (c1 - 1) / 2 + c2 - c1; }
 
+// Four waves, each on 32-row steps of its own.  Lane (m, g) of a step loads columns 8 m .. 8 m + 7 of rows
+// 8 g .. 8 g + 7 (bf16: one 16-byte load a row, four whole rows an instruction) and pairs the rows up
+// (v_perm_b32; fp32: the conversion packs them): operand c then holds eight consecutive rows of column
+// 8 m + c, which is what v_mfma_f32_16x16x32_bf16 takes on either side, so a step needs no LDS, no barrier
+// and, G being symmetric, 36 of 64 tiles.  A column of ones on the other side gives the column sums.  What
+// bounds it is the read of the keys: one wave per SIMD with 512 registers holds the 36 tiles and two
+// steps' loads (bf16 with three 2 us more, with four 18).  32 heads x 65536 keys, us: bf16 (512 MiB) 95 (5.6 TB/s), fp32 190; through a tile
+// transposed in LDS, with two barriers a tile and all 64 tiles, 131 (4.1 TB/s) and 267.
 // NT = bf16 terms per element: 1 for bf16 storage, 2 for fp32 storage (value, remainder).
 template <int NT>
-__global__ __launch_bounds__(kGramThreads) void gram_kernel(const void* __restrict__ keys,
-                                                            float* __restrict__ gram_part,
-                                                            float* __restrict__ sum_part,
-                                                            long long N, int rows_per_chunk) {
-  constexpr int kColsPerChunk = NT == 1 ? 8 : 4;          // columns in a 16-byte chunk
-  constexpr int kChunksPerRow = kD / kColsPerChunk;       // 16 or 32
-  constexpr int kRowsPerPass = kGramThreads / kChunksPerRow;  // 16 or 8
-  constexpr int kPasses = kGramTile / kRowsPerPass;       // 2 or 4
-  __shared__ __align__(16) unsigned char s_t[NT][kD * kGramPitch];
-  __shared__ float s_sum[kRowsPerPass][kD];
+__global__ __launch_bounds__(kGramThreads, 1) void gram_kernel(const void* __restrict__ keys,
+                                                               float* __restrict__ gram_part,
+                                                               float* __restrict__ sum_part,
+                                                               long long N, int rows_per_chunk) {
+  constexpr int kBufs = 2;               // steps whose loads are in flight
+  constexpr int kWords = 8 * NT;           // 16-byte loads of a step
+  constexpr size_t kRowBytes = (size_t)kD * (NT == 1 ? 2 : 4);
+  __shared__ __align__(16) float4 s_red[kGramWaves / 2][kGramTiles * 64];
+  __shared__ float s_sum[kGramWaves][kD];
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int r16 = lane & 15, kgrp = lane >> 4;
+  const int lane = threadIdx.x & 63, r16 = lane & 15, kgrp = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int chunk = blockIdx.x, head = blockIdx.y, nchunks = gridDim.x;
   const long long r0 = (long long)chunk * rows_per_chunk;
-  const long long r1 = min(N, r0 + rows_per_chunk);
-  const int c = tid % kChunksPerRow, rr = tid / kChunksPerRow;
-  const size_t row_bytes = (size_t)kD * (NT == 1 ? 2 : 4);
-  const char* base = static_cast<const char*>(keys) + (size_t)head * N * row_bytes + (size_t)c * 16;
+  const int rows = (int)max(min(N - r0, (long long)rows_per_chunk), 0LL);
+  const char* base = static_cast<const char*>(keys) + ((size_t)head * N + r0 + 8 * kgrp) * kRowBytes + (size_t)r16 * 16 * NT;
 
-  cal_f32x4_t acc[2][8];
+  cal_f32x4_t acc[kGramTiles], total[kGramSets];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < kGramTiles; ++i) acc[i] = cal_f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int j = 0; j < 8; ++j) acc[i][j] = cal_f32x4_t{0.f, 0.f, 0.f, 0.f};
-  float csum[kColsPerChunk];
-#pragma unroll
-  for (int e = 0; e < kColsPerChunk; ++e) csum[e] = 0.f;
+  for (int i = 0; i < kGramSets; ++i) total[i] = cal_f32x4_t{0.f, 0.f, 0.f, 0.f};
 
-  auto load_tile = [&](long long t0, uint4 (&raw)[kPasses]) {
+  uint4 raw[kBufs][kWords];
+  auto load_step = [&](int t0, uint4 (&x)[kWords]) {  // rows t0 .. t0 + 31 of the chunk, zeros past its end
+    const char* p = base + (size_t)t0 * kRowBytes;
+    if (t0 + kGramStep <= rows) {  // (uniform)
 #pragma unroll
-    for (int p = 0; p < kPasses; ++p) {
-      const long long row = t0 + p * kRowsPerPass + rr;
-      raw[p] = row < r1 ? load16(base + (size_t)row * row_bytes) : make_uint4(0, 0, 0, 0);
+      for (int e = 0; e < 8; ++e)
+#pragma unroll
+        for (int t = 0; t < NT; ++t) x[NT * e + t] = load16(p + e * kRowBytes + 16 * t);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+          x[NT * e + t] = t0 + 8 * kgrp + e < rows ? load16(p + e * kRowBytes + 16 * t) : make_uint4(0, 0, 0, 0);
     }
   };
+  auto word = [](const uint4& x, int i) { return i == 0 ? x.x : i == 1 ? x.y : i == 2 ? x.z : x.w; };
+  const cal_bf16x8_t ones = __builtin_bit_cast(cal_bf16x8_t, make_uint4(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u));
 
-  uint4 raw[kPasses];
-  load_tile(r0, raw);
-  for (long long t0 = r0; t0 < r1; t0 += kGramTile) {
-    __syncthreads();  // the previous tile's operand reads are done
 #pragma unroll
-    for (int p = 0; p < kPasses; ++p) {
-      const int row = p * kRowsPerPass + rr;  // row inside the tile
-      if constexpr (NT == 1) {
-        float f[8];
-        BF16::unpack(raw[p], f);
-        const uint32_t w[4] = {raw[p].x, raw[p].y, raw[p].z, raw[p].w};
+  for (int b = 0; b < kBufs; ++b) load_step((wave + kGramWaves * b) * kGramStep, raw[b]);
+  for (int t0 = wave * kGramStep; t0 < rows; t0 += kGramWaves * kGramStep * kBufs) {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          csum[e] += f[e];
-          const uint16_t h = (uint16_t)((e & 1) ? (w[e >> 1] >> 16) : (w[e >> 1] & 0xffffu));
-          *reinterpret_cast<uint16_t*>(&s_t[0][(8 * c + e) * kGramPitch + (((row >> 3) ^ gram_swizzle(8 * c + e)) << 4) + (row & 7) * 2]) = h;
+    for (int b = 0; b < kBufs; ++b) {
+      cal_bf16x8_t op[NT][kGramSets];
+#pragma unroll
+      for (int c = 0; c < kGramSets; ++c) {
+        uint32_t w[NT][4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          if constexpr (NT == 1) {
+            w[0][j] = __builtin_amdgcn_perm(word(raw[b][2 * j + 1], c / 2), word(raw[b][2 * j], c / 2), c % 2 ? 0x07060302u : 0x05040100u);
+          } else {
+            const float x0 = __uint_as_float(word(raw[b][4 * j + c / 4], c % 4));
+            const float x1 = __uint_as_float(word(raw[b][4 * j + 2 + c / 4], c % 4));
+            w[0][j] = BF16::round2(x0, x1);
+            w[NT - 1][j] = BF16::round2(x0 - __uint_as_float(w[0][j] << 16), x1 - __uint_as_float(w[0][j] & 0xffff0000u));
+          }
         }
-      } else {
-        float f[4];
-        F32::unpack(raw[p], f);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          csum[e] += f[e];
-          const uint16_t hi = BF16::round(f[e]);
-          const uint16_t lo = BF16::round(f[e] - __uint_as_float((uint32_t)hi << 16));
-          *reinterpret_cast<uint16_t*>(&s_t[0][(4 * c + e) * kGramPitch + (((row >> 3) ^ gram_swizzle(4 * c + e)) << 4) + (row & 7) * 2]) = hi;
-          *reinterpret_cast<uint16_t*>(&s_t[NT - 1][(4 * c + e) * kGramPitch + (((row >> 3) ^ gram_swizzle(4 * c + e)) << 4) + (row & 7) * 2]) = lo;
-        }
+        for (int t = 0; t < NT; ++t) op[t][c] = __builtin_bit_cast(cal_bf16x8_t, make_uint4(w[t][0], w[t][1], w[t][2], w[t][3]));
       }
+      load_step(t0 + (b + kBufs) * kGramWaves * kGramStep, raw[b]);
+      if constexpr (NT == 2) {  // smallest terms first; remainder x remainder is below fp32's last place
+#pragma unroll
+        for (int c1 = 0; c1 < kGramSets; ++c1)
+#pragma unroll
+          for (int c2 = c1; c2 < kGramSets; ++c2) {
+            const int i = gram_tile(c1, c2);
+            acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(op[1][c1], op[0][c2], acc[i], 0, 0, 0);
+          }
+#pragma unroll
+        for (int c1 = 0; c1 < kGramSets; ++c1)
+#pragma unroll
+          for (int c2 = c1; c2 < kGramSets; ++c2) {
+            const int i = gram_tile(c1, c2);
+            acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(op[0][c1], op[1][c2], acc[i], 0, 0, 0);
+          }
+#pragma unroll
+        for (int c = 0; c < kGramSets; ++c) total[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, op[1][c], total[c], 0, 0, 0);
+      }
+#pragma unroll
+      for (int c1 = 0; c1 < kGramSets; ++c1)
+#pragma unroll
+        for (int c2 = c1; c2 < kGramSets; ++c2) {
+          const int i = gram_tile(c1, c2);
+          acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(op[0][c1], op[0][c2], acc[i], 0, 0, 0);
+        }
+#pragma unroll
+      for (int c = 0; c < kGramSets; ++c) total[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, op[0][c], total[c], 0, 0, 0);
     }
+  }
+
+  // the waves' sums, added pairwise in a fixed order
+#pragma unroll
+  for (int half = kGramWaves / 2; half > 0; half >>= 1) {
+    if (wave >= half && wave < 2 * half)
+#pragma unroll
+      for (int i = 0; i < kGramTiles; ++i)
+        s_red[wave - half][i * 64 + lane] = make_float4(acc[i][0], acc[i][1], acc[i][2], acc[i][3]);
     __syncthreads();
-    load_tile(t0 + kGramTile, raw);  // next tile's loads fly during the products (zeros past the end)
-    // wave w owns output rows 32 w .. 32 w + 31 (two 16-row tiles) of all 128 columns
-    cal_bf16x8_t a[NT][2];
+    if (wave < half)
 #pragma unroll
-    for (int t = 0; t < NT; ++t)
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-        a[t][i] = *reinterpret_cast<const cal_bf16x8_t*>(
-            &s_t[t][(32 * wave + 16 * i + r16) * kGramPitch + ((kgrp ^ gram_swizzle(32 * wave + 16 * i + r16)) << 4)]);
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      cal_bf16x8_t b[NT];
-#pragma unroll
-      for (int t = 0; t < NT; ++t)
-        b[t] = *reinterpret_cast<const cal_bf16x8_t*>(
-            &s_t[t][(16 * j + r16) * kGramPitch + ((kgrp ^ gram_swizzle(16 * j + r16)) << 4)]);
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        if constexpr (NT == 2) {  // smallest terms first; remainder x remainder is below fp32's last place
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[1][i], b[0], acc[i][j], 0, 0, 0);
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0][i], b[1], acc[i][j], 0, 0, 0);
-        }
-        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0][i], b[0], acc[i][j], 0, 0, 0);
+      for (int i = 0; i < kGramTiles; ++i) {
+        const float4 o = s_red[wave][i * 64 + lane];
+        acc[i] = cal_f32x4_t{acc[i][0] + o.x, acc[i][1] + o.y, acc[i][2] + o.z, acc[i][3] + o.w};
       }
-    }
+    __syncthreads();
   }
-
-  // partial Gram matrix: lane holds rows 4 kgrp + e, column r16 of each 16 x 16 tile
-  float* gp = gram_part + ((size_t)head * nchunks + chunk) * kD * kD;
+  // (every row of a tile of column sums is the same)
+  if (kgrp == 0)
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+    for (int c = 0; c < kGramSets; ++c) s_sum[wave][8 * r16 + c] = total[c][0];
+  const size_t part = (size_t)head * nchunks + chunk;
+  if (wave == 0) {
+    float4* gp = reinterpret_cast<float4*>(gram_part + part * kGramPartWords);
 #pragma unroll
-    for (int j = 0; j < 8; ++j)
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        gp[(size_t)(32 * wave + 16 * i + 4 * kgrp + e) * kD + 16 * j + r16] = acc[i][j][e];
-  // column sums: the kRowsPerPass threads that share a chunk are added in a fixed order
-#pragma unroll
-  for (int e = 0; e < kColsPerChunk; ++e) s_sum[rr][kColsPerChunk * c + e] = csum[e];
+    for (int i = 0; i < kGramTiles; ++i) gp[i * 64 + lane] = make_float4(acc[i][0], acc[i][1], acc[i][2], acc[i][3]);
+  }
   __syncthreads();
-  if (tid < kD) {
-    float s = 0.f;
-#pragma unroll
-    for (int r = 0; r < kRowsPerPass; ++r) s += s_sum[r][tid];
-    sum_part[((size_t)head * nchunks + chunk) * kD + tid] = s;
-  }
+  if (threadIdx.x < kD)
+    sum_part[part * kD + threadIdx.x] = (s_sum[0][threadIdx.x] + s_sum[1][threadIdx.x]) + (s_sum[2][threadIdx.x] + s_sum[3][threadIdx.x]);
 }
 
-// C = (G - s s^T / N) / (N - 1), chunk partials added in order in fp64, and exactly symmetric: G's two
-// halves are averaged (with fp32 keys they differ in the last place, value x remainder and
-// remainder x value being added in the opposite order; a skew part, however small, never leaves a
-// Jacobi iteration, which then took all of its 30 sweeps: 9.9 ms for 4 heads).  Block (tile pair,
-// head): a 32 x 32 tile on or above the diagonal and its mirror image, exchanged through LDS.
-constexpr int kCovTile = 32;
-constexpr int kCovTiles = kD / kCovTile;
-constexpr int kCovPairs = kCovTiles * (kCovTiles + 1) / 2;
-__global__ __launch_bounds__(kCovTile * kCovTile) void cov_reduce_kernel(const float* __restrict__ gram_part,
-                                                                         const float* __restrict__ sum_part,
-                                                                         double* __restrict__ cov, long long N,
-                                                                         int nchunks) {
-  __shared__ double s_mirror[kCovTile][kCovTile + 1];
-  const int head = blockIdx.y;
-  int ti = 0, tj = blockIdx.x;
-  while (tj >= kCovTiles - ti) {
-    tj -= kCovTiles - ti;
-    ++ti;
-  }
-  tj += ti;
-  const int r = threadIdx.x / kCovTile, c = threadIdx.x % kCovTile;
-  const int row = ti * kCovTile + r, col = tj * kCovTile + c;            // this thread's entry of the tile
-  const int mrow = tj * kCovTile + r, mcol = ti * kCovTile + c;          // and of its mirror image
-  const float* gp = gram_part + (size_t)head * nchunks * kD * kD;
-  const float* sp = sum_part + (size_t)head * nchunks * kD;
-  double g = 0.0, gm = 0.0, sr = 0.0, sc = 0.0;
+// C = (G - s s^T / N) / (N - 1), chunk partials added in order in fp64.  Block (set, head): rows set, set + 8, ..
+// of C, thread (c2, lane) the four entries that this lane holds of tile (set, c2), or of its mirror image where only
+// that exists; the rows are put together in LDS and leave whole.  Both places of an entry are computed from
+// the same numbers, so C is exactly symmetric (a skew part, however small, never leaves a Jacobi iteration, which
+// then took all of its 30 sweeps: 9.9 ms for 4 heads).
+constexpr int kCovThreads = kGramSets * 64;
+constexpr int kCovPitch = kD + 4;  // doubles per row in LDS
+__global__ __launch_bounds__(kCovThreads) void cov_reduce_kernel(const float* __restrict__ gram_part,
+                                                                 const float* __restrict__ sum_part,
+                                                                 double* __restrict__ cov, long long N,
+                                                                 int nchunks) {
+  __shared__ double s_sum[kD];
+  __shared__ __align__(16) double s_row[kD / kGramSets][kCovPitch];
+  const int set = blockIdx.x, head = blockIdx.y, tid = threadIdx.x;
+  const int c2 = tid >> 6, lane = tid & 63;
+  const int tile = set <= c2 ? gram_tile(set, c2) : gram_tile(c2, set);
+  const float4* gp = reinterpret_cast<const float4*>(gram_part + (size_t)head * nchunks * kGramPartWords) + tile * 64 + lane;
+  const float* sp = sum_part + (size_t)head * nchunks * kD + tid;
+  double g[4] = {0.0, 0.0, 0.0, 0.0}, s = 0.0;
+#pragma unroll 4
   for (int cc = 0; cc < nchunks; ++cc) {
-    g += (double)gp[(size_t)cc * kD * kD + (size_t)row * kD + col];
-    gm += (double)gp[(size_t)cc * kD * kD + (size_t)mrow * kD + mcol];
-    sr += (double)sp[cc * kD + row];
-    sc += (double)sp[cc * kD + col];
+    const float4 x = gp[(size_t)cc * (kGramPartWords / 4)];
+    g[0] += (double)x.x;
+    g[1] += (double)x.y;
+    g[2] += (double)x.z;
+    g[3] += (double)x.w;
+    if (tid < kD) s += (double)sp[(size_t)cc * kD];
   }
-  s_mirror[r][c] = gm;
+  if (tid < kD) s_sum[tid] = s;
   __syncthreads();
   const double n = (double)N;
-  const double x = (0.5 * (g + s_mirror[c][r]) - sr * sc / n) / (n > 1.0 ? n - 1.0 : 1.0);
-  cov[(size_t)head * kD * kD + (size_t)row * kD + col] = x;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    // row i of the tile, column j; on the diagonal the upper half serves both
+    const int i = 4 * (lane >> 4) + e, j = lane & 15;
+    const bool swap = set > c2;
+    const int row = kGramSets * i + (swap ? c2 : set), col = kGramSets * j + (swap ? set : c2);
+    const double x = (g[e] - s_sum[row] * s_sum[col] / n) / (n > 1.0 ? n - 1.0 : 1.0);
+    if (swap) {
+      s_row[j][row] = x;
+    } else if (set < c2 || i <= j) {
+      s_row[i][col] = x;
+      if (set == c2) s_row[j][row] = x;
+    }
+  }
   __syncthreads();
-  s_mirror[c][r] = x;
-  __syncthreads();
-  cov[(size_t)head * kD * kD + (size_t)mrow * kD + mcol] = s_mirror[r][c];
+  double* C = cov + (size_t)head * kD * kD;
+#pragma unroll
+  for (int u = tid; u < kD / kGramSets * kD / 2; u += kCovThreads) {
+    const int i = u / (kD / 2), at = 2 * (u % (kD / 2));
+    *reinterpret_cast<double2*>(C + (size_t)(kGramSets * i + set) * kD + at) = *reinterpret_cast<const double2*>(&s_row[i][at]);
+  }
 }
 
 // Eq. 2: the smallest d whose leading normalised eigenvalues sum to at least v percent.
@@ -267,18 +295,41 @@ __global__ __launch_bounds__(256) void jaccard_kernel(const int32_t* __restrict_
 }
 
 // ---- launchers ----------------------------------------------------------------------------------
-int pca_chunks(int Hkv, long long N, int* rows_per_chunk) {
-  long long want = (2 * device_cus() + Hkv - 1) / Hkv;  // about two blocks per CU over all heads
+// What the workspace is laid out for: a partial Gram matrix of 64 KiB for every 1024 rows, at most two for every
+// CU over all heads (the eigensolver uses the space again).
+static int pca_chunks(int Hkv, long long N) {
+  const long long want = (2 * device_cus() + Hkv - 1) / Hkv;
   long long rows = (N + want - 1) / want;
   if (rows < 1024) rows = 1024;
-  rows = (rows + kGramTile - 1) / kGramTile * kGramTile;
+  rows = (rows + 31) / 32 * 32;
+  return (int)((N + rows - 1) / rows);
+}
+
+// Chunks of a head in the Gram pass, never more than pca_chunks: a CU holds one block, so as many as
+// make whole rounds of blocks, one round if that leaves no CU idle (32 heads: 8 chunks), else the number of rounds at
+// which rounds x (rows of a chunk + the 256 that a block's start and end cost) is least.
+static int gram_chunks(int Hkv, long long N, int* rows_per_chunk) {
+  constexpr long long kWhole = kGramWaves * kGramStep;
+  const int most = pca_chunks(Hkv, N);
+  long long best = -1;
+  int chunks = 1;
+  for (int rounds = 1; rounds <= 4 || best < 0; ++rounds) {
+    const long long n = std::min<long long>(most, (long long)rounds * device_cus() / Hkv);
+    if (n < 1) continue;
+    const long long rows = (N + n - 1) / n, used = ((N + rows - 1) / rows * Hkv + device_cus() - 1) / device_cus();
+    const long long cost = used * (rows + 256);
+    if (best < 0 || cost < best) {
+      best = cost;
+      chunks = (int)n;
+    }
+  }
+  const long long rows = ((N + chunks - 1) / chunks + kWhole - 1) / kWhole * kWhole;
   *rows_per_chunk = (int)rows;
   return (int)((N + rows - 1) / rows);
 }
 
 size_t pca_workspace_bytes(int Hkv, long long N) {
-  int rpc;
-  const int nc = pca_chunks(Hkv, N, &rpc);
+  const int nc = pca_chunks(Hkv, N);
   size_t b = 0;
   b += (size_t)Hkv * nc * kD * kD * sizeof(float);  // partial Gram matrices
   b += (size_t)Hkv * nc * kD * sizeof(float);       // partial column sums
@@ -293,8 +344,9 @@ size_t pca_workspace_bytes(int Hkv, long long N) {
 // stage 0: partial Gram matrices; 1: covariance; 2: eigensolver
 hipError_t launch_pca_stage(int stage, int Hkv, int dtype, const void* keys, long long N, float* P,
                             float* eigenvalues, void* workspace, hipStream_t st) {
+  static_assert(kGramPartWords <= kD * kD, "a partial Gram matrix fits the space laid out for it");
   int rpc;
-  const int nc = pca_chunks(Hkv, N, &rpc);
+  const int nc = pca_chunks(Hkv, N), chunks = gram_chunks(Hkv, N, &rpc);
   char* w = static_cast<char*>(workspace);
   float* gram_part = reinterpret_cast<float*>(w);
   float* sum_part = gram_part + (size_t)Hkv * nc * kD * kD;
@@ -304,14 +356,14 @@ hipError_t launch_pca_stage(int stage, int Hkv, int dtype, const void* keys, lon
   double* mat = cov + (size_t)Hkv * kD * kD;
   if (stage == 0) {
     if (dtype == 0)
-      hipLaunchKernelGGL(gram_kernel<2>, dim3(nc, Hkv), dim3(kGramThreads), 0, st, keys, gram_part,
+      hipLaunchKernelGGL(gram_kernel<2>, dim3(chunks, Hkv), dim3(kGramThreads), 0, st, keys, gram_part,
                          sum_part, N, rpc);
     else
-      hipLaunchKernelGGL(gram_kernel<1>, dim3(nc, Hkv), dim3(kGramThreads), 0, st, keys, gram_part,
+      hipLaunchKernelGGL(gram_kernel<1>, dim3(chunks, Hkv), dim3(kGramThreads), 0, st, keys, gram_part,
                          sum_part, N, rpc);
   } else if (stage == 1) {
-    hipLaunchKernelGGL(cov_reduce_kernel, dim3(kCovPairs, Hkv), dim3(kCovTile * kCovTile), 0, st, gram_part,
-                       sum_part, cov, N, nc);
+    hipLaunchKernelGGL(cov_reduce_kernel, dim3(kGramSets, Hkv), dim3(kCovThreads), 0, st, gram_part, sum_part, cov, N,
+                       chunks);
   } else {
     EigRegions r;
     r.cov = cov;

@@ -71,6 +71,22 @@ def test_pca_fit_matches_oracle(dtype, Hkv, N):
         assert np.all(big > 0)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("Hkv,N", [(1, 31), (1, 129), (3, 1153), (40, 1089), (257, 161)])
+def test_covariance_at_the_edges_of_a_step(dtype, Hkv, N):
+    """Rows that do not fill a 32-row step, a chunk or a round of blocks; more heads than CUs.  P diag(lambda) P^T
+    against the float64 covariance: the bounds of test_pca_fit_matches_oracle (fp32 sums of at most a few
+    thousand terms, remainder x remainder of fp32 keys dropped: below 2^-16 of a term)."""
+    keys = calibration_keys(5 + N, Hkv, N, dtype)
+    P, lam, _ = fit(keys, dtype)
+    for h in (0, Hkv // 2, Hkv - 1):
+        cov = np.cov(keys[h].astype(np.float64), rowvar=False)
+        rec = np.linalg.norm(P[h] @ np.diag(lam[h]) @ P[h].T - cov) / np.linalg.norm(cov)
+        say(f"case {dtype} Hkv {Hkv} N {N} head {h}: reconstruction {rec:.2e}")
+        assert rec < 2e-5
+        assert np.max(np.abs(P[h].T @ P[h] - np.eye(128))) < 1e-6
+
+
 def test_pca_fit_then_rotate_then_decode_is_exact_attention():
     """Lemma 4.1 with the GPU's own basis: keys rotated by the fitted P, full rank and every
     row kept, give dense attention on the unrotated keys."""
