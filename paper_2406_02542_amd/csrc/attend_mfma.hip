@@ -116,7 +116,7 @@ __global__ __launch_bounds__(kAmThreads, 2) void attend_mfma_kernel(
   const AmAddr<KSTEPS> ad = am_make_addr<KSTEPS, LO_ONLY>(k_a, k_b, v, addr_unit, S_cap, kRotated ? d : kD);
   AmState st;
   st.init();
-  am_attend_rows<GATHER, KSTEPS, QT, kAmWaves>(ad, bq, s_idx, r0, r1, st);
+  am_attend_rows<GATHER, KSTEPS, QT>(ad, bq, s_idx, r0, AmRoundRobin<kAmWaves>(r0, r1), st, [] {});
   am_publish<NH, kAmWaves>(st, s_merge);
 
   for (int i = tid; i < NH * kD; i += kAmThreads) {

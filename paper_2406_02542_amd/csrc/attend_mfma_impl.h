@@ -107,21 +107,37 @@ struct AmState {
   }
 };
 
-// List entries r in [r0, r1): cache row = GATHER ? s_idx[r - r0] : r; the block's WAVES waves
-// take steps of 32 entries round-robin.  s_idx: 16-byte aligned.
-template <bool GATHER, int KSTEPS, int QT, int WAVES>
+// Which steps a wave takes.  next(base, end): the wave's next step, entries [base, base + 32) of which those
+// below `end` exist; false: no more, base = end (uniform for the wave).  early(): whether the first step may be
+// asked for, and its rows loaded, before the list is complete.
+// The block's WAVES waves take the steps of entries [r0, r1) round-robin; entries below `there` are there early.
+template <int WAVES>
+struct AmRoundRobin {
+  int at, r1, there;
+  __device__ __forceinline__ AmRoundRobin(int r0, int r1_, int there_ = 0)
+      : at(r0 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) * kAmRows), r1(r1_), there(there_) {}
+  __device__ __forceinline__ bool early() const { return at + kAmRows <= there; }
+  __device__ __forceinline__ bool next(int& base, int& end) {
+    base = min(at, r1);
+    end = r1;
+    at += WAVES * kAmRows;
+    return base < r1;
+  }
+};
+
+// Cache row of list entry r = GATHER ? s_idx[r - r0] : r.  s_idx: 16-byte aligned.  complete(): called once by
+// every wave, completes the list; the loads of a first step that may be asked for early are in flight meanwhile.
+template <bool GATHER, int KSTEPS, int QT, typename Steps, typename Complete>
 __device__ __forceinline__ void am_attend_rows(const AmAddr<KSTEPS>& ad,
                                                const am_bf16x8_t (&bq)[KSTEPS][QT],
-                                               const int32_t* s_idx, int r0, int r1, AmState& st) {
+                                               const int32_t* s_idx, int r0, Steps steps, AmState& st, Complete complete) {
   const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int r16 = lane & 15, kgrp = lane >> 4;
-  int base = r0 + wave * kAmRows;
-  if (base >= r1) return;
+  int base, end;
 
   uint4 kraw[2][KSTEPS], vraw[8];
   // two 16-row tiles of K (A operands); rows past the end re-read the last one
-  auto issue_k = [&](int b) {
+  auto issue_k = [&](int b, int r1) {
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
       const int r = min(b + 16 * t + r16, r1 - 1);
@@ -131,7 +147,7 @@ __device__ __forceinline__ void am_attend_rows(const AmAddr<KSTEPS>& ad,
     }
   };
   // this k-group's rows of V: e = 4 t + i is row 16 t + 4 kgrp + i of the step
-  auto issue_v = [&](int b) {
+  auto issue_v = [&](int b, int r1) {
     int row[8];
     if (GATHER && b + kAmRows <= r1) {  // (uniform)
 #pragma unroll
@@ -152,10 +168,20 @@ __device__ __forceinline__ void am_attend_rows(const AmAddr<KSTEPS>& ad,
 #pragma unroll
     for (int e = 0; e < 8; ++e) vraw[e] = load16(ad.vptr + (size_t)row[e] * (kD * 2));
   };
-  issue_k(base);
-  issue_v(base);
-  for (; base < r1; base += WAVES * kAmRows) {
-    // ---- S = K q^T: acc[t][i] = logit of row base + 16 t + 4 kgrp + i for head r16 -----------
+  const bool early = steps.early();
+  if (early) {
+    steps.next(base, end);
+    issue_k(base, end);
+    issue_v(base, end);
+  }
+  complete();
+  if (!early) {
+    if (!steps.next(base, end)) return;
+    issue_k(base, end);
+    issue_v(base, end);
+  }
+  for (bool more = true; more;) {
+    // ---- S = K q^T: acc[t][i] = logit of entry base + 16 t + 4 kgrp + i for head r16 -----------
     am_f32x4_t s_acc[2];
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
@@ -167,7 +193,9 @@ __device__ __forceinline__ void am_attend_rows(const AmAddr<KSTEPS>& ad,
           s_acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
               __builtin_bit_cast(am_bf16x8_t, kraw[t][step]), bq[step][qt], s_acc[t], 0, 0, 0);
     }
-    issue_k(base + WAVES * kAmRows);
+    const int b0 = base, r1 = end;
+    more = steps.next(base, end);  // (no more: the loads below re-read the last row)
+    issue_k(base, end);
     // ---- softmax scalars of head r16 -----------------------------------------------------------
     float logit[2][4];
     float smax = kNegBig;
@@ -175,7 +203,7 @@ __device__ __forceinline__ void am_attend_rows(const AmAddr<KSTEPS>& ad,
     for (int t = 0; t < 2; ++t)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const bool ok = base + 16 * t + 4 * kgrp + i < r1;
+        const bool ok = b0 + 16 * t + 4 * kgrp + i < r1;
         logit[t][i] = ok ? s_acc[t][i] * kSoftmaxScaleLog2 : kNegBig;
         smax = fmaxf(smax, logit[t][i]);
       }
@@ -189,7 +217,7 @@ __device__ __forceinline__ void am_attend_rows(const AmAddr<KSTEPS>& ad,
     for (int t = 0; t < 2; ++t)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const bool ok = base + 16 * t + 4 * kgrp + i < r1;
+        const bool ok = b0 + 16 * t + 4 * kgrp + i < r1;
         p[4 * t + i] = ok ? fast_exp2(logit[t][i] - m_new) : 0.f;
         psum += p[4 * t + i];
       }
@@ -226,7 +254,7 @@ __device__ __forceinline__ void am_attend_rows(const AmAddr<KSTEPS>& ad,
       st.o[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a_lo, bv, st.o[c], 0, 0, 0);
       st.o[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a_hi, bv, st.o[c], 0, 0, 0);
     }
-    issue_v(base + WAVES * kAmRows);
+    issue_v(base, end);
   }
 }
 

@@ -19,6 +19,7 @@
 
 namespace loki {
 
+constexpr int kClusterCandCap = 8192;  // candidates of a unit that are ranked from a list
 constexpr int kClusterRounds = 3;     // histogram exchanges of one launch at most (11 + 11 + 10 bits)
 
 // Device memory of the exchange (all of it inside the caller's workspace).
@@ -29,7 +30,7 @@ struct ClusterArgs {
   uint32_t* error = nullptr;     // one word: set when a block gave up waiting
   uint32_t* xhist = nullptr;     // [units][kClusterRounds][C][threads] slots: suffix sums of the digit histograms
   size_t xhist_bytes = 0;
-  uint32_t* xcand = nullptr;     // [units][candidate capacity] low key bits of the threshold-bin rows
+  uint32_t* xcand = nullptr;     // [units][kClusterCandCap] low key bits of the threshold-bin rows
   size_t xcand_bytes = 0;
   float* partial = nullptr;      // [units * G][C][kD + 2] attention partials
   int C = 1;                     // blocks per unit
@@ -40,7 +41,6 @@ struct ClusterArgs {
 struct ClusterSmem {
   uint32_t bin, rem;
   uint32_t above[kClusterMax], inbin[kClusterMax];
-  uint32_t red[2];
   int ok;
 };
 
@@ -58,23 +58,27 @@ __device__ __forceinline__ uint32_t cluster_load_u32(const uint32_t* p) {
 // not arrive within spin_limit polls.  Every thread of the block calls it.
 // poisoned (thread 0's value counts): the workspace's error word was set when the launch began —
 // an earlier launch on it gave up and left flags behind; the wait then fails at once.
+// cluster_wave_wait: the block's first wave alone, with the stores of the block acknowledged.
+__device__ __forceinline__ bool cluster_wave_wait(uint32_t* flags, int C, int c, uint32_t meet, uint32_t spin_limit) {
+  const int lane = threadIdx.x & 63;
+  if (lane == 0) cluster_store_u32(flags + c * kClusterFlagStride, meet);
+  const uint32_t* f = flags + (lane < C ? lane : 0) * kClusterFlagStride;
+  bool ok = lane >= C || lane == c || cluster_load_u32(f) >= meet;
+  uint32_t spins = 0;
+  while (__ballot(!ok) != 0ull && spins < spin_limit) {
+    __builtin_amdgcn_s_sleep(1);
+    if (!ok) ok = cluster_load_u32(f) >= meet;
+    ++spins;
+  }
+  return __ballot(!ok) == 0ull;
+}
 __device__ __forceinline__ bool cluster_arrive_and_wait(uint32_t* flags, int C, int c, uint32_t meet,
                                                         uint32_t spin_limit, bool poisoned, ClusterSmem& cs) {
   __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this thread's stores are acknowledged
   __syncthreads();
   if (threadIdx.x < 64) {
-    const int lane = threadIdx.x;
-    if (lane == 0) cluster_store_u32(flags + c * kClusterFlagStride, meet);
-    const uint32_t* f = flags + (lane < C ? lane : 0) * kClusterFlagStride;
-    bool ok = lane >= C || lane == c || cluster_load_u32(f) >= meet;
-    uint32_t spins = 0;
-    while (__ballot(!ok) != 0ull && spins < spin_limit) {
-      __builtin_amdgcn_s_sleep(1);
-      if (!ok) ok = cluster_load_u32(f) >= meet;
-      ++spins;
-    }
-    const bool all = __ballot(!ok) == 0ull;
-    if (lane == 0) cs.ok = (all && !poisoned) ? 1 : 0;
+    const bool all = cluster_wave_wait(flags, C, c, meet, spin_limit);
+    if (threadIdx.x == 0) cs.ok = (all && !poisoned) ? 1 : 0;
   }
   __syncthreads();
   return cs.ok != 0;
@@ -102,8 +106,10 @@ __device__ __forceinline__ void cluster_store_x4(__amdgpu_buffer_rsrc_t rs, uint
 // hold at least rem keys.  Returns false when the wait gave up.
 // xh / xh_off: the exchange area and the byte offset of this unit's arrays for this round,
 // [C][THREADS] slots of kClusterSlotBytes: thread t's slot holds the suffix sums of its own
-// bins (ascending) and of the bin above them, so that a reader needs no other thread's slot.
-constexpr int kClusterSlotBytes = 32;
+// bins (ascending) and of the bin above them, so that a reader needs no other thread's slot; a slice has at most
+// 16384 rows, so they are 16-bit numbers.  (As 32-bit numbers in 32 bytes an exchange took 5.5 us between 2 blocks, 3.4 now, and 8.7
+// between 8, 5.0 now.)
+constexpr int kClusterSlotBytes = 16;
 template <int THREADS>
 __device__ __forceinline__ bool cluster_hist_round(const uint32_t* hist, __amdgpu_buffer_rsrc_t xh,
                                                    uint32_t xh_off, int C, int c, uint32_t* flags,
@@ -132,25 +138,20 @@ __device__ __forceinline__ bool cluster_hist_round(const uint32_t* hist, __amdgp
     // keys in bins >= top - 3, top - 2, top - 1, top and top + 1
     const uint32_t s0 = incl, s1 = s0 - cbin[3], s2 = s1 - cbin[2], s3 = s2 - cbin[1], s4 = s3 - cbin[0];
     const uint32_t slot = xh_off + (uint32_t)(c * THREADS + tid) * kClusterSlotBytes;
-    cluster_store_x4(xh, slot, cluster_u32x4{s0, s1, s2, s3});
-    cluster_store_x4(xh, slot + 16, cluster_u32x4{s4, 0u, 0u, 0u});
+    cluster_store_x4(xh, slot, cluster_u32x4{s0 | (s1 << 16), s2 | (s3 << 16), s4, 0u});
   }
   if (!cluster_arrive_and_wait(flags, C, c, meet, spin_limit, poisoned, cs)) return false;
   // sc[cc][j]: block cc's suffix sum at bin top - 3 + j (j = 4: the bin above this thread's)
   uint32_t sc[kClusterMax][BPT + 1];
 #pragma unroll
   for (int cc = 0; cc < kClusterMax; ++cc) {
-    cluster_u32x4 a = {0u, 0u, 0u, 0u}, b = {0u, 0u, 0u, 0u};
-    if (cc < C) {  // (uniform)
-      const uint32_t slot = xh_off + (uint32_t)(cc * THREADS + tid) * kClusterSlotBytes;
-      a = cluster_load_x4(xh, slot);
-      b = cluster_load_x4(xh, slot + 16);
-    }
-    sc[cc][0] = a[0];
-    sc[cc][1] = a[1];
-    sc[cc][2] = a[2];
-    sc[cc][3] = a[3];
-    sc[cc][4] = b[0];
+    cluster_u32x4 a = {0u, 0u, 0u, 0u};
+    if (cc < C) a = cluster_load_x4(xh, xh_off + (uint32_t)(cc * THREADS + tid) * kClusterSlotBytes);  // (uniform)
+    sc[cc][0] = a[0] & 0xffffu;
+    sc[cc][1] = a[0] >> 16;
+    sc[cc][2] = a[1] & 0xffffu;
+    sc[cc][3] = a[1] >> 16;
+    sc[cc][4] = a[2];
   }
   uint32_t tot[BPT + 1];
 #pragma unroll
@@ -178,18 +179,19 @@ __device__ __forceinline__ bool cluster_hist_round(const uint32_t* hist, __amdgp
 struct ClusterRound {
   uint32_t bin, rem;
   uint32_t own_above, lower_above;  // keys above the bin: in this block, in the blocks before it
-  uint32_t own_inbin, lower_inbin, total_inbin;
+  uint32_t own_inbin, lower_inbin, total_inbin, most_inbin;  // keys inside it: also in the unit, and the most of a block
 };
 __device__ __forceinline__ ClusterRound cluster_round_result(const ClusterSmem& cs, int C, int c) {
   ClusterRound r;
   r.bin = cs.bin;
   r.rem = cs.rem;
-  r.own_above = r.lower_above = r.own_inbin = r.lower_inbin = r.total_inbin = 0;
+  r.own_above = r.lower_above = r.own_inbin = r.lower_inbin = r.total_inbin = r.most_inbin = 0;
 #pragma unroll
   for (int cc = 0; cc < kClusterMax; ++cc) {
     const uint32_t a = cs.above[cc], b = cs.inbin[cc];
     if (cc < C) {
       r.total_inbin += b;
+      r.most_inbin = max(r.most_inbin, b);
       if (cc < c) {
         r.lower_above += a;
         r.lower_inbin += b;
@@ -201,13 +203,6 @@ __device__ __forceinline__ ClusterRound cluster_round_result(const ClusterSmem& 
     }
   }
   return r;
-}
-
-// Sum over the block of a per-thread pair of counts (two 16-bit halves, each total below 65536)
-// into cs.red[which]; cs.red[which] must be zero on entry.  The caller's next barrier publishes it.
-__device__ __forceinline__ void cluster_block_add(uint32_t packed, ClusterSmem& cs, int which) {
-  const uint32_t incl = wave_inclusive_scan_u32(packed);
-  if ((threadIdx.x & 63) == 63 && incl != 0u) atomicAdd(&cs.red[which], incl);
 }
 
 }  // namespace loki

@@ -79,7 +79,7 @@ ClusterPlan cluster_plan(const Shape& s, int C) {
   p.xhist = off;
   off += up(units * kClusterRounds * C * kClusterThreads * kClusterSlotBytes);
   p.xcand = off;
-  off += up(units * (size_t)GqaLds<kClusterThreads, 2, true>::kCandCap * 4);
+  off += up(units * (size_t)kClusterCandCap * 4);
   p.partial = off;
   off += up(units * s.G * C * (size_t)kPartialStride * 4);
   p.total = off;

@@ -29,10 +29,10 @@ __host__ __device__ inline int gqa_keys_per_thread(int S, int threads) {
 
 // LDS of one block beyond the static part: one region that the stages use in turn — the
 // rotation's partial sums; then the score keys (padded, select_impl.h) followed by the list of
-// threshold-bin candidates; then the merge of the waves — and behind it the index list.
+// threshold-bin candidates; then (CLUSTER) the keys of the whole unit's candidates; then the merge of the
+// waves — and behind it the index list.
 // CLUSTER (several blocks per unit, each on a slice of the rows): S is the longest slice, k
-// the longest list a block can end up with; the candidates' keys live in device memory, only
-// their positions in LDS.
+// the longest list a block can end up with.
 template <int THREADS, int G, bool CLUSTER = false>
 struct GqaLds {
   static constexpr int kWaves = THREADS / 64;
@@ -40,9 +40,11 @@ struct GqaLds {
   static constexpr size_t kMergeBytes = sizeof(MergeSmem<kWaves, G>);
   static constexpr int kCandPerThread = 8;
   static constexpr int kCandCap = kCandPerThread * THREADS;  // threshold-bin candidates kept as a compact list
-  static constexpr size_t kCandBytes = (size_t)kCandCap * (CLUSTER ? 4 : 8);  // (key, position)
+  static constexpr size_t kCandBytes = (size_t)kCandCap * 8;  // (key, position)
+  static constexpr size_t kUnitCandBytes = CLUSTER ? (size_t)kClusterCandCap * 4 : 0;
   __host__ __device__ static size_t cand_offset(int S) {
-    const size_t b = padded_words((size_t)THREADS * gqa_keys_per_thread(S, THREADS)) * sizeof(uint32_t);
+    size_t b = padded_words((size_t)THREADS * gqa_keys_per_thread(S, THREADS)) * sizeof(uint32_t);
+    b = b > kUnitCandBytes ? b : kUnitCandBytes;
     return (b + 15) & ~(size_t)15;
   }
   __host__ __device__ static size_t region_bytes(int S) {
@@ -56,6 +58,57 @@ struct GqaLds {
 
 // Rows of a slice when C blocks share a unit of S rows: equal parts in whole 64-row groups.
 __host__ __device__ inline int gqa_slice_rows(int S, int C) { return ((S + C - 1) / C + 63) / 64 * 64; }
+
+// CLUSTER: what the first wave leaves for the others once it has ranked the candidates.
+struct GqaList {
+  int state;  // 0: not yet; 1: the list is complete; 2: the other blocks of the unit did not show up
+  int n;      // entries of the list
+};
+
+// The attention steps of a block whose list is still growing: entries [0, n_def) are there, the first wave adds
+// the chosen candidates.  The other waves take the whole steps of those n_def (T1 of them) in turn; the steps
+// behind them, of which everybody knows once the list is complete, go where steps are missing: the first wave, whose ranking
+// counts as one, gets level with the others, then those of them with one step less, then all in turn.
+template <int WAVES>
+struct GqaSteps {
+  const GqaList* list;
+  int wave, T1, q, r, i;
+  bool ahead;
+  __device__ __forceinline__ GqaSteps(const GqaList* list_, int n_def, bool ahead_)
+      : list(list_), wave(__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6))), T1(n_def / kAmRows),
+        q(T1 / (WAVES - 1)), r(T1 % (WAVES - 1)), i(0), ahead(ahead_) {}
+  __device__ __forceinline__ bool early() const { return ahead && wave > 0 && wave - 1 < T1; }
+  __device__ __forceinline__ bool next(int& base, int& end) {
+    const int n1 = wave == 0 ? 0 : q + (wave - 1 < r ? 1 : 0);
+    int i2 = i - n1;
+    if (i2 < 0) {
+      base = (wave - 1 + (WAVES - 1) * i++) * kAmRows;
+      end = T1 * kAmRows;
+      return true;
+    }
+    ++i;
+    const volatile int* state = &list->state;
+    while (*state == 0) __builtin_amdgcn_s_sleep(1);  // (the first wave always gets there: its own waits are bounded)
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    const int first = max(q - 1, 0), level = q > 0 ? 1 : 0;  // steps of the first wave up to the others' level
+    const int turns = T1 + first + level + (WAVES - 1 - r);   // from here on all in turn
+    int step;
+    if (wave == 0)
+      step = i2 < first + level ? T1 + i2 : turns + WAVES * (i2 - first - level);
+    else if (wave > r)
+      step = i2 == 0 ? T1 + first + level + (wave - 1 - r) : turns + WAVES * (i2 - 1) + wave;
+    else
+      step = turns + WAVES * i2 + wave;
+    const int n = __builtin_amdgcn_readfirstlane(list->n);
+    if (__builtin_amdgcn_readfirstlane(list->state) != 1 || step * kAmRows >= n) {
+      base = end = n1 > 0 ? T1 * kAmRows : n;  // (a row that this wave has read before)
+      return false;
+    }
+    base = step * kAmRows;
+    end = n;
+    return true;
+  }
+};
 
 // THREADS = 256: two blocks share a CU (S <= 8192); 512: one block per CU (S <= 16384).
 // NCH = 16-byte chunks per slab row (d = 8 NCH); KPT = keys a thread holds in the select stage.
@@ -89,6 +142,7 @@ __global__ __launch_bounds__(THREADS, THREADS == 256 ? 2 : 1) void fused_gqa_ker
   __shared__ int32_t s_pages[PAGED ? kGqaMaxPages : 1];
   __shared__ ResidentSelectSmem<THREADS> s_sel;
   __shared__ ClusterSmem s_cl;
+  __shared__ GqaList s_list;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r16 = lane & 15;
@@ -261,10 +315,28 @@ __global__ __launch_bounds__(THREADS, THREADS == 256 ? 2 : 1) void fused_gqa_ker
   int32_t* gidx = out_idx ? out_idx + (size_t)unit * k_max : nullptr;
   if (gidx && cidx == 0)
     for (int i = k + tid; i < k_max; i += THREADS) gidx[i] = -1;  // a sequence keeping fewer rows
-  constexpr int kCandCap = Lds::kCandCap;  // candidates resolved from a compact list (else: all keys)
-  // what the stage leaves: s_idx[0, n_list) = this block's selected rows as two ascending runs,
-  // [0, n_def) and [n_def, n_list); gidx_base = selected rows of the unit below this block's
-  int n_list = k, n_def = 0, gidx_base = 0;
+  constexpr int kCandCap = Lds::kCandCap;  // candidates of this block ranked from a compact list (else: all keys)
+  uint32_t* s_ckey = reinterpret_cast<uint32_t*>(dyn_smem + Lds::cand_offset(L_max));  // behind the keys
+  int32_t* s_cpos = reinterpret_cast<int32_t*>(s_ckey + kCandCap);
+  // Rows above the threshold's leading digits are certain and go straight into the list (ascending), the rows that
+  // share them are the candidates, of which the chosen are appended (ascending).  The attention begins
+  // in between, so that the memory system does not wait for the ranking.  One block per unit: every wave loads the rows of its
+  // first step and then ranks the candidates by itself, without a barrier, all writing the same list.  CLUSTER: the first
+  // wave ranks them with the other blocks of the unit while the other waves attend over the certain rows.
+  // Ranked by all threads of the block first, with the attention behind it, us per step: 16 sequences of 32/8 heads, S = 16384, k = 2048 (two
+  // blocks per unit) 66.8 -> 61.5; 4 of S = 131072, k = 8192 (eight, and the 6000 candidates of a unit took a second
+  // histogram exchange) 79.3 -> 69.3; one block per unit, 64 of 64/8 heads, S = 8192: 101.7 -> 102.1, which memory bounds (6 TB/s
+  // with the lines that the gather reads in part).
+  int n_def = 0, gidx_base = 0;  // certain rows in s_idx; selected rows of the unit below this block's
+  int n_rank = 0;                // candidates still to be ranked (0: the list is complete)
+  uint32_t rem1 = 0;             // of which this many are chosen
+  int cl_shift = 0, cl_own = 0, cl_lower = 0, cl_above = 0;  // CLUSTER: their bits; candidates here, in the blocks before; rows above there
+  uint32_t cl_meet = 0;
+  // the list holds rows the attention stage can address, unless the caller wants positions first
+  auto to_row = [&](int pos) -> int32_t {
+    if constexpr (PAGED) return gidx ? pos : (int32_t)slab.pool_row(pos);
+    else return pos;
+  };
   if constexpr (CLUSTER) {
     const int C = cl.C;
     const int n = row1 - row0;
@@ -272,7 +344,6 @@ __global__ __launch_bounds__(THREADS, THREADS == 256 ? 2 : 1) void fused_gqa_ker
     const __amdgpu_buffer_rsrc_t xh = cluster_buffer(cl.xhist, cl.xhist_bytes);
     const uint32_t round_bytes = (uint32_t)(C * THREADS * kClusterSlotBytes);
     const uint32_t xh_unit = (uint32_t)unit * kClusterRounds * round_bytes;
-    int32_t* s_cpos = reinterpret_cast<int32_t*>(dyn_smem + Lds::cand_offset(L_max));  // behind the keys
     const uint32_t* run = s_key + padded_pos(tid * per_thread);  // this thread's keys (select_impl.h)
     const uint32_t vmask = contiguous_valid_mask(n, per_thread);
     // The threshold key is fixed digit by digit (11 + 11 + 10 bits, as in select_impl.h), each
@@ -310,88 +381,9 @@ __global__ __launch_bounds__(THREADS, THREADS == 256 ? 2 : 1) void fused_gqa_ker
       own_inbin = r.own_inbin;
       lower_inbin = r.lower_inbin;
       total_inbin = r.total_inbin;
-      if (total_inbin <= (uint32_t)kCandCap) break;
+      if (total_inbin <= (uint32_t)kClusterCandCap && r.most_inbin <= (uint32_t)kCandCap) break;
     }
     LOKI_STAMP(11);
-    if (ok && shift > 0) {
-      // Rows above the threshold's leading digits are certain: straight into the list.  The rows
-      // that share them are the candidates: their remaining key bits go to the unit's candidate
-      // array (block after block, so it is in position order), their positions stay here.
-      const __amdgpu_buffer_rsrc_t xc = cluster_buffer(cl.xcand, cl.xcand_bytes);
-      const uint32_t xc_unit = (uint32_t)unit * (uint32_t)kCandCap * 4u;
-      uint32_t* xc_words = cl.xcand + (size_t)unit * kCandCap;
-      const uint32_t low_mask = (1u << shift) - 1u;
-      contiguous_partition<THREADS, KPT>(
-          s_key, n, per_thread, shift, prefix, s_sel.wave[0], [&](int rank, int pos) { s_idx[rank] = row0 + pos; },
-          [&](int rank, int pos, uint32_t kk) {
-            cluster_store_u32(xc_words + lower_inbin + rank, kk & low_mask);
-            s_cpos[rank] = row0 + pos;
-          });
-      for (int i = tid; i < 2048; i += THREADS) s_sel.hist[0][i] = 0u;  // (read for the last time inside the round)
-      if (tid == 0) s_cl.red[0] = s_cl.red[1] = 0u;
-      ++meet;
-      ok = cluster_arrive_and_wait(counter, C, cidx, meet, cl.spin_limit, poisoned, s_cl);
-      LOKI_STAMP(4);
-      if (ok) {
-        // every block ranks all candidates (on their remaining bits, moved to the top of the
-        // word) and finds the same threshold
-        constexpr int CPT = Lds::kCandPerThread;
-        static_assert(CPT % 4 == 0, "candidates are read four at a time");
-        uint32_t ck[CPT], vm = 0;
-        const int c0 = resident_pos0(CPT);
-#pragma unroll
-        for (int j = 0; j < CPT / 4; ++j) {
-          const int ci = c0 + 256 * j;  // the layout resident_compact emits in: 4 consecutive candidates
-          const cluster_u32x4 w = cluster_load_x4(xc, xc_unit + (uint32_t)min(ci, kCandCap - 4) * 4u);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const bool in = (uint32_t)(ci + e) < total_inbin;
-            ck[4 * j + e] = in ? (w[e] << (32 - shift)) : 0u;
-            vm |= (in ? 1u : 0u) << (4 * j + e);
-          }
-        }
-        uint32_t Tp, need_eq;
-        resident_threshold<THREADS, CPT>(ck, vm, rem, s_sel, Tp, need_eq);
-        LOKI_STAMP(12);
-        // candidates above / equal to the threshold in the blocks before this one and in this one
-        uint32_t cnt_lower = 0, cnt_own = 0;
-#pragma unroll
-        for (int e = 0; e < CPT; ++e) {
-          const uint32_t ci = (uint32_t)(c0 + 256 * (e / 4) + (e % 4));
-          const uint32_t one = ((vm >> e) & 1u) ? ((ck[e] > Tp ? 1u : 0u) | (ck[e] == Tp ? 0x10000u : 0u)) : 0u;
-          cnt_lower += ci < lower_inbin ? one : 0u;
-          cnt_own += (ci >= lower_inbin && ci < lower_inbin + own_inbin) ? one : 0u;
-        }
-        cluster_block_add(cnt_lower, s_cl, 0);
-        cluster_block_add(cnt_own, s_cl, 1);
-        __syncthreads();
-        const uint32_t lower_gt = s_cl.red[0] & 0xffffu, lower_eq = s_cl.red[0] >> 16;
-        const uint32_t own_gt = s_cl.red[1] & 0xffffu, own_eq = s_cl.red[1] >> 16;
-        const uint32_t base_lower = lower_gt + min(lower_eq, need_eq);  // chosen candidates before this block's
-        const uint32_t take_eq = min(own_eq, need_eq > lower_eq ? need_eq - lower_eq : 0u);
-        resident_compact<THREADS, CPT>(ck, vm, CPT, Tp, need_eq, 0u, 0u, s_sel.wave[0], s_sel.wave[1],
-                                       [&](int rank, int ci, float) {
-                                         const uint32_t local = (uint32_t)ci - lower_inbin;
-                                         if (local < own_inbin)
-                                           s_idx[own_above + ((uint32_t)rank - base_lower)] = s_cpos[local];
-                                       });
-        n_def = (int)own_above;
-        n_list = (int)(own_above + own_gt + take_eq);
-        gidx_base = (int)(lower_above + base_lower);
-      }
-    } else if (ok) {
-      // all 32 bits are fixed (long runs of equal scores): the rows equal to the threshold are taken
-      // in position order, so a block takes what the blocks before it leave of the rem needed
-      const uint32_t take_eq = min(own_inbin, rem > lower_inbin ? rem - lower_inbin : 0u);
-      contiguous_partition<THREADS, KPT>(
-          s_key, n, per_thread, 0, prefix, s_sel.wave[0], [&](int rank, int pos) { s_idx[rank] = row0 + pos; },
-          [&](int rank, int pos, uint32_t) {
-            if ((uint32_t)rank < take_eq) s_idx[own_above + rank] = row0 + pos;
-          });
-      n_def = (int)own_above;
-      n_list = (int)(own_above + take_eq);
-      gidx_base = (int)(lower_above + min(lower_inbin, rem));
-    }
     if (!ok) {
       // the other blocks of the unit did not show up in time: say so and leave a result that
       // cannot be mistaken for one (all threads take this branch together)
@@ -399,91 +391,151 @@ __global__ __launch_bounds__(THREADS, THREADS == 256 ? 2 : 1) void fused_gqa_ker
       for (int i = tid; i < G * kD; i += THREADS) out[head0 * kD + i] = 0x7fc0u;  // NaN
       return;
     }
-  } else {
-  // The histogram of the leading 11 key bits is complete: find the bin that holds the k-th
-  // largest score.  Rows in higher bins are selected for certain (n_def of them); the rows
-  // inside the bin are the candidates among which the exact threshold is found.
-  resident_find_bin<THREADS>(s_sel, 0, (uint32_t)k);
-  const uint32_t bin1 = s_sel.out[0][0], rem1 = s_sel.out[0][1];
-  const uint32_t n_cand = s_sel.hist[0][bin1];
-  n_def = k - (int)rem1;
-  uint32_t* s_ckey = reinterpret_cast<uint32_t*>(dyn_smem + Lds::cand_offset(S_max));  // behind the keys
-  int32_t* s_cpos = reinterpret_cast<int32_t*>(s_ckey + kCandCap);
-  LOKI_STAMP(11);
-  if (n_cand <= (uint32_t)kCandCap) {
-    // certain rows straight into the list, the bin's rows into the candidate list
+    // (shift = 0: all 32 bits are fixed, long runs of equal scores: the rows equal to the threshold are taken
+    // in position order, so a block takes what the blocks before it leave of the rem needed)
+    const uint32_t take_eq = min(own_inbin, rem > lower_inbin ? rem - lower_inbin : 0u);
+    const uint32_t low_mask = (1u << (shift & 31)) - 1u;
+    n_def = (int)own_above;
+    if (tid == 0) {
+      s_list.state = shift > 0 ? 0 : 1;
+      s_list.n = (int)(own_above + take_eq);
+    }
+    // The remaining bits of this block's candidates also go to the unit's candidate array (block after block, so it
+    // is in position order); with all of them there every block finds the same threshold.
+    uint32_t* xc_words = cl.xcand + (size_t)unit * kClusterCandCap;
     contiguous_partition<THREADS, KPT>(
-        s_key, S, per_thread, 21, bin1, s_sel.wave[0], [&](int rank, int pos) { s_idx[rank] = pos; },
+        s_key, n, per_thread, shift, prefix, s_sel.wave[0], [&](int rank, int pos) { s_idx[rank] = to_row(row0 + pos); },
         [&](int rank, int pos, uint32_t kk) {
-          s_ckey[rank] = kk;
-          s_cpos[rank] = pos;
+          if (shift > 0) {
+            cluster_store_u32(xc_words + lower_inbin + rank, kk & low_mask);
+            s_ckey[rank] = kk & low_mask;
+            s_cpos[rank] = row0 + pos;
+          } else if ((uint32_t)rank < take_eq) {
+            s_idx[own_above + rank] = to_row(row0 + pos);
+          }
         });
-    for (int i = tid; i < 2048; i += THREADS) s_sel.hist[0][i] = 0u;  // everyone has read n_cand
-    __syncthreads();
-    LOKI_STAMP(13);
-    // exact threshold among the candidates (they agree on the leading 11 bits: rank on the
-    // remaining 21, moved to the top of the word) and ordered emission of the rem1 best
-    constexpr int CPT = Lds::kCandPerThread;
-    uint32_t ck[CPT], vm = 0;
-    const int c0 = resident_pos0(CPT);
-#pragma unroll
-    for (int e = 0; e < CPT; ++e) {
-      const int ci = c0 + 256 * (e / 4) + (e % 4);  // the layout resident_compact emits in
-      const bool ok = (uint32_t)ci < n_cand;
-      ck[e] = ok ? (s_ckey[ci] << 11) : 0u;
-      vm |= (ok ? 1u : 0u) << e;
-    }
-    uint32_t Tp, need_eq;
-    resident_threshold<THREADS, CPT>(ck, vm, rem1, s_sel, Tp, need_eq);
-    resident_compact<THREADS, CPT>(ck, vm, CPT, Tp, need_eq, 0u, 0u, s_sel.wave[0], s_sel.wave[1],
-                                   [&](int rank, int local, float) { s_idx[n_def + rank] = s_cpos[local]; });
+    gidx_base = (int)(lower_above + min(lower_inbin, rem));
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this thread's stores are acknowledged
+    __syncthreads();  // the certain rows and the candidates are in LDS; the keys are dead
+    n_rank = shift > 0 ? (int)total_inbin : 0;
+    rem1 = rem;
+    cl_shift = shift;
+    cl_meet = meet + 1;
+    cl_own = (int)own_inbin;
+    cl_lower = (int)lower_inbin;
+    cl_above = (int)lower_above;
   } else {
-    // long runs of (nearly) equal scores: the plain selection over all keys, held in registers;
-    // the list is again two ascending runs: the keys above the threshold, then the first
-    // need_eq keys equal to it
-    uint32_t key[KPT];
-    uint32_t valid_mask;
-    contiguous_load_keys<KPT>(s_key, S, per_thread, key, valid_mask);
-    __syncthreads();  // everyone has read n_cand
-    for (int i = tid; i < 2048; i += THREADS) s_sel.hist[0][i] = 0u;
-    __syncthreads();
-    uint32_t T, need_eq;
-    resident_threshold<THREADS, KPT>(key, valid_mask, (uint32_t)k, s_sel, T, need_eq);
-    n_def = k - (int)need_eq;
-    __syncthreads();  // s_sel.wave is free again
-    contiguous_partition<THREADS, KPT>(
-        s_key, S, per_thread, 0, T, s_sel.wave[0], [&](int rank, int pos) { s_idx[rank] = pos; },
-        [&](int rank, int pos, uint32_t) {
-          if (rank < (int)need_eq) s_idx[n_def + rank] = pos;
-        });
-  }
-  }
-  __syncthreads();  // the index list is complete; the scores are dead, the region turns into the merge
-  LOKI_STAMP(6);
-  if (gidx) {
-    // the list holds the certain rows (ascending) followed by the chosen candidates (ascending);
-    // the caller's copy is the merge of the two (CLUSTER: behind the rows of the blocks before)
-    const int n_chosen = n_list - n_def;
-    for (int i = tid; i < n_list; i += THREADS) {
-      const int pos = s_idx[i];
-      const bool certain = i < n_def;
-      const int32_t* other = certain ? s_idx + n_def : s_idx;
-      int lo = 0, hi = certain ? n_chosen : n_def;
-      while (lo < hi) {  // entries of the other run below pos
-        const int mid = (lo + hi) >> 1;
-        if (other[mid] < pos) lo = mid + 1;
-        else hi = mid;
-      }
-      gidx[gidx_base + (certain ? i : i - n_def) + lo] = pos;
+    // The histogram of the leading 11 key bits is complete: find the bin that holds the k-th
+    // largest score.  Rows in higher bins are certain (n_def of them); the rows inside the bin are the
+    // candidates among which the exact threshold is found.
+    resident_find_bin<THREADS>(s_sel, 0, (uint32_t)k);
+    const uint32_t bin1 = s_sel.out[0][0];
+    const uint32_t n_cand = s_sel.hist[0][bin1];
+    rem1 = s_sel.out[0][1];
+    LOKI_STAMP(11);
+    if (n_cand <= (uint32_t)kCandCap) {
+      n_def = k - (int)rem1;
+      n_rank = (int)n_cand;
+      contiguous_partition<THREADS, KPT>(
+          s_key, S, per_thread, 21, bin1, s_sel.wave[0], [&](int rank, int pos) { s_idx[rank] = to_row(pos); },
+          [&](int rank, int pos, uint32_t kk) {
+            s_ckey[rank] = kk & ((1u << 21) - 1u);
+            s_cpos[rank] = pos;
+          });
+      __syncthreads();  // the certain rows and the candidates are in LDS
+      LOKI_STAMP(13);
+    } else {
+      // long runs of (nearly) equal scores: the plain selection over all keys, held in registers;
+      // the list is again two ascending runs: the keys above the threshold, then the first
+      // need_eq keys equal to it
+      uint32_t key[KPT];
+      uint32_t valid_mask;
+      contiguous_load_keys<KPT>(s_key, S, per_thread, key, valid_mask);
+      __syncthreads();  // everyone has read n_cand
+      for (int i = tid; i < 2048; i += THREADS) s_sel.hist[0][i] = 0u;
+      __syncthreads();
+      uint32_t T, need_eq;
+      resident_threshold<THREADS, KPT>(key, valid_mask, (uint32_t)k, s_sel, T, need_eq);
+      n_def = k - (int)need_eq;
+      __syncthreads();  // s_sel.wave is free again
+      contiguous_partition<THREADS, KPT>(
+          s_key, S, per_thread, 0, T, s_sel.wave[0], [&](int rank, int pos) { s_idx[rank] = to_row(pos); },
+          [&](int rank, int pos, uint32_t) {
+            if (rank < (int)need_eq) s_idx[n_def + rank] = to_row(pos);
+          });
+      __syncthreads();  // the index list is complete
     }
   }
-
-  if constexpr (PAGED) {
-    // the attention stage addresses the pools from their start: positions -> pool rows
-    __syncthreads();  // the merge above has read the positions
-    for (int i = tid; i < n_list; i += THREADS) s_idx[i] = (int32_t)slab.pool_row(s_idx[i]);
-    __syncthreads();
-  }
+  auto complete = [&]() {
+    if constexpr (CLUSTER) {
+      if (wave == 0 && n_rank > 0) {
+        uint32_t* counter = cl.counters + (size_t)unit * kClusterCounterStride;
+        const bool ok = cluster_wave_wait(counter, cl.C, cidx, cl_meet, cl.spin_limit);
+        LOKI_STAMP(4);
+        if (ok) {
+          const __amdgpu_buffer_rsrc_t xc = cluster_buffer(cl.xcand, cl.xcand_bytes);
+          const uint32_t xc_unit = (uint32_t)unit * (uint32_t)kClusterCandCap * 4u;
+          uint32_t* s_all = s_key;  // [kClusterCandCap] the unit's candidates
+          constexpr int kBatch = 16;  // (a round trip waits behind the row loads of the other waves)
+          for (int i0 = 0; i0 < n_rank; i0 += 256 * kBatch) {
+            cluster_u32x4 w[kBatch];
+#pragma unroll
+            for (int j = 0; j < kBatch; ++j)
+              w[j] = cluster_load_x4(xc, xc_unit + (uint32_t)min(i0 + 256 * j + 4 * lane, kClusterCandCap - 4) * 4u);
+#pragma unroll
+            for (int j = 0; j < kBatch; ++j)
+              if (i0 + 256 * j + 4 * lane < kClusterCandCap)
+                *reinterpret_cast<cluster_u32x4*>(s_all + i0 + 256 * j + 4 * lane) = w[j];
+          }
+          wave_lds_fence();
+          LOKI_STAMP(14);
+          const WaveThreshold t = wave_threshold(s_all, n_rank, cl_shift, rem1);
+          LOKI_STAMP(13);
+          uint32_t lower_gt, lower_eq;
+          wave_count(s_all, cl_lower, t.T, lower_gt, lower_eq);
+          const int chosen = wave_choose(s_ckey, cl_own, t, lower_eq,
+                                         [&](int rank, int i) { s_idx[n_def + rank] = to_row(s_cpos[i]); });
+          gidx_base = cl_above + (int)(lower_gt + min(lower_eq, t.need_eq));
+          if (lane == 0) s_list.n = n_def + chosen;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        if (lane == 0) *const_cast<volatile int*>(&s_list.state) = ok ? 1 : 2;
+        LOKI_STAMP(6);
+      }
+    } else if (n_rank > 0) {
+      const WaveThreshold t = wave_threshold(s_ckey, n_rank, 21, rem1);
+      LOKI_STAMP(14);
+      wave_choose(s_ckey, n_rank, t, 0u, [&](int rank, int i) { s_idx[n_def + rank] = to_row(s_cpos[i]); });
+      wave_lds_fence();
+      LOKI_STAMP(6);
+    }
+    if (gidx) {
+      // the list holds the certain rows (ascending) followed by the chosen candidates (ascending);
+      // the caller's copy is the merge of the two (CLUSTER: behind the rows of the blocks before)
+      __shared__ int s_gidx_base;
+      if (tid == 0) s_gidx_base = gidx_base;
+      __syncthreads();  // the list is complete
+      const int n_list = !CLUSTER ? k : s_list.state == 1 ? s_list.n : 0, n_chosen = n_list - n_def;
+      for (int i = tid; i < n_list; i += THREADS) {
+        const int pos = s_idx[i];
+        const bool certain = i < n_def;
+        const int32_t* other = certain ? s_idx + n_def : s_idx;
+        int lo = 0, hi = certain ? n_chosen : n_def;
+        while (lo < hi) {  // entries of the other run below pos
+          const int mid = (lo + hi) >> 1;
+          if (other[mid] < pos) lo = mid + 1;
+          else hi = mid;
+        }
+        gidx[s_gidx_base + (certain ? i : i - n_def) + lo] = pos;
+      }
+      if constexpr (PAGED) {
+        // the attention stage addresses the pools from their start: positions -> pool rows
+        __syncthreads();  // the merge above has read the positions
+        for (int i = tid; i < n_list; i += THREADS) s_idx[i] = (int32_t)slab.pool_row(s_idx[i]);
+        __syncthreads();
+      }
+    }
+  };
 
   // ---- exact attention over the selected rows, all G heads ---------------------------------------
   {
@@ -493,9 +545,21 @@ __global__ __launch_bounds__(THREADS, THREADS == 256 ? 2 : 1) void fused_gqa_ker
     const AmAddr<4> ad = am_make_addr<4, false>(klo, khi, v, PAGED ? (size_t)0 : (size_t)unit, S_cap, d);
     AmState st;
     st.init();
-    am_attend_rows<true, 4, 2, kWaves>(ad, bq, s_idx, 0, n_list, st);
+    // (with a copy for the caller the rows wait for the merged list)
+    if constexpr (CLUSTER)
+      am_attend_rows<true, 4, 2>(ad, bq, s_idx, 0, GqaSteps<kWaves>(&s_list, n_def, gidx == nullptr), st, complete);
+    else
+      am_attend_rows<true, 4, 2>(ad, bq, s_idx, 0, AmRoundRobin<kWaves>(0, k, gidx == nullptr ? n_def : 0), st, complete);
     LOKI_STAMP(7);
-    am_publish<G, kWaves>(st, s_merge);
+    if constexpr (!CLUSTER) __syncthreads();  // every wave has ranked the candidates: their place turns into the merge
+    am_publish<G, kWaves>(st, s_merge);  // (CLUSTER: no wave is done before the list is)
+  }
+  if constexpr (CLUSTER) {
+    if (s_list.state != 1) {  // as above: the others did not show up for the candidates
+      if (tid == 0) cluster_store_u32(cl.error, 1u);
+      for (int i = tid; i < G * kD; i += THREADS) out[head0 * kD + i] = 0x7fc0u;  // NaN
+      return;
+    }
   }
   for (int i = tid; i < G * kD; i += THREADS) {
     const int g = i / kD, col = i % kD;

@@ -175,7 +175,7 @@ __global__ __launch_bounds__(kSaThreads, 2) void select_attend_mfma_kernel(
   const AmAddr<4> ad = am_make_addr<4, false>(klo, khi, v, addr_unit, a.S_cap, a.d);
   AmState st;
   st.init();
-  am_attend_rows<true, 4, 2, kSaWaves>(ad, bq, s_idx, r0, r1, st);
+  am_attend_rows<true, 4, 2>(ad, bq, s_idx, r0, AmRoundRobin<kSaWaves>(r0, r1), st, [] {});
   am_publish<NH, kSaWaves>(st, s_merge);
   finish_share<BF16, NH>(a, s_merge, head0, unit, split, out);
 }

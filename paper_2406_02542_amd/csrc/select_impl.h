@@ -540,6 +540,138 @@ __device__ __forceinline__ void contiguous_partition(const uint32_t* s_key, int 
   }
 }
 
+// ---- a candidate list ranked by one wave, without a barrier ---------------------------------------
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// What is chosen: keys above T and the first need_eq of those equal to it.
+struct WaveThreshold {
+  uint32_t T, need_eq;
+};
+
+// Sum over the wave, uniform.
+__device__ __forceinline__ uint32_t wave_sum_u32(uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_scan_u32(x), 63);
+}
+
+// The rem largest (1 <= rem <= n) of n keys of at most `bits` bits: a search on the number of keys at or above a trial
+// value, by interpolation first (the keys of one histogram bin lie almost evenly: about five trials for a
+// thousand of them) and by halves after that, until a trial has exactly rem of them or the threshold is known to
+// the last bit.  count(x): keys >= x, x >= 1, uniform.
+template <typename Count>
+__device__ __forceinline__ WaveThreshold wave_search(int n, int bits, uint32_t rem, Count count) {
+  if (rem >= (uint32_t)n) return {0u, (uint32_t)n};
+  uint32_t lo = 0, hi = 1u << bits, n_lo = (uint32_t)n, n_hi = 0;  // keys >= lo: n_lo > rem; keys >= hi: n_hi < rem
+  for (int trial = 0; hi - lo > 1; ++trial) {
+    uint32_t mid = (lo + hi) >> 1;
+    if (trial < 12 && (trial & 3) != 3) {
+      const float at = (float)(hi - lo) * ((float)(n_lo - rem) * __builtin_amdgcn_rcpf((float)(n_lo - n_hi)));
+      mid = min(max(lo + (uint32_t)at, lo + 1u), hi - 1u);
+    }
+    mid = (uint32_t)__builtin_amdgcn_readfirstlane((int)mid);
+    const uint32_t c = count(mid);
+    if (c == rem) return {mid - 1u, 0u};
+    if (c > rem) {
+      lo = mid;
+      n_lo = c;
+    } else {
+      hi = mid;
+      n_hi = c;
+    }
+  }
+  return {lo, rem - n_hi};
+}
+
+// Up to 64 KPT keys in registers (one wave alone issues an instruction every five cycles or so: two a key
+// and trial, and a scan).
+template <int KPT>
+__device__ __forceinline__ WaveThreshold wave_search_regs(const uint32_t* a, int n, int bits, uint32_t rem) {
+  const int lane = threadIdx.x & 63;
+  uint32_t key[KPT];
+#pragma unroll
+  for (int j = 0; j < KPT; ++j) {
+    const uint32_t x = a[min(lane + 64 * j, n - 1)];
+    key[j] = lane + 64 * j < n ? x : 0u;
+  }
+  return wave_search(n, bits, rem, [&](uint32_t x) {
+    uint32_t c = 0;
+#pragma unroll
+    for (int j = 0; j < KPT; ++j) c += key[j] >= x ? 1u : 0u;
+    return wave_sum_u32(c);
+  });
+}
+
+// a: LDS, 16-byte aligned, with room up to the next multiple of 256 keys, which is overwritten.
+__device__ __forceinline__ WaveThreshold wave_threshold(uint32_t* a, int n, int bits, uint32_t rem) {
+  const int lane = threadIdx.x & 63;
+  n = __builtin_amdgcn_readfirstlane(n);  // (uniform, and so told to the compiler)
+  rem = (uint32_t)__builtin_amdgcn_readfirstlane((int)rem);
+  bits = __builtin_amdgcn_readfirstlane(bits);
+  if (n <= 256) return wave_search_regs<4>(a, n, bits, rem);
+  if (n <= 1024) return wave_search_regs<16>(a, n, bits, rem);
+  const int padded = (n + 255) & ~255;
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+    if (n + 64 * j + lane < padded) a[n + 64 * j + lane] = 0u;
+  wave_lds_fence();
+  return wave_search(n, bits, rem, [&](uint32_t x) {
+    uint32_t c = 0;
+#pragma unroll 4
+    for (int i = 4 * lane; i < padded; i += 256) {
+      const uint4 w = *reinterpret_cast<const uint4*>(a + i);
+      c += (w.x >= x ? 1u : 0u) + (w.y >= x ? 1u : 0u) + (w.z >= x ? 1u : 0u) + (w.w >= x ? 1u : 0u);
+    }
+    return wave_sum_u32(c);
+  });
+}
+
+// Keys of a[0, n) above T, and equal to it.
+__device__ __forceinline__ void wave_count(const uint32_t* a, int n, uint32_t T, uint32_t& gt, uint32_t& eq) {
+  const int lane = threadIdx.x & 63;
+  n = __builtin_amdgcn_readfirstlane(n);
+  uint32_t c = 0, e = 0;
+#pragma unroll 8
+  for (int i = lane; i < n; i += 64) {
+    const uint32_t x = a[i];
+    c += x > T ? 1u : 0u;
+    e += x == T ? 1u : 0u;
+  }
+  gt = wave_sum_u32(c);
+  eq = wave_sum_u32(e);
+}
+
+// The wave emits the chosen of a[0, n) in order: emit(rank, i) for every key above T and for the first need_eq equal
+// to it, eq_before equal ones having been seen before.  Returns how many.
+template <typename Emit>
+__device__ __forceinline__ int wave_choose(const uint32_t* a, int n, const WaveThreshold& t, uint32_t eq_before, Emit emit) {
+  const int lane = threadIdx.x & 63;
+  const unsigned long long below = (1ull << lane) - 1ull;
+  constexpr int kBatch = 4;
+  int rank = 0;
+  n = __builtin_amdgcn_readfirstlane(n);
+  for (int i0 = 0; i0 < n; i0 += 64 * kBatch) {
+    uint32_t x[kBatch];
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j) x[j] = a[min(i0 + 64 * j + lane, n - 1)];
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j) {
+      const int i = i0 + 64 * j + lane;
+      bool take = i < n && x[j] > t.T;
+      if (t.need_eq > 0) {  // (uniform; else nothing that equals T is chosen)
+        const unsigned long long meq = __ballot(i < n && x[j] == t.T);
+        take = take || (i < n && x[j] == t.T && eq_before + (uint32_t)__popcll(meq & below) < t.need_eq);
+        eq_before += (uint32_t)__popcll(meq);
+      }
+      const unsigned long long m = __ballot(take);
+      if (take) emit(rank + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u)), i);
+      rank += (int)__popcll(m);
+    }
+  }
+  return rank;
+}
+
 // Whole selection for S <= THREADS*C: emit(rank, pos, score) is called exactly k times, rank
 // in [0, k) ascending with pos.
 template <int THREADS, int KPT, typename Emit>
