@@ -67,7 +67,7 @@ __device__ __forceinline__ RowAddr make_row_addr(const void* k_a, const void* k_
 
 // Processes list entries r in [r0, r1): cache row = GATHER ? s_idx[r - r0] : r.  NGROUPS lane
 // groups of the block share the entries round-robin; `gid` is this lane's group.
-// s_a: REUSE_LO: the saved score of entry r at r - r0 (SCORE_BY_ROW: of cache row `row` at row).
+// s_a: REUSE_LO: the saved score of entry r at r - r0 (SCORE_BY_ROW: the key of cache row `row`, at its padded position).
 template <typename T, int NH, int NGROUPS, bool GATHER, bool REUSE_LO, bool SCORE_BY_ROW = false>
 __device__ __forceinline__ void attend_rows(AttendAcc<T, NH>& acc, const float (&qr)[NH][T::EPC],
                                             const RowAddr& ra, const int32_t* s_idx,
@@ -88,7 +88,10 @@ __device__ __forceinline__ void attend_rows(AttendAcc<T, NH>& acc, const float (
       alo[j] = 0.f;
       if (ok[j]) {
         row = GATHER ? s_idx[r - r0] : r;
-        if constexpr (REUSE_LO) alo[j] = s_a[SCORE_BY_ROW ? row : r - r0];
+        if constexpr (REUSE_LO && SCORE_BY_ROW)
+          alo[j] = key_to_float(reinterpret_cast<const uint32_t*>(s_a)[row + (row >> 5)]);
+        else if constexpr (REUSE_LO)
+          alo[j] = s_a[r - r0];
       }
       kraw[j] = (ok[j] && ra.k_load) ? load16(ra.k_base + (size_t)row * ra.k_row_bytes)
                                      : make_uint4(0, 0, 0, 0);

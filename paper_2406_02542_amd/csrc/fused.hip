@@ -16,16 +16,26 @@ constexpr int kFusedThreads = 512;
 constexpr int kFusedWaves = kFusedThreads / 64;
 constexpr int kFusedKPT = kFusedMaxS / kFusedThreads;  // keys a thread may hold in the select stage
 
-// bytes of the region that holds the rotation's partial sums (query, new key) and then the scores
-__host__ __device__ inline size_t fused_region_bytes(int S) {
-  const size_t scores = ((size_t)S * 4 + 15) & ~(size_t)15, rot = 2 * kRotParts * kD * sizeof(float);
-  return scores > rot ? scores : rot;
-}
-
 // positions per thread in the select stage: ceil(S / threads) rounded up to a multiple of 4
 __host__ __device__ inline int fused_keys_per_thread(int S) {
   const int c = (S + kFusedThreads - 1) / kFusedThreads;
   return (c + 3) & ~3;
+}
+
+// Beyond 16 keys a thread (S > 8192) the selection runs on keys in LDS, whose leading 11 bits the scoring has counted
+// (contiguous_select), else on scores read back into registers (block_select_topk_resident).  us per step, registers / LDS:
+// groups of 4, every head for itself, 512 heads, S = 12345, k = 1543 88.4 / 85.9; 256 heads, S = 12000 54.6 / 51.3; 512 heads, S
+// = 9000, d = 64, pages of unequal sequences 58.8 / 54.6; 64 heads, S = 14000 42.9 / 42.8; but 256 heads, S = 7900 72.4 /
+// 72.1, 512 groups' heads, S = 8000 58.3 / 58.4, and 8 fp32 heads, S = 1024 12.0 / 12.9, where one wave's search among
+// the candidates is a longer chain than the whole block's.
+constexpr int kFusedRegisterKeys = 16;
+__host__ __device__ inline bool fused_keys_in_lds(int S) { return fused_keys_per_thread(S) > kFusedRegisterKeys; }
+
+// bytes of the region that holds the rotation's partial sums (query, new key) and then the scores or their keys (padded)
+__host__ __device__ inline size_t fused_region_bytes(int S) {
+  const size_t words = fused_keys_in_lds(S) ? padded_words((size_t)S) : (size_t)S;
+  const size_t scores = (words * 4 + 15) & ~(size_t)15, rot = 2 * kRotParts * kD * sizeof(float);
+  return scores > rot ? scores : rot;
 }
 
 // Which (sequence, head) unit a block works on.  Uniform batches: unit = block.  Ragged batches
@@ -59,7 +69,7 @@ constexpr int kFusedMaxPages = kFusedMaxS / 256;  // pages are at least 256 rows
 // PAGED: the three slabs are pools addressed through the sequence's page list (see Paging).
 // Two blocks share a CU (4 waves per SIMD) as far as LDS allows: the register budget is 128 VGPRs and the compiler
 // is told not to trade load-level parallelism for a higher occupancy that cannot happen.  LDS allows it while the
-// dynamic part, 4 (S + k) bytes (4 S + 8 k up to 8192 rows or on a paged cache), leaves room for 22 KB of static arrays in
+// dynamic part, 4 (33/32 S + k) bytes (4 S + 8 k up to 8192 rows, 33/8 S + 8 k on a paged cache), leaves room for 18 KB of static arrays in
 // half of 160 KB: S = 12345, k = 1543 fits, S = 16384 does not, and a block has its CU to itself at the same budget.
 // KPT = keys a thread holds in the select stage (8 for S <= 4096, 16 for S <= 8192, else 32).
 // GROUPED: G query heads to a KV head, every one selecting for itself.
@@ -75,23 +85,25 @@ fused_decode_kernel(
   constexpr int LPRV = kD / EPC;
   constexpr int RPW = 64 / LPRV;
 
-  // The rotation's partial sums and then the scores, the index list, and the scores of its entries;
+  // The rotation's partial sums and then the scores' keys, the index list, and the scores of its entries;
   // long sequences (KPT = 32) leave those out, so that two blocks share a CU's LDS up to S + k = 14800,
   // and look a row's score up by its position (a paged cache's entries are pool rows and need the copy).
-  constexpr bool kScoreByRow = KPT > 16 && !PAGED;
+  constexpr bool kKeysInLds = KPT > kFusedRegisterKeys, kScoreByRow = kKeysInLds && !PAGED;
   extern __shared__ __align__(16) unsigned char dyn_smem[];
-  const int per_thread = fused_keys_per_thread(S_max);           // multiple of 4, <= KPT
+  const int per_thread = kKeysInLds ? KPT : fused_keys_per_thread(S_max);  // multiple of 4, <= KPT
   float* s_score = reinterpret_cast<float*>(dyn_smem);           // [S_max]
+  uint32_t* s_key = reinterpret_cast<uint32_t*>(dyn_smem);       // kKeysInLds: instead, padded
   float(*s_part)[kD] = reinterpret_cast<float(*)[kD]>(dyn_smem);   // [kRotParts][kD]: the query's; then the new key's
   int32_t* s_idx = reinterpret_cast<int32_t*>(dyn_smem + fused_region_bytes(S_max));  // [k_max]
-  float* s_a = kScoreByRow ? s_score : reinterpret_cast<float*>(s_idx + k_max);
+  float* s_a = kScoreByRow ? reinterpret_cast<float*>(s_key) : reinterpret_cast<float*>(s_idx + k_max);
 
   __shared__ __align__(16) float s_q[kD];
   __shared__ float s_qhat[1][kD];
   __shared__ __align__(16) float s_kn[APPEND ? kD : 4];                       // the new key
   static_assert(kFusedWaves == kRotParts, "one wave per part of the rotation");
-  __shared__ ResidentSelectSmem<kFusedThreads> s_sel;
-  __shared__ MergeSmem<kFusedWaves, 1> s_merge;
+  __shared__ __align__(16) ResidentSelectSmem<kFusedThreads> s_sel;
+  MergeSmem<kFusedWaves, 1>& s_merge = *reinterpret_cast<MergeSmem<kFusedWaves, 1>*>(&s_sel);  // behind the selection
+  static_assert(sizeof(s_merge) <= sizeof(s_sel), "the merge fits the histograms");
   __shared__ int32_t s_pages[PAGED ? kFusedMaxPages : 1];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -228,7 +240,15 @@ fused_decode_kernel(
     float qr[1][EPC];
 #pragma unroll
     for (int e = 0; e < EPC; ++e) qr[0][e] = cact ? s_qhat[0][cs * EPC + e] : 0.f;
-    auto to_lds = [&](int row, const float (&sc)[1]) { s_score[row] = sc[0]; };
+    auto to_lds = [&](int row, const float (&sc)[1]) {
+      if constexpr (kKeysInLds) {
+        const uint32_t key = float_to_key(sc[0]);
+        s_key[padded_pos(row)] = key;
+        atomicAdd(&s_sel.hist[0][key >> 21], 1u);
+      } else {
+        s_score[row] = sc[0];
+      }
+    };
     if constexpr (kPipelined)
       score_rows_pipelined<T, LPR, 1, kFusedWaves>(slab, qr, 0, S, first_trip, second_trip, to_lds);
     else
@@ -241,13 +261,17 @@ fused_decode_kernel(
   int32_t* gidx = out_idx ? out_idx + (size_t)head * k_max : nullptr;
   if (gidx)
     for (int i = k + tid; i < k_max; i += kFusedThreads) gidx[i] = -1;  // a sequence keeping fewer rows
-  block_select_topk_resident<kFusedThreads, KPT>(s_score, S, k, per_thread, s_sel,
-                                                       [&](int rank, int pos, float score) {
+  auto put = [&](int rank, int pos, float score) {
     if constexpr (PAGED) s_idx[rank] = (int32_t)slab.pool_row(pos);  // the attention stage reads pool rows
     else s_idx[rank] = pos;
     if constexpr (!kScoreByRow) s_a[rank] = score;
     if (gidx) gidx[rank] = pos;
-  });
+  };
+  if constexpr (kKeysInLds)
+    contiguous_select<kFusedThreads, KPT>(s_key, S, per_thread, k, s_sel,
+                                          [&](int rank, int pos, uint32_t key) { put(rank, pos, key_to_float(key)); });
+  else
+    block_select_topk_resident<kFusedThreads, KPT>(s_score, S, k, per_thread, s_sel, put);
   __syncthreads();
   LOKI_STAMP(6);
 
@@ -277,7 +301,7 @@ extern "C" int loki_debug_read_phase_ts(unsigned long long* host_dst, size_t cou
 #endif
 
 size_t fused_dynamic_lds(const Shape& s) {
-  const bool score_by_row = fused_keys_per_thread(s.S) > 16 && s.pg.table == nullptr;
+  const bool score_by_row = fused_keys_in_lds(s.S) && s.pg.table == nullptr;
   return fused_region_bytes(s.S) + (size_t)s.k * (score_by_row ? 4 : 8);
 }
 
@@ -328,7 +352,7 @@ bool fused_preferred(const Shape& s) {
     const double spare = heads > cus / 8 ? 6.4 * (double)(heads - cus / 8) / (double)cus : 0.0;
     return 2 * heads >= cus || mb <= 0.5 + spare * (s.S < 8192 ? s.S / 8192.0 : 1.0);
   }
-  if (heads > cus && s.G > 2 && fused_dynamic_lds(s) > 58 * 1024) return false;
+  if (heads > cus && s.G > 2 && 4 * ((size_t)s.S + (size_t)s.k * (fused_keys_in_lds(s.S) && s.pg.table == nullptr ? 1 : 2)) > 58 * 1024) return false;
   const int row_bytes = s.d * s.elem_bytes;
   if (heads > cus && row_bytes > 256) return false;
   if (heads > 2 * cus && (s.G == 8 ? row_bytes > 64 : s.G == 4 && row_bytes > 192)) return false;
@@ -350,7 +374,7 @@ static hipError_t launch_fused_k(const Shape& s, const void* q, const float* P, 
   const size_t lds = fused_dynamic_lds(s);
   static std::atomic<unsigned long long> lds_allowed{0};  // per instantiation: devices already set up
   const hipError_t ea = allow_dynamic_lds(reinterpret_cast<const void*>(kern),
-                                          (int)(kFusedMaxS * 4 + kFusedMaxK * 8), lds_allowed);
+                                          (int)(fused_region_bytes(kFusedMaxS) + kFusedMaxK * 8), lds_allowed);
   if (ea != hipSuccess) return ea;
   hipLaunchKernelGGL(kern, dim3(GROUPED ? (s.B * s.Hkv + 7) / 8 * 8 * s.G : s.B * s.Hkv), dim3(kFusedThreads), lds, st,
                      static_cast<const ST*>(klo), static_cast<const ST*>(khi),
@@ -381,7 +405,7 @@ static hipError_t launch_fused_r(const Shape& s, const void* q, const float* P, 
                                  void* v, void* out, int32_t* out_idx, hipStream_t st) {
   if (fused_keys_per_thread(s.S) <= 8)
     return launch_fused_a<T, LPR, REUSE_LO, 8>(s, q, P, klo, khi, v, out, out_idx, st);
-  if (fused_keys_per_thread(s.S) <= 16)
+  if (!fused_keys_in_lds(s.S))
     return launch_fused_a<T, LPR, REUSE_LO, 16>(s, q, P, klo, khi, v, out, out_idx, st);
   return launch_fused_a<T, LPR, REUSE_LO, kFusedKPT>(s, q, P, klo, khi, v, out, out_idx, st);
 }

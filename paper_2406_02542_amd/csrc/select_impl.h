@@ -672,6 +672,92 @@ __device__ __forceinline__ int wave_choose(const uint32_t* a, int n, const WaveT
   return rank;
 }
 
+// Whole selection of keys in LDS (padded as above) whose leading 11 bits are counted in sm.hist[0], the rest of sm
+// being clear: emit(rank, pos, key) is called exactly k times, rank in [0, k) ascending with pos.  Every thread
+// looks at its run once: the rows above the threshold's bin and the rows inside it, the candidates, become two bit
+// masks.  The candidates' keys are collected in any order, the first wave finds the exact threshold among them
+// (wave_threshold), and every thread then looks at its own candidates again.  More candidates than hist[1] holds (long
+// runs of equal scores): three digit passes over all keys (resident_threshold).
+template <int THREADS, int KPT, typename Emit>
+__device__ __forceinline__ void contiguous_select(const uint32_t* s_key, int n, int C, int k, ResidentSelectSmem<THREADS>& sm,
+                                                  Emit emit) {
+  constexpr int kWaves = THREADS / 64, kCap = 2048;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int r0 = tid * C;
+  const uint32_t* run = s_key + padded_pos(r0 < n ? r0 : 0);  // (threads without rows read the first run and mask it out)
+  const uint32_t vm = contiguous_valid_mask(n, C);
+  resident_find_bin<THREADS>(sm, 0, (uint32_t)k);
+  const uint32_t bin = sm.out[0][0], rem = sm.out[0][1];
+  const int n_cand = __builtin_amdgcn_readfirstlane((int)sm.hist[0][bin]);
+  LOKI_STAMP(13);
+  uint32_t gt = 0, eq = 0, T, need_eq;
+  if (n_cand <= kCap) {
+#pragma unroll
+    for (int e = 0; e < KPT; ++e) {
+      const uint32_t b = run[e] >> 21;
+      gt |= (b > bin ? 1u : 0u) << e;
+      eq |= (b == bin ? 1u : 0u) << e;
+    }
+    gt &= vm;
+    eq &= vm;
+    if (eq) {
+      uint32_t slot = atomicAdd(&sm.ncand, (uint32_t)__popc(eq));
+      for (uint32_t m = eq; m; m &= m - 1) sm.hist[1][slot++] = run[__ffs((int)m) - 1] & ((1u << 21) - 1u);
+    }
+    __syncthreads();
+    LOKI_STAMP(14);
+    if (wave == 0) {
+      const WaveThreshold t = wave_threshold(sm.hist[1], n_cand, 21, rem);
+      if (lane == 0) {
+        sm.out[1][0] = (bin << 21) + t.T;
+        sm.out[1][1] = t.need_eq;
+      }
+    }
+    __syncthreads();
+    T = sm.out[1][0];
+    need_eq = sm.out[1][1];
+    uint32_t m = eq;
+    eq = 0;
+    for (; m; m &= m - 1) {
+      const uint32_t x = run[__ffs((int)m) - 1], bit = m & (0u - m);
+      gt |= x > T ? bit : 0u;
+      eq |= x == T ? bit : 0u;
+    }
+  } else {
+    uint32_t key[KPT];
+#pragma unroll
+    for (int e = 0; e < KPT; ++e) key[e] = run[e];
+    __syncthreads();  // everyone has read n_cand
+    for (int i = tid; i < 2048; i += THREADS) sm.hist[0][i] = 0u;
+    __syncthreads();
+    resident_threshold<THREADS, KPT>(key, vm, (uint32_t)k, sm, T, need_eq);
+#pragma unroll
+    for (int e = 0; e < KPT; ++e) {
+      gt |= (key[e] > T ? 1u : 0u) << e;
+      eq |= (key[e] == T ? 1u : 0u) << e;
+    }
+    gt &= vm;
+    eq &= vm;
+  }
+  LOKI_STAMP(4);
+  const uint32_t mine = (uint32_t)__popc(gt) | ((uint32_t)__popc(eq) << 16);
+  const uint32_t incl = wave_inclusive_scan_u32(mine);
+  if (lane == 63) sm.wave[0][wave] = incl;  // (last read several barriers ago)
+  __syncthreads();
+  uint32_t before = incl - mine;
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) before += (w < wave) ? sm.wave[0][w] : 0u;
+  int g_rank = (int)(before & 0xffffu), e_rank = (int)(before >> 16);
+  for (uint32_t m = gt | eq; m; m &= m - 1) {
+    const int e = __ffs((int)m) - 1;
+    const bool is_eq = (eq >> e) & 1u;
+    if (!is_eq || e_rank < (int)need_eq) emit(g_rank + min(e_rank, (int)need_eq), r0 + e, run[e]);
+    g_rank += is_eq ? 0 : 1;
+    e_rank += is_eq ? 1 : 0;
+  }
+  LOKI_STAMP(12);
+}
+
 // Whole selection for S <= THREADS*C: emit(rank, pos, score) is called exactly k times, rank
 // in [0, k) ascending with pos.
 template <int THREADS, int KPT, typename Emit>

@@ -1,5 +1,5 @@
-"""Ranking of the candidates of the threshold's histogram bin in the grouped single-launch kernels: by one wave from
-registers or from LDS, or (too many of them) by further digits.  Scores are made exactly: the query is
+"""Ranking of the candidates of the threshold's histogram bin in the single-launch kernels (grouped heads; one block per
+head beyond 8192 rows): by one wave from registers or from LDS, or (too many of them) by further digits.  Scores are made exactly: the query is
 (1, 1, 1, 0, ..) under P = 1 and a row holds (1, j 2^-10, i 2^-18), so that its score, 1 + j 2^-10 + i 2^-18 < 1.25, is exact in
 fp32 and all such rows share the 11 leading key bits; rows above and below lie in other bins.  The index list
 must be the stable one to the last entry, and the result the same whether or not it is asked for."""
@@ -13,8 +13,8 @@ from tests.parity import check_out
 pytestmark = pytest.mark.gpu
 
 
-def _check(path, G, S, above, inside, chosen, kinds, first_rows, paged):
-    Hkv, D, d = 2, 128, 16
+def _check(path, G, S, above, inside, chosen, kinds, first_rows, paged, copies=1):
+    Hkv, D, d = 2, 128, 16  # (copies: of the two KV heads, where the route needs many)
     k = above + chosen
     print("case", path, G, S, above, inside, chosen, kinds, first_rows, paged, flush=True)
     rng = np.random.default_rng(S + inside + kinds)
@@ -34,6 +34,7 @@ def _check(path, G, S, above, inside, chosen, kinds, first_rows, paged):
     dt = torch.bfloat16
     kd = torch.from_numpy(kh).cuda().to(dt)[None]
     v = torch.randn((1, Hkv, S, D), generator=torch.Generator(device="cuda").manual_seed(S), device="cuda").to(dt)
+    kd, v, Hkv = kd.repeat(1, copies, 1, 1), v.repeat(1, copies, 1, 1), Hkv * copies
     q = torch.zeros((1, Hkv * G, D), device="cuda")
     q[..., :3] = 1.0
     q[:, 1::G, d:] = 0.5  # (ranks nothing: the slab has no such column)
@@ -54,16 +55,18 @@ def _check(path, G, S, above, inside, chosen, kinds, first_rows, paged):
         klo, khi, vv = to_pool(klo), to_pool(khi), to_pool(v)
         step = dict(page_table=table, page_rows=256, n_pages=n + 2)
     lay = api.make_layout(1, Hkv * G, Hkv, D, d, S, dt)
-    ws = api.alloc_workspace(lay, S, d, k, 1)
+    mode = 1 if G > 1 else 0
+    ws = api.alloc_workspace(lay, S, d, k, mode)
     idx = torch.full((1, Hkv, k), -7, dtype=torch.int32, device="cuda")
     outs = []
     for want in (idx, None):
         out = torch.full((1, Hkv * G, D), float("nan"), dtype=dt, device="cuda")
-        api.loki_decode_step(lay, q, P, klo, khi, vv, S, d, k, 1 | path, ws, out, want, **step)
+        api.loki_decode_step(lay, q, P, klo, khi, vv, S, d, k, mode | path, ws, out, want, **step)
         outs.append(out)
     torch.cuda.synchronize()
     assert torch.equal(outs[0], outs[1])
-    for h in range(Hkv):
+    assert torch.equal(idx, idx[:, :2].repeat(1, copies, 1))
+    for h in range(2):
         sel = np.sort(np.argsort(-score[h], kind="stable")[:k])
         assert np.array_equal(idx[0, h].cpu().numpy(), sel)
         rows, val = kd[0, h].double().cpu().numpy()[sel], v[0, h].double().cpu().numpy()[sel]
@@ -92,3 +95,12 @@ def test_candidates_one_block(S, above, inside, chosen, kinds, paged):
     (40000, 3000, 30000, 1, 30000, False)])
 def test_candidates_several_blocks(S, above, inside, chosen, kinds, first):
     _check(api.PATH_CLUSTER, 8 if S < 10000 else 2, S, above, inside, chosen, kinds, first, S <= 16000 and chosen % 2 == 0)
+
+
+# one block per head, keys in LDS: lists of up to 2048 candidates
+@pytest.mark.parametrize("S,above,inside,chosen,kinds,paged", [
+    (8193, 0, 1, 1, 9, False), (9000, 700, 256, 255, 999, True), (9000, 700, 1024, 1, 9999, False), (12000, 64, 1025, 600, 9999, False),
+    (9000, 64, 2048, 1000, 9999, True), (9000, 64, 2049, 1000, 9999, False), (9000, 900, 1900, 700, 2, False),
+    (9000, 900, 1900, 1100, 1, False), (9000, 0, 9000, 2048, 9999, False)])
+def test_candidates_one_block_per_head(S, above, inside, chosen, kinds, paged):
+    _check(0, 1, S, above, inside, chosen, kinds, False, paged, copies=64)
