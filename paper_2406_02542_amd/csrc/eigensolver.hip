@@ -122,51 +122,59 @@ __device__ __forceinline__ double fast_rsqrt_f64(double x) {  // likewise
 // all waves keep live rows to the end, every wave sees whole rows (norms and dot products need no
 // exchange) and a row's value read from LDS serves two columns.  Reflector j is u = x - beta e(j+1)
 // with x the row's part beyond j (zeros up to j) and H = I - u u^T / h: u differs from x in one
-// place, so the product with A starts on x while the norm is still being taken.  A step is two
-// barriers: one for p = A u (summed over the waves), one for the next row.  Measured, 32 heads:
-// 131 us; as two 64-row halves with four barriers a step, the library's square root and divisions and a
-// branch around every group of rows 197 us.
+// place, so the product with A starts on x while the norm is still being taken.  A step is one
+// barrier, behind which the four partial sums of p = A u and row j + 1 as it was are in LDS: every wave then has
+// all of p and brings that row up to date for itself, so the next step begins without an exchange.  What bounds it is the
+// chain of a step (two sums over a wave, a square root, a reciprocal), about 2000 cycles.  Measured, 32 heads:
+// TRI_NEW us; with a second barrier, for the next row from the wave that owns it, 131; with eight waves and that barrier 146; as
+// two 64-row halves with four barriers a step, the library's square root and divisions and a branch around every
+// group of rows 197.
 __global__ __launch_bounds__(kEigThreads) void tridiag_kernel(EigBufs bufs) {
   constexpr int kWaves = kEigThreads / 64, kRows = kD / kWaves, kPitch = kRows + 2;
   constexpr int kChunk = 4;  // rows of a wave that are skipped together once they are done
-  __shared__ __align__(16) double s_xx[2][kWaves][kPitch], s_p[kWaves][kD], s_pr[kWaves][kPitch];  // (rows take turns)
+  static_assert(kWaves == 4, "four partial sums");
+  // (a wave is at most one barrier ahead of another: two sets take turns)
+  __shared__ __align__(16) double s_p[2][kWaves][kD], s_row[2][kD];
+  __shared__ __align__(16) double s_pr[kWaves][kPitch], s_xr[kWaves][kPitch];  // a wave's own rows, for itself
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, head = blockIdx.x;
   const double* C = bufs.cov + (size_t)head * kD * kD;
   double* tri = eig_tri(bufs, head);
   double* refl = eig_refl(bufs, head);
   if (tid == 0) bufs.state[head] = 0;
 
-  double a[kRows][2];
+  double a[kRows][2], x[2];
 #pragma unroll
   for (int u = 0; u < kRows; ++u)
 #pragma unroll
     for (int h = 0; h < 2; ++h) a[u][h] = C[(size_t)(kWaves * u + wave) * kD + lane + 64 * h];
-  // row `row` goes to LDS for step `row`: its entries beyond the diagonal; the diagonal is done
-  auto leave_row = [&](int row, const double (&x)[2]) {
-    double(*s_x)[kPitch] = s_xx[row & 1];
+  // `row` up to date: its entries beyond the diagonal become x, the diagonal is done
+  auto take_row = [&](int row, const double (&v)[2]) {
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       const int c = lane + 64 * h;
-      s_x[c % kWaves][c / kWaves] = c > row ? x[h] : 0.0;
-      if (c == row) tri[row] = x[h];
+      x[h] = c > row ? v[h] : 0.0;
+      if (wave == 0 && c == row) tri[row] = v[h];
+      if (c % kWaves == wave) s_xr[wave][c / kWaves] = x[h];
     }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
   };
-  if (wave == 0) leave_row(0, a[0]);
-  __syncthreads();
+  auto at_column = [&](const double (&v)[2], int c) { return readlane_f64(c < 64 ? v[0] : v[1], c & 63); };
+  {
+    const double first[2] = {C[lane], C[lane + 64]};
+    take_row(0, first);
+  }
 
   // the steps whose next row lies in rows 16 seg .. 16 seg + 15: straight-line code over the live rows
   auto steps = [&](auto seg) {
     constexpr int kLive = decltype(seg)::value * kChunk;  // first live row index of a wave
     for (int j = max(kWaves * kLive - 1, 0); j < min(kWaves * (kLive + kChunk) - 1, kD - 2); ++j) {
-      const double(*s_x)[kPitch] = s_xx[j & 1];
-      const int next = j + 1, next_wave = next % kWaves, next_u = next / kWaves;
-      double x[2], u[2], xr[kRows], p[2] = {0.0, 0.0}, p2[2] = {0.0, 0.0};
-#pragma unroll
-      for (int h = 0; h < 2; ++h) x[h] = s_x[lane % kWaves][(lane + 64 * h) / kWaves];
-      const double alpha = s_x[next_wave][next_u];
+      const int next = j + 1, next_wave = next % kWaves, next_u = next / kWaves, set = j & 1;
+      double u[2], xr[kRows], p[2] = {0.0, 0.0}, p2[2] = {0.0, 0.0};
+      const double alpha = at_column(x, next);
 #pragma unroll
       for (int i = kLive; i < kRows; i += 2) {
-        const double2 v = *reinterpret_cast<const double2*>(&s_x[wave][i]);
+        const double2 v = *reinterpret_cast<const double2*>(&s_xr[wave][i]);
         xr[i] = v.x;
         xr[i + 1] = v.y;
       }
@@ -176,6 +184,7 @@ __global__ __launch_bounds__(kEigThreads) void tridiag_kernel(EigBufs bufs) {
         sel[h] = a[kLive][h];
 #pragma unroll
         for (int i = kLive + 1; i < kLive + kChunk; ++i) sel[h] = i == next_u ? a[i][h] : sel[h];
+        if (wave == next_wave) s_row[set][lane + 64 * h] = sel[h];
         sel[h] = wave == next_wave ? sel[h] : 0.0;
       }
       const double t0 = lane > next ? x[0] : 0.0, t1 = lane + 64 > next ? x[1] : 0.0;
@@ -198,7 +207,7 @@ __global__ __launch_bounds__(kEigThreads) void tridiag_kernel(EigBufs bufs) {
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
         u[h] = lane + 64 * h == next ? top : x[h];
-        s_p[wave][lane + 64 * h] = fma(-beta, sel[h], p[h] + p2[h]);
+        s_p[set][wave][lane + 64 * h] = fma(-beta, sel[h], p[h] + p2[h]);
       }
       if (wave == 0) {
 #pragma unroll
@@ -209,25 +218,26 @@ __global__ __launch_bounds__(kEigThreads) void tridiag_kernel(EigBufs bufs) {
         }
       }
       __syncthreads();
+      double row[2];
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
         const int c = lane + 64 * h;
-        p[h] = (s_p[0][c] + s_p[1][c]) + (s_p[2][c] + s_p[3][c]);
-        if (c % kWaves == wave) s_pr[wave][c / kWaves] = p[h];  // this wave's rows, for itself
+        row[h] = s_row[set][c];
+        p[h] = (s_p[set][0][c] + s_p[set][1][c]) + (s_p[set][2][c] + s_p[set][3][c]);
+        if (c % kWaves == wave) s_pr[wave][c / kWaves] = p[h];
       }
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       __builtin_amdgcn_wave_barrier();
       // A -= u w^T + w u^T with w = p / h - k u: row r, column c lose u_r (p_c / h - 2 k u_c) + p_r u_c / h
       const double k2 = inv_h * inv_h * wave_sum_f64(fma(p[0], u[0], p[1] * u[1]));
-      const double pn = s_pr[wave][next_u];
+      const double pn = at_column(p, next);
       double f[2], g[2];
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
         f[h] = fma(-k2, u[h], p[h] * inv_h);
         g[h] = inv_h * u[h];
-        sel[h] = fma(-top, f[h], fma(-pn, g[h], sel[h]));
+        row[h] = fma(-top, f[h], fma(-pn, g[h], row[h]));
       }
-      if (wave == next_wave) leave_row(next, sel);
 #pragma unroll
       for (int i = kLive; i < kRows; i += 2) {  // (row j + 1, where u is not x, is done)
         const double2 pr = *reinterpret_cast<const double2*>(&s_pr[wave][i]);
@@ -237,7 +247,7 @@ __global__ __launch_bounds__(kEigThreads) void tridiag_kernel(EigBufs bufs) {
           a[i + 1][h] = fma(-xr[i + 1], f[h], fma(-pr.y, g[h], a[i + 1][h]));
         }
       }
-      __syncthreads();
+      take_row(next, row);
     }
   };
   steps(std::integral_constant<int, 0>{});
@@ -249,8 +259,8 @@ __global__ __launch_bounds__(kEigThreads) void tridiag_kernel(EigBufs bufs) {
   steps(std::integral_constant<int, 6>{});
   steps(std::integral_constant<int, 7>{});
   static_assert(kRows == 8 * kChunk, "eight segments");
-  // rows 126 (left in s_x) and 127
-  if (tid == 0) tri[kD + kD - 2] = s_xx[kD & 1][(kD - 1) % kWaves][(kD - 1) / kWaves];
+  // rows 126 (left in x) and 127
+  if (tid == 63) tri[kD + kD - 2] = x[1];
   if (tid == kEigThreads - 1) tri[kD - 1] = a[kRows - 1][1];
 }
 
