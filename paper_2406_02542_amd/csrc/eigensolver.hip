@@ -17,8 +17,8 @@
 // What bounds it: chains of dependent fp64 steps, not throughput (4 M multiply-adds per head and
 // product).  Jacobi alone, one block per head, needed 12 sweeps of 127 rounds at 2.1 us a round and
 // 74 us a sweep more for the vectors: 4.1 of the 4.23 ms of a fit of 32 heads x 65536 keys, now
-// 0.40 ms (tridiag 131 us, eigvec 89, orthonormalise 14, project 15, the five Jacobi launches 23,
-// finish 7; the Gram pass 130).  Tridiagonalisation is 126 steps of two barriers, and everything
+// 0.36 ms (tridiag 125 us, eigvec 89, orthonormalise 14, project 15, the five Jacobi launches 23,
+// finish 7; the Gram pass 96).  Tridiagonalisation is 126 steps of one barrier, and everything
 // behind it is spread over 8 blocks per head.
 #include "eigensolver.h"
 
@@ -126,7 +126,7 @@ __device__ __forceinline__ double fast_rsqrt_f64(double x) {  // likewise
 // barrier, behind which the four partial sums of p = A u and row j + 1 as it was are in LDS: every wave then has
 // all of p and brings that row up to date for itself, so the next step begins without an exchange.  What bounds it is the
 // chain of a step (two sums over a wave, a square root, a reciprocal), about 2000 cycles.  Measured, 32 heads:
-// TRI_NEW us; with a second barrier, for the next row from the wave that owns it, 131; with eight waves and that barrier 146; as
+// 125 us; with a second barrier, for the next row from the wave that owns it, 131; with eight waves and that barrier 146; as
 // two 64-row halves with four barriers a step, the library's square root and divisions and a branch around every
 // group of rows 197.
 __global__ __launch_bounds__(kEigThreads) void tridiag_kernel(EigBufs bufs) {
