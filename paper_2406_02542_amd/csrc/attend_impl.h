@@ -65,6 +65,54 @@ __device__ __forceinline__ RowAddr make_row_addr(const void* k_a, const void* k_
   return ra;
 }
 
+// One trip: R rows of this lane group (ok: the row exists), their chunks and saved scores loaded.
+template <typename T, int NH, int R, bool REUSE_LO>
+__device__ __forceinline__ void attend_trip(AttendAcc<T, NH>& acc, const float (&qr)[NH][T::EPC], const uint4 (&kraw)[R],
+                                            const uint4 (&vraw)[R], const float (&alo)[R], const bool (&ok)[R]) {
+  constexpr int EPC = T::EPC;
+  constexpr int LPRV = kD / EPC;
+  float logit[NH][R];
+#pragma unroll
+  for (int j = 0; j < R; ++j) {
+    float kf[EPC];
+    T::unpack(kraw[j], kf);
+#pragma unroll
+    for (int g = 0; g < NH; ++g) {
+      float p = 0.f;
+#pragma unroll
+      for (int e = 0; e < EPC; ++e) p = fmaf(kf[e], qr[g][e], p);
+      p = group_allreduce_sum<LPRV>(p);
+      if constexpr (REUSE_LO) p += alo[j];
+      logit[g][j] = ok[j] ? p * kSoftmaxScaleLog2 : kNegBig;
+    }
+  }
+  float vf[R][EPC];
+#pragma unroll
+  for (int j = 0; j < R; ++j) T::unpack(vraw[j], vf[j]);
+#pragma unroll
+  for (int g = 0; g < NH; ++g) {
+    float mn = acc.m[g];
+#pragma unroll
+    for (int j = 0; j < R; ++j) mn = fmaxf(mn, logit[g][j]);
+    const float corr = fast_exp2(acc.m[g] - mn);
+    acc.m[g] = mn;
+    float pj[R], ps = 0.f;
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+      pj[j] = ok[j] ? fast_exp2(logit[g][j] - mn) : 0.f;
+      ps += pj[j];
+    }
+    acc.l[g] = fmaf(acc.l[g], corr, ps);
+#pragma unroll
+    for (int e = 0; e < EPC; ++e) {
+      float a = acc.o[g][e] * corr;
+#pragma unroll
+      for (int j = 0; j < R; ++j) a = fmaf(pj[j], vf[j][e], a);
+      acc.o[g][e] = a;
+    }
+  }
+}
+
 // Processes list entries r in [r0, r1): cache row = GATHER ? s_idx[r - r0] : r.  NGROUPS lane
 // groups of the block share the entries round-robin; `gid` is this lane's group.
 // s_a: REUSE_LO: the saved score of entry r at r - r0 (SCORE_BY_ROW: the key of cache row `row`, at its padded position).
@@ -72,8 +120,6 @@ template <typename T, int NH, int NGROUPS, bool GATHER, bool REUSE_LO, bool SCOR
 __device__ __forceinline__ void attend_rows(AttendAcc<T, NH>& acc, const float (&qr)[NH][T::EPC],
                                             const RowAddr& ra, const int32_t* s_idx,
                                             const float* s_a, int gid, int r0, int r1) {
-  constexpr int EPC = T::EPC;
-  constexpr int LPRV = kD / EPC;
   constexpr int R = kRowsInFlight;
   static_assert(!REUSE_LO || NH == 1, "score reuse needs one query head per selection");
   for (int t0 = r0; t0 < r1; t0 += NGROUPS * R) {
@@ -97,46 +143,51 @@ __device__ __forceinline__ void attend_rows(AttendAcc<T, NH>& acc, const float (
                                      : make_uint4(0, 0, 0, 0);
       vraw[j] = ok[j] ? load16(ra.v_base + (size_t)row * ra.v_row_bytes) : make_uint4(0, 0, 0, 0);
     }
-    float logit[NH][R];
+    attend_trip<T, NH, R, REUSE_LO>(acc, qr, kraw, vraw, alo, ok);
+  }
+}
+
+// The same over a list that is still growing: entries below `there` exist when the call begins, and those of the
+// first trip are loaded before complete(), which completes the list (every wave calls it once).  R: rows of a lane
+// group in flight; a launch of one block per CU or less waits for the latency of every trip.
+template <typename T, int NH, int NGROUPS, bool REUSE_LO, int R, typename Complete>
+__device__ __forceinline__ void attend_growing(AttendAcc<T, NH>& acc, const float (&qr)[NH][T::EPC],
+                                               const RowAddr& ra, const int32_t* s_idx, const float* s_a, int gid,
+                                               int r0, int r1, int there, Complete complete) {
+  uint4 kraw[R], vraw[R];
+  float alo[R];
+  auto clear = [&]() {
 #pragma unroll
     for (int j = 0; j < R; ++j) {
-      float kf[EPC];
-      T::unpack(kraw[j], kf);
+      kraw[j] = vraw[j] = make_uint4(0, 0, 0, 0);
+      alo[j] = 0.f;
+    }
+  };
+  auto load = [&](int t0, int lo, int hi) {  // the trip's entries in [lo, hi)
 #pragma unroll
-      for (int g = 0; g < NH; ++g) {
-        float p = 0.f;
-#pragma unroll
-        for (int e = 0; e < EPC; ++e) p = fmaf(kf[e], qr[g][e], p);
-        p = group_allreduce_sum<LPRV>(p);
-        if constexpr (REUSE_LO) p += alo[j];
-        logit[g][j] = ok[j] ? p * kSoftmaxScaleLog2 : kNegBig;
+    for (int j = 0; j < R; ++j) {
+      const int r = t0 + j * NGROUPS + gid;
+      if (r >= lo && r < hi) {
+        const int row = s_idx[r - r0];
+        if constexpr (REUSE_LO) alo[j] = s_a[r - r0];
+        if (ra.k_load) kraw[j] = load16(ra.k_base + (size_t)row * ra.k_row_bytes);
+        vraw[j] = load16(ra.v_base + (size_t)row * ra.v_row_bytes);
       }
     }
-    float vf[R][EPC];
-#pragma unroll
-    for (int j = 0; j < R; ++j) T::unpack(vraw[j], vf[j]);
-#pragma unroll
-    for (int g = 0; g < NH; ++g) {
-      float mn = acc.m[g];
-#pragma unroll
-      for (int j = 0; j < R; ++j) mn = fmaxf(mn, logit[g][j]);
-      const float corr = fast_exp2(acc.m[g] - mn);
-      acc.m[g] = mn;
-      float pj[R], ps = 0.f;
-#pragma unroll
-      for (int j = 0; j < R; ++j) {
-        pj[j] = ok[j] ? fast_exp2(logit[g][j] - mn) : 0.f;
-        ps += pj[j];
-      }
-      acc.l[g] = fmaf(acc.l[g], corr, ps);
-#pragma unroll
-      for (int e = 0; e < EPC; ++e) {
-        float a = acc.o[g][e] * corr;
-#pragma unroll
-        for (int j = 0; j < R; ++j) a = fmaf(pj[j], vf[j][e], a);
-        acc.o[g][e] = a;
-      }
+  };
+  clear();
+  if (there > r0) load(r0, r0, min(r1, there));
+  complete();
+  if (there < r1) load(r0, max(r0, there), r1);
+  for (int t0 = r0; t0 < r1; t0 += NGROUPS * R) {
+    if (t0 > r0) {
+      clear();
+      load(t0, r0, r1);
     }
+    bool ok[R];
+#pragma unroll
+    for (int j = 0; j < R; ++j) ok[j] = t0 + j * NGROUPS + gid < r1;
+    attend_trip<T, NH, R, REUSE_LO>(acc, qr, kraw, vraw, alo, ok);
   }
 }
 

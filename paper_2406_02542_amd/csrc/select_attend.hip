@@ -62,6 +62,77 @@ __device__ __forceinline__ void select_share(const SelectAttendArgs& a, int sel,
   __syncthreads();
 }
 
+// The same selection in two parts, so that the attention can begin in between (GROWING): begin() leaves the entries
+// that are certain, below the value returned; complete() appends the chosen candidates, ranked by the first wave while every
+// wave has its first rows' loads in flight, and writes the caller's ascending copy.  The list is two ascending
+// runs, or one where the bin held too many candidates.
+template <int KPT>
+struct SelectShare {
+  RunKeys<KPT> keys;
+  RunSelect rs;
+  int32_t* user;
+  bool ordered;
+
+  __device__ __forceinline__ int32_t row_of(const SelectAttendArgs& a, int hkv, const int32_t* s_pages, int pos) const {
+    const int lg = a.pg.lg_rows;
+    return a.pg.table != nullptr ? ((s_pages[pos >> lg] * a.Hkv + hkv) << lg) | (pos & ((1 << lg) - 1)) : pos;
+  }
+
+  __device__ __forceinline__ int begin(const SelectAttendArgs& a, int sel, int b, int hkv, int S, int k, int r0, int r1,
+                                       bool write_user, ResidentSelectSmem<kSaThreads>& sm, int32_t* s_pages, int32_t* s_idx,
+                                       float* s_a) {
+    run_load_keys<KPT>(a.scores + (size_t)sel * a.S_max, S, a.per_thread, keys);
+    user = write_user && a.user_idx != nullptr ? a.user_idx + (size_t)sel * a.k_max : nullptr;
+    if (user)
+      for (int i = k + (int)threadIdx.x; i < a.k_max; i += kSaThreads) user[i] = -1;  // a sequence keeping fewer rows
+    // a paged cache: the pages of the sequence's rows, clamped into the pool
+    if (a.pg.table != nullptr && (int)threadIdx.x <= (S - 1) >> a.pg.lg_rows) {
+      const int32_t* table = a.pg.table + (size_t)(b / max(a.rg.queries, 1)) * a.pg.pages_per_seq;
+      s_pages[threadIdx.x] = min(max(table[threadIdx.x], 0), a.pg.n_pages - 1);
+    }
+    resident_select_clear<kSaThreads>(sm);
+    __syncthreads();
+    LOKI_STAMP(1);
+    rs = run_select_certain<kSaThreads, KPT>(keys, k, sm, true, [&](int rank, int pos, uint32_t key) {
+      if (rank >= r0 && rank < r1) {
+        s_idx[rank - r0] = row_of(a, hkv, s_pages, pos);
+        if (s_a) s_a[rank - r0] = key_to_float(key);
+      }
+    });
+    LOKI_STAMP(12);
+    ordered = rs.n_cand == 0;
+    return ordered ? 0 : rs.n_def;
+  }
+
+  __device__ __forceinline__ void complete(const SelectAttendArgs& a, int hkv, int r0, int r1, ResidentSelectSmem<kSaThreads>& sm,
+                                           const int32_t* s_pages, int32_t* s_idx, float* s_a) {
+    __shared__ WaveThreshold s_t;
+    auto put = [&](int rank, int pos, uint32_t key) {
+      if (rank >= r0 && rank < r1) {
+        s_idx[rank - r0] = row_of(a, hkv, s_pages, pos);
+        if (s_a) s_a[rank - r0] = key_to_float(key);
+      }
+    };
+    if (threadIdx.x < 64) {
+      const WaveThreshold t = run_threshold<kSaThreads>(rs, sm);
+      if (threadIdx.x == 0) s_t = t;
+      if (!ordered)
+        wave_choose(sm.hist[1], rs.n_cand, WaveThreshold{t.T - (rs.bin << 21), t.need_eq}, 0u, [&](int rank, int i) {
+          put(rs.n_def + rank, (int)sm.hist[1][kRunCand + i], (rs.bin << 21) | sm.hist[1][i]);
+        });
+    }
+    __syncthreads();
+    if (ordered || user) {  // (uniform)
+      run_emit<kSaThreads, KPT>(keys, s_t, sm, [&](int rank, int pos, uint32_t key) {
+        if (user) user[rank] = pos;
+        if (ordered) put(rank, pos, key);
+      });
+      __syncthreads();
+    }
+    LOKI_STAMP(6);
+  }
+};
+
 // The block's merged (max, sum, output) of NH heads: the result, or its part of it, merged by the
 // block of the head group that finishes last (see splits_all_done).
 template <typename T, int NH>
@@ -99,7 +170,7 @@ __device__ __forceinline__ void share_of(int k, int nsplit, int split, int& r0, 
 
 // Vector form.  NH = query heads that share a selection; with one, the ranking score is the
 // low-rank part of the logit and the slab is not read again (REUSE_LO).
-template <typename T, int NH, int KPT>
+template <typename T, int NH, int KPT, bool GROWING>
 __global__ __launch_bounds__(kSaThreads, NH == 1 ? 4 : 2) void select_attend_kernel(
     const void* __restrict__ klo, const void* __restrict__ khi, const void* __restrict__ v,
     const float* __restrict__ qhat, typename T::store_t* __restrict__ out, SelectAttendArgs a) {
@@ -137,13 +208,22 @@ __global__ __launch_bounds__(kSaThreads, NH == 1 ? 4 : 2) void select_attend_ker
   for (int g = 0; g < NH; ++g)
 #pragma unroll
     for (int e = 0; e < EPC; ++e) qr[g][e] = qhat[(head0 + g) * kD + c * EPC + e];
-  select_share<KPT>(a, sel, b, hkv, S, k, r0, r1, split == 0, s_sel, s_idx, REUSE_LO ? s_a : nullptr);
+  float* score = REUSE_LO ? s_a : nullptr;
+  __shared__ int32_t s_pages[GROWING ? kSaThreads * KPT / 256 : 1];
+  SelectShare<KPT> share;
+  int there = 0;
+  if constexpr (GROWING) there = share.begin(a, sel, b, hkv, S, k, r0, r1, split == 0, s_sel, s_pages, s_idx, score);
+  else select_share<KPT>(a, sel, b, hkv, S, k, r0, r1, split == 0, s_sel, s_idx, score);
 
   const size_t unit = a.pg.table != nullptr ? (size_t)0 : (size_t)cache_unit(a.rg, b * a.Hkv + hkv, a.Hkv);
   const RowAddr ra = make_row_addr<T, REUSE_LO>(klo, khi, v, unit, a.S_cap, a.d, c);
   AttendAcc<T, NH> acc;
   acc.init();
-  attend_rows<T, NH, kSaWaves * RPW, true, REUSE_LO>(acc, qr, ra, s_idx, s_a, wave * RPW + rg, r0, r1);
+  if constexpr (GROWING)
+    attend_growing<T, NH, kSaWaves * RPW, REUSE_LO, kRowsInFlight>(
+        acc, qr, ra, s_idx, s_a, wave * RPW + rg, r0, r1, there, [&] { share.complete(a, hkv, r0, r1, s_sel, s_pages, s_idx, score); });
+  else
+    attend_rows<T, NH, kSaWaves * RPW, true, REUSE_LO>(acc, qr, ra, s_idx, s_a, wave * RPW + rg, r0, r1);
   attend_publish<T, NH, kSaWaves>(acc, s_merge);
   finish_share<T, NH>(a, s_merge, head0, sel, split, out);
 }
@@ -167,7 +247,9 @@ __global__ __launch_bounds__(kSaThreads, 2) void select_attend_mfma_kernel(
   int r0, r1;
   share_of(k, a.nsplit, split, r0, r1);
 
-  select_share<KPT>(a, unit, b, unit % a.Hkv, S, k, r0, r1, split == 0, s_sel, s_idx, nullptr);
+  __shared__ int32_t s_pages[kSaThreads * KPT / 256];
+  SelectShare<KPT> share;
+  const int there = share.begin(a, unit, b, unit % a.Hkv, S, k, r0, r1, split == 0, s_sel, s_pages, s_idx, nullptr);
 
   am_bf16x8_t bq[4][2];
   am_query_operands<4, 2>(qhat + (head0 + (head_ok ? r16 : 0)) * kD, head_ok, kD, bq);
@@ -175,7 +257,8 @@ __global__ __launch_bounds__(kSaThreads, 2) void select_attend_mfma_kernel(
   const AmAddr<4> ad = am_make_addr<4, false>(klo, khi, v, addr_unit, a.S_cap, a.d);
   AmState st;
   st.init();
-  am_attend_rows<true, 4, 2>(ad, bq, s_idx, r0, AmRoundRobin<kSaWaves>(r0, r1), st, [] {});
+  am_attend_rows<true, 4, 2>(ad, bq, s_idx, r0, AmRoundRobin<kSaWaves>(r0, r1, there), st,
+                             [&] { share.complete(a, unit % a.Hkv, r0, r1, s_sel, s_pages, s_idx, nullptr); });
   am_publish<NH, kSaWaves>(st, s_merge);
   finish_share<BF16, NH>(a, s_merge, head0, unit, split, out);
 }
@@ -221,17 +304,31 @@ bool select_attend_applies(const Shape& s, int select_mode) {
   return n == 1 || one_round || (n == 2 && s.rg.queries <= 1);
 }
 
+template <typename T, int NH, bool GROWING>
+static hipError_t launch_sa_g(const SelectAttendArgs& a, dim3 grid, const void* klo, const void* khi, const void* v,
+                              const float* qhat, void* out, hipStream_t st) {
+  auto* o = static_cast<typename T::store_t*>(out);
+  if (a.per_thread <= 8)
+    hipLaunchKernelGGL((select_attend_kernel<T, NH, 8, GROWING>), grid, dim3(kSaThreads), 0, st, klo, khi, v, qhat, o, a);
+  else if (a.per_thread <= 16)
+    hipLaunchKernelGGL((select_attend_kernel<T, NH, 16, GROWING>), grid, dim3(kSaThreads), 0, st, klo, khi, v, qhat, o, a);
+  else
+    hipLaunchKernelGGL((select_attend_kernel<T, NH, 32, GROWING>), grid, dim3(kSaThreads), 0, st, klo, khi, v, qhat, o, a);
+  return hipGetLastError();
+}
+
+// Attention that begins before the list is complete: where its blocks wait for memory and nothing else runs beside them (one
+// round of blocks, bf16), and the heads do not share their rows (which walk them in step in one ascending list).  us per
+// step, apart / begun early: 32 heads, S = 4096, k = 1024 19.1 / 18.2; 16 heads, S = 7544, k = 471 21.9 / 21.3; on the matrix
+// cores, always one round, 32/8 heads, S = 8192 21.4 / 20.8, 4 tokens of 32/8 heads, S = 4374 27.6 / 27.0; but fp32, 24 heads, S = 3473, k =
+// 217 17.4 / 18.3, and 2 tokens of 4 sequences, S = 1920 24.5 / 25.5.
 template <typename T, int NH>
 static hipError_t launch_sa(const SelectAttendArgs& a, dim3 grid, const void* klo, const void* khi, const void* v,
                             const float* qhat, void* out, hipStream_t st) {
-  auto* o = static_cast<typename T::store_t*>(out);
-  if (a.per_thread <= 8)
-    hipLaunchKernelGGL((select_attend_kernel<T, NH, 8>), grid, dim3(kSaThreads), 0, st, klo, khi, v, qhat, o, a);
-  else if (a.per_thread <= 16)
-    hipLaunchKernelGGL((select_attend_kernel<T, NH, 16>), grid, dim3(kSaThreads), 0, st, klo, khi, v, qhat, o, a);
-  else
-    hipLaunchKernelGGL((select_attend_kernel<T, NH, 32>), grid, dim3(kSaThreads), 0, st, klo, khi, v, qhat, o, a);
-  return hipGetLastError();
+  if constexpr (T::kBytes == 2 && NH == 1)
+    if (a.xcd_group_blocks == 0 && (int)(grid.x * grid.y) <= device_cus())
+      return launch_sa_g<T, NH, true>(a, grid, klo, khi, v, qhat, out, st);
+  return launch_sa_g<T, NH, false>(a, grid, klo, khi, v, qhat, out, st);
 }
 
 template <int NH>

@@ -758,6 +758,148 @@ __device__ __forceinline__ void contiguous_select(const uint32_t* s_key, int n, 
   LOKI_STAMP(12);
 }
 
+// ---- selection of keys that the block's threads hold, in two parts --------------------------------
+// Thread t holds positions [t C, (t + 1) C) (C <= KPT, a multiple of 4), so ranks follow the thread order.
+//   run_select_certain  one digit histogram: the rows above the threshold's bin are certain; the bin's rows, the
+//                       candidates, go to a list of their own.  Three barriers, and one at the end
+//   run_threshold       the exact threshold among the candidates, by one wave, without a barrier, so that a caller can
+//                       have the certain rows' loads in flight
+// A bin of more than kRunCand rows (long runs of nearly equal scores) makes run_select_certain find the exact
+// threshold with resident_threshold.
+constexpr int kRunCand = 1024;
+
+template <int KPT>
+struct RunKeys {
+  uint32_t key[KPT];
+  uint32_t valid;  // bit i: key[i] exists
+  int pos0;
+};
+
+struct RunSelect {
+  int n_def;          // certain rows
+  int n_cand;         // candidates listed (0: the threshold is known)
+  uint32_t bin, rem;  // the threshold's bin; rows needed from it
+  WaveThreshold t;    // on whole keys, once known
+};
+
+template <int KPT>
+__device__ __forceinline__ void run_load_keys(const float* a, int n, int C, RunKeys<KPT>& rk) {
+  const int p0 = (int)threadIdx.x * C;
+  const bool aligned = (reinterpret_cast<uintptr_t>(a) & 15u) == 0;  // (uniform)
+  rk.pos0 = p0;
+  const int nv = max(0, min(C, n - p0));
+  rk.valid = nv >= 32 ? 0xffffffffu : ((1u << nv) - 1u);
+#pragma unroll
+  for (int i = 0; i < KPT; i += 4) {
+    float4 f = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (i < C) {
+      if (aligned && p0 + i + 3 < n) {
+        f = *reinterpret_cast<const float4*>(a + p0 + i);
+      } else {
+        if (p0 + i < n) f.x = a[p0 + i];
+        if (p0 + i + 1 < n) f.y = a[p0 + i + 1];
+        if (p0 + i + 2 < n) f.z = a[p0 + i + 2];
+        if (p0 + i + 3 < n) f.w = a[p0 + i + 3];
+      }
+    }
+    rk.key[i] = float_to_key(f.x);
+    rk.key[i + 1] = float_to_key(f.y);
+    rk.key[i + 2] = float_to_key(f.z);
+    rk.key[i + 3] = float_to_key(f.w);
+  }
+}
+
+// Keys whose leading bits exceed thr / equal it, and the block-wide ranks of this thread's first ones (one
+// barrier; wave_tot: a word per wave that nobody else touches until the next barrier).
+template <int THREADS, int KPT>
+__device__ __forceinline__ void run_partition(const RunKeys<KPT>& rk, int shift, uint32_t thr, uint32_t* wave_tot,
+                                              uint32_t& gt, uint32_t& eq, int& g_rank, int& e_rank) {
+  constexpr int kWaves = THREADS / 64;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  gt = eq = 0;
+#pragma unroll
+  for (int i = 0; i < KPT; ++i) {
+    const uint32_t b = rk.key[i] >> shift;
+    gt |= (b > thr ? 1u : 0u) << i;
+    eq |= (b == thr ? 1u : 0u) << i;
+  }
+  gt &= rk.valid;
+  eq &= rk.valid;
+  const uint32_t mine = (uint32_t)__popc(gt) | ((uint32_t)__popc(eq) << 16);
+  const uint32_t incl = wave_inclusive_scan_u32(mine);
+  if (lane == 63) wave_tot[wave] = incl;
+  __syncthreads();
+  uint32_t before = incl - mine;
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) before += (w < wave) ? wave_tot[w] : 0u;
+  g_rank = (int)(before & 0xffffu);
+  e_rank = (int)(before >> 16);
+}
+
+// emit(rank, pos, key) for every certain row, ranks ascending with the position, unless `certain` is false (or
+// the threshold has been found instead).  sm.hist clear and rk loaded by every thread; sm.hist[1] holds the
+// candidates afterwards.
+template <int THREADS, int KPT, typename Emit>
+__device__ __forceinline__ RunSelect run_select_certain(const RunKeys<KPT>& rk, int k, ResidentSelectSmem<THREADS>& sm, bool certain,
+                                                        Emit emit) {
+#pragma unroll
+  for (int i = 0; i < KPT; ++i)
+    if ((rk.valid >> i) & 1u) atomicAdd(&sm.hist[0][rk.key[i] >> 21], 1u);
+  __syncthreads();
+  resident_find_bin<THREADS>(sm, 0, (uint32_t)k);
+  LOKI_STAMP(13);
+  RunSelect rs;
+  rs.bin = sm.out[0][0];
+  rs.rem = sm.out[0][1];
+  rs.n_def = k - (int)rs.rem;
+  rs.n_cand = (int)sm.hist[0][rs.bin];
+  rs.t = WaveThreshold{0u, 0u};
+  if (rs.n_cand <= kRunCand) {
+    uint32_t gt, eq;
+    int g_rank, e_rank;
+    run_partition<THREADS, KPT>(rk, 21, rs.bin, sm.wave[1], gt, eq, g_rank, e_rank);
+#pragma unroll
+    for (int i = 0; i < KPT; ++i) {
+      if ((eq >> i) & 1u) {
+        sm.hist[1][e_rank] = rk.key[i] & ((1u << 21) - 1u);
+        sm.hist[1][kRunCand + e_rank] = (uint32_t)(rk.pos0 + i);
+        ++e_rank;
+      }
+      if (certain && ((gt >> i) & 1u)) emit(g_rank++, rk.pos0 + i, rk.key[i]);
+    }
+  } else {
+    __syncthreads();  // everyone has read n_cand
+    for (int i = threadIdx.x; i < 2048; i += THREADS) sm.hist[0][i] = 0u;
+    __syncthreads();
+    resident_threshold<THREADS, KPT>(rk.key, rk.valid, (uint32_t)k, sm, rs.t.T, rs.t.need_eq);
+    rs.n_cand = 0;
+  }
+  __syncthreads();
+  return rs;
+}
+
+template <int THREADS>
+__device__ __forceinline__ WaveThreshold run_threshold(const RunSelect& rs, ResidentSelectSmem<THREADS>& sm) {
+  if (rs.n_cand == 0) return rs.t;
+  const WaveThreshold t = wave_threshold(sm.hist[1], rs.n_cand, 21, rs.rem);
+  return {(rs.bin << 21) + t.T, t.need_eq};
+}
+
+// emit(rank, pos, key) for every selected row, ranks ascending with the position.  One barrier.
+template <int THREADS, int KPT, typename Emit>
+__device__ __forceinline__ void run_emit(const RunKeys<KPT>& rk, const WaveThreshold& t, ResidentSelectSmem<THREADS>& sm, Emit emit) {
+  uint32_t gt, eq;
+  int g_rank, e_rank;
+  run_partition<THREADS, KPT>(rk, 0, t.T, sm.wave[0], gt, eq, g_rank, e_rank);
+#pragma unroll
+  for (int i = 0; i < KPT; ++i) {
+    const bool is_eq = (eq >> i) & 1u, is_gt = (gt >> i) & 1u;
+    if (is_gt || (is_eq && (uint32_t)e_rank < t.need_eq)) emit(g_rank + min(e_rank, (int)t.need_eq), rk.pos0 + i, rk.key[i]);
+    g_rank += is_gt ? 1 : 0;
+    e_rank += is_eq ? 1 : 0;
+  }
+}
+
 // Whole selection for S <= THREADS*C: emit(rank, pos, score) is called exactly k times, rank
 // in [0, k) ascending with pos.
 template <int THREADS, int KPT, typename Emit>

@@ -1,5 +1,5 @@
 """Ranking of the candidates of the threshold's histogram bin in the single-launch kernels (grouped heads; one block per
-head beyond 8192 rows): by one wave from registers or from LDS, or (too many of them) by further digits.  Scores are made exactly: the query is
+head beyond 8192 rows) and in the attention launch of the split path: by one wave from registers or from LDS, or (too many of them) by further digits.  Scores are made exactly: the query is
 (1, 1, 1, 0, ..) under P = 1 and a row holds (1, j 2^-10, i 2^-18), so that its score, 1 + j 2^-10 + i 2^-18 < 1.25, is exact in
 fp32 and all such rows share the 11 leading key bits; rows above and below lie in other bins.  The index list
 must be the stable one to the last entry, and the result the same whether or not it is asked for."""
@@ -104,3 +104,13 @@ def test_candidates_several_blocks(S, above, inside, chosen, kinds, first):
     (9000, 900, 1900, 1100, 1, False), (9000, 0, 9000, 2048, 9999, False)])
 def test_candidates_one_block_per_head(S, above, inside, chosen, kinds, paged):
     _check(0, 1, S, above, inside, chosen, kinds, False, paged, copies=64)
+
+
+# selection inside the attention launch, which begins with the certain rows: lists of up to 1024 candidates
+@pytest.mark.parametrize("G", [1, 4])
+@pytest.mark.parametrize("S,above,inside,chosen,kinds,paged", [
+    (300, 0, 1, 1, 9, False), (700, 40, 3, 2, 9, True), (4000, 700, 256, 255, 999, True), (4097, 700, 1024, 1000, 9999, False),
+    (8000, 64, 1024, 700, 3, True), (8000, 64, 1025, 700, 9999, False), (12000, 900, 600, 300, 9999, True), (12000, 0, 12000, 3000, 9999, False),
+    (16384, 3000, 900, 500, 1, False)])
+def test_candidates_in_the_attention_launch(G, S, above, inside, chosen, kinds, paged):
+    _check(api.PATH_SPLIT, G, S, above, inside, chosen, kinds, False, paged)
