@@ -229,7 +229,7 @@ __global__ __launch_bounds__(kSaThreads, NH == 1 ? 4 : 2) void select_attend_ker
 }
 
 // Matrix-core form for 4 or 8 query heads that share a selection (bf16 caches, attend_mfma_impl.h).
-template <int NH, int KPT>
+template <int NH, int KPT, bool GROWING>
 __global__ __launch_bounds__(kSaThreads, 2) void select_attend_mfma_kernel(
     const void* __restrict__ klo, const void* __restrict__ khi, const void* __restrict__ v,
     const float* __restrict__ qhat, uint16_t* __restrict__ out, SelectAttendArgs a) {
@@ -247,9 +247,11 @@ __global__ __launch_bounds__(kSaThreads, 2) void select_attend_mfma_kernel(
   int r0, r1;
   share_of(k, a.nsplit, split, r0, r1);
 
-  __shared__ int32_t s_pages[kSaThreads * KPT / 256];
+  __shared__ int32_t s_pages[GROWING ? kSaThreads * KPT / 256 : 1];
   SelectShare<KPT> share;
-  const int there = share.begin(a, unit, b, unit % a.Hkv, S, k, r0, r1, split == 0, s_sel, s_pages, s_idx, nullptr);
+  int there = 0;
+  if constexpr (GROWING) there = share.begin(a, unit, b, unit % a.Hkv, S, k, r0, r1, split == 0, s_sel, s_pages, s_idx, nullptr);
+  else select_share<KPT>(a, unit, b, unit % a.Hkv, S, k, r0, r1, split == 0, s_sel, s_idx, nullptr);
 
   am_bf16x8_t bq[4][2];
   am_query_operands<4, 2>(qhat + (head0 + (head_ok ? r16 : 0)) * kD, head_ok, kD, bq);
@@ -258,7 +260,9 @@ __global__ __launch_bounds__(kSaThreads, 2) void select_attend_mfma_kernel(
   AmState st;
   st.init();
   am_attend_rows<true, 4, 2>(ad, bq, s_idx, r0, AmRoundRobin<kSaWaves>(r0, r1, there), st,
-                             [&] { share.complete(a, unit % a.Hkv, r0, r1, s_sel, s_pages, s_idx, nullptr); });
+                             [&] {
+                               if constexpr (GROWING) share.complete(a, unit % a.Hkv, r0, r1, s_sel, s_pages, s_idx, nullptr);
+                             });
   am_publish<NH, kSaWaves>(st, s_merge);
   finish_share<BF16, NH>(a, s_merge, head0, unit, split, out);
 }
@@ -304,43 +308,55 @@ bool select_attend_applies(const Shape& s, int select_mode) {
   return n == 1 || one_round || (n == 2 && s.rg.queries <= 1);
 }
 
-template <typename T, int NH, bool GROWING>
-static hipError_t launch_sa_g(const SelectAttendArgs& a, dim3 grid, const void* klo, const void* khi, const void* v,
-                              const float* qhat, void* out, hipStream_t st) {
-  auto* o = static_cast<typename T::store_t*>(out);
-  if (a.per_thread <= 8)
-    hipLaunchKernelGGL((select_attend_kernel<T, NH, 8, GROWING>), grid, dim3(kSaThreads), 0, st, klo, khi, v, qhat, o, a);
-  else if (a.per_thread <= 16)
-    hipLaunchKernelGGL((select_attend_kernel<T, NH, 16, GROWING>), grid, dim3(kSaThreads), 0, st, klo, khi, v, qhat, o, a);
-  else
-    hipLaunchKernelGGL((select_attend_kernel<T, NH, 32, GROWING>), grid, dim3(kSaThreads), 0, st, klo, khi, v, qhat, o, a);
-  return hipGetLastError();
+// Attention that begins before the list is complete: where its blocks wait for memory and nothing else runs beside them (one
+// round of blocks, bf16), the heads do not share their rows (whose blocks walk them in step in one ascending list), and the rows
+// are between 2049, below which the selection is short, and 8192, beyond which a thread holds 32 keys.  us per step, apart /
+// begun early: 32 heads, S = 4096, k = 1024 19.1 / 18.2; 32 heads, S = 8000, k = 2000 26.5 / 24.6; 16 heads, S = 7544, k = 471 21.9 / 21.3; on
+// the matrix cores, always one round, 32/8 heads, S = 8192 21.4 / 20.8, S = 3000, k = 750 18.9 / 18.0, 4 tokens of 32/8 heads, S = 4374
+// 27.6 / 27.0 (60 shapes in this range: 3.5 % less on average, three of them 1.7 to 2.1 % more); but S = 1200, k = 150 19.6 / 20.3, S =
+// 11000, k = 2750 35.1 / 36.7, fp32, 24 heads, S = 3473, k = 217 17.4 / 18.3, and 2 tokens of 4 sequences, S = 1920 24.5 / 25.5.
+static bool attention_begins_early(const SelectAttendArgs& a, dim3 grid) {
+  return a.S_max > 2048 && a.S_max <= 8192 && a.xcd_group_blocks == 0 && (int)(grid.x * grid.y) <= device_cus();
 }
 
-// Attention that begins before the list is complete: where its blocks wait for memory and nothing else runs beside them (one
-// round of blocks, bf16), and the heads do not share their rows (which walk them in step in one ascending list).  us per
-// step, apart / begun early: 32 heads, S = 4096, k = 1024 19.1 / 18.2; 16 heads, S = 7544, k = 471 21.9 / 21.3; on the matrix
-// cores, always one round, 32/8 heads, S = 8192 21.4 / 20.8, 4 tokens of 32/8 heads, S = 4374 27.6 / 27.0; but fp32, 24 heads, S = 3473, k =
-// 217 17.4 / 18.3, and 2 tokens of 4 sequences, S = 1920 24.5 / 25.5.
 template <typename T, int NH>
 static hipError_t launch_sa(const SelectAttendArgs& a, dim3 grid, const void* klo, const void* khi, const void* v,
                             const float* qhat, void* out, hipStream_t st) {
+  auto* o = static_cast<typename T::store_t*>(out);
   if constexpr (T::kBytes == 2 && NH == 1)
-    if (a.xcd_group_blocks == 0 && (int)(grid.x * grid.y) <= device_cus())
-      return launch_sa_g<T, NH, true>(a, grid, klo, khi, v, qhat, out, st);
-  return launch_sa_g<T, NH, false>(a, grid, klo, khi, v, qhat, out, st);
+    if (attention_begins_early(a, grid)) {
+      if (a.per_thread <= 8)
+        hipLaunchKernelGGL((select_attend_kernel<T, NH, 8, true>), grid, dim3(kSaThreads), 0, st, klo, khi, v, qhat, o, a);
+      else
+        hipLaunchKernelGGL((select_attend_kernel<T, NH, 16, true>), grid, dim3(kSaThreads), 0, st, klo, khi, v, qhat, o, a);
+      return hipGetLastError();
+    }
+  if (a.per_thread <= 8)
+    hipLaunchKernelGGL((select_attend_kernel<T, NH, 8, false>), grid, dim3(kSaThreads), 0, st, klo, khi, v, qhat, o, a);
+  else if (a.per_thread <= 16)
+    hipLaunchKernelGGL((select_attend_kernel<T, NH, 16, false>), grid, dim3(kSaThreads), 0, st, klo, khi, v, qhat, o, a);
+  else
+    hipLaunchKernelGGL((select_attend_kernel<T, NH, 32, false>), grid, dim3(kSaThreads), 0, st, klo, khi, v, qhat, o, a);
+  return hipGetLastError();
 }
 
 template <int NH>
 static hipError_t launch_sa_mfma(const SelectAttendArgs& a, dim3 grid, const void* klo, const void* khi, const void* v,
                                  const float* qhat, void* out, hipStream_t st) {
   auto* o = static_cast<uint16_t*>(out);
+  if (attention_begins_early(a, grid)) {
+    if (a.per_thread <= 8)
+      hipLaunchKernelGGL((select_attend_mfma_kernel<NH, 8, true>), grid, dim3(kSaThreads), 0, st, klo, khi, v, qhat, o, a);
+    else
+      hipLaunchKernelGGL((select_attend_mfma_kernel<NH, 16, true>), grid, dim3(kSaThreads), 0, st, klo, khi, v, qhat, o, a);
+    return hipGetLastError();
+  }
   if (a.per_thread <= 8)
-    hipLaunchKernelGGL((select_attend_mfma_kernel<NH, 8>), grid, dim3(kSaThreads), 0, st, klo, khi, v, qhat, o, a);
+    hipLaunchKernelGGL((select_attend_mfma_kernel<NH, 8, false>), grid, dim3(kSaThreads), 0, st, klo, khi, v, qhat, o, a);
   else if (a.per_thread <= 16)
-    hipLaunchKernelGGL((select_attend_mfma_kernel<NH, 16>), grid, dim3(kSaThreads), 0, st, klo, khi, v, qhat, o, a);
+    hipLaunchKernelGGL((select_attend_mfma_kernel<NH, 16, false>), grid, dim3(kSaThreads), 0, st, klo, khi, v, qhat, o, a);
   else
-    hipLaunchKernelGGL((select_attend_mfma_kernel<NH, 32>), grid, dim3(kSaThreads), 0, st, klo, khi, v, qhat, o, a);
+    hipLaunchKernelGGL((select_attend_mfma_kernel<NH, 32, false>), grid, dim3(kSaThreads), 0, st, klo, khi, v, qhat, o, a);
   return hipGetLastError();
 }
 
