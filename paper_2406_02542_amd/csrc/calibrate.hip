@@ -31,8 +31,8 @@ __host__ __device__ constexpr int gram_tile(int c1, int c2) { return c1 * kGramS
 // 8 g .. 8 g + 7 (bf16: one 16-byte load a row, four whole rows an instruction) and pairs the rows up
 // (v_perm_b32; fp32: the conversion packs them): operand c then holds eight consecutive rows of column
 // 8 m + c, which is what v_mfma_f32_16x16x32_bf16 takes on either side, so a step needs no LDS, no barrier
-// and, G being symmetric, 36 of 64 tiles.  A column of ones on the other side gives the column sums.  What
-// bounds it is the read of the keys: one wave per SIMD with 512 registers holds the 36 tiles and two
+// and, G being symmetric, 36 of 64 tiles.  Column sums: bf16 by a column of ones on the other side, fp32 by adding the
+// fp32 values themselves.  What bounds it is the read of the keys: one wave per SIMD with 512 registers holds the 36 tiles and two
 // steps' loads (bf16 with three 2 us more, with four 18).  32 heads x 65536 keys, us: bf16 (512 MiB) 95 (5.6 TB/s), fp32 190; through a tile
 // transposed in LDS, with two barriers a tile and all 64 tiles, 131 (4.1 TB/s) and 267.
 // NT = bf16 terms per element: 1 for bf16 storage, 2 for fp32 storage (value, remainder).
@@ -54,11 +54,14 @@ __global__ __launch_bounds__(kGramThreads, 1) void gram_kernel(const void* __res
   const int rows = (int)max(min(N - r0, (long long)rows_per_chunk), 0LL);
   const char* base = static_cast<const char*>(keys) + ((size_t)head * N + r0 + 8 * kgrp) * kRowBytes + (size_t)r16 * 16 * NT;
 
-  cal_f32x4_t acc[kGramTiles], total[kGramSets];
+  cal_f32x4_t acc[kGramTiles], total[NT == 1 ? kGramSets : 1];
+  float csum[NT == 1 ? 1 : kGramSets];  // of this k-group's rows, column 8 r16 + c
 #pragma unroll
   for (int i = 0; i < kGramTiles; ++i) acc[i] = cal_f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int i = 0; i < kGramSets; ++i) total[i] = cal_f32x4_t{0.f, 0.f, 0.f, 0.f};
+  for (auto& t : total) t = cal_f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (auto& t : csum) t = 0.f;
 
   uint4 raw[kBufs][kWords];
   auto load_step = [&](int t0, uint4 (&x)[kWords]) {  // rows t0 .. t0 + 31 of the chunk, zeros past its end
@@ -99,11 +102,17 @@ __global__ __launch_bounds__(kGramThreads, 1) void gram_kernel(const void* __res
             w[NT - 1][j] = BF16::round2(x0 - __uint_as_float(w[0][j] << 16), x1 - __uint_as_float(w[0][j] & 0xffff0000u));
           }
         }
+        if constexpr (NT == 2) {
+          float x[8];
+#pragma unroll
+          for (int e = 0; e < 8; ++e) x[e] = __uint_as_float(word(raw[b][2 * e + c / 4], c % 4));
+          csum[c] += ((x[0] + x[1]) + (x[2] + x[3])) + ((x[4] + x[5]) + (x[6] + x[7]));
+        }
 #pragma unroll
         for (int t = 0; t < NT; ++t) op[t][c] = __builtin_bit_cast(cal_bf16x8_t, make_uint4(w[t][0], w[t][1], w[t][2], w[t][3]));
       }
       load_step(t0 + (b + kBufs) * kGramWaves * kGramStep, raw[b]);
-      if constexpr (NT == 2) {  // smallest terms first; remainder x remainder is below fp32's last place
+      if constexpr (NT == 2) {  // smallest terms first; remainder x remainder, at most 2^-18 of a term, is left out
 #pragma unroll
         for (int c1 = 0; c1 < kGramSets; ++c1)
 #pragma unroll
@@ -118,8 +127,6 @@ __global__ __launch_bounds__(kGramThreads, 1) void gram_kernel(const void* __res
             const int i = gram_tile(c1, c2);
             acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(op[0][c1], op[1][c2], acc[i], 0, 0, 0);
           }
-#pragma unroll
-        for (int c = 0; c < kGramSets; ++c) total[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, op[1][c], total[c], 0, 0, 0);
       }
 #pragma unroll
       for (int c1 = 0; c1 < kGramSets; ++c1)
@@ -128,8 +135,9 @@ __global__ __launch_bounds__(kGramThreads, 1) void gram_kernel(const void* __res
           const int i = gram_tile(c1, c2);
           acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(op[0][c1], op[0][c2], acc[i], 0, 0, 0);
         }
+      if constexpr (NT == 1)
 #pragma unroll
-      for (int c = 0; c < kGramSets; ++c) total[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, op[0][c], total[c], 0, 0, 0);
+        for (int c = 0; c < kGramSets; ++c) total[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, op[0][c], total[c], 0, 0, 0);
     }
   }
 
@@ -149,10 +157,18 @@ __global__ __launch_bounds__(kGramThreads, 1) void gram_kernel(const void* __res
       }
     __syncthreads();
   }
-  // (every row of a tile of column sums is the same)
-  if (kgrp == 0)
+  // (every row of a tile of column sums is the same; fp32: the four k-groups' sums are added pairwise)
 #pragma unroll
-    for (int c = 0; c < kGramSets; ++c) s_sum[wave][8 * r16 + c] = total[c][0];
+  for (int c = 0; c < kGramSets; ++c) {
+    float sum;
+    if constexpr (NT == 1) {
+      sum = total[c][0];
+    } else {
+      sum = csum[c] + __shfl_xor(csum[c], 16);
+      sum += __shfl_xor(sum, 32);
+    }
+    if (kgrp == 0) s_sum[wave][8 * r16 + c] = sum;
+  }
   const size_t part = (size_t)head * nchunks + chunk;
   if (wave == 0) {
     float4* gp = reinterpret_cast<float4*>(gram_part + part * kGramPartWords);

@@ -76,7 +76,7 @@ def test_pca_fit_matches_oracle(dtype, Hkv, N):
 def test_covariance_at_the_edges_of_a_step(dtype, Hkv, N):
     """Rows that do not fill a 32-row step, a chunk or a round of blocks; more heads than CUs.  P diag(lambda) P^T
     against the float64 covariance: the bounds of test_pca_fit_matches_oracle (fp32 sums of at most a few
-    thousand terms, remainder x remainder of fp32 keys dropped: below 2^-16 of a term)."""
+    thousand terms, remainder x remainder of fp32 keys dropped: at most 2^-18 of a term)."""
     keys = calibration_keys(5 + N, Hkv, N, dtype)
     P, lam, _ = fit(keys, dtype)
     for h in (0, Hkv // 2, Hkv - 1):
@@ -85,6 +85,19 @@ def test_covariance_at_the_edges_of_a_step(dtype, Hkv, N):
         say(f"case {dtype} Hkv {Hkv} N {N} head {h}: reconstruction {rec:.2e}")
         assert rec < 2e-5
         assert np.max(np.abs(P[h].T @ P[h] - np.eye(128))) < 1e-6
+
+
+def test_column_sums_of_fp32_keys_keep_all_their_bits():
+    """One column alternates between 1 and -1, the other 127 hold x = 1 + 2^-9 - 2^-19 in each of 32 rows, so that their
+    covariance is 0.  x needs 19 bits; its two bf16 terms are 1 and 2^-9, so the products the Gram pass keeps, 1 + 2^-8,
+    are x^2 to 2^-27, and the sum 32 x is exact in fp32: an entry of the covariance is off by 2^-27 32 / 31 and a
+    rounding, an eigenvalue by 127 times that, below 2e-6.  Sums of the two terms are 32 2^-19 too large: -5e-4."""
+    keys = np.full((1, 32, 128), 1 + 2.0 ** -9 - 2.0 ** -19, np.float32)
+    keys[0, :, 5] = 1 - 2.0 * (np.arange(32) % 2)
+    _, lam, _ = fit(keys, "f32")
+    say(f"eigenvalues {lam[0, 0]} .. {lam[0, -1]}")
+    assert abs(lam[0, 0] - 32 / 31) < 2e-6
+    assert np.all(np.abs(lam[0, 1:]) < 2e-6)
 
 
 def test_pca_fit_then_rotate_then_decode_is_exact_attention():
