@@ -129,14 +129,19 @@ __device__ __forceinline__ double fast_rsqrt_f64(double x) {  // likewise
 // 125 us; with a second barrier, for the next row from the wave that owns it, 131; with eight waves and that barrier 146; as
 // two 64-row halves with four barriers a step, the library's square root and divisions and a branch around every
 // group of rows 197.
-__global__ __launch_bounds__(kEigThreads) void tridiag_kernel(EigBufs bufs) {
+// PER_CU = 2, for more heads than CUs: two blocks share a CU, a wave having at most 256 registers.  The next row is
+// then taken before the rows of the matrix are updated, so that it need not be kept beside them (240 registers for 292,
+// 2 us more for a block alone).  257 heads: 177 us as before that kernel had one barrier, with one block per CU 254.
+template <int PER_CU>
+__global__ __launch_bounds__(kEigThreads, PER_CU) void tridiag_kernel(EigBufs bufs) {
   constexpr int kWaves = kEigThreads / 64, kRows = kD / kWaves, kPitch = kRows + 2;
   constexpr int kChunk = 4;  // rows of a wave that are skipped together once they are done
   static_assert(kWaves == 4, "four partial sums");
   // (a wave is at most one barrier ahead of another: two sets take turns)
   __shared__ __align__(16) double s_p[2][kWaves][kD], s_row[2][kD];
   __shared__ __align__(16) double s_pr[kWaves][kPitch], s_xr[kWaves][kPitch];  // a wave's own rows, for itself
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, head = blockIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63, head = blockIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const double* C = bufs.cov + (size_t)head * kD * kD;
   double* tri = eig_tri(bufs, head);
   double* refl = eig_refl(bufs, head);
@@ -238,6 +243,7 @@ __global__ __launch_bounds__(kEigThreads) void tridiag_kernel(EigBufs bufs) {
         g[h] = inv_h * u[h];
         row[h] = fma(-top, f[h], fma(-pn, g[h], row[h]));
       }
+      if constexpr (PER_CU == 2) take_row(next, row);  // (this step's own rows are in xr)
 #pragma unroll
       for (int i = kLive; i < kRows; i += 2) {  // (row j + 1, where u is not x, is done)
         const double2 pr = *reinterpret_cast<const double2*>(&s_pr[wave][i]);
@@ -247,7 +253,7 @@ __global__ __launch_bounds__(kEigThreads) void tridiag_kernel(EigBufs bufs) {
           a[i + 1][h] = fma(-xr[i + 1], f[h], fma(-pr.y, g[h], a[i + 1][h]));
         }
       }
-      take_row(next, row);
+      if constexpr (PER_CU == 1) take_row(next, row);
     }
   };
   steps(std::integral_constant<int, 0>{});
@@ -902,7 +908,10 @@ hipError_t launch_eigensolver(int Hkv, const EigRegions& r, float* P, float* eig
   const hipError_t ea = allow_dynamic_lds(reinterpret_cast<const void*>(jacobi_kernel), (int)lds, lds_allowed);
   if (ea != hipSuccess) return ea;
   const dim3 slices(kEigSlices, Hkv);
-  hipLaunchKernelGGL(tridiag_kernel, dim3(Hkv), dim3(kEigThreads), 0, st, b);
+  if (Hkv > device_cus())
+    hipLaunchKernelGGL(tridiag_kernel<2>, dim3(Hkv), dim3(kEigThreads), 0, st, b);
+  else
+    hipLaunchKernelGGL(tridiag_kernel<1>, dim3(Hkv), dim3(kEigThreads), 0, st, b);
   hipLaunchKernelGGL(eigvec_kernel, slices, dim3(kEigThreads), 0, st, b);
   hipLaunchKernelGGL(orthonormalise_kernel, slices, dim3(kEigThreads), 0, st, b);
   hipLaunchKernelGGL(project_kernel, slices, dim3(kEigThreads), 0, st, b);
