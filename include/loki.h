@@ -370,6 +370,13 @@ int loki_profile_read(loki_profile* p, int* n_kernels, float* ms, const char** n
 int loki_debug_cluster_spin_limit(unsigned polls);
 
 /*
+ * Test aid for LOKI_PATH_CLUSTER: with `on` not 0 every block behaves as if the other blocks of its unit had not
+ * shown up for the list of candidates that the last of their meetings completes (a launch whose rows are told apart
+ * without such a list is not affected).  Process-wide; affects launches enqueued afterwards.
+ */
+int loki_debug_cluster_give_up_at_list(int on);
+
+/*
  * Whether a LOKI_PATH_CLUSTER launch on this workspace gave up waiting since its control words
  * were last cleared (by the clearing kernel in front of every launch without
  * LOKI_WORKSPACE_ZEROED, else by the caller's zero fill): *gave_up = 1 or 0 (host pointer).

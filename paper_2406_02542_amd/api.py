@@ -93,6 +93,8 @@ def lib() -> ctypes.CDLL:
     L.loki_profile_attach.argtypes = [vp]
     L.loki_debug_cluster_spin_limit.restype = i32
     L.loki_debug_cluster_spin_limit.argtypes = [ctypes.c_uint]
+    L.loki_debug_cluster_give_up_at_list.restype = i32
+    L.loki_debug_cluster_give_up_at_list.argtypes = [i32]
     L.loki_cluster_gave_up.restype = i32
     L.loki_cluster_gave_up.argtypes = [vp, ctypes.POINTER(i32), vp]
     L.loki_stream_read.restype = i32
@@ -411,6 +413,11 @@ def loki_debug_cluster_spin_limit(polls: int) -> None:
     """Sets how many polls a block of a PATH_CLUSTER launch waits for its unit's other blocks
     (0 restores the default)."""
     _check(lib().loki_debug_cluster_spin_limit(int(polls)), "loki_debug_cluster_spin_limit")
+
+
+def loki_debug_cluster_give_up_at_list(on: bool) -> None:
+    """Makes the blocks of PATH_CLUSTER launches give up at the list of candidates (until switched off)."""
+    _check(lib().loki_debug_cluster_give_up_at_list(int(on)), "loki_debug_cluster_give_up_at_list")
 
 
 def loki_cluster_gave_up(workspace: torch.Tensor, stream=None) -> bool:

@@ -748,6 +748,11 @@ int loki_debug_cluster_spin_limit(unsigned polls) {
   return LOKI_OK;
 }
 
+int loki_debug_cluster_give_up_at_list(int on) {
+  set_cluster_give_up_at_list(on != 0);
+  return LOKI_OK;
+}
+
 int loki_cluster_gave_up(const void* workspace, int* gave_up, void* stream) {
   if (!workspace || !gave_up) return LOKI_ERR_INVALID_ARG;
   if (!aligned256(workspace)) return LOKI_ERR_ALIGNMENT;

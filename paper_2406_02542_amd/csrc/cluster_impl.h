@@ -36,6 +36,7 @@ struct ClusterArgs {
   int C = 1;                     // blocks per unit
   int units = 0;                 // units of the launch (the grid is padded)
   uint32_t spin_limit = kClusterSpinLimit;
+  bool give_up_at_list = false;  // test aid: as if the other blocks did not show up for the candidates
 };
 
 struct ClusterSmem {

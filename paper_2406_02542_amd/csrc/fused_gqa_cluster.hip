@@ -79,6 +79,8 @@ bool fused_gqa_cluster_preferred(const Shape& s, int select_mode) {
 
 static std::atomic<uint32_t> g_spin_limit{kClusterSpinLimit};
 void set_cluster_spin_limit(uint32_t polls) { g_spin_limit.store(polls, std::memory_order_relaxed); }
+static std::atomic<bool> g_give_up_at_list{false};
+void set_cluster_give_up_at_list(bool on) { g_give_up_at_list.store(on, std::memory_order_relaxed); }
 
 namespace {
 struct ClusterPlan {
@@ -131,6 +133,7 @@ static hipError_t launch_cluster_k(const Shape& s, int C, const void* q, const f
   cl.C = C;
   cl.units = s.B * s.Hkv;
   cl.spin_limit = spin_limit;
+  cl.give_up_at_list = g_give_up_at_list.load(std::memory_order_relaxed);
   // the arrival flags and tickets start at zero: unless the caller vouches for the workspace,
   // clear them (with a kernel, not a memset: a caller may be capturing the stream into a graph)
   if (!ctl_clean) {

@@ -79,6 +79,9 @@ struct GqaSteps {
         q(T1 / (WAVES - 1)), r(T1 % (WAVES - 1)), i(0), ahead(ahead_) {}
   __device__ __forceinline__ bool early() const { return ahead && wave > 0 && wave - 1 < T1; }
   __device__ __forceinline__ bool next(int& base, int& end) {
+    // Not ahead: the list's state is final by now.  Where the unit's other blocks did not show up the entries are
+    // still positions, which a paged cache's loads must not take for rows of the pool.
+    if (!ahead && i == 0 && __builtin_amdgcn_readfirstlane(list->state) != 1) return false;
     const int n1 = wave == 0 ? 0 : q + (wave - 1 < r ? 1 : 0);
     int i2 = i - n1;
     if (i2 < 0) {
@@ -470,7 +473,7 @@ __global__ __launch_bounds__(THREADS, THREADS == 256 ? 2 : 1) void fused_gqa_ker
     if constexpr (CLUSTER) {
       if (wave == 0 && n_rank > 0) {
         uint32_t* counter = cl.counters + (size_t)unit * kClusterCounterStride;
-        const bool ok = cluster_wave_wait(counter, cl.C, cidx, cl_meet, cl.spin_limit);
+        const bool ok = !cl.give_up_at_list && cluster_wave_wait(counter, cl.C, cidx, cl_meet, cl.spin_limit);
         LOKI_STAMP(4);
         if (ok) {
           const __amdgpu_buffer_rsrc_t xc = cluster_buffer(cl.xcand, cl.xcand_bytes);

@@ -179,6 +179,7 @@ constexpr int kClusterCounterStride = (kClusterMax + 1) * kClusterFlagStride;  /
 // the control words of every unit a cluster launch can have, and the error word behind them
 constexpr size_t kClusterCtlBytes = ((size_t)kClusterMaxUnits * kClusterCounterStride + 64) * 4;
 void set_cluster_spin_limit(uint32_t polls);
+void set_cluster_give_up_at_list(bool on);
 // ctl: the workspace's control words (Workspace::cluster_ctl); ctl_clean: they are known to be
 // zero (a workspace the caller cleared once and only this library has written since: every
 // finished launch leaves them zero), so no clearing kernel goes in front.

@@ -383,6 +383,45 @@ def test_cluster_wait_gives_up_cleanly():
     assert not api.loki_cluster_gave_up(ws)
 
 
+@pytest.mark.parametrize("want_idx", [False, True])
+@pytest.mark.parametrize("paged", [False, True])
+def test_cluster_gives_up_at_the_candidates(paged, want_idx):
+    """The last meeting of a unit's blocks, where the list of candidates is complete: made to fail by the host, every
+    output is NaN, the workspace says so, and the next launch on a cleared one is regular.  The pool holds fewer rows
+    than the sequence (pages listed several times): positions taken for pool rows would leave it."""
+    S, k, d, Hkv, G, D = 5000, 600, 32, 2, 4, 128
+    say(f"case paged {paged} idx {want_idx}")
+    g = torch.Generator(device="cuda").manual_seed(5)
+    lead = (3, Hkv, 256) if paged else (1, Hkv, S)
+    klo, khi, v = (torch.randn((*lead, n), generator=g, device="cuda").to(torch.bfloat16) for n in (d, D - d, D))
+    q = torch.randn((1, Hkv * G, D), generator=g, device="cuda").to(torch.bfloat16)
+    P = torch.eye(D, device="cuda").repeat(Hkv, 1, 1)
+    lay = api.make_layout(1, Hkv * G, Hkv, D, d, S, torch.bfloat16)
+    ws = api.alloc_workspace(lay, S, d, k, 1)
+    pages = -(-S // 256)
+    step = dict(page_table=(torch.arange(pages, dtype=torch.int32, device="cuda") % 3)[None].contiguous(), page_rows=256,
+                n_pages=3) if paged else {}
+
+    def run():
+        out = torch.zeros((1, Hkv * G, D), dtype=torch.bfloat16, device="cuda")
+        idx = torch.full((1, Hkv, k), -7, dtype=torch.int32, device="cuda") if want_idx else None
+        api.loki_decode_step(lay, q, P, klo, khi, v, S, d, k, 1 | api.PATH_CLUSTER, ws, out, idx, **step)
+        torch.cuda.synchronize()
+        return out, idx
+
+    ref, idx_ref = run()
+    assert torch.isfinite(ref).all() and not api.loki_cluster_gave_up(ws)
+    api.loki_debug_cluster_give_up_at_list(True)
+    try:
+        out, _ = run()
+    finally:
+        api.loki_debug_cluster_give_up_at_list(False)
+    assert torch.isnan(out).all() and api.loki_cluster_gave_up(ws)
+    out, idx = run()
+    assert torch.equal(out, ref) and not api.loki_cluster_gave_up(ws)
+    assert not want_idx or torch.equal(idx, idx_ref)
+
+
 def test_heavy_hitters_are_selected():
     """The peaked-attention recipe of the long-context config at reduced size: the planted
     positions carry > 90 % of the mass and must all be among the selected rows."""
