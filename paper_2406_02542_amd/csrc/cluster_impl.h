@@ -19,7 +19,7 @@
 
 namespace loki {
 
-constexpr int kClusterCandCap = 8192;  // candidates of a unit that are ranked from a list
+constexpr int kClusterCandCap = 8192;  // candidates of a unit that are ranked from a list, at most (ClusterArgs::rank_cap)
 constexpr int kClusterRounds = 3;     // histogram exchanges of one launch at most (11 + 11 + 10 bits)
 
 // Device memory of the exchange (all of it inside the caller's workspace).
@@ -36,6 +36,7 @@ struct ClusterArgs {
   int C = 1;                     // blocks per unit
   int units = 0;                 // units of the launch (the grid is padded)
   uint32_t spin_limit = kClusterSpinLimit;
+  int rank_cap = kClusterCandCap;  // with more candidates than this the next digit is exchanged first
   bool give_up_at_list = false;  // test aid: as if the other blocks did not show up for the candidates
 };
 

@@ -77,6 +77,22 @@ bool fused_gqa_cluster_preferred(const Shape& s, int select_mode) {
   return unit_bytes >= 1310720 && !one_block;
 }
 
+// Up to how many candidates of a unit one wave of every block ranks while the others attend over
+// the certain rows; more are told apart by another histogram exchange first (4 to 5 us).  1024 fit
+// that wave's registers; a list in LDS costs it about 3 us per thousand, which the other waves are
+// busy for where the rows of all units' lists, 512 bytes each, take as long: one candidate for every
+// 32 KB of them (7 ns at 5 TB/s).  us per step, 1024 / this rule / 8192 / all of them ranked by
+// the whole block, with an exchange from 4096 on: 24 units of 8 heads, S = 45686, k = 1427, d = 64
+// 47.8 / 47.8 / 59.4 / 49.7; S = 24908, k = 3113 35.8 / 35.8 / 44.9 / 39.1; 32 units of 8, S = 39386,
+// k = 4923 48.5 / 48.5 / 62.3 / 54.6; 8 of 4, S = 49409, k = 6176 37.3 / 37.3 / 47.8 / 47.7; but 128
+// of 4, S = 16384, k = 2048 58.8 / 56.6 / 56.6 / 62.3; 32 of 4, S = 19531, k = 6510 43.7 / 40.3 / 40.3 /
+// 47.6; 64 of 2, S = 64325, k = 8192 89.4 / 85.0 / 85.0 / 95.7.  350 shapes of 4 to 128 units: never
+// above the whole block's ranking, 11 % below it on average; 4.6 % below 8192, four shapes 3 to 4.5 % above.
+static int cluster_rank_cap(const Shape& s) {
+  const long long cap = (long long)s.B * s.Hkv * s.k * (2 * kD * 2) / 32768;
+  return (int)(cap < 1024 ? 1024 : cap > kClusterCandCap ? kClusterCandCap : cap);
+}
+
 static std::atomic<uint32_t> g_spin_limit{kClusterSpinLimit};
 void set_cluster_spin_limit(uint32_t polls) { g_spin_limit.store(polls, std::memory_order_relaxed); }
 static std::atomic<bool> g_give_up_at_list{false};
@@ -133,6 +149,7 @@ static hipError_t launch_cluster_k(const Shape& s, int C, const void* q, const f
   cl.C = C;
   cl.units = s.B * s.Hkv;
   cl.spin_limit = spin_limit;
+  cl.rank_cap = cluster_rank_cap(s);
   cl.give_up_at_list = g_give_up_at_list.load(std::memory_order_relaxed);
   // the arrival flags and tickets start at zero: unless the caller vouches for the workspace,
   // clear them (with a kernel, not a memset: a caller may be capturing the stream into a graph)

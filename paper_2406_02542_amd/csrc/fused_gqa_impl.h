@@ -384,7 +384,7 @@ __global__ __launch_bounds__(THREADS, THREADS == 256 ? 2 : 1) void fused_gqa_ker
       own_inbin = r.own_inbin;
       lower_inbin = r.lower_inbin;
       total_inbin = r.total_inbin;
-      if (total_inbin <= (uint32_t)kClusterCandCap && r.most_inbin <= (uint32_t)kCandCap) break;
+      if (total_inbin <= (uint32_t)cl.rank_cap && r.most_inbin <= (uint32_t)kCandCap) break;
     }
     LOKI_STAMP(11);
     if (!ok) {

@@ -87,7 +87,7 @@ def test_candidates_one_block(S, above, inside, chosen, kinds, paged):
     _check(api.PATH_FUSED, 4, S, above, inside, chosen, kinds, False, paged)
 
 
-# several blocks: up to 8192 candidates of a unit and 4096 of a block are exchanged as a list
+# several blocks: up to 1024 candidates of a unit are exchanged as a list, more take another histogram
 @pytest.mark.parametrize("S,above,inside,chosen,kinds,first", [
     (2000, 40, 3, 2, 9, False), (16000, 1000, 1024, 500, 9999, False), (16000, 1000, 1025, 1024, 9999, True),
     (16000, 50, 5000, 2500, 9999, False), (16000, 50, 5000, 2500, 5, False), (40000, 100, 8192, 3000, 9999, False),
@@ -95,6 +95,16 @@ def test_candidates_one_block(S, above, inside, chosen, kinds, paged):
     (40000, 3000, 30000, 1, 30000, False)])
 def test_candidates_several_blocks(S, above, inside, chosen, kinds, first):
     _check(api.PATH_CLUSTER, 8 if S < 10000 else 2, S, above, inside, chosen, kinds, first, S <= 16000 and chosen % 2 == 0)
+
+
+# the same with lists whose rows take long: 64 units, as many candidates as there are rows in a unit's list, up to
+# 8192 and 4096 of a block
+@pytest.mark.parametrize("S,above,inside,chosen,kinds,first", [
+    (17000, 100, 1025, 925, 9999, False), (17000, 100, 4000, 3900, 9999, False), (17000, 100, 4001, 3900, 9999, False),
+    (17000, 2000, 4000, 2000, 3, True), (40000, 1192, 8192, 7000, 9999, False), (40000, 1192, 8193, 7000, 9999, False),
+    (40000, 1192, 6000, 5000, 9999, True), (40000, 4000, 4096, 4096, 9999, True)])
+def test_candidates_of_long_lists(S, above, inside, chosen, kinds, first):
+    _check(api.PATH_CLUSTER, 2, S, above, inside, chosen, kinds, first, False, copies=32)
 
 
 # one block per head, keys in LDS: lists of up to 2048 candidates
