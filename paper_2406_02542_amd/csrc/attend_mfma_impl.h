@@ -116,7 +116,8 @@ struct AmRoundRobin {
   int at, r1, there;
   __device__ __forceinline__ AmRoundRobin(int r0, int r1_, int there_ = 0)
       : at(r0 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) * kAmRows), r1(r1_), there(there_) {}
-  __device__ __forceinline__ bool early() const { return at + kAmRows <= there; }
+  // (a wave without a step has nothing to load)
+  __device__ __forceinline__ bool early() const { return at < r1 && at + kAmRows <= there; }
   __device__ __forceinline__ bool next(int& base, int& end) {
     base = min(at, r1);
     end = r1;
