@@ -201,25 +201,15 @@ __device__ __forceinline__ void resident_find_bin(ResidentSelectSmem<THREADS>& s
   __syncthreads();
 }
 
-// Exact threshold of the rem-th largest of the block's register-resident keys: returns the
-// key T and how many keys equal to T are needed (need_eq >= 1).  valid_mask bit i says whether
-// key[i] takes part.  Both histograms and sm.ncand must be clear on entry (see
-// resident_select_clear) and every thread must be past any earlier use of sm.
-template <int THREADS, int KPT>
-__device__ __forceinline__ void resident_threshold(const uint32_t (&key)[KPT], uint32_t valid_mask,
-                                                   uint32_t rem_in, ResidentSelectSmem<THREADS>& sm,
-                                                   uint32_t& T, uint32_t& need_eq) {
-  const int tid = threadIdx.x;
 #define LOKI_SEL_VALID(i) ((valid_mask >> (i)) & 1u)
-  // pass 1: bits 31..21 of every key
-#pragma unroll
-  for (int i = 0; i < KPT; ++i)
-    if (LOKI_SEL_VALID(i)) atomicAdd(&sm.hist[0][key[i] >> 21], 1u);
-  __syncthreads();
-  resident_find_bin<THREADS>(sm, 0, rem_in);
+// resident_threshold (below) from its second pass on: sm.out[0] as resident_find_bin left it for the leading
+// 11 bits, histogram 1 and sm.ncand clear.
+template <int THREADS, int KPT>
+__device__ __forceinline__ void resident_threshold_in_bin(const uint32_t (&key)[KPT], uint32_t valid_mask,
+                                                          ResidentSelectSmem<THREADS>& sm, uint32_t& T,
+                                                          uint32_t& need_eq) {
+  const int tid = threadIdx.x;
   const uint32_t bin1 = sm.out[0][0];
-  LOKI_STAMP(13);
-
   // pass 2: bits 20..10 of the keys inside the threshold bin
 #pragma unroll
   for (int i = 0; i < KPT; ++i)
@@ -270,8 +260,26 @@ __device__ __forceinline__ void resident_threshold(const uint32_t (&key)[KPT], u
     T = (top22 << 10) | (sm.out[0][0] - 1024u);
     need_eq = sm.out[0][1];
   }
-#undef LOKI_SEL_VALID
 }
+
+// Exact threshold of the rem-th largest of the block's register-resident keys: returns the
+// key T and how many keys equal to T are needed (need_eq >= 1).  valid_mask bit i says whether
+// key[i] takes part.  Both histograms and sm.ncand must be clear on entry (see
+// resident_select_clear) and every thread must be past any earlier use of sm.
+template <int THREADS, int KPT>
+__device__ __forceinline__ void resident_threshold(const uint32_t (&key)[KPT], uint32_t valid_mask,
+                                                   uint32_t rem_in, ResidentSelectSmem<THREADS>& sm,
+                                                   uint32_t& T, uint32_t& need_eq) {
+  // pass 1: bits 31..21 of every key
+#pragma unroll
+  for (int i = 0; i < KPT; ++i)
+    if (LOKI_SEL_VALID(i)) atomicAdd(&sm.hist[0][key[i] >> 21], 1u);
+  __syncthreads();
+  resident_find_bin<THREADS>(sm, 0, rem_in);
+  LOKI_STAMP(13);
+  resident_threshold_in_bin<THREADS, KPT>(key, valid_mask, sm, T, need_eq);
+}
+#undef LOKI_SEL_VALID
 
 // The block's positions are laid out wave by wave: wave w owns the 64*C consecutive positions
 // from w*64*C in tiles of 256, and inside a tile lane l holds the 4 positions from 4l — one
@@ -677,7 +685,7 @@ __device__ __forceinline__ int wave_choose(const uint32_t* a, int n, const WaveT
 // looks at its run once: the rows above the threshold's bin and the rows inside it, the candidates, become two bit
 // masks.  The candidates' keys are collected in any order, the first wave finds the exact threshold among them
 // (wave_threshold), and every thread then looks at its own candidates again.  More candidates than hist[1] holds (long
-// runs of equal scores): three digit passes over all keys (resident_threshold).
+// runs of equal scores): the further digit passes of resident_threshold over all keys.
 template <int THREADS, int KPT, typename Emit>
 __device__ __forceinline__ void contiguous_select(const uint32_t* s_key, int n, int C, int k, ResidentSelectSmem<THREADS>& sm,
                                                   Emit emit) {
@@ -727,10 +735,7 @@ __device__ __forceinline__ void contiguous_select(const uint32_t* s_key, int n, 
     uint32_t key[KPT];
 #pragma unroll
     for (int e = 0; e < KPT; ++e) key[e] = run[e];
-    __syncthreads();  // everyone has read n_cand
-    for (int i = tid; i < 2048; i += THREADS) sm.hist[0][i] = 0u;
-    __syncthreads();
-    resident_threshold<THREADS, KPT>(key, vm, (uint32_t)k, sm, T, need_eq);
+    resident_threshold_in_bin<THREADS, KPT>(key, vm, sm, T, need_eq);
 #pragma unroll
     for (int e = 0; e < KPT; ++e) {
       gt |= (key[e] > T ? 1u : 0u) << e;
@@ -764,8 +769,8 @@ __device__ __forceinline__ void contiguous_select(const uint32_t* s_key, int n, 
 //                       candidates, go to a list of their own.  Three barriers, and one at the end
 //   run_threshold       the exact threshold among the candidates, by one wave, without a barrier, so that a caller can
 //                       have the certain rows' loads in flight
-// A bin of more than kRunCand rows (long runs of nearly equal scores) makes run_select_certain find the exact
-// threshold with resident_threshold.
+// A bin of more than kRunCand rows (a quarter of a long sequence kept, or long runs of nearly equal scores) makes
+// run_select_certain find the exact threshold with resident_threshold's further passes.
 constexpr int kRunCand = 1024;
 
 template <int KPT>
@@ -868,10 +873,7 @@ __device__ __forceinline__ RunSelect run_select_certain(const RunKeys<KPT>& rk, 
       if (certain && ((gt >> i) & 1u)) emit(g_rank++, rk.pos0 + i, rk.key[i]);
     }
   } else {
-    __syncthreads();  // everyone has read n_cand
-    for (int i = threadIdx.x; i < 2048; i += THREADS) sm.hist[0][i] = 0u;
-    __syncthreads();
-    resident_threshold<THREADS, KPT>(rk.key, rk.valid, (uint32_t)k, sm, rs.t.T, rs.t.need_eq);
+    resident_threshold_in_bin<THREADS, KPT>(rk.key, rk.valid, sm, rs.t.T, rs.t.need_eq);
     rs.n_cand = 0;
   }
   __syncthreads();
