@@ -192,12 +192,12 @@ __device__ __forceinline__ void attend_trip(AttendAcc<T, NH>& acc, const float (
 }
 
 // The same over a list that is still growing: entries below `there` exist when the call begins, and those of the
-// first trip are loaded before complete(), which completes the list (every wave calls it once).  R: rows of a lane
-// group in flight; a launch of one block per CU or less waits for the latency of every trip.
-template <typename T, int NH, int NGROUPS, bool REUSE_LO, int R, typename Complete>
+// first trip are loaded before complete(), which completes the list (every wave calls it once).
+template <typename T, int NH, int NGROUPS, bool REUSE_LO, typename Complete>
 __device__ __forceinline__ void attend_growing(AttendAcc<T, NH>& acc, const float (&qr)[NH][T::EPC],
                                                const RowAddr& ra, const int32_t* s_idx, const float* s_a, int gid,
                                                int r0, int r1, int there, Complete complete) {
+  constexpr int R = kRowsInFlight;
   uint4 kraw[R], vraw[R];
   float alo[R];
   auto clear = [&]() {

@@ -93,7 +93,7 @@ struct SelectShare {
     resident_select_clear<kSaThreads>(sm);
     __syncthreads();
     LOKI_STAMP(1);
-    rs = run_select_certain<kSaThreads, KPT>(keys, k, sm, true, [&](int rank, int pos, uint32_t key) {
+    rs = run_select_certain<kSaThreads, KPT>(keys, k, sm, [&](int rank, int pos, uint32_t key) {
       if (rank >= r0 && rank < r1) {
         s_idx[rank - r0] = row_of(a, hkv, s_pages, pos);
         if (s_a) s_a[rank - r0] = key_to_float(key);
@@ -220,7 +220,7 @@ __global__ __launch_bounds__(kSaThreads, NH == 1 ? 4 : 2) void select_attend_ker
   AttendAcc<T, NH> acc;
   acc.init();
   if constexpr (GROWING)
-    attend_growing<T, NH, kSaWaves * RPW, REUSE_LO, kRowsInFlight>(
+    attend_growing<T, NH, kSaWaves * RPW, REUSE_LO>(
         acc, qr, ra, s_idx, s_a, wave * RPW + rg, r0, r1, there, [&] { share.complete(a, hkv, r0, r1, s_sel, s_pages, s_idx, score); });
   else
     attend_rows<T, NH, kSaWaves * RPW, true, REUSE_LO>(acc, qr, ra, s_idx, s_a, wave * RPW + rg, r0, r1);

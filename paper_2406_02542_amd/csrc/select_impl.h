@@ -841,11 +841,10 @@ __device__ __forceinline__ void run_partition(const RunKeys<KPT>& rk, int shift,
   e_rank = (int)(before >> 16);
 }
 
-// emit(rank, pos, key) for every certain row, ranks ascending with the position, unless `certain` is false (or
-// the threshold has been found instead).  sm.hist clear and rk loaded by every thread; sm.hist[1] holds the
-// candidates afterwards.
+// emit(rank, pos, key) for every certain row, ranks ascending with the position, unless the threshold has been
+// found instead.  sm.hist clear and rk loaded by every thread; sm.hist[1] holds the candidates afterwards.
 template <int THREADS, int KPT, typename Emit>
-__device__ __forceinline__ RunSelect run_select_certain(const RunKeys<KPT>& rk, int k, ResidentSelectSmem<THREADS>& sm, bool certain,
+__device__ __forceinline__ RunSelect run_select_certain(const RunKeys<KPT>& rk, int k, ResidentSelectSmem<THREADS>& sm,
                                                         Emit emit) {
 #pragma unroll
   for (int i = 0; i < KPT; ++i)
@@ -870,7 +869,7 @@ __device__ __forceinline__ RunSelect run_select_certain(const RunKeys<KPT>& rk, 
         sm.hist[1][kRunCand + e_rank] = (uint32_t)(rk.pos0 + i);
         ++e_rank;
       }
-      if (certain && ((gt >> i) & 1u)) emit(g_rank++, rk.pos0 + i, rk.key[i]);
+      if ((gt >> i) & 1u) emit(g_rank++, rk.pos0 + i, rk.key[i]);
     }
   } else {
     resident_threshold_in_bin<THREADS, KPT>(rk.key, rk.valid, sm, rs.t.T, rs.t.need_eq);
