@@ -13,7 +13,7 @@ from tests.parity import check_out
 pytestmark = pytest.mark.gpu
 
 
-def _check(path, G, S, above, inside, chosen, kinds, first_rows, paged, copies=1):
+def _check(path, G, S, above, inside, chosen, kinds, first_rows, paged, copies=1, last_stage="fused_decode"):
     Hkv, D, d = 2, 128, 16  # (copies: of the two KV heads, where the route needs many)
     k = above + chosen
     print("case", path, G, S, above, inside, chosen, kinds, first_rows, paged, flush=True)
@@ -59,11 +59,17 @@ def _check(path, G, S, above, inside, chosen, kinds, first_rows, paged, copies=1
     ws = api.alloc_workspace(lay, S, d, k, mode)
     idx = torch.full((1, Hkv, k), -7, dtype=torch.int32, device="cuda")
     outs = []
-    for want in (idx, None):
-        out = torch.full((1, Hkv * G, D), float("nan"), dtype=dt, device="cuda")
-        api.loki_decode_step(lay, q, P, klo, khi, vv, S, d, k, mode | path, ws, out, want, **step)
-        outs.append(out)
+    prof = api.Profile()
+    prof.attach()
+    try:
+        for want in (idx, None):
+            out = torch.full((1, Hkv * G, D), float("nan"), dtype=dt, device="cuda")
+            api.loki_decode_step(lay, q, P, klo, khi, vv, S, d, k, mode | path, ws, out, want, **step)
+            outs.append(out)
+    finally:
+        prof.detach()
     torch.cuda.synchronize()
+    assert prof.read()[-1][0] == last_stage
     assert torch.equal(outs[0], outs[1])
     assert torch.equal(idx, idx[:, :2].repeat(1, copies, 1))
     for h in range(2):
@@ -116,11 +122,23 @@ def test_candidates_one_block_per_head(S, above, inside, chosen, kinds, paged):
     _check(0, 1, S, above, inside, chosen, kinds, False, paged, copies=64)
 
 
-# selection inside the attention launch, which begins with the certain rows: lists of up to 1024 candidates
+# selection inside the attention launch, which begins with the certain rows from 2049 to 8192 rows on (S stays beside
+# that line: both forms report the same stage): lists of up to 1024 candidates, shares with and without certain rows
 @pytest.mark.parametrize("G", [1, 4])
 @pytest.mark.parametrize("S,above,inside,chosen,kinds,paged", [
-    (300, 0, 1, 1, 9, False), (700, 40, 3, 2, 9, True), (4000, 700, 256, 255, 999, True), (4097, 700, 1024, 1000, 9999, False),
-    (8000, 64, 1024, 700, 3, True), (8000, 64, 1025, 700, 9999, False), (12000, 900, 600, 300, 9999, True), (12000, 0, 12000, 3000, 9999, False),
-    (16384, 3000, 900, 500, 1, False)])
+    (2049, 0, 1, 1, 9, False), (2500, 40, 3, 2, 9, True), (4000, 700, 256, 255, 999, True), (4097, 700, 1024, 1000, 9999, False),
+    (8000, 64, 1024, 700, 3, True), (8000, 64, 1025, 700, 9999, False), (8191, 100, 1000, 900, 9999, False), (3001, 0, 1024, 1024, 999, False),
+    (5001, 1500, 900, 500, 1, True), (8192, 0, 8192, 2500, 9999, True), (8192, 100, 3000, 2000, 2, False), (2050, 33, 1300, 1, 9999, False)])
 def test_candidates_in_the_attention_launch(G, S, above, inside, chosen, kinds, paged):
-    _check(api.PATH_SPLIT, G, S, above, inside, chosen, kinds, False, paged)
+    assert 2048 < S <= 8192
+    _check(api.PATH_SPLIT, G, S, above, inside, chosen, kinds, False, paged, last_stage="select_attend")
+
+
+# the same launch with the whole list before the attention, and the selection in a launch of its own
+@pytest.mark.parametrize("G,S,above,inside,chosen,kinds,paged,last_stage", [
+    (1, 700, 40, 3, 2, 9, True, "select_attend"), (4, 2048, 40, 1025, 700, 99, False, "select_attend"),
+    (4, 12000, 900, 600, 300, 9999, True, "select_attend"), (4, 16384, 3000, 900, 500, 1, False, "select_attend"),
+    (1, 12000, 0, 12000, 3000, 9999, False, "gather_attend")])
+def test_candidates_before_the_attention(G, S, above, inside, chosen, kinds, paged, last_stage):
+    assert S <= 2048 or S > 8192
+    _check(api.PATH_SPLIT, G, S, above, inside, chosen, kinds, False, paged, last_stage=last_stage)

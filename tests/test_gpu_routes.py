@@ -9,8 +9,8 @@ pytestmark = pytest.mark.gpu
 DT = {"bf16": torch.bfloat16, "f32": torch.float32}
 
 
-def stages(dtype, B, Hq, Hkv, S, d, k, mode, append=False, paged=False, lengths=False):
-    """Names of the kernels that one step launches."""
+def run(dtype, B, Hq, Hkv, S, d, k, mode, append=False, paged=False, lengths=False):
+    """Names of the kernels that one step launches, and whether they wrote to the workspace."""
     dt, D = DT[dtype], 128
     lay = api.make_layout(B, Hq, Hkv, D, d, S, dt)
     per = -(-S // 256)
@@ -26,7 +26,7 @@ def stages(dtype, B, Hq, Hkv, S, d, k, mode, append=False, paged=False, lengths=
     if paged:
         step["page_table"] = torch.arange(B * per, dtype=torch.int32, device="cuda").reshape(B, per)
         step["page_rows"], step["n_pages"] = 256, B * per
-    ws = api.alloc_workspace(lay, S, d, k, mode)
+    ws = api.alloc_workspace(lay, S, d, k, mode, zeroed=True)
     out = torch.empty_like(q)
     prof = api.Profile()
     prof.attach()
@@ -38,7 +38,20 @@ def stages(dtype, B, Hq, Hkv, S, d, k, mode, append=False, paged=False, lengths=
     names = [n for n, _ in prof.read()]
     print(dtype, B, Hq, Hkv, S, d, k, hex(mode), append, paged, names, flush=True)
     assert torch.all(out == 0)  # (the values are zeros)
-    return names
+    return names, bool((ws != 0).any())
+
+
+def stages(*args, **kw):
+    return run(*args, **kw)[0]
+
+
+def group_launch(*args, **kw):
+    """The sequence of a step with one selection per KV head.  Both single launches report the same stage; several
+    blocks per unit exchange counts through the workspace, one block writes nothing there."""
+    names, wrote = run(*args, **kw)
+    if names != ["fused_decode"]:
+        return "split"
+    return "several" if wrote else "one"
 
 
 @pytest.mark.parametrize("one_launch,dtype,B,Hq,Hkv,S,d,k,mode", [
@@ -94,10 +107,28 @@ def test_selection_in_a_launch_of_its_own(dtype, B, Hkv, G, mode, S, d, k):
     (True, 8, 8, 8, 1024, 32, 256, False, False), (True, 16, 8, 2, 2048, 64, 1024, False, False),
     # fewer units, fewer bytes a row: 2 heads 92 bytes at 80 units, 4 heads 120 bytes at 64 and 80 units
     (True, 10, 8, 2, 4096, 16, 512, True, False), (False, 10, 8, 2, 4096, 32, 512, False, True),
-    (False, 8, 8, 4, 4096, 32, 512, True, False), (True, 5, 16, 4, 4096, 32, 512, False, False)])
+    (False, 8, 8, 4, 4096, 32, 512, True, False), (True, 5, 16, 4, 4096, 32, 512, False, False),
+    # 120 bytes a row at 64 units: 2 heads under the line from 4097 rows on, 8 heads under it
+    (True, 8, 8, 2, 6000, 32, 750, True, False), (False, 8, 8, 2, 4096, 32, 512, True, False), (True, 8, 8, 8, 4096, 32, 512, True, False)])
 def test_one_block_per_group(one_launch, B, Hkv, G, S, d, k, append, paged):
-    names = stages("bf16", B, G * Hkv, Hkv, S, d, k, 1, append=append, paged=paged)
-    assert (names == ["fused_decode"]) == one_launch
+    launch = group_launch("bf16", B, G * Hkv, Hkv, S, d, k, 1, append=append, paged=paged)
+    assert launch == ("one" if one_launch else "split")
+
+
+@pytest.mark.parametrize("launch,B,Hkv,G,S,d,k", [
+    # up to 64 units: beyond 8192 rows, or 1.8 MB a unit
+    ("several", 1, 8, 4, 8193, 16, 64), ("split", 1, 8, 4, 8192, 16, 64), ("several", 8, 8, 8, 8193, 32, 512),
+    ("several", 1, 8, 8, 8192, 64, 1500), ("split", 1, 8, 8, 8192, 64, 1400),
+    # 64 columns and over 4096 rows: from 32 units 1.31 MB, from 64 units 1 MB
+    ("several", 4, 8, 4, 8192, 64, 512), ("split", 4, 8, 4, 8192, 64, 511), ("split", 3, 8, 4, 8192, 64, 512),
+    ("several", 8, 8, 4, 6000, 64, 454), ("split", 8, 8, 4, 4096, 64, 1024), ("several", 8, 8, 4, 4097, 64, 1024),
+    # 65 to 128 units: 64 columns as there; else from 12288 rows on unless one block per unit applies and keeps under a twelfth,
+    # and below that 1.31 MB where it does not apply
+    ("several", 16, 8, 4, 5000, 64, 704), ("one", 16, 8, 4, 5000, 64, 703), ("several", 16, 8, 4, 12288, 32, 1024),
+    ("one", 16, 8, 4, 12288, 32, 1023), ("several", 9, 8, 4, 12287, 32, 1025), ("split", 9, 8, 4, 12287, 32, 1024),
+    ("one", 17, 8, 4, 12288, 32, 1024)])  # (136 units: two blocks each are more than the CUs)
+def test_several_blocks_per_group(launch, B, Hkv, G, S, d, k):
+    assert group_launch("bf16", B, G * Hkv, Hkv, S, d, k, 1) == launch
 
 
 @pytest.mark.parametrize("one_launch,dtype,B,S,d,k,append,paged", [
@@ -179,5 +210,4 @@ def test_dense_sequences_of_equal_length_given_as_lengths(dtype, B, G, S, n):
     (True, 10, 4, False, False), (False, 10, 4, False, True), (True, 10, 4, True, True)])
 def test_one_block_per_group_on_pages_and_with_lengths(one_launch, B, G, paged, lengths):
     """120 bytes of slab and list a row, 96 units of 2 heads and 80 of 4."""
-    names = stages("bf16", B, G * 8, 8, 4096, 32, 512, 1, paged=paged, lengths=lengths)
-    assert (names == ["fused_decode"]) == one_launch
+    assert group_launch("bf16", B, G * 8, 8, 4096, 32, 512, 1, paged=paged, lengths=lengths) == ("one" if one_launch else "split")
