@@ -68,9 +68,10 @@ constexpr int kFusedMaxPages = kFusedMaxS / 256;  // pages are at least 256 rows
 
 // PAGED: the three slabs are pools addressed through the sequence's page list (see Paging).
 // Two blocks share a CU (4 waves per SIMD) as far as LDS allows: the register budget is 128 VGPRs and the compiler
-// is told not to trade load-level parallelism for a higher occupancy that cannot happen.  LDS allows it while the
-// dynamic part, 4 (33/32 S + k) bytes (4 S + 8 k up to 8192 rows, 33/8 S + 8 k on a paged cache), leaves room for 18 KB of static arrays in
-// half of 160 KB: S = 12345, k = 1543 fits, S = 16384 does not, and a block has its CU to itself at the same budget.
+// is told not to trade load-level parallelism for a higher occupancy that cannot happen.  LDS allows
+// it (fused_two_per_cu) while the dynamic part, 4 (33/32 S + k) bytes (4 S + 8 k up to 8192 rows, 33/8 S + 8 k
+// on a paged cache), leaves room for the static arrays in half of 160 KB: S = 13800, k = 1725 fits,
+// S = 16384 does not, and a block has its CU to itself at the same budget.
 // KPT = keys a thread holds in the select stage (8 for S <= 4096, 16 for S <= 8192, else 32).
 // GROUPED: G query heads to a KV head, every one selecting for itself.
 template <typename T, int LPR, bool REUSE_LO, int KPT, bool APPEND, bool PAGED, bool GROUPED>
@@ -86,8 +87,8 @@ fused_decode_kernel(
   constexpr int RPW = 64 / LPRV;
 
   // The rotation's partial sums and then the scores' keys, the index list, and the scores of its entries;
-  // long sequences (KPT = 32) leave those out, so that two blocks share a CU's LDS up to S + k = 14800,
-  // and look a row's score up by its position (a paged cache's entries are pool rows and need the copy).
+  // long sequences (KPT = 32) leave those out, so that two blocks share a CU's LDS for longer, and look a
+  // row's score up by its position (a paged cache's entries are pool rows and need the copy).
   constexpr bool kKeysInLds = KPT > kFusedRegisterKeys, kScoreByRow = kKeysInLds && !PAGED;
   extern __shared__ __align__(16) unsigned char dyn_smem[];
   const int per_thread = kKeysInLds ? KPT : fused_keys_per_thread(S_max);  // multiple of 4, <= KPT
@@ -305,6 +306,16 @@ size_t fused_dynamic_lds(const Shape& s) {
   return fused_region_bytes(s.S) + (size_t)s.k * (score_by_row ? 4 : 8);
 }
 
+// The static arrays of a block of grouped heads: the query before and after its rotation, the selection, the page list.
+static size_t fused_static_lds(const Shape& s) {
+  const size_t select = (sizeof(ResidentSelectSmem<kFusedThreads>) + 15) / 16 * 16;
+  return select + 2 * kD * sizeof(float) + (s.pg.table != nullptr ? kFusedMaxPages * sizeof(int32_t) : 0);
+}
+
+static bool fused_two_per_cu(const Shape& s) {
+  return 2 * (fused_dynamic_lds(s) + fused_static_lds(s)) <= 160 * 1024;
+}
+
 bool fused_eligible(const Shape& s) {
   // several new tokens per sequence: a block would read rows appended by other blocks of the launch
   if (s.rg.queries > 1) return false;
@@ -328,8 +339,11 @@ bool fused_pinnable(const Shape& s) {
 //   groups: 0.49 MB 32 heads 16.6 / 16.8; 0.74 MB 64 heads 22.2 / 22.7; 0.98 MB 64 heads 26.9 / 24.0, 128
 //   29.5 / 29.5; 1.5 MB 128 heads 49.2 / 48.1, 256 59.1 / 70.6, 512 88.8 / 115.6
 // With groups every head's block rotates its query from P_h again: 1024 heads of 0.12 MB 29.4 / 25.0, of 0.25 MB
-// 38.8 / 39.3.  Past the length at which two blocks share a CU's LDS a second round of blocks costs more than the
-// split path: S = 16384, k = 2048, groups of 4, 256 heads 71.6 / 76.4, 512 139 / 132.  A group's appended row
+// 38.8 / 39.3.  Past the length at which two blocks share a CU's LDS (fused_two_per_cu) a second round of blocks costs
+// groups of 8 more than the split path and leaves groups of 4 level: 1024 heads in groups of 8, S = 13800, k = 1725 156 / 179,
+// S = 14300, k = 893 124 / 141, k = 1787, one block per CU, 198 / 184, on pages S = 14000, k = 700 118 / 132, S = 13000, k = 1300
+// 177 / 162; 512 heads in groups of 4, S = 13800, k = 1725 91.9 / 114, S = 14800, k = 462 53.9 / 67.4, k = 925 88.7 / 88.3; but
+// S = 16384, k = 2048, 256 heads 71.6 / 76.4, 512 139 / 132.  A group's appended row
 // needs a launch of its own in front (about 4 us): groups of 4, 0.49 MB, 512 heads 38.6 / 42.2, 0.98 MB 256 heads
 // 43.8 / 44.2; groups of 8, 0.49 MB 512 heads 35.5 / 32.2, 0.98 MB 256 heads 38.6 / 37.3, 512 56.7 / 60.3.
 // The G heads of a unit each stream the slab, which the scoring of the split path reads once, and pay for it in L2
@@ -352,7 +366,7 @@ bool fused_preferred(const Shape& s) {
     const double spare = heads > cus / 8 ? 6.4 * (double)(heads - cus / 8) / (double)cus : 0.0;
     return 2 * heads >= cus || mb <= 0.5 + spare * (s.S < 8192 ? s.S / 8192.0 : 1.0);
   }
-  if (heads > cus && s.G > 2 && 4 * ((size_t)s.S + (size_t)s.k * (fused_keys_in_lds(s.S) && s.pg.table == nullptr ? 1 : 2)) > 58 * 1024) return false;
+  if (heads > cus && s.G > 2 && !fused_two_per_cu(s)) return false;
   const int row_bytes = s.d * s.elem_bytes;
   if (heads > cus && row_bytes > 256) return false;
   if (heads > 2 * cus && (s.G == 8 ? row_bytes > 64 : s.G == 4 && row_bytes > 192)) return false;

@@ -145,10 +145,20 @@ def test_one_block_per_head_of_its_own_kv_head(one_launch, dtype, B, S, d, k, ap
     (True, "bf16", 16, 4, 1100, 32, 400, False), (True, "f32", 4, 4, 1000, 128, 250, False), (False, "f32", 16, 4, 1000, 128, 250, False),
     (False, "f32", 33, 2, 1000, 96, 250, False), (False, "bf16", 64, 4, 1000, 128, 250, False), (True, "bf16", 64, 2, 1000, 128, 250, False),
     (True, "bf16", 32, 4, 1500, 64, 375, False), (False, "bf16", 50, 4, 1500, 64, 375, False), (False, "bf16", 16, 8, 1500, 64, 375, False),
-    (True, "bf16", 16, 8, 1500, 32, 375, False), (False, "bf16", 32, 8, 1200, 32, 400, False), (False, "bf16", 64, 4, 1000, 64, 250, True)])
+    (True, "bf16", 16, 8, 1500, 32, 375, False), (False, "bf16", 32, 8, 1200, 32, 400, False), (False, "bf16", 64, 4, 1000, 64, 250, True),
+    # the LDS of two blocks on a CU: 4 (33/32 S + 33 + k) bytes and 17760 each
+    (True, "bf16", 16, 4, 13800, 32, 1775, False), (False, "bf16", 16, 4, 13800, 32, 1777, False),
+    (True, "f32", 16, 8, 14800, 16, 742, False), (False, "f32", 16, 8, 14800, 16, 750, False)])
 def test_one_block_per_head_of_a_group(one_launch, dtype, B, G, S, d, k, append):
     names = stages(dtype, B, 8 * G, 8, S, d, k, 0, append=append)
     assert (names == (["append", "fused_decode"] if append else ["fused_decode"])) == one_launch
+
+
+@pytest.mark.parametrize("one_launch,k", [(True, 752), (False, 754)])
+def test_one_block_per_head_of_a_group_on_pages(one_launch, k):
+    """As there, 4 (33/32 S + 33) + 8 k bytes and 18016 each: 752 rows of 14000."""
+    names = stages("bf16", 16, 32, 8, 14000, 32, k, 0, paged=True)
+    assert (names == ["fused_decode"]) == one_launch
 
 
 @pytest.mark.parametrize("split,dtype,B,Hq,Hkv,S,ragged", [
