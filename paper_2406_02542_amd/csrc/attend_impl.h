@@ -65,84 +65,6 @@ __device__ __forceinline__ RowAddr make_row_addr(const void* k_a, const void* k_
   return ra;
 }
 
-// Processes list entries r in [r0, r1): cache row = GATHER ? s_idx[r - r0] : r.  NGROUPS lane
-// groups of the block share the entries round-robin; `gid` is this lane's group.
-// s_a: REUSE_LO: the saved score of entry r at r - r0 (SCORE_BY_ROW: the key of cache row `row`, at its padded position).
-// The arithmetic of a trip stands here and, for attend_growing, in attend_trip once more: called from here it compiles to
-// kernels that load a trip's rows later (fp32, 4 heads, 88 registers for 94), which costs dense attention over 2 to 7
-// sequences of 32/8 fp32 heads, S = 546 to 2310, 4 to 13 % (18.3 -> 20.4 us at 2 x 990 rows) and large ones 0.6 %.
-template <typename T, int NH, int NGROUPS, bool GATHER, bool REUSE_LO, bool SCORE_BY_ROW = false>
-__device__ __forceinline__ void attend_rows(AttendAcc<T, NH>& acc, const float (&qr)[NH][T::EPC],
-                                            const RowAddr& ra, const int32_t* s_idx,
-                                            const float* s_a, int gid, int r0, int r1) {
-  constexpr int EPC = T::EPC;
-  constexpr int LPRV = kD / EPC;
-  constexpr int R = kRowsInFlight;
-  static_assert(!REUSE_LO || NH == 1, "score reuse needs one query head per selection");
-  for (int t0 = r0; t0 < r1; t0 += NGROUPS * R) {
-    bool ok[R];
-    uint4 kraw[R], vraw[R];
-    float alo[R];
-#pragma unroll
-    for (int j = 0; j < R; ++j) {
-      const int r = t0 + j * NGROUPS + gid;
-      ok[j] = r < r1;
-      int row = 0;
-      alo[j] = 0.f;
-      if (ok[j]) {
-        row = GATHER ? s_idx[r - r0] : r;
-        if constexpr (REUSE_LO && SCORE_BY_ROW)
-          alo[j] = key_to_float(reinterpret_cast<const uint32_t*>(s_a)[row + (row >> 5)]);
-        else if constexpr (REUSE_LO)
-          alo[j] = s_a[r - r0];
-      }
-      kraw[j] = (ok[j] && ra.k_load) ? load16(ra.k_base + (size_t)row * ra.k_row_bytes)
-                                     : make_uint4(0, 0, 0, 0);
-      vraw[j] = ok[j] ? load16(ra.v_base + (size_t)row * ra.v_row_bytes) : make_uint4(0, 0, 0, 0);
-    }
-    float logit[NH][R];
-#pragma unroll
-    for (int j = 0; j < R; ++j) {
-      float kf[EPC];
-      T::unpack(kraw[j], kf);
-#pragma unroll
-      for (int g = 0; g < NH; ++g) {
-        float p = 0.f;
-#pragma unroll
-        for (int e = 0; e < EPC; ++e) p = fmaf(kf[e], qr[g][e], p);
-        p = group_allreduce_sum<LPRV>(p);
-        if constexpr (REUSE_LO) p += alo[j];
-        logit[g][j] = ok[j] ? p * kSoftmaxScaleLog2 : kNegBig;
-      }
-    }
-    float vf[R][EPC];
-#pragma unroll
-    for (int j = 0; j < R; ++j) T::unpack(vraw[j], vf[j]);
-#pragma unroll
-    for (int g = 0; g < NH; ++g) {
-      float mn = acc.m[g];
-#pragma unroll
-      for (int j = 0; j < R; ++j) mn = fmaxf(mn, logit[g][j]);
-      const float corr = fast_exp2(acc.m[g] - mn);
-      acc.m[g] = mn;
-      float pj[R], ps = 0.f;
-#pragma unroll
-      for (int j = 0; j < R; ++j) {
-        pj[j] = ok[j] ? fast_exp2(logit[g][j] - mn) : 0.f;
-        ps += pj[j];
-      }
-      acc.l[g] = fmaf(acc.l[g], corr, ps);
-#pragma unroll
-      for (int e = 0; e < EPC; ++e) {
-        float a = acc.o[g][e] * corr;
-#pragma unroll
-        for (int j = 0; j < R; ++j) a = fmaf(pj[j], vf[j][e], a);
-        acc.o[g][e] = a;
-      }
-    }
-  }
-}
-
 // One trip: R rows of this lane group (ok: the row exists), their chunks and saved scores loaded.
 template <typename T, int NH, int R, bool REUSE_LO>
 __device__ __forceinline__ void attend_trip(AttendAcc<T, NH>& acc, const float (&qr)[NH][T::EPC], const uint4 (&kraw)[R],
@@ -187,6 +109,89 @@ __device__ __forceinline__ void attend_trip(AttendAcc<T, NH>& acc, const float (
 #pragma unroll
       for (int j = 0; j < R; ++j) a = fmaf(pj[j], vf[j][e], a);
       acc.o[g][e] = a;
+    }
+  }
+}
+
+// Processes list entries r in [r0, r1): cache row = GATHER ? s_idx[r - r0] : r.  NGROUPS lane
+// groups of the block share the entries round-robin; `gid` is this lane's group.
+// s_a: REUSE_LO: the saved score of entry r at r - r0 (SCORE_BY_ROW: the key of cache row `row`, at its padded position).
+// APART: the arithmetic of a trip is attend_trip's, else it stands here once more: the compiler then loads a trip's
+// rows earlier (fp32, 4 heads, 94 registers for 88).  apart / here, us: dense attention over 2 sequences of 990
+// rows, 32/8 fp32 heads, 20.4 / 18.3, 2 to 7 of 546 to 2310 rows 4 to 13 % more, large ones 0.6 %; but one block per head beyond
+// 8192 rows, 512 heads in groups of 4, S = 12800, k = 400 46.4 / 47.3, S = 13300, k = 831 62.7 / 64.0.
+template <typename T, int NH, int NGROUPS, bool GATHER, bool REUSE_LO, bool SCORE_BY_ROW = false, bool APART = false>
+__device__ __forceinline__ void attend_rows(AttendAcc<T, NH>& acc, const float (&qr)[NH][T::EPC],
+                                            const RowAddr& ra, const int32_t* s_idx,
+                                            const float* s_a, int gid, int r0, int r1) {
+  constexpr int EPC = T::EPC;
+  constexpr int LPRV = kD / EPC;
+  constexpr int R = kRowsInFlight;
+  static_assert(!REUSE_LO || NH == 1, "score reuse needs one query head per selection");
+  for (int t0 = r0; t0 < r1; t0 += NGROUPS * R) {
+    bool ok[R];
+    uint4 kraw[R], vraw[R];
+    float alo[R];
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+      const int r = t0 + j * NGROUPS + gid;
+      ok[j] = r < r1;
+      int row = 0;
+      alo[j] = 0.f;
+      if (ok[j]) {
+        row = GATHER ? s_idx[r - r0] : r;
+        if constexpr (REUSE_LO && SCORE_BY_ROW)
+          alo[j] = key_to_float(reinterpret_cast<const uint32_t*>(s_a)[row + (row >> 5)]);
+        else if constexpr (REUSE_LO)
+          alo[j] = s_a[r - r0];
+      }
+      kraw[j] = (ok[j] && ra.k_load) ? load16(ra.k_base + (size_t)row * ra.k_row_bytes)
+                                     : make_uint4(0, 0, 0, 0);
+      vraw[j] = ok[j] ? load16(ra.v_base + (size_t)row * ra.v_row_bytes) : make_uint4(0, 0, 0, 0);
+    }
+    if constexpr (APART) {
+      attend_trip<T, NH, R, REUSE_LO>(acc, qr, kraw, vraw, alo, ok);
+    } else {
+      float logit[NH][R];
+#pragma unroll
+      for (int j = 0; j < R; ++j) {
+        float kf[EPC];
+        T::unpack(kraw[j], kf);
+#pragma unroll
+        for (int g = 0; g < NH; ++g) {
+          float p = 0.f;
+#pragma unroll
+          for (int e = 0; e < EPC; ++e) p = fmaf(kf[e], qr[g][e], p);
+          p = group_allreduce_sum<LPRV>(p);
+          if constexpr (REUSE_LO) p += alo[j];
+          logit[g][j] = ok[j] ? p * kSoftmaxScaleLog2 : kNegBig;
+        }
+      }
+      float vf[R][EPC];
+#pragma unroll
+      for (int j = 0; j < R; ++j) T::unpack(vraw[j], vf[j]);
+#pragma unroll
+      for (int g = 0; g < NH; ++g) {
+        float mn = acc.m[g];
+#pragma unroll
+        for (int j = 0; j < R; ++j) mn = fmaxf(mn, logit[g][j]);
+        const float corr = fast_exp2(acc.m[g] - mn);
+        acc.m[g] = mn;
+        float pj[R], ps = 0.f;
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+          pj[j] = ok[j] ? fast_exp2(logit[g][j] - mn) : 0.f;
+          ps += pj[j];
+        }
+        acc.l[g] = fmaf(acc.l[g], corr, ps);
+#pragma unroll
+        for (int e = 0; e < EPC; ++e) {
+          float a = acc.o[g][e] * corr;
+#pragma unroll
+          for (int j = 0; j < R; ++j) a = fmaf(pj[j], vf[j][e], a);
+          acc.o[g][e] = a;
+        }
+      }
     }
   }
 }

@@ -284,7 +284,7 @@ fused_decode_kernel(
   const RowAddr ra = make_row_addr<T, REUSE_LO>(klo, khi, v, PAGED ? (size_t)0 : (size_t)unit, S_cap, d, c);
   AttendAcc<T, 1> acc;
   acc.init();
-  attend_rows<T, 1, kFusedWaves * RPW, true, REUSE_LO, kScoreByRow>(acc, qr, ra, s_idx, s_a, wave * RPW + rg, 0, k);
+  attend_rows<T, 1, kFusedWaves * RPW, true, REUSE_LO, kScoreByRow, kKeysInLds>(acc, qr, ra, s_idx, s_a, wave * RPW + rg, 0, k);
   LOKI_STAMP(7);
   attend_publish<T, 1, kFusedWaves>(acc, s_merge);
   if (tid < kD) {
