@@ -62,10 +62,11 @@ __device__ __forceinline__ void select_share(const SelectAttendArgs& a, int sel,
   __syncthreads();
 }
 
-// The same selection in two parts, so that the attention can begin in between (GROWING): begin() leaves the entries
-// that are certain, below the value returned; complete() appends the chosen candidates, ranked by the first wave while every
-// wave has its first rows' loads in flight, and writes the caller's ascending copy.  The list is two ascending
-// runs, or one where the bin held too many candidates.
+// The same selection in two parts, so that the attention can begin in between (GROWING): begin()
+// leaves the entries that are certain, below the value returned; complete() appends the chosen
+// candidates, ranked by the first wave while every wave has its first rows' loads in flight, and
+// writes the caller's ascending copy.  The list is two ascending runs, or one where the bin held
+// too many candidates.
 template <int KPT>
 struct SelectShare {
   RunKeys<KPT> keys;
@@ -285,20 +286,22 @@ static int select_attend_splits(const Shape& s, int select_mode) {
   return n > 1 ? n : 1;
 }
 
-// One launch, or selection and attention in two?  Every block here selects for itself, on 512 threads, so what
-// counts is how often a CU has to do that.  Both ways timed behind the same scoring on 1239 shapes, us per
-// step, one launch / two:
-//   matrix cores, and eight heads on the vector units (one block per CU fits): one round of blocks and no
-//     more.  128 units of 4 heads, S = 12000, k = 3000 (2 splits: one round) 75.4 / 76.6, 256 units (two rounds) 154 / 141,
-//     512 units 325 / 291; 256 units of 8 heads, fp32, S = 8192, k = 1024 136 / 143, 512 units, S = 4096 203 / 199
-//   vector units, S <= 8192: one split per head always (4096 heads, S = 8192, k = 2048 488 / 529; 512 heads, S = 600 19.7 /
-//     22.8), several in one round, and two of them in any number of rounds (k up to 4096; 1024 heads, k = 2500 353 / 373) but
-//     for several tokens per sequence, whose heads share their rows (768 heads, k = 2139 91 / 84)
-//   vector units, S > 8192, where a thread holds 20 to 32 keys and the selection alone has twice the threads:
-//     one split per head in more than one round (512 heads, S = 16384, k = 2048 227 / 236; 2048 heads 494 / 517); in one
-//     round the two are level (256 heads, S = 9000 43.4 / 44.1; 48 heads, 5 splits 42.8 / 38.0) and with forced
-//     splits every block selects again (4096 heads, S = 16384, k = 4096, 4 tokens 983 / 847; 320 heads, S = 14745, k = 7372
-//     219 / 180).
+// One launch, or selection and attention in two?  Every block here selects for itself, on 512
+// threads, so what counts is how often a CU has to do that.  Both ways timed behind the same
+// scoring on 1239 shapes, us per step, one launch / two:
+//   matrix cores, and eight heads on the vector units (one block per CU fits): one round of blocks
+//     and no more.  128 units of 4 heads, S = 12000, k = 3000 (2 splits: one round) 75.4 / 76.6,
+//     256 units (two rounds) 154 / 141, 512 units 325 / 291; 256 units of 8 heads, fp32, S = 8192,
+//     k = 1024 136 / 143, 512 units, S = 4096 203 / 199
+//   vector units, S <= 8192: one split per head always (4096 heads, S = 8192, k = 2048 488 / 529;
+//     512 heads, S = 600 19.7 / 22.8), several in one round, and two of them in any number of
+//     rounds (k up to 4096; 1024 heads, k = 2500 353 / 373) but for several tokens per sequence,
+//     whose heads share their rows (768 heads, k = 2139 91 / 84)
+//   vector units, S > 8192, where a thread holds 20 to 32 keys and the selection alone has twice
+//     the threads: one split per head in more than one round (512 heads, S = 16384, k = 2048 227 /
+//     236; 2048 heads 494 / 517); in one round the two are level (256 heads, S = 9000 43.4 / 44.1;
+//     48 heads, 5 splits 42.8 / 38.0) and with forced splits every block selects again (4096 heads,
+//     S = 16384, k = 4096, 4 tokens 983 / 847; 320 heads, S = 14745, k = 7372 219 / 180).
 bool select_attend_applies(const Shape& s, int select_mode) {
   if (s.S > kSaThreads * 32) return false;
   const int NH = select_mode == 1 ? s.G : 1, n = select_attend_splits(s, select_mode);
@@ -308,14 +311,25 @@ bool select_attend_applies(const Shape& s, int select_mode) {
   return n == 1 || one_round || (n == 2 && s.rg.queries <= 1);
 }
 
-// Attention that begins before the list is complete: where its blocks wait for memory and nothing else runs beside them (one
-// round of blocks, bf16), the heads do not share their rows (whose blocks walk them in step in one ascending list), and the rows
-// are between 2049, below which the selection is short, and 8192, beyond which a thread holds 32 keys.  us per step, apart /
-// begun early: 32 heads, S = 4096, k = 1024 19.1 / 18.2; 32 heads, S = 8000, k = 2000 26.5 / 24.6; 16 heads, S = 7544, k = 471 21.9 / 21.3; on
-// the matrix cores, always one round, 32/8 heads, S = 8192 21.4 / 20.8, S = 3000, k = 750 18.9 / 18.0, 4 tokens of 32/8 heads, S = 4374
-// 27.6 / 27.0 (60 shapes in this range: 3.5 % less on average, three of them 1.7 to 2.1 % more); but S = 1200, k = 150 19.6 / 20.3, S =
-// 11000, k = 2750 35.1 / 36.7, fp32, 24 heads, S = 3473, k = 217 17.4 / 18.3, and 2 tokens of 4 sequences, S = 1920 24.5 / 25.5.
+// Attention that begins before the list is complete: where its blocks wait for memory and nothing
+// else runs beside them (one round of blocks, bf16), the heads do not walk shared rows in step in
+// one ascending list (xcd_group_blocks, on the vector units), and the rows are between 2049, below
+// which the selection is short, and 8192, beyond which a thread holds 32 keys. us per step, apart /
+// begun early: 32 heads, S = 4096, k = 1024 19.1 / 18.2; 32 heads, S = 8000, k = 2000 26.5 / 24.6;
+// 16 heads, S = 7544, k = 471 21.9 / 21.3; on the matrix cores, always one round, 32/8 heads, S =
+// 8192 21.4 / 20.8, S = 4685, k = 146 19.9 / 18.4 (147 such shapes: 2 % less on average, single
+// ones up to 8 % more, S = 3057, k = 764 19.7 / 21.1, where one unit's search among the candidates
+// takes long); but S = 1200, k = 150 19.6 / 20.3, S = 11000, k = 2750 35.1 / 36.7, fp32, 24 heads,
+// S = 3473, k = 217 17.4 / 18.3, and on the vector units 2 tokens of 4 sequences, S = 1920 24.5 /
+// 25.5.
+// Several tokens per sequence on the matrix cores: with lists of up to 1536 rows (336 shapes of 2
+// and 4 tokens: 1 % less on average; 2 tokens of 2 sequences of 32/8 heads, S = 4374, k = 546 27.4
+// / 26.1, 4 of 8, S = 8192, k = 1024 45.5 / 44.0), beyond which the bin often holds more candidates
+// than the list (4 of 2, S = 7426, k = 1856 33.0 / 34.5, 4 of 8 54.4 / 59.0), and again from three
+// tenths of the rows on, where the threshold lies nearer to 0 and its bin is narrower (2 of 1, S =
+// 5100, k = 1700 27.9 / 25.4, S = 7704, k = 3852 31.1 / 28.4).
 static bool attention_begins_early(const SelectAttendArgs& a, dim3 grid) {
+  if (a.rg.queries > 1 && a.k_max > 1536 && 10 * a.k_max < 3 * a.S_max) return false;
   return a.S_max > 2048 && a.S_max <= 8192 && a.xcd_group_blocks == 0 && (int)(grid.x * grid.y) <= device_cus();
 }
 
