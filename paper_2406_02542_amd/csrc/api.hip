@@ -86,21 +86,22 @@ static int max_dense_splits(const Shape& s) {
   return n > max_n ? max_n : n;
 }
 
-// Row splits of dense attention and of Algorithm 2, of at least 256 rows.  As many as make two blocks per
-// CU in bf16 and four in fp32, where that fills nine tenths of those places: a block's set-up and merge,
-// and the parts the combine launch reads, cost more than a smoother last round gains, and a few blocks
-// over a full round cost most.  Against eight per CU, us: 16 sequences of 32/8 heads at S = 16384 191 -> 181
-// (three per CU 183, four 186), 7 of them at S = 12000 73 -> 66 (rounded up to 2.2 per CU: 80), 32/32 heads at
-// S = 4096 188 -> 178, 64/8 heads at S = 8192 105 -> 97; Algorithm 2 121 -> 114, 129 -> 120, 136 -> 125; fp32, 9
-// sequences of 32/16 heads at S = 5790 154 -> 149.  Otherwise eight per CU (10 sequences of 32 heads, S = 4000:
-// 116, unsplit 120), and also where that makes one full round of three small blocks per CU (48 units,
-// S = 4186: 25.2, two larger per CU 26.0), and for long blocks of fp32 groups of 8, of which a CU holds three (132
-// units, S = 16159: eight 439, four 467; short ones, 33 units, S = 10370: 92.5, 82.1).
-// Sequences of unequal length: the same counts, and for bf16 first three per CU, as many as are resident (16 of
-// 32/8 heads, S = 16384: two 133, three 130, four 131), where the blocks are dealt out by length (dense_balanced); never
-// unsplit, which ends with the longest sequence (25 of 40 fp32 heads, S = 2076, most of them short: eight 46, unsplit
-// 78), and in fp32 from eight sequences on only dealt out (14 of 24/12 heads, S = 1798, eight 16.0, four 17.3; 6 of 32/4, S =
-// 15561, 79.0, 69.4).
+// Row splits of dense attention and of Algorithm 2, of at least 256 rows.  As many as make two
+// blocks per CU in bf16 and four in fp32, where that fills nine tenths of those places: a block's
+// set-up and merge, and the parts the combine launch reads, cost more than a smoother last round
+// gains, and a few blocks over a full round cost most.  Against eight per CU, us: 16 sequences of
+// 32/8 heads at S = 16384 191 -> 181 (three per CU 183, four 186), 7 of them at S = 12000 73 -> 66
+// (rounded up to 2.2 per CU: 80), 32/32 heads at S = 4096 188 -> 178, 64/8 heads at S = 8192 105 ->
+// 97; Algorithm 2 121 -> 114, 129 -> 120, 136 -> 125; fp32, 9 sequences of 32/16 heads at S = 5790
+// 154 -> 149.  Otherwise eight per CU (10 sequences of 32 heads, S = 4000: 116, unsplit 120), and
+// also where that makes one full round of three small blocks per CU (48 units, S = 4186: 25.2, two
+// larger per CU 26.0), and for long blocks of fp32 groups of 8, of which a CU holds three (132
+// units, S = 16159: eight 439, four 467; short ones, 33 units, S = 10370: 92.5, 82.1). Sequences of
+// unequal length: the same counts, and for bf16 first three per CU, as many as are resident (16 of
+// 32/8 heads, S = 16384: two 133, three 130, four 131), where the blocks are dealt out by length
+// (dense_balanced); never unsplit, which ends with the longest sequence (25 of 40 fp32 heads, S =
+// 2076, most of them short: eight 46, unsplit 78), and in fp32 from eight sequences on only dealt
+// out (14 of 24/12 heads, S = 1798, eight 16.0, four 17.3; 6 of 32/4, S = 15561, 79.0, 69.4).
 int dense_splits(const Shape& s, bool ragged) {
   const int units = s.B * s.Hkv, cus = device_cus();
   const int max_n = s.S / 256 > 0 ? s.S / 256 : 1;
@@ -118,11 +119,12 @@ int dense_splits(const Shape& s, bool ragged) {
   return n;
 }
 
-// Whether dense attention over sequences of unequal length deals its blocks out by length (dense_runs; a kernel
-// variant of its own): up to 64 sequences, and only where a block has at least 512 rows of the longest: working it out
-// takes about 1 us, which shorter blocks do not win back (16 units, S = 3000: 14.1 -> 15.0 us).  Every round of
-// blocks pays it anew; with eight per CU, as cut / dealt out: 288 units of one head, S = 6338, lengths from S / 4 on 128 / 114,
-// 320 units, S = 18990 417 / 399; but 800 units, S = 2687, most of them an eighth as long 26.6 / 28.7.
+// Whether dense attention over sequences of unequal length deals its blocks out by length
+// (dense_runs; a kernel variant of its own): up to 64 sequences, and only where a block has at
+// least 512 rows of the longest: working it out takes about 1 us, which shorter blocks do not win
+// back (16 units, S = 3000: 14.1 -> 15.0 us).  Every round of blocks pays it anew; with eight per
+// CU, as cut / dealt out: 288 units of one head, S = 6338, lengths from S / 4 on 128 / 114, 320
+// units, S = 18990 417 / 399; but 800 units, S = 2687, most of them an eighth as long 26.6 / 28.7.
 bool dense_balanced(const Shape& s, int nsplit) {
   return s.rg.seq_lens != nullptr && nsplit > 1 && s.B <= kDenseMaxRagged && s.S >= 512 * nsplit;
 }

@@ -115,11 +115,13 @@ __device__ __forceinline__ void attend_trip(AttendAcc<T, NH>& acc, const float (
 
 // Processes list entries r in [r0, r1): cache row = GATHER ? s_idx[r - r0] : r.  NGROUPS lane
 // groups of the block share the entries round-robin; `gid` is this lane's group.
-// s_a: REUSE_LO: the saved score of entry r at r - r0 (SCORE_BY_ROW: the key of cache row `row`, at its padded position).
-// APART: the arithmetic of a trip is attend_trip's, else it stands here once more: the compiler then loads a trip's
-// rows earlier (fp32, 4 heads, 94 registers for 88).  apart / here, us: dense attention over 2 sequences of 990
-// rows, 32/8 fp32 heads, 20.4 / 18.3, 2 to 7 of 546 to 2310 rows 4 to 13 % more, large ones 0.6 %; but one block per head beyond
-// 8192 rows, 512 heads in groups of 4, S = 12800, k = 400 46.4 / 47.3, S = 13300, k = 831 62.7 / 64.0.
+// s_a: REUSE_LO: the saved score of entry r at r - r0 (SCORE_BY_ROW: the key of cache row `row`, at
+// its padded position).
+// APART: the arithmetic of a trip is attend_trip's, else it stands here once more: the compiler
+// then loads a trip's rows earlier (fp32, 4 heads, 94 registers for 88).  apart / here, us: dense
+// attention over 2 sequences of 990 rows, 32/8 fp32 heads, 20.4 / 18.3, 2 to 7 of 546 to 2310 rows
+// 4 to 13 % more, large ones 0.6 %; but one block per head beyond 8192 rows, 512 heads in groups of
+// 4, S = 12800, k = 400 46.4 / 47.3, S = 13300, k = 831 62.7 / 64.0.
 template <typename T, int NH, int NGROUPS, bool GATHER, bool REUSE_LO, bool SCORE_BY_ROW = false, bool APART = false>
 __device__ __forceinline__ void attend_rows(AttendAcc<T, NH>& acc, const float (&qr)[NH][T::EPC],
                                             const RowAddr& ra, const int32_t* s_idx,
@@ -196,8 +198,9 @@ __device__ __forceinline__ void attend_rows(AttendAcc<T, NH>& acc, const float (
   }
 }
 
-// The same over a list that is still growing: entries below `there` exist when the call begins, and those of the
-// first trip are loaded before complete(), which completes the list (every wave calls it once).
+// The same over a list that is still growing: entries below `there` exist when the call begins, and
+// those of the first trip are loaded before complete(), which completes the list (every wave calls
+// it once).
 template <typename T, int NH, int NGROUPS, bool REUSE_LO, typename Complete>
 __device__ __forceinline__ void attend_growing(AttendAcc<T, NH>& acc, const float (&qr)[NH][T::EPC],
                                                const RowAddr& ra, const int32_t* s_idx, const float* s_a, int gid,
@@ -255,7 +258,8 @@ __device__ __forceinline__ void dense_runs(const Ragged& rg, int B, int S_max, i
   const int len = lane < B ? seq_rows(rg, lane, S_max) : 0;
   const int total = __builtin_amdgcn_readlane((int)wave_inclusive_scan_u32((uint32_t)len), 63);
   const int X = nsplit * B;
-  // equal lengths: nothing to deal out (440 units of 8 heads, S = 3440, eight blocks per CU: 161 us with the search below)
+  // equal lengths: nothing to deal out (440 units of 8 heads, S = 3440, eight blocks per CU: 161 us
+  // with the search below)
   const int first = __builtin_amdgcn_readlane(len, 0);
   if (first >= nsplit * kDenseMinRun && __ballot(lane < B && len != first) == 0ull) {
     runs = lane < B ? nsplit : 0;

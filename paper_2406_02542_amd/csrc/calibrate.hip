@@ -27,14 +27,16 @@ constexpr int kGramTiles = kGramSets * (kGramSets + 1) / 2;  // 16 x 16 tiles of
 constexpr int kGramPartWords = kGramTiles * 64 * 4;          // a partial: [tile][lane][4] as the accumulators lie
 __host__ __device__ constexpr int gram_tile(int c1, int c2) { return c1 * kGramSets - c1 * (c1 - 1) / 2 + c2 - c1; }
 
-// Four waves, each on 32-row steps of its own.  Lane (m, g) of a step loads columns 8 m .. 8 m + 7 of rows
-// 8 g .. 8 g + 7 (bf16: one 16-byte load a row, four whole rows an instruction) and pairs the rows up
-// (v_perm_b32; fp32: the conversion packs them): operand c then holds eight consecutive rows of column
-// 8 m + c, which is what v_mfma_f32_16x16x32_bf16 takes on either side, so a step needs no LDS, no barrier
-// and, G being symmetric, 36 of 64 tiles.  Column sums: bf16 by a column of ones on the other side, fp32 by adding the
-// fp32 values themselves.  What bounds it is the read of the keys: one wave per SIMD with 512 registers holds the 36 tiles and two
-// steps' loads (bf16 with three 2 us more, with four 18).  32 heads x 65536 keys, us: bf16 (512 MiB) 95 (5.6 TB/s), fp32 190; through a tile
-// transposed in LDS, with two barriers a tile and all 64 tiles, 131 (4.1 TB/s) and 267.
+// Four waves, each on 32-row steps of its own.  Lane (m, g) of a step loads columns 8 m .. 8 m + 7
+// of rows 8 g .. 8 g + 7 (bf16: one 16-byte load a row, four whole rows an instruction) and pairs
+// the rows up (v_perm_b32; fp32: the conversion packs them): operand c then holds eight consecutive
+// rows of column 8 m + c, which is what v_mfma_f32_16x16x32_bf16 takes on either side, so a step
+// needs no LDS, no barrier and, G being symmetric, 36 of 64 tiles.  Column sums: bf16 by a column
+// of ones on the other side, fp32 by adding the fp32 values themselves.  What bounds it is the read
+// of the keys: one wave per SIMD with 512 registers holds the 36 tiles and two steps' loads (bf16
+// with three 2 us more, with four 18).  32 heads x 65536 keys, us: bf16 (512 MiB) 95 (5.6 TB/s),
+// fp32 190; through a tile transposed in LDS, with two barriers a tile and all 64 tiles, 131 (4.1
+// TB/s) and 267.
 // NT = bf16 terms per element: 1 for bf16 storage, 2 for fp32 storage (value, remainder).
 template <int NT>
 __global__ __launch_bounds__(kGramThreads, 1) void gram_kernel(const void* __restrict__ keys,
@@ -180,11 +182,12 @@ __global__ __launch_bounds__(kGramThreads, 1) void gram_kernel(const void* __res
     sum_part[part * kD + threadIdx.x] = (s_sum[0][threadIdx.x] + s_sum[1][threadIdx.x]) + (s_sum[2][threadIdx.x] + s_sum[3][threadIdx.x]);
 }
 
-// C = (G - s s^T / N) / (N - 1), chunk partials added in order in fp64.  Block (set, head): rows set, set + 8, ..
-// of C, thread (c2, lane) the four entries that this lane holds of tile (set, c2), or of its mirror image where only
-// that exists; the rows are put together in LDS and leave whole.  Both places of an entry are computed from
-// the same numbers, so C is exactly symmetric (a skew part, however small, never leaves a Jacobi iteration, which
-// then took all of its 30 sweeps: 9.9 ms for 4 heads).
+// C = (G - s s^T / N) / (N - 1), chunk partials added in order in fp64.  Block (set, head): rows
+// set, set + 8, .. of C, thread (c2, lane) the four entries that this lane holds of tile (set, c2),
+// or of its mirror image where only that exists; the rows are put together in LDS and leave whole.
+// Both places of an entry are computed from the same numbers, so C is exactly symmetric (a skew
+// part, however small, never leaves a Jacobi iteration, which then took all of its 30 sweeps: 9.9
+// ms for 4 heads).
 constexpr int kCovThreads = kGramSets * 64;
 constexpr int kCovPitch = kD + 4;  // doubles per row in LDS
 __global__ __launch_bounds__(kCovThreads) void cov_reduce_kernel(const float* __restrict__ gram_part,
@@ -311,8 +314,8 @@ __global__ __launch_bounds__(256) void jaccard_kernel(const int32_t* __restrict_
 }
 
 // ---- launchers ----------------------------------------------------------------------------------
-// What the workspace is laid out for: a partial Gram matrix of 64 KiB for every 1024 rows, at most two for every
-// CU over all heads (the eigensolver uses the space again).
+// What the workspace is laid out for: a partial Gram matrix of 64 KiB for every 1024 rows, at most
+// two for every CU over all heads (the eigensolver uses the space again).
 static int pca_chunks(int Hkv, long long N) {
   const long long want = (2 * device_cus() + Hkv - 1) / Hkv;
   long long rows = (N + want - 1) / want;
@@ -321,9 +324,10 @@ static int pca_chunks(int Hkv, long long N) {
   return (int)((N + rows - 1) / rows);
 }
 
-// Chunks of a head in the Gram pass, never more than pca_chunks: a CU holds one block, so as many as
-// make whole rounds of blocks, one round if that leaves no CU idle (32 heads: 8 chunks), else the number of rounds at
-// which rounds x (rows of a chunk + the 256 that a block's start and end cost) is least.
+// Chunks of a head in the Gram pass, never more than pca_chunks: a CU holds one block, so as many
+// as make whole rounds of blocks, one round if that leaves no CU idle (32 heads: 8 chunks), else
+// the number of rounds at which rounds x (rows of a chunk + the 256 that a block's start and end
+// cost) is least.
 static int gram_chunks(int Hkv, long long N, int* rows_per_chunk) {
   constexpr long long kWhole = kGramWaves * kGramStep;
   const int most = pca_chunks(Hkv, N);

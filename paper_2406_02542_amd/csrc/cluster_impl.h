@@ -107,10 +107,10 @@ __device__ __forceinline__ void cluster_store_x4(__amdgpu_buffer_rsrc_t rs, uint
 // above the bin (cs.above) and inside it (cs.inbin).  rem >= 1 and the histograms together
 // hold at least rem keys.  Returns false when the wait gave up.
 // xh / xh_off: the exchange area and the byte offset of this unit's arrays for this round,
-// [C][THREADS] slots of kClusterSlotBytes: thread t's slot holds the suffix sums of its own
-// bins (ascending) and of the bin above them, so that a reader needs no other thread's slot; a slice has at most
-// 16384 rows, so they are 16-bit numbers.  (As 32-bit numbers in 32 bytes an exchange took 5.5 us between 2 blocks, 3.4 now, and 8.7
-// between 8, 5.0 now.)
+// [C][THREADS] slots of kClusterSlotBytes: thread t's slot holds the suffix sums of its own bins
+// (ascending) and of the bin above them, so that a reader needs no other thread's slot; a slice has
+// at most 16384 rows, so they are 16-bit numbers.  (As 32-bit numbers in 32 bytes an exchange took
+// 5.5 us between 2 blocks, 3.4 now, and 8.7 between 8, 5.0 now.)
 constexpr int kClusterSlotBytes = 16;
 template <int THREADS>
 __device__ __forceinline__ bool cluster_hist_round(const uint32_t* hist, __amdgpu_buffer_rsrc_t xh,

@@ -123,15 +123,17 @@ __device__ __forceinline__ double fast_rsqrt_f64(double x) {  // likewise
 // exchange) and a row's value read from LDS serves two columns.  Reflector j is u = x - beta e(j+1)
 // with x the row's part beyond j (zeros up to j) and H = I - u u^T / h: u differs from x in one
 // place, so the product with A starts on x while the norm is still being taken.  A step is one
-// barrier, behind which the four partial sums of p = A u and row j + 1 as it was are in LDS: every wave then has
-// all of p and brings that row up to date for itself, so the next step begins without an exchange.  What bounds it is the
-// chain of a step (two sums over a wave, a square root, a reciprocal), about 2000 cycles.  Measured, 32 heads:
-// 125 us; with a second barrier, for the next row from the wave that owns it, 131; with eight waves and that barrier 146; as
-// two 64-row halves with four barriers a step, the library's square root and divisions and a branch around every
+// barrier, behind which the four partial sums of p = A u and row j + 1 as it was are in LDS: every
+// wave then has all of p and brings that row up to date for itself, so the next step begins without
+// an exchange.  What bounds it is the chain of a step (two sums over a wave, a square root, a
+// reciprocal), about 2000 cycles.  Measured, 32 heads: 125 us; with a second barrier, for the next
+// row from the wave that owns it, 131; with eight waves and that barrier 146; as two 64-row halves
+// with four barriers a step, the library's square root and divisions and a branch around every
 // group of rows 197.
-// PER_CU = 2, for more heads than CUs: two blocks share a CU, a wave having at most 256 registers.  The next row is
-// then taken before the rows of the matrix are updated, so that it need not be kept beside them (240 registers for 292,
-// 2 us more for a block alone).  257 heads: 177 us as before that kernel had one barrier, with one block per CU 254.
+// PER_CU = 2, for more heads than CUs: two blocks share a CU, a wave having at most 256 registers.
+// The next row is then taken before the rows of the matrix are updated, so that it need not be kept
+// beside them (240 registers for 292, 2 us more for a block alone).  257 heads: 177 us as before
+// that kernel had one barrier, with one block per CU 254.
 template <int PER_CU>
 __global__ __launch_bounds__(kEigThreads, PER_CU) void tridiag_kernel(EigBufs bufs) {
   constexpr int kWaves = kEigThreads / 64, kRows = kD / kWaves, kPitch = kRows + 2;

@@ -22,16 +22,19 @@ __host__ __device__ inline int fused_keys_per_thread(int S) {
   return (c + 3) & ~3;
 }
 
-// Beyond 16 keys a thread (S > 8192) the selection runs on keys in LDS, whose leading 11 bits the scoring has counted
-// (contiguous_select), else on scores read back into registers (block_select_topk_resident).  us per step, registers / LDS:
-// groups of 4, every head for itself, 512 heads, S = 12345, k = 1543 88.4 / 85.9; 256 heads, S = 12000 54.6 / 51.3; 512 heads, S
-// = 9000, d = 64, pages of unequal sequences 58.8 / 54.6; 64 heads, S = 14000 42.9 / 42.8; but 256 heads, S = 7900 72.4 /
-// 72.1, 512 groups' heads, S = 8000 58.3 / 58.4, and 8 fp32 heads, S = 1024 12.0 / 12.9, where one wave's search among
-// the candidates is a longer chain than the whole block's.
+// Beyond 16 keys a thread (S > 8192) the selection runs on keys in LDS, whose leading 11 bits the
+// scoring has counted (contiguous_select), else on scores read back into registers
+// (block_select_topk_resident).  us per step, registers / LDS: groups of 4, every head for itself,
+// 512 heads, S = 12345, k = 1543 88.4 / 85.9; 256 heads, S = 12000 54.6 / 51.3; 512 heads, S =
+// 9000, d = 64, pages of unequal sequences 58.8 / 54.6; 64 heads, S = 14000 42.9 / 42.8; but 256
+// heads, S = 7900 72.4 / 72.1, 512 groups' heads, S = 8000 58.3 / 58.4, and 8 fp32 heads, S = 1024
+// 12.0 / 12.9, where one wave's search among the candidates is a longer chain than the whole
+// block's.
 constexpr int kFusedRegisterKeys = 16;
 __host__ __device__ inline bool fused_keys_in_lds(int S) { return fused_keys_per_thread(S) > kFusedRegisterKeys; }
 
-// bytes of the region that holds the rotation's partial sums (query, new key) and then the scores or their keys (padded)
+// bytes of the region that holds the rotation's partial sums (query, new key) and then the scores
+// or their keys (padded)
 __host__ __device__ inline size_t fused_region_bytes(int S) {
   const size_t words = fused_keys_in_lds(S) ? padded_words((size_t)S) : (size_t)S;
   const size_t scores = (words * 4 + 15) & ~(size_t)15, rot = 2 * kRotParts * kD * sizeof(float);
@@ -66,12 +69,13 @@ __device__ __forceinline__ int fused_unit_of_block(const Ragged& rag, int B, int
 // block reads this unit's rows.
 constexpr int kFusedMaxPages = kFusedMaxS / 256;  // pages are at least 256 rows
 
-// PAGED: the three slabs are pools addressed through the sequence's page list (see Paging).
-// Two blocks share a CU (4 waves per SIMD) as far as LDS allows: the register budget is 128 VGPRs and the compiler
-// is told not to trade load-level parallelism for a higher occupancy that cannot happen.  LDS allows
-// it (fused_two_per_cu) while the dynamic part, 4 (33/32 S + k) bytes (4 S + 8 k up to 8192 rows, 33/8 S + 8 k
-// on a paged cache), leaves room for the static arrays in half of 160 KB: S = 13800, k = 1725 fits,
-// S = 16384 does not, and a block has its CU to itself at the same budget.
+// PAGED: the three slabs are pools addressed through the sequence's page list (see Paging). Two
+// blocks share a CU (4 waves per SIMD) as far as LDS allows: the register budget is 128 VGPRs and
+// the compiler is told not to trade load-level parallelism for a higher occupancy that cannot
+// happen.  LDS allows it (fused_two_per_cu) while the dynamic part, 4 (33/32 S + k) bytes (4 S + 8
+// k up to 8192 rows, 33/8 S + 8 k on a paged cache), leaves room for the static arrays in half of
+// 160 KB: S = 13800, k = 1725 fits, S = 16384 does not, and a block has its CU to itself at the
+// same budget.
 // KPT = keys a thread holds in the select stage (8 for S <= 4096, 16 for S <= 8192, else 32).
 // GROUPED: G query heads to a KV head, every one selecting for itself.
 template <typename T, int LPR, bool REUSE_LO, int KPT, bool APPEND, bool PAGED, bool GROUPED>
@@ -306,7 +310,8 @@ size_t fused_dynamic_lds(const Shape& s) {
   return fused_region_bytes(s.S) + (size_t)s.k * (score_by_row ? 4 : 8);
 }
 
-// The static arrays of a block of grouped heads: the query before and after its rotation, the selection, the page list.
+// The static arrays of a block of grouped heads: the query before and after its rotation, the
+// selection, the page list.
 static size_t fused_static_lds(const Shape& s) {
   const size_t select = (sizeof(ResidentSelectSmem<kFusedThreads>) + 15) / 16 * 16;
   return select + 2 * kD * sizeof(float) + (s.pg.table != nullptr ? kFusedMaxPages * sizeof(int32_t) : 0);
@@ -330,34 +335,42 @@ bool fused_pinnable(const Shape& s) {
 // One block per query head, or the heads' rows spread over the chip by the split path's two launches?
 // A block's time grows with what its head has to read, the split path's hardly as long as the chip is
 // not full.  Measured at 8 to 1024 heads, S = 512 to 16384, both types, us (one launch / split):
-//   one query head per KV head: 0.36 MB a head (S = 2048, k = 512) 8 heads 13.8 / 15.0; 0.72 MB 32 heads
-//   21.5 / 19.2, 64 21.8 / 22.1; 1.4 MB 64 heads 45.5 / 36.0, 96 48.7 / 47.5, 128 50.8 / 56.8.  Below half the CUs the
-//   MB at which the two meet grow with the heads and, up to 8192 rows, with S (a long row's selection costs the
-//   split path more than its bytes): 56 heads, S = 8192, k = 512, d = 16 on pages 20.9 / 31.0, 56 fp32, S = 2500, k = 625
-//   22.5 / 17.4, 48 fp32, S = 4096, k = 1024, d = 64 42.7 / 28.1; 112 heads, S = 8192, k = 1024, d = 32 29.2 / 37.2, 96 fp32, S =
-//   8192, k = 512, d = 32 34.5 / 41.5, k = 2048 61.6 / 47.5
-//   groups: 0.49 MB 32 heads 16.6 / 16.8; 0.74 MB 64 heads 22.2 / 22.7; 0.98 MB 64 heads 26.9 / 24.0, 128
-//   29.5 / 29.5; 1.5 MB 128 heads 49.2 / 48.1, 256 59.1 / 70.6, 512 88.8 / 115.6
-// With groups every head's block rotates its query from P_h again: 1024 heads of 0.12 MB 29.4 / 25.0, of 0.25 MB
-// 38.8 / 39.3.  Past the length at which two blocks share a CU's LDS (fused_two_per_cu) a second round of blocks costs
-// groups of 8 more than the split path and leaves groups of 4 level: 1024 heads in groups of 8, S = 13800, k = 1725 156 / 179,
-// S = 14300, k = 893 124 / 141, k = 1787, one block per CU, 198 / 184, on pages S = 14000, k = 700 118 / 132, S = 13000, k = 1300
-// 177 / 162; 512 heads in groups of 4, S = 13800, k = 1725 91.9 / 114, S = 14800, k = 462 53.9 / 67.4, k = 925 88.7 / 88.3; but
-// S = 16384, k = 2048, 256 heads 71.6 / 76.4, 512 139 / 132.  A group's appended row
-// needs a launch of its own in front (about 4 us): groups of 4, 0.49 MB, 512 heads 38.6 / 42.2, 0.98 MB 256 heads
-// 43.8 / 44.2; groups of 8, 0.49 MB 512 heads 35.5 / 32.2, 0.98 MB 256 heads 38.6 / 37.3, 512 56.7 / 60.3.
-// The G heads of a unit each stream the slab, which the scoring of the split path reads once, and pay for it in L2
-// once the chip is full several times over, the more the wider the rows.  Every figure one launch / split as it is now /
-// as the step was in four launches, a rotation of its own, selection and attention apart:
-//   rows of over 256 bytes (fp32, d > 64; the kernel spills too), more heads than CUs: groups of 4, S = 4096, k = 512, d =
-//     128, 512 heads 206 / 87 / 95, 2048 heads 763 / 315 / 325; groups of 2, d = 96, S = 1740, 2560 heads 512 / 298 / 325
-//   groups of 8, rows of over 64 bytes, more than two heads per CU: S = 8192, d = 64, 4096 heads k = 512 391 / 317 / 328, k =
-//     1024 469 / 380 / 407, k = 2048 605 / 488 / 528; 1024 heads k = 512 100 / 85 / 87, 512 heads k = 1024 66.6 / 71 / 71;
-//     64-byte rows stay: k = 512 300 / 296 / 306, k = 2048 521 / 487 / 539, d = 16, k = 512 252 / 295 / 295
-//   groups of 4, rows of over 192 bytes, more than two heads per CU: S = 4096, k = 512, d = 128, 1024 heads 106 / 99 / 101, 2048
-//     heads 202 / 178 / 190; rows of over 64 bytes, more than six: S = 4096, k = 256, d = 64, 2048 heads 117 / 103 / 105
-// Many heads of little work pay more for their own rotations: from six per CU on 0.3 MB a head and not 0.2 (2048
-// heads, groups of 4, S = 1000, d = 64, 0.22 MB 64.6 / 56.1 / 62.3; 4032, groups of 8, S = 2383, 0.22 MB 146 / 129 / 131).
+//   one query head per KV head: 0.36 MB a head (S = 2048, k = 512) 8 heads 13.8 / 15.0; 0.72 MB 32
+//     heads 21.5 / 19.2, 64 21.8 / 22.1; 1.4 MB 64 heads 45.5 / 36.0, 96 48.7 / 47.5, 128 50.8 /
+//     56.8. Below half the CUs the MB at which the two meet grow with the heads and, up to 8192
+//     rows, with S (a long row's selection costs the split path more than its bytes): 56 heads, S =
+//     8192, k = 512, d = 16 on pages 20.9 / 31.0, 56 fp32, S = 2500, k = 625 22.5 / 17.4, 48 fp32,
+//     S = 4096, k = 1024, d = 64 42.7 / 28.1; 112 heads, S = 8192, k = 1024, d = 32 29.2 / 37.2, 96
+//     fp32, S = 8192, k = 512, d = 32 34.5 / 41.5, k = 2048 61.6 / 47.5
+//   groups: 0.49 MB 32 heads 16.6 / 16.8; 0.74 MB 64 heads 22.2 / 22.7; 0.98 MB 64 heads 26.9 /
+//     24.0, 128 29.5 / 29.5; 1.5 MB 128 heads 49.2 / 48.1, 256 59.1 / 70.6, 512 88.8 / 115.6
+// With groups every head's block rotates its query from P_h again: 1024 heads of 0.12 MB 29.4 /
+// 25.0, of 0.25 MB 38.8 / 39.3.  Past the length at which two blocks share a CU's LDS
+// (fused_two_per_cu) a second round of blocks costs groups of 8 more than the split path and leaves
+// groups of 4 level: 1024 heads in groups of 8, S = 13800, k = 1725 156 / 179, S = 14300, k = 893
+// 124 / 141, k = 1787, one block per CU, 198 / 184, on pages S = 14000, k = 700 118 / 132, S =
+// 13000, k = 1300 177 / 162; 512 heads in groups of 4, S = 13800, k = 1725 91.9 / 114, S = 14800, k
+// = 462 53.9 / 67.4, k = 925 88.7 / 88.3; but S = 16384, k = 2048, 256 heads 71.6 / 76.4, 512 139 /
+// 132.  A group's appended row needs a launch of its own in front (about 4 us): groups of 4, 0.49
+// MB, 512 heads 38.6 / 42.2, 0.98 MB 256 heads 43.8 / 44.2; groups of 8, 0.49 MB 512 heads 35.5 /
+// 32.2, 0.98 MB 256 heads 38.6 / 37.3, 512 56.7 / 60.3.
+// The G heads of a unit each stream the slab, which the scoring of the split path reads once, and
+// pay for it in L2 once the chip is full several times over, the more the wider the rows.  Every
+// figure one launch / split as it is now / as the step was in four launches, a rotation of its own,
+// selection and attention apart:
+//   rows of over 256 bytes (fp32, d > 64; the kernel spills too), more heads than CUs: groups of 4,
+//     S = 4096, k = 512, d = 128, 512 heads 206 / 87 / 95, 2048 heads 763 / 315 / 325; groups of 2,
+//     d = 96, S = 1740, 2560 heads 512 / 298 / 325
+//   groups of 8, rows of over 64 bytes, more than two heads per CU: S = 8192, d = 64, 4096 heads k
+//     = 512 391 / 317 / 328, k = 1024 469 / 380 / 407, k = 2048 605 / 488 / 528; 1024 heads k = 512
+//     100 / 85 / 87, 512 heads k = 1024 66.6 / 71 / 71; 64-byte rows stay: k = 512 300 / 296 / 306,
+//     k = 2048 521 / 487 / 539, d = 16, k = 512 252 / 295 / 295
+//   groups of 4, rows of over 192 bytes, more than two heads per CU: S = 4096, k = 512, d = 128,
+//     1024 heads 106 / 99 / 101, 2048 heads 202 / 178 / 190; rows of over 64 bytes, more than six:
+//     S = 4096, k = 256, d = 64, 2048 heads 117 / 103 / 105
+// Many heads of little work pay more for their own rotations: from six per CU on 0.3 MB a head and
+// not 0.2 (2048 heads, groups of 4, S = 1000, d = 64, 0.22 MB 64.6 / 56.1 / 62.3; 4032, groups of
+// 8, S = 2383, 0.22 MB 146 / 129 / 131).
 bool fused_preferred(const Shape& s) {
   if (!fused_eligible(s)) return false;
   const long long heads = (long long)s.B * s.Hq, cus = device_cus();

@@ -29,26 +29,33 @@ bool fused_gqa_eligible(const Shape& s, int select_mode) {
   return s.S <= 16384 && s.k <= kGqaMaxK;
 }
 
-// One block per unit: worth it from a quarter of the CUs on (three eighths beyond 8192 rows); below that the
-// split path's many blocks per unit win.  From half the CUs on with 2 query heads per KV head, three eighths with 4
-// and five sixteenths with 8 it is so whatever a row costs.  Below that line a block's time grows with the bytes
-// of slab and list a row costs its unit, 2 (d + (256 - d) k / S), the split path's selection with the rows alone: it is
-// so under 150 bytes at the line (160 with 8 heads, 250 with 2 beyond 4096 rows, where the split path's selection has 16
-// keys a thread), less in proportion with fewer units, 20 more on a paged cache (the split path's kernels look
-// pages up more often), 10 less for lengths that may differ (the longest sequence's block ends the step), and never from
-// 140 bytes on.  (266 such shapes, mean time above the better of the two: 0.7 %, without the 20 and the 10 1.0 %, with 140
-// bytes for any number of units 2.9 %.)  Below 2048 rows,
-// where every kernel is short, all but the 64-byte slab rows that the split path rotates and scores fastest.
-// Measured at 64 to 176 units, S = 1024 to 12000, contiguous, paged, appended, ragged, us (one launch / split):
-//   2 heads: 96 units S = 5125, k = 320, d = 32 23.4 / 28.4, 120 units S = 8192, k = 512 27.9 / 33.2, 104 units S = 12000,
-//     k = 750, d = 16 31.7 / 50.5, 80 units S = 4096, k = 512, d = 16 22.4 / 25.3; 64 units S = 4096, k = 512, d = 32, ragged
-//     23.0 / 19.1, S = 3000, k = 375 21.0 / 17.9, 80 units S = 8192, k = 1024, ragged 32.8 / 27.9; 64 units S = 4096, k = 512, d = 64
-//     33.1 / 25.8; 64 units, appended, S = 4096, k = 512, d = 32 20.6 / 19.5, S = 6000, k = 750 23.0 / 26.0, S = 8192, k = 1024 28.0 /
-//     29.0; 120 units k = 1024 39.4 / 35.3, 64 units S = 1024, k = 256, d = 32 18.2 / 15.8, 128 units S = 8192 42.5 / 42.8
-//   4 heads: 64 units S = 8192, k = 1024, d = 16 32.2 / 37.9, 80 units S = 4096, k = 256 20.0 / 25.3; 64 units S = 4096,
-//     k = 512, d = 32 24.7 / 21.8; 72 units S = 4096, k = 1024, d = 64 41.1 / 32.8; 96 units S = 4096 26.1 / 25.9
-//   8 heads: 80 units S = 8192, k = 512, d = 32 29.5 / 35.1, 64 units S = 4096, k = 256, d = 16 21.2 / 28.1, k = 512, d = 64
-//     36.1 / 28.6; 64 units, appended, k = S / 8, d = 32, S = 4096 23.3 / 25.4, S = 8192 30.0 / 31.8
+// One block per unit: worth it from a quarter of the CUs on (three eighths beyond 8192 rows); below
+// that the split path's many blocks per unit win.  From half the CUs on with 2 query heads per KV
+// head, three eighths with 4 and five sixteenths with 8 it is so whatever a row costs.  Below that
+// line a block's time grows with the bytes of slab and list a row costs its unit, 2 (d + (256 - d)
+// k / S), the split path's selection with the rows alone: it is so under 150 bytes at the line (160
+// with 8 heads, 250 with 2 beyond 4096 rows, where the split path's selection has 16 keys a
+// thread), less in proportion with fewer units, 20 more on a paged cache (the split path's kernels
+// look pages up more often), 10 less for lengths that may differ (the longest sequence's block ends
+// the step), and never from 140 bytes on.  (266 such shapes, mean time above the better of the two:
+// 0.7 %, without the 20 and the 10 1.0 %, with 140 bytes for any number of units 2.9 %.)  Below
+// 2048 rows, where every kernel is short, all but the 64-byte slab rows that the split path rotates
+// and scores fastest.
+// Measured at 64 to 176 units, S = 1024 to 12000, contiguous, paged, appended, ragged, us (one
+// launch / split):
+//   2 heads: 96 units S = 5125, k = 320, d = 32 23.4 / 28.4, 120 units S = 8192, k = 512 27.9 /
+//     33.2, 104 units S = 12000, k = 750, d = 16 31.7 / 50.5, 80 units S = 4096, k = 512, d = 16
+//     22.4 / 25.3; 64 units S = 4096, k = 512, d = 32, ragged 23.0 / 19.1, S = 3000, k = 375 21.0 /
+//     17.9, 80 units S = 8192, k = 1024, ragged 32.8 / 27.9; 64 units S = 4096, k = 512, d = 64
+//     33.1 / 25.8; 64 units, appended, S = 4096, k = 512, d = 32 20.6 / 19.5, S = 6000, k = 750
+//     23.0 / 26.0, S = 8192, k = 1024 28.0 / 29.0; 120 units k = 1024 39.4 / 35.3, 64 units S =
+//     1024, k = 256, d = 32 18.2 / 15.8, 128 units S = 8192 42.5 / 42.8
+//   4 heads: 64 units S = 8192, k = 1024, d = 16 32.2 / 37.9, 80 units S = 4096, k = 256 20.0 /
+//     25.3; 64 units S = 4096, k = 512, d = 32 24.7 / 21.8; 72 units S = 4096, k = 1024, d = 64
+//     41.1 / 32.8; 96 units S = 4096 26.1 / 25.9
+//   8 heads: 80 units S = 8192, k = 512, d = 32 29.5 / 35.1, 64 units S = 4096, k = 256, d = 16
+//     21.2 / 28.1, k = 512, d = 64 36.1 / 28.6; 64 units, appended, k = S / 8, d = 32, S = 4096
+//     23.3 / 25.4, S = 8192 30.0 / 31.8
 bool fused_gqa_preferred(const Shape& s, int select_mode) {
   if (!fused_gqa_eligible(s, select_mode)) return false;
   const long long units = (long long)s.B * s.Hkv, cus = device_cus();

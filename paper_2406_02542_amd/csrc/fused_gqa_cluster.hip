@@ -56,15 +56,20 @@ bool fused_gqa_cluster_eligible(const Shape& s, int select_mode) {
 
 bool fused_gqa_cluster_preferred(const Shape& s, int select_mode) {
   if (!fused_gqa_cluster_eligible(s, select_mode)) return false;
-  // An exchange between a unit's blocks and the wait for the slowest of them cost 5 to 8 us, which many rows, wide slab
-  // rows or a long list pay for.  Measured at 8 to 128 units of 2, 4 and 8 heads, S = 2500 to 14000, appended, us
-  // (cluster / the better of one block per unit and the split path):
-  //   up to 64 units (four or eight blocks): S = 9500, d = 16, k = 1187 21.8 / 24.6 to 28.3 / 31.3 (2 heads), 26.8 / 31.2 to 32.6 / 34.3
-  //     (8 heads; beyond 8192 rows a thread of the split path's selection holds 32 keys), S = 11000, d = 32, k = 687 24.7 / 25.3 to 30.3 / 30.4; but S = 8192, k = 1024 22.7 / 20.8 to 28.5 / 28.0, k = 2048 25.4 / 22.9 (8
-  //     units) to 33.8 / 33.8 (64); 64-column rows there 25.0 / 23.4 (8 units), 27.8 / 29.4 (32), 32.7 / 36.0 (64), S = 6000 29.9 / 34.8
-  //   65 to 128 units (two blocks): 64-column rows, S = 6000, k = 750 37.9 / 41.4, S = 8192 43.8 / 47.6; else, where one block per
-  //     unit applies, S = 8192, k = 2048 46.6 / 44.9, S = 11000 40.1 / 39.1, 45.5 / 43.0, S = 14000 48.4 / 48.2, 53.5 / 53.1 (k = S / 8), 43.1 / 38.9 (k
-  //     = S / 16), S = 16384, k = 2048 51.1 / 55.5, 59.1 / 63.2, k = 1024 48.9 / 44.4
+  // An exchange between a unit's blocks and the wait for the slowest of them cost 5 to 8 us, which
+  // many rows, wide slab rows or a long list pay for.  Measured at 8 to 128 units of 2, 4 and 8
+  // heads, S = 2500 to 14000, appended, us (cluster / the better of one block per unit and the
+  // split path):
+  //   up to 64 units (four or eight blocks): S = 9500, d = 16, k = 1187 21.8 / 24.6 to 28.3 / 31.3
+  //     (2 heads), 26.8 / 31.2 to 32.6 / 34.3 (8 heads; beyond 8192 rows a thread of the split
+  //     path's selection holds 32 keys), S = 11000, d = 32, k = 687 24.7 / 25.3 to 30.3 / 30.4; but
+  //     S = 8192, k = 1024 22.7 / 20.8 to 28.5 / 28.0, k = 2048 25.4 / 22.9 (8 units) to 33.8 /
+  //     33.8 (64); 64-column rows there 25.0 / 23.4 (8 units), 27.8 / 29.4 (32), 32.7 / 36.0 (64),
+  //     S = 6000 29.9 / 34.8
+  //   65 to 128 units (two blocks): 64-column rows, S = 6000, k = 750 37.9 / 41.4, S = 8192 43.8 /
+  //     47.6; else, where one block per unit applies, S = 8192, k = 2048 46.6 / 44.9, S = 11000
+  //     40.1 / 39.1, 45.5 / 43.0, S = 14000 48.4 / 48.2, 53.5 / 53.1 (k = S / 8), 43.1 / 38.9 (k =
+  //     S / 16), S = 16384, k = 2048 51.1 / 55.5, 59.1 / 63.2, k = 1024 48.9 / 44.4
   const long long units = (long long)s.B * s.Hkv, cus = device_cus();
   const long long unit_bytes = (long long)s.S * s.d * 2 + (long long)s.k * kD * 4;
   if (4 * units <= cus) {

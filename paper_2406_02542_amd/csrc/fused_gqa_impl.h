@@ -65,10 +65,11 @@ struct GqaList {
   int n;      // entries of the list
 };
 
-// The attention steps of a block whose list is still growing: entries [0, n_def) are there, the first wave adds
-// the chosen candidates.  The other waves take the whole steps of those n_def (T1 of them) in turn; the steps
-// behind them, of which everybody knows once the list is complete, go where steps are missing: the first wave, whose ranking
-// counts as one, gets level with the others, then those of them with one step less, then all in turn.
+// The attention steps of a block whose list is still growing: entries [0, n_def) are there, the
+// first wave adds the chosen candidates.  The other waves take the whole steps of those n_def (T1
+// of them) in turn; the steps behind them, of which everybody knows once the list is complete, go
+// where steps are missing: the first wave, whose ranking counts as one, gets level with the others,
+// then those of them with one step less, then all in turn.
 template <int WAVES>
 struct GqaSteps {
   const GqaList* list;
@@ -79,8 +80,9 @@ struct GqaSteps {
         q(T1 / (WAVES - 1)), r(T1 % (WAVES - 1)), i(0), ahead(ahead_) {}
   __device__ __forceinline__ bool early() const { return ahead && wave > 0 && wave - 1 < T1; }
   __device__ __forceinline__ bool next(int& base, int& end) {
-    // Not ahead: the list's state is final by now.  Where the unit's other blocks did not show up the entries are
-    // still positions, which a paged cache's loads must not take for rows of the pool.
+    // Not ahead: the list's state is final by now.  Where the unit's other blocks did not show up
+    // the entries are still positions, which a paged cache's loads must not take for rows of the
+    // pool.
     if (!ahead && i == 0 && __builtin_amdgcn_readfirstlane(list->state) != 1) return false;
     const int n1 = wave == 0 ? 0 : q + (wave - 1 < r ? 1 : 0);
     int i2 = i - n1;
@@ -321,15 +323,18 @@ __global__ __launch_bounds__(THREADS, THREADS == 256 ? 2 : 1) void fused_gqa_ker
   constexpr int kCandCap = Lds::kCandCap;  // candidates of this block ranked from a compact list (else: all keys)
   uint32_t* s_ckey = reinterpret_cast<uint32_t*>(dyn_smem + Lds::cand_offset(L_max));  // behind the keys
   int32_t* s_cpos = reinterpret_cast<int32_t*>(s_ckey + kCandCap);
-  // Rows above the threshold's leading digits are certain and go straight into the list (ascending), the rows that
-  // share them are the candidates, of which the chosen are appended (ascending).  The attention begins
-  // in between, so that the memory system does not wait for the ranking.  One block per unit: every wave loads the rows of its
-  // first step and then ranks the candidates by itself, without a barrier, all writing the same list.  CLUSTER: the first
-  // wave ranks them with the other blocks of the unit while the other waves attend over the certain rows.
-  // Ranked by all threads of the block first, with the attention behind it, us per step: 16 sequences of 32/8 heads, S = 16384, k = 2048 (two
-  // blocks per unit) 66.8 -> 61.5; 4 of S = 131072, k = 8192 (eight, and the 6000 candidates of a unit took a second
-  // histogram exchange) 79.3 -> 69.3; one block per unit, 64 of 64/8 heads, S = 8192: 101.7 -> 102.1, which memory bounds (6 TB/s
-  // with the lines that the gather reads in part).
+  // Rows above the threshold's leading digits are certain and go straight into the list
+  // (ascending), the rows that share them are the candidates, of which the chosen are appended
+  // (ascending).  The attention begins in between, so that the memory system does not wait for the
+  // ranking.  One block per unit: every wave loads the rows of its first step and then ranks the
+  // candidates by itself, without a barrier, all writing the same list.  CLUSTER: the first wave
+  // ranks them with the other blocks of the unit while the other waves attend over the certain
+  // rows.
+  // Ranked by all threads of the block first, with the attention behind it, us per step: 16
+  // sequences of 32/8 heads, S = 16384, k = 2048 (two blocks per unit) 67.5 -> 61.4; 4 of S =
+  // 131072, k = 8192 (eight) 80.2 -> 70.6, with 16-byte slots and a list of at most 4096 candidates
+  // (cluster_rank_cap); one block per unit, 64 of 64/8 heads, S = 8192 as before, 102, which memory
+  // bounds (6 TB/s with the lines that the gather reads in part).
   int n_def = 0, gidx_base = 0;  // certain rows in s_idx; selected rows of the unit below this block's
   int n_rank = 0;                // candidates still to be ranked (0: the list is complete)
   uint32_t rem1 = 0;             // of which this many are chosen
@@ -403,8 +408,9 @@ __global__ __launch_bounds__(THREADS, THREADS == 256 ? 2 : 1) void fused_gqa_ker
       s_list.state = shift > 0 ? 0 : 1;
       s_list.n = (int)(own_above + take_eq);
     }
-    // The remaining bits of this block's candidates also go to the unit's candidate array (block after block, so it
-    // is in position order); with all of them there every block finds the same threshold.
+    // The remaining bits of this block's candidates also go to the unit's candidate array (block
+    // after block, so it is in position order); with all of them there every block finds the same
+    // threshold.
     uint32_t* xc_words = cl.xcand + (size_t)unit * kClusterCandCap;
     contiguous_partition<THREADS, KPT>(
         s_key, n, per_thread, shift, prefix, s_sel.wave[0], [&](int rank, int pos) { s_idx[rank] = to_row(row0 + pos); },

@@ -10,12 +10,12 @@
 //                      appended row.  Against a rotation launch in front of it, us per step: one
 //                      sequence of 32 heads, S = 4096, 20.4 -> 19.4; of 32/8 heads, S = 8192,
 //                      25.0 -> 22.3; 16 of 32/8 heads, S = 12345, per-head selection 118.3 -> 115.0
-//   qrot_kernel first  everything else: with many blocks their own rotations cost more than the launch
-//                      (rotate_score_applies), with several tokens per sequence a block reads rows that
-//                      another one appends, and the histograms of a long sequence's selection
-//                      have to be clear before the scoring begins.  A score block then needs no LDS and no barrier: its
-//                      slice of qhat goes straight to registers while the first slab loads are
-//                      already in flight.
+//   qrot_kernel first  everything else: with many blocks their own rotations cost more than the
+//                      launch (rotate_score_applies), with several tokens per sequence a block
+//                      reads rows that another one appends, and the histograms of a long sequence's
+//                      selection have to be clear before the scoring begins.  A score block then
+//                      needs no LDS and no barrier: its slice of qhat goes straight to registers
+//                      while the first slab loads are already in flight.
 #include "score_impl.h"
 #include "score_mfma_impl.h"
 
@@ -389,8 +389,8 @@ __global__ __launch_bounds__(256) void score_mfma_kernel(
     __syncthreads();
   }
 
-  // (ahead of the slab addresses: behind them the kernel holds 100 registers in place of 96 at NCH = 16, four waves
-  // per SIMD in place of five: 64 sequences of 8 KV heads, S = 8192, 207 / 198 us)
+  // (ahead of the slab addresses: behind them the kernel holds 100 registers in place of 96 at NCH
+  // = 16, four waves per SIMD in place of five: 64 sequences of 8 KV heads, S = 8192, 207 / 198 us)
   bf16x8_t bq[ScoreMfmaGeom<NCH>::NB][3];
   if constexpr (!ROT) score_mfma_operands<NCH>(qhat + head * kD, head_ok, bq);
 
@@ -651,19 +651,22 @@ hipError_t launch_score(const Shape& s, int select_mode, const void* klo, float*
   return launch_score_any(s, select_mode, klo, scores, qhat, hist_part, hist_chunks, nullptr, st);
 }
 
-// Rotation inside the scoring, or a launch in front of it?  It saves that launch, about 3 us, and costs every
-// score block a rotation of its own, of all G heads of the group, and the score kernel the registers
-// that hold a pass's P_h across the first slab loads (matrix cores, waves per SIMD without / with: d = 32 7 / 4,
-// d = 64 6 / 3, d = 128 4 / 2).  So it is taken while all blocks are soon resident: at most 18 per CU, where a
-// unit's four rotating blocks count as eight (each reads a quarter of P_h and stores qhat), and everything
-// counts twice at 64 columns (two passes) and eight times beyond; on the vector units twice again
-// with several heads per KV head, but no more than twice for bf16 rows of over 64 columns, which hold no slab loads in
-// flight.  fp32 rows of over 64 columns spill in this form: never.
-// One launch / two, us per step, both with the same stages behind them (1287 shapes, 8 to 4096 heads, S = 500 to 131072):
-// 32 units, S = 4096, k = 512, d = 32 18.4 / 20.2 (fp32, contiguous), 19.6 / 20.5 (bf16, paged); 4 sequences of 32/8 heads, S =
-// 131072, d = 16 206.9 / 210.0; 512 units, S = 12000, d = 32 271 / 247; 64 sequences of 64/8 heads, S = 8192, d = 64, every
-// head selecting for itself, k = 512 377 / 317, k = 1024 438 / 380, k = 2048 545 / 488 (the scoring alone 209 / 142); of 32/8
-// heads, S = 4096, d = 48, one selection per group 149 / 115; 16 of 32/8, S = 4096, fp32, d = 128 99 / 87.
+// Rotation inside the scoring, or a launch in front of it?  It saves that launch, about 3 us, and
+// costs every score block a rotation of its own, of all G heads of the group, and the score kernel
+// the registers that hold a pass's P_h across the first slab loads (matrix cores, waves per SIMD
+// without / with: d = 32 7 / 4, d = 64 6 / 3, d = 128 4 / 2).  So it is taken while all blocks are
+// soon resident: at most 18 per CU, where a unit's four rotating blocks count as eight (each reads
+// a quarter of P_h and stores qhat), and everything counts twice at 64 columns (two passes) and
+// eight times beyond; on the vector units twice again with several heads per KV head, but no more
+// than twice for bf16 rows of over 64 columns, which hold no slab loads in flight.  fp32 rows of
+// over 64 columns spill in this form: never.
+// One launch / two, us per step, both with the same stages behind them (1287 shapes, 8 to 4096
+// heads, S = 500 to 131072): 32 units, S = 4096, k = 512, d = 32 18.4 / 20.2 (fp32, contiguous),
+// 19.6 / 20.5 (bf16, paged); 4 sequences of 32/8 heads, S = 131072, d = 16 206.9 / 210.0; 512
+// units, S = 12000, d = 32 271 / 247; 64 sequences of 64/8 heads, S = 8192, d = 64, every head
+// selecting for itself, k = 512 377 / 317, k = 1024 438 / 380, k = 2048 545 / 488 (the scoring
+// alone 209 / 142); of 32/8 heads, S = 4096, d = 48, one selection per group 149 / 115; 16 of 32/8,
+// S = 4096, fp32, d = 128 99 / 87.
 bool rotate_score_applies(const Shape& s, int select_mode) {
   if (s.rg.queries > 1) return false;
   const int rpb = score_rows_per_block(s), passes = (s.d + kQrotCols - 1) / kQrotCols;

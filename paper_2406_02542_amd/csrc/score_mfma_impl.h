@@ -152,10 +152,11 @@ __device__ __forceinline__ void score_mfma_prefetch(const Rows& rows, int row0, 
 
 // Scores rows [row0, row_end) with the block's WAVES waves; `bufs` holds the first two buffers
 // (score_mfma_prefetch with the same arguments).  `rows` maps a row to this lane's chunk of it
-// (score_mfma_contiguous for rows that follow each other in memory, 16 NCH bytes each); emit(rowbase, acc) is called by every lane with acc[i] =
-// score of head (lane % 16) at row rowbase + i, rowbase = ... + 4 (lane / 16); rows at or past
-// row_end carry the values of the last row and must not be used.  A buffer is refilled right
-// after it is consumed, so that a wave always has loads in flight while it computes.
+// (score_mfma_contiguous for rows that follow each other in memory, 16 NCH bytes each);
+// emit(rowbase, acc) is called by every lane with acc[i] = score of head (lane % 16) at row rowbase
+// + i, rowbase = ... + 4 (lane / 16); rows at or past row_end carry the values of the last row and
+// must not be used.  A buffer is refilled right after it is consumed, so that a wave always has
+// loads in flight while it computes.
 // DEPTH = 16-byte loads a lane keeps in flight (both buffers together).
 // HEADS_IN_REGS: the two operands trade places (qhat is the A operand, the row tile the B
 // operand), so that the accumulator holds the scores of ONE row per lane and four heads per

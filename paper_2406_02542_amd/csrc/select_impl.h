@@ -564,10 +564,11 @@ __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t x) {
   return (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_scan_u32(x), 63);
 }
 
-// The rem largest (1 <= rem <= n) of n keys of at most `bits` bits: a search on the number of keys at or above a trial
-// value, by interpolation first (the keys of one histogram bin lie almost evenly: about five trials for a
-// thousand of them) and by halves after that, until a trial has exactly rem of them or the threshold is known to
-// the last bit.  count(x): keys >= x, x >= 1, uniform.
+// The rem largest (1 <= rem <= n) of n keys of at most `bits` bits: a search on the number of keys
+// at or above a trial value, by interpolation first (the keys of one histogram bin lie almost
+// evenly: about five trials for a thousand of them) and by halves after that, until a trial has
+// exactly rem of them or the threshold is known to the last bit.  count(x): keys >= x, x >= 1,
+// uniform.
 template <typename Count>
 __device__ __forceinline__ WaveThreshold wave_search(int n, int bits, uint32_t rem, Count count) {
   if (rem >= (uint32_t)n) return {0u, (uint32_t)n};
@@ -650,8 +651,8 @@ __device__ __forceinline__ void wave_count(const uint32_t* a, int n, uint32_t T,
   eq = wave_sum_u32(e);
 }
 
-// The wave emits the chosen of a[0, n) in order: emit(rank, i) for every key above T and for the first need_eq equal
-// to it, eq_before equal ones having been seen before.  Returns how many.
+// The wave emits the chosen of a[0, n) in order: emit(rank, i) for every key above T and for the
+// first need_eq equal to it, eq_before equal ones having been seen before.  Returns how many.
 template <typename Emit>
 __device__ __forceinline__ int wave_choose(const uint32_t* a, int n, const WaveThreshold& t, uint32_t eq_before, Emit emit) {
   const int lane = threadIdx.x & 63;
@@ -680,12 +681,13 @@ __device__ __forceinline__ int wave_choose(const uint32_t* a, int n, const WaveT
   return rank;
 }
 
-// Whole selection of keys in LDS (padded as above) whose leading 11 bits are counted in sm.hist[0], the rest of sm
-// being clear: emit(rank, pos, key) is called exactly k times, rank in [0, k) ascending with pos.  Every thread
-// looks at its run once: the rows above the threshold's bin and the rows inside it, the candidates, become two bit
-// masks.  The candidates' keys are collected in any order, the first wave finds the exact threshold among them
-// (wave_threshold), and every thread then looks at its own candidates again.  More candidates than hist[1] holds (long
-// runs of equal scores): the further digit passes of resident_threshold over all keys.
+// Whole selection of keys in LDS (padded as above) whose leading 11 bits are counted in sm.hist[0],
+// the rest of sm being clear: emit(rank, pos, key) is called exactly k times, rank in [0, k)
+// ascending with pos.  Every thread looks at its run once: the rows above the threshold's bin and
+// the rows inside it, the candidates, become two bit masks.  The candidates' keys are collected in
+// any order, the first wave finds the exact threshold among them (wave_threshold), and every thread
+// then looks at its own candidates again.  More candidates than hist[1] holds (long runs of equal
+// scores): the further digit passes of resident_threshold over all keys.
 template <int THREADS, int KPT, typename Emit>
 __device__ __forceinline__ void contiguous_select(const uint32_t* s_key, int n, int C, int k, ResidentSelectSmem<THREADS>& sm,
                                                   Emit emit) {
@@ -765,12 +767,14 @@ __device__ __forceinline__ void contiguous_select(const uint32_t* s_key, int n, 
 
 // ---- selection of keys that the block's threads hold, in two parts --------------------------------
 // Thread t holds positions [t C, (t + 1) C) (C <= KPT, a multiple of 4), so ranks follow the thread order.
-//   run_select_certain  one digit histogram: the rows above the threshold's bin are certain; the bin's rows, the
-//                       candidates, go to a list of their own.  Three barriers, and one at the end
+//   run_select_certain  one digit histogram: the rows above the threshold's bin are certain; the
+//                       bin's rows, the candidates, go to a list of their own.  Three barriers, and
+//                       one at the end
 //   run_threshold       the exact threshold among the candidates, by one wave, without a barrier, so that a caller can
 //                       have the certain rows' loads in flight
-// A bin of more than kRunCand rows (a quarter of a long sequence kept, or long runs of nearly equal scores) makes
-// run_select_certain find the exact threshold with resident_threshold's further passes.
+// A bin of more than kRunCand rows (a quarter of a long sequence kept, or long runs of nearly equal
+// scores) makes run_select_certain find the exact threshold with resident_threshold's further
+// passes.
 constexpr int kRunCand = 1024;
 
 template <int KPT>
@@ -841,8 +845,9 @@ __device__ __forceinline__ void run_partition(const RunKeys<KPT>& rk, int shift,
   e_rank = (int)(before >> 16);
 }
 
-// emit(rank, pos, key) for every certain row, ranks ascending with the position, unless the threshold has been
-// found instead.  sm.hist clear and rk loaded by every thread; sm.hist[1] holds the candidates afterwards.
+// emit(rank, pos, key) for every certain row, ranks ascending with the position, unless the
+// threshold has been found instead.  sm.hist clear and rk loaded by every thread; sm.hist[1] holds
+// the candidates afterwards.
 template <int THREADS, int KPT, typename Emit>
 __device__ __forceinline__ RunSelect run_select_certain(const RunKeys<KPT>& rk, int k, ResidentSelectSmem<THREADS>& sm,
                                                         Emit emit) {
