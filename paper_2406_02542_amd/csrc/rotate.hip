@@ -2,301 +2,275 @@
 // (Algorithm 1 lines 3-4 of arXiv 2406.02542): khat = k P_h, fp32 accumulation, one
 // rounding to the storage type, columns [0,d) to the low-rank slab and [d,D) to the residual.
 //
-// All rows that share a KV head share P_h, whatever their batch index, so a block works on a
-// run of (batch, row) items of ONE head with P_h resident in LDS.
-#include <type_traits>
-
+// All rows that share a KV head share P_h, whatever their batch index, so a block works on rows
+// of (batch, row) items of ONE head with P_h resident in its waves' registers.
 #include "common.h"
 #include "launch.h"
 
 namespace loki {
 
-constexpr int kRotThreads = 256;
-constexpr int kRotTile = 32;          // rows multiplied per step
-constexpr int kRotRowsPerThread = 16; // kRotTile / (kRotThreads / kD)
-
-template <typename T>
-__global__ __launch_bounds__(kRotThreads) void rotate_kernel(
-    const typename T::store_t* __restrict__ k_new, const float* __restrict__ P,
-    typename T::store_t* __restrict__ klo, typename T::store_t* __restrict__ khi, int Hkv,
-    int S_cap, int d, int pos, int n_new, int n_items, int items_per_block, Paging pg) {
-  using ST = typename T::store_t;
-  __shared__ float s_P[kD * kD];        // [128][128]
-  __shared__ float s_K[kRotTile * kD];  // [kRotTile][128]
-
-  const int tid = threadIdx.x;
-  const int h = blockIdx.y;
-  const float* Ph = P + (size_t)h * kD * kD;
-  for (int i = tid * 4; i < kD * kD; i += kRotThreads * 4)
-    *reinterpret_cast<float4*>(s_P + i) = *reinterpret_cast<const float4*>(Ph + i);
-
-  const int j = tid % kD;
-  const int rbase = (tid / kD) * kRotRowsPerThread;
-  const int item0 = blockIdx.x * items_per_block;
-  const int item1 = min(n_items, item0 + items_per_block);
-
-  for (int t0 = item0; t0 < item1; t0 += kRotTile) {
-    __syncthreads();  // previous tile fully consumed (and s_P complete on the first trip)
-    for (int i = tid; i < kRotTile * kD; i += kRotThreads) {
-      const int it = t0 + i / kD;
-      float x = 0.f;
-      if (it < item1) {
-        const int b = it / n_new, r = it % n_new;
-        x = T::load1(k_new + ((size_t)(b * Hkv + h) * n_new + r) * kD + (i % kD));
-      }
-      s_K[i] = x;
-    }
-    __syncthreads();
-    float acc[kRotRowsPerThread];
-#pragma unroll
-    for (int r = 0; r < kRotRowsPerThread; ++r) acc[r] = 0.f;
-    for (int i4 = 0; i4 < kD; i4 += 4) {
-      const float p0 = s_P[(i4 + 0) * kD + j], p1 = s_P[(i4 + 1) * kD + j];
-      const float p2 = s_P[(i4 + 2) * kD + j], p3 = s_P[(i4 + 3) * kD + j];
-#pragma unroll
-      for (int r = 0; r < kRotRowsPerThread; ++r) {
-        const float4 kv = *reinterpret_cast<const float4*>(s_K + (rbase + r) * kD + i4);
-        acc[r] = fmaf(kv.x, p0, acc[r]);
-        acc[r] = fmaf(kv.y, p1, acc[r]);
-        acc[r] = fmaf(kv.z, p2, acc[r]);
-        acc[r] = fmaf(kv.w, p3, acc[r]);
-      }
-    }
-#pragma unroll
-    for (int r = 0; r < kRotRowsPerThread; ++r) {
-      const int it = t0 + rbase + r;
-      if (it < item1) {
-        const int b = it / n_new, rr = it % n_new;
-        const size_t row = (size_t)cache_row(pg, b, h, Hkv, S_cap, pos + rr);
-        if (j < d)
-          T::store1(klo + row * d + j, acc[r]);
-        else
-          T::store1(khi + row * (kD - d) + (j - d), acc[r]);
-      }
-    }
-  }
-}
-
-// ---- matrix-core variant for bf16 caches --------------------------------------------------------
-// Khat = K P_h over a run of rows is a genuine [n, 128] x [128, 128] contraction.  A wave's
-// 16-byte-per-lane load of a 16-row tile of K is directly the A operand of
-// v_mfma_f32_16x16x32_bf16 (lane l: row l%16, columns 8*(l/16)..+7 of a 32-column step).  The B
-// operand is P_h, which is fp32: it is split once per block into three bf16 terms (24
-// significant bits, so every product is exact and only the fp32 accumulation order differs
-// from the vector kernel) and parked in LDS already in operand layout, 96 KiB.  Every wave
-// owns whole 16-row tiles (each key row is read from HBM once), prefetches its next tile while
-// the 96 matrix instructions of the current one run, packs pairs of neighbouring columns into
-// a staging tile in LDS, and writes whole rows from there.
 typedef __bf16 rot_bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float rot_f32x4_t __attribute__((ext_vector_type(4)));
+typedef unsigned int rot_u32x4_t __attribute__((ext_vector_type(4)));
 
-constexpr int kRotMfmaThreads = 512;
-constexpr int kRotMfmaWaves = kRotMfmaThreads / 64;
-constexpr int kRotMfmaMinItems = 1024;  // rows per block, at least and at most
-constexpr int kRotMfmaMaxItems = 8192;
-constexpr int kRotMfmaTPW = 2;        // tiles a wave multiplies per operand fetch
-constexpr int kRotTerms = 3;          // bf16 terms P enters with (3: every product exact)
+// What bounds it: memory, while a head has rows for its blocks. The rows of a trip go through LDS,
+// loaded whole rows at a time and left whole rows at a time, and every wave multiplies all of them
+// by its own 32 columns of P_h, so that P_h costs registers once and no LDS traffic. Blocks of four
+// waves, two to a CU, whose barriers fall apart, with four trips of rows on their way: 16 x 32 x
+// 4096 rows 220 us (4.9 TB/s read + write; a copy of the same bytes 204 to 218), with one block of
+// eight waves per CU 233, and 245 with P_h in LDS in operand layout (96 KB read per 32 rows and
+// wave) and every block on 8192 rows of its own: the blocks' positions are then megabytes apart and
+// alike in their low address bits, which alone costs a tenth (a copy of the bytes in that order
+// 231 us, in this one 210). Small calls: 11 x 124 rows of 8 heads 23 -> 8.4 us, where a block had at
+// least 1024 rows; fp32, then on the vector units, 2848 rows of 32 heads 277 -> 37 us.
+constexpr int kRotThreads = 256;
+constexpr int kRotPerCU = 2;                                      // blocks that share a CU
+constexpr int kRotColGroups = 4;                                  // waves side by side: 32 columns each
+constexpr int kRotRowGroups = kRotThreads / 64 / kRotColGroups;   // waves on rows of their own
+constexpr int kRotAhead = 4;                                      // trips whose rows are on their way
+constexpr int kRotTripBytes = 8192 * kRotRowGroups;               // key rows of a trip
+constexpr int kRotLoads = kRotTripBytes / 16 / kRotThreads;       // 16-byte loads a thread makes per trip
 
-// PAGED: the output rows go through the page table (a separate instantiation, so that the
-// contiguous kernel's store addresses stay plain arithmetic).
-template <bool PAGED>
-__global__ __launch_bounds__(kRotMfmaThreads) void rotate_mfma_kernel(
-    const uint16_t* __restrict__ k_new, const float* __restrict__ P, uint16_t* __restrict__ klo,
-    uint16_t* __restrict__ khi, int Hkv, int S_cap, int d, int pos, int n_new, int n_items,
-    int items_per_block, Paging pg) {
-  __shared__ uint4 s_B[kRotTerms][4][8][64];  // [term][32-column step of K][16-column block of Khat][lane]
-  // per wave: the rotated tiles of a trip, bf16, before they leave as whole rows (with three
-  // terms the two arrays fill the 160 KiB of a CU exactly)
-  __shared__ uint4 s_stage[kRotMfmaWaves][kRotMfmaTPW * 16 * 16];
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform: row bases stay scalar
-  const int kgrp = lane >> 4, r16 = lane & 15;
-  const int h = blockIdx.y;
-  const float* Ph = P + (size_t)h * kD * kD;
+// The 32 columns of P_h that a wave multiplies by, in registers as the A operand (the columns of P_h
+// are the rows of the product, the key rows its columns).  multiply(kv, acc): adds the products of a
+// 16-row tile, kv[t] = the lane's 16 bytes of key row lane % 16 for step t.
+template <typename T>
+struct RotOperand;
 
-  // element P[i][col] belongs to operand (step i/32, block col/16), lane ((i%32)/8)*16 + col%16,
-  // slot i%8
-  constexpr int kPrep = kD * kD / kRotMfmaThreads;  // 32 elements per thread, all loads in flight
-  float pv[kPrep];
+// P_h enters as three bf16 terms (24 significant bits): every product is exact, and only the order of
+// the fp32 sums differs from a vector product.  Lane l supplies
+// k = 32 step + 8 (l / 16) .. + 7 of column 8 (m / 4) + 4 nb + m % 4, m = l % 16, so that the
+// accumulators of nb = 0 and 1 hold eight neighbouring columns of one row.
+template <>
+struct RotOperand<BF16> {
+  static constexpr int kTiles = 2;  // 16-row tiles of a trip per wave
+  static constexpr int kSteps = 4;
+  static constexpr int kTerms = 3;
+  rot_bf16x8_t p[kTerms][kSteps][2];
+  __device__ __forceinline__ void load(const float* Ph, int cg, int r16, int kgrp) {
+    float x[kSteps][2][8];
 #pragma unroll
-  for (int n = 0; n < kPrep; ++n) pv[n] = Ph[tid + n * kRotMfmaThreads];
+    for (int t = 0; t < kSteps; ++t)
 #pragma unroll
-  for (int n = 0; n < kPrep; ++n) {
-    const int idx = tid + n * kRotMfmaThreads;
-    const int i = idx / kD, col = idx % kD;
-    float rest = pv[n];
-    uint16_t* base = reinterpret_cast<uint16_t*>(&s_B[0][i / 32][col / 16][((i % 32) / 8) * 16 + col % 16]) + (i % 8);
+      for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
-    for (int t = 0; t < kRotTerms; ++t) {
-      const uint16_t hb = BF16::round(rest);
-      rest -= __uint_as_float((uint32_t)hb << 16);  // exact in fp32
-      base[(size_t)t * (sizeof(s_B[0]) / 2)] = hb;
-    }
-  }
-  __syncthreads();
-
-  const int item0 = blockIdx.x * items_per_block;
-  const int item1 = min(n_items, item0 + items_per_block);
-
-  // Loads never branch: rows past the block's end re-read its last row (item1 > item0 always)
-  // and are simply not stored.  Straight-line loads and stores let the compiler count
-  // outstanding memory operations exactly, which keeps the prefetch of the next trip in flight
-  // during the matrix work instead of being waited for together with the stores.
-  // item -> (batch, row): one scalar division per tile base, then a short carry per lane
-  auto split_item = [&](int base, int off, int& b, int& r) {
-    b = base / n_new;
-    r = base % n_new + off;  // off < 64
-    while (r >= n_new) {
-      r -= n_new;
-      ++b;
-    }
-  };
-  auto load_tile = [&](int t0, uint4 (&raw)[4]) {
-    const int itb = min(t0, item1 - 1);
-    int b, r;
-    split_item(itb, min(t0 + r16, item1 - 1) - itb, b, r);
-    const char* src = reinterpret_cast<const char*>(k_new) +
-                      ((size_t)(b * Hkv + h) * n_new + r) * (kD * 2) + (size_t)kgrp * 16;
+        for (int e = 0; e < 8; ++e)
+          x[t][nb][e] = Ph[(32 * t + 8 * kgrp + e) * kD + 32 * cg + 8 * (r16 / 4) + 4 * nb + r16 % 4];
 #pragma unroll
-    for (int step = 0; step < 4; ++step) raw[step] = load16(src + step * 64);
-  };
-
-  constexpr int TPW = kRotMfmaTPW;
-  constexpr int kStride = 16 * TPW * kRotMfmaWaves;  // rows the block covers per trip
-
-  // One trip: TPW tiles starting at row t0; FULL = every row of them exists.
-  // Results go through the wave's staging tile so that every store instruction writes whole
-  // rows (16 bytes per lane, four rows per instruction); stored straight from the accumulator
-  // layout a row leaves in 32-byte pieces spread over the trip, which measured 10 % slower.
-  // A row of the tile is 256 bytes = 8 units of 32 bytes; unit c of row r sits at unit
-  // c ^ ((r >> 1) & 7), which spreads the 8-byte writes (16 rows x one 32-byte unit) and the
-  // 16-byte reads over the banks without padding.
-  typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
-  unsigned char* stage = reinterpret_cast<unsigned char*>(&s_stage[wave][0]);
-  auto trip = [&](int t0, const uint4 (&raw)[TPW][4], auto full_tag) {
-    constexpr bool FULL = decltype(full_tag)::value;
-    // The operands in LDS never change, but they must be re-read for every trip: hoisted out of
-    // the loop, all 96 of them would live in registers and spill.  An offset the compiler
-    // cannot see through (always 0) keeps the reads inside the trip.
-    uint32_t opaque = 0;
-    __asm__ volatile("" : "+v"(opaque));
-    const uint4* bop = &s_B[0][0][0][0] + opaque;
-    // P_h is the A operand and the key tile the B operand (the operand layouts are alike, so
-    // the LDS image and the key loads are what they would be the other way round): the
-    // accumulator of column block nb then holds, for this lane's ONE row r16, the four
-    // neighbouring columns 16 nb + 4 kgrp .. + 3, which are packed in registers and leave as one
-    // 8-byte LDS store (with the keys as A operand a lane held one column of four rows, and
-    // pairing neighbouring columns took a lane exchange and two selects per value).
+    for (int t = 0; t < kSteps; ++t)
 #pragma unroll
-    for (int nb = 0; nb < 8; nb += 2) {
-      rot_f32x4_t acc[TPW][2];
+      for (int nb = 0; nb < 2; ++nb) {
+        uint32_t w[kTerms][4];
 #pragma unroll
-      for (int u = 0; u < TPW; ++u)
+        for (int e2 = 0; e2 < 4; ++e2) {
+          float a = x[t][nb][2 * e2], b = x[t][nb][2 * e2 + 1];
 #pragma unroll
-        for (int half = 0; half < 2; ++half) acc[u][half] = rot_f32x4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int t = kRotTerms - 1; t >= 0; --t)  // smallest terms first
-#pragma unroll
-        for (int step = 0; step < 4; ++step) {
-          const rot_bf16x8_t b0 =
-              __builtin_bit_cast(rot_bf16x8_t, bop[((t * 4 + step) * 8 + nb) * 64 + lane]);
-          const rot_bf16x8_t b1 =
-              __builtin_bit_cast(rot_bf16x8_t, bop[((t * 4 + step) * 8 + nb + 1) * 64 + lane]);
-#pragma unroll
-          for (int u = 0; u < TPW; ++u) {
-            const rot_bf16x8_t a = __builtin_bit_cast(rot_bf16x8_t, raw[u][step]);
-            acc[u][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b0, a, acc[u][0], 0, 0, 0);
-            acc[u][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b1, a, acc[u][1], 0, 0, 0);
+          for (int n = 0; n < kTerms; ++n) {
+            const uint32_t pk = BF16::round2(a, b);
+            a -= __uint_as_float(pk << 16);  // exact in fp32
+            b -= __uint_as_float(pk & 0xffff0000u);
+            w[n][e2] = pk;
           }
         }
 #pragma unroll
-      for (int u = 0; u < TPW; ++u)
-#pragma unroll
-        for (int half = 0; half < 2; ++half) {
-          const int rt = r16;  // row of the tile
-          const int unit = (nb + half) ^ ((rt >> 1) & 7);
-          *reinterpret_cast<uint2*>(stage + (u * 16 + rt) * 256 + unit * 32 + kgrp * 8) =
-              make_uint2(BF16::round2(acc[u][half][0], acc[u][half][1]),
-                         BF16::round2(acc[u][half][2], acc[u][half][3]));
-        }
-    }
-    __builtin_amdgcn_wave_barrier();
-    // whole rows out: lane l takes chunk l%16 (8 columns) of row l/16 + 4*pass
-    const int itb = min(t0, item1 - 1);
-#pragma unroll
-    for (int u = 0; u < TPW; ++u)
-#pragma unroll
-      for (int pass = 0; pass < 4; ++pass) {
-        const int rt = 4 * pass + kgrp, c = r16;
-        const int it = t0 + 16 * u + rt;
-        int b, r;
-        split_item(itb, min(it, item1 - 1) - itb, b, r);
-        size_t row;
-        if constexpr (PAGED) row = (size_t)cache_row(pg, b, h, Hkv, S_cap, pos + r);
-        else row = (size_t)(b * Hkv + h) * S_cap + pos + r;
-        const int unit = (c >> 1) ^ ((rt >> 1) & 7);
-        const u32x4_t val = *reinterpret_cast<const u32x4_t*>(stage + (u * 16 + rt) * 256 + unit * 32 + (c & 1) * 16);
-        const int col = 8 * c;
-        uint16_t* dst = (col < d) ? klo + row * d + col : khi + row * (kD - d) + (col - d);
-        if (FULL || it < item1) *reinterpret_cast<u32x4_t*>(dst) = val;
+        for (int n = 0; n < kTerms; ++n) p[n][t][nb] = __builtin_bit_cast(rot_bf16x8_t, make_uint4(w[n][0], w[n][1], w[n][2], w[n][3]));
       }
-    __builtin_amdgcn_wave_barrier();
+  }
+  // acc[nb]: 16 rows of keys times 16 columns
+  __device__ __forceinline__ void multiply(const uint4 (&kv)[kSteps], rot_f32x4_t (&acc)[2]) const {
+#pragma unroll
+    for (int n = kTerms - 1; n >= 0; --n)  // smallest terms first
+#pragma unroll
+      for (int t = 0; t < kSteps; ++t)
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb)
+          acc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(p[n][t][nb], __builtin_bit_cast(rot_bf16x8_t, kv[t]), acc[nb], 0, 0, 0);
+  }
+  // the row's 16-byte chunks that this lane holds: one, columns 32 cg + 8 kgrp .. + 7
+  static constexpr int kChunks = 1;
+  __device__ static __forceinline__ int chunk(int cg, int kgrp, int) { return 4 * cg + kgrp; }
+  __device__ static __forceinline__ uint4 packed(const rot_f32x4_t (&acc)[2], int) {
+    return make_uint4(BF16::round2(acc[0][0], acc[0][1]), BF16::round2(acc[0][2], acc[0][3]),
+                      BF16::round2(acc[1][0], acc[1][1]), BF16::round2(acc[1][2], acc[1][3]));
+  }
+};
+
+// fp32 products and sums.  Step t holds k = 16 t .. + 15: lane l supplies k = 16 t + 4 (l / 16) + j to
+// the step's matrix instruction j, which is what the lane's 16 bytes of a key row hold.
+template <>
+struct RotOperand<F32> {
+  static constexpr int kTiles = 1;
+  static constexpr int kSteps = 8;
+  float p[kSteps][4][2];
+  __device__ __forceinline__ void load(const float* Ph, int cg, int r16, int kgrp) {
+#pragma unroll
+    for (int t = 0; t < kSteps; ++t)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb) p[t][j][nb] = Ph[(16 * t + 4 * kgrp + j) * kD + 32 * cg + 16 * nb + r16];
+  }
+  __device__ __forceinline__ void multiply(const uint4 (&kv)[kSteps], rot_f32x4_t (&acc)[2]) const {
+#pragma unroll
+    for (int t = 0; t < kSteps; ++t) {
+      float f[4];
+      F32::unpack(kv[t], f);
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb) acc[nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(p[t][j][nb], f[j], acc[nb], 0, 0, 0);
+    }
+  }
+  static constexpr int kChunks = 2;  // columns 32 cg + 16 nb + 4 kgrp .. + 3
+  __device__ static __forceinline__ int chunk(int cg, int kgrp, int nb) { return 8 * cg + 4 * nb + kgrp; }
+  __device__ static __forceinline__ uint4 packed(const rot_f32x4_t (&acc)[2], int nb) {
+    return __builtin_bit_cast(uint4, acc[nb]);
+  }
+};
+
+// Block (x, head): trips x, x + gridDim.x, ... of the head's items, kRows rows each.
+// PAGED: the output rows go through the page table (a separate instantiation, so that the
+// contiguous kernel's store addresses stay plain arithmetic).
+template <typename T, bool PAGED, bool PASS_CACHES>
+__global__ __launch_bounds__(kRotThreads, kRotPerCU) void rotate_kernel(
+    const char* __restrict__ k_new, const float* __restrict__ P, char* __restrict__ klo, char* __restrict__ khi,
+    int Hkv, int S_cap, int d, int pos, int n_new, int n_items, Paging pg) {
+  using Op = RotOperand<T>;
+  constexpr int kTiles = Op::kTiles, kRows = 16 * kTiles * kRotRowGroups;
+  constexpr int kRowBytes = kD * T::kBytes, kChunks = kRowBytes / 16;  // 16-byte chunks of a row
+  static_assert(kRows * kRowBytes == kRotTripBytes, "a trip fills a buffer");
+  constexpr int kRowStep = kRotThreads / kChunks;  // rows from one of a thread's chunks to the next
+  // Chunk c of row r sits at c ^ (r % 16): 16 rows' equal chunks, and a row's chunks, are in different banks.
+  __shared__ uint4 s_in[2][kRotTripBytes / 16], s_out[2][kRotTripBytes / 16];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int cg = wave % kRotColGroups, rg = wave / kRotColGroups;
+  const int kgrp = lane >> 4, r16 = lane & 15;
+  const int h = blockIdx.y;
+  const int my_row = tid / kChunks, my_chunk = tid % kChunks;
+  auto my_slot = [&](int n) {
+    const int row = my_row + n * kRowStep;
+    return row * kChunks + (my_chunk ^ (row & 15));
   };
 
-  uint4 nxt[TPW][4];
+  // item -> (batch, row), a scalar division per trip and a carry per lane; rows past the end are the last row
+  const float inv_n = 1.0f / (float)n_new;
+  auto place = [&](int trip, int off, int& b, int& r) {
+    const int base = min(trip * kRows, n_items - 1);  // (uniform)
+    const int b0 = base / n_new;
+    const int x = base - b0 * n_new + min(off, n_items - 1 - base);  // < n_new + kRows
+    const int carry = n_new >= kRows ? (x >= n_new ? 1 : 0) : (int)(((float)x + 0.5f) * inv_n);
+    b = b0 + carry;
+    r = x - carry * n_new;
+  };
+  auto load_trip = [&](int trip, uint4 (&raw)[kRotLoads]) {
 #pragma unroll
-  for (int u = 0; u < TPW; ++u) load_tile(item0 + 16 * (TPW * wave + u), nxt[u]);
-  int t0 = item0 + 16 * TPW * wave;
-  for (; t0 + 16 * TPW <= item1; t0 += kStride) {  // trips whose rows all exist
-    uint4 raw[TPW][4];
+    for (int n = 0; n < kRotLoads; ++n) {
+      int b, r;
+      place(trip, my_row + n * kRowStep, b, r);
+      const char* src = k_new + ((size_t)(b * Hkv + h) * n_new + r) * kRowBytes + my_chunk * 16;
+      raw[n] = load16(src);
+    }
+  };
+  auto store_trip = [&](int trip, int buf) {
 #pragma unroll
-    for (int u = 0; u < TPW; ++u)
+    for (int n = 0; n < kRotLoads; ++n) {
+      const int off = my_row + n * kRowStep;
+      int b, r;
+      place(trip, off, b, r);
+      size_t row;
+      if constexpr (PAGED) row = (size_t)cache_row(pg, b, h, Hkv, S_cap, pos + r);
+      else row = (size_t)(b * Hkv + h) * S_cap + pos + r;
+      const int col = my_chunk * T::EPC;
+      char* dst = col < d ? klo + (row * d + col) * T::kBytes : khi + (row * (kD - d) + (col - d)) * T::kBytes;
+      const rot_u32x4_t val = __builtin_bit_cast(rot_u32x4_t, s_out[buf][my_slot(n)]);
+      if (trip * kRows + off < n_items) {
+        if constexpr (PASS_CACHES) __builtin_nontemporal_store(val, reinterpret_cast<rot_u32x4_t*>(dst));
+        else *reinterpret_cast<rot_u32x4_t*>(dst) = val;
+      }
+    }
+  };
+
+  const int n_trips = (n_items + kRows - 1) / kRows, stride = gridDim.x;
+  uint4 raw[kRotAhead][kRotLoads];
+  load_trip(blockIdx.x, raw[0]);
+  Op op;
+  op.load(P + (size_t)h * kD * kD, cg, r16, kgrp);
 #pragma unroll
-      for (int step = 0; step < 4; ++step) raw[u][step] = nxt[u][step];
+  for (int a = 1; a < kRotAhead; ++a) load_trip(blockIdx.x + a * stride, raw[a]);
+
+  int trip = blockIdx.x, buf = 0;
+  bool first = true;
+  for (bool more = true; more;) {
 #pragma unroll
-    for (int u = 0; u < TPW; ++u) load_tile(t0 + kStride + 16 * u, nxt[u]);
-    trip(t0, raw, std::true_type{});
+    for (int a = 0; a < kRotAhead; ++a) {
+      if (trip >= n_trips) {
+        more = false;
+        break;
+      }
+#pragma unroll
+      for (int n = 0; n < kRotLoads; ++n) s_in[buf][my_slot(n)] = raw[a][n];
+      load_trip(trip + kRotAhead * stride, raw[a]);
+      __syncthreads();
+      if (!first) store_trip(trip - stride, buf ^ 1);
+      first = false;
+#pragma unroll
+      for (int u = 0; u < kTiles; ++u) {
+        const int row = (rg * kTiles + u) * 16 + r16;
+        uint4 kv[Op::kSteps];
+#pragma unroll
+        for (int t = 0; t < Op::kSteps; ++t) kv[t] = s_in[buf][row * kChunks + ((4 * t + kgrp) ^ r16)];
+        rot_f32x4_t acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+        op.multiply(kv, acc);
+#pragma unroll
+        for (int c = 0; c < Op::kChunks; ++c)
+          s_out[buf][row * kChunks + (Op::chunk(cg, kgrp, c) ^ r16)] = Op::packed(acc, c);
+      }
+      trip += stride;
+      buf ^= 1;
+    }
   }
-  if (t0 < item1) trip(t0, nxt, std::false_type{});  // ragged last trip of this wave
+  __syncthreads();
+  store_trip(trip - stride, buf ^ 1);
+}
+
+template <typename T>
+static hipError_t launch_rotate_t(const Shape& s, const void* k_new, const float* P, void* klo, void* khi, int pos,
+                                  int n_new, int n_items, hipStream_t st) {
+  constexpr int kRows = 16 * RotOperand<T>::kTiles * kRotRowGroups;
+  const int cus = device_cus(), trips = (n_items + kRows - 1) / kRows;
+  // One round of blocks, or as many more (up to four) as leave the last round less idle: a round costs
+  // its longest block's trips and about two trips of set-up (P_h into registers, the first rows).
+  int blocks = 1;
+  long long best = -1;
+  for (int rounds = 1; rounds <= 4; ++rounds) {
+    int nb = (int)((long long)rounds * kRotPerCU * cus / s.Hkv);
+    nb = nb < 1 ? 1 : nb > trips ? trips : nb;
+    const long long cost = (long long)rounds * ((trips + nb - 1) / nb + 2);
+    if (best < 0 || cost < best) {
+      best = cost;
+      blocks = nb;
+    }
+  }
+  // Rows are written past the caches while input and output fit the last-level cache (256 MiB), into
+  // which a cache that has just been cleared has been written.  us, past / through the caches, a
+  // repeated call and one on new buffers: 55 MB 14.8 / 16.7 and 54 / 58, 98 MB 23.0 / 25.9 and 62 / 67,
+  // 268 MB 57.5 / 59.3 and 107 / 105, 537 MB 108.5 / 111.7 and 200 / 174.
+  const bool pass_caches = 2ll * n_items * s.Hkv * kD * T::kBytes <= 256ll << 20;
+  const dim3 grid(blocks, s.Hkv);
+  const auto kernel = s.pg.table != nullptr ? (pass_caches ? rotate_kernel<T, true, true> : rotate_kernel<T, true, false>)
+                                            : (pass_caches ? rotate_kernel<T, false, true> : rotate_kernel<T, false, false>);
+  hipLaunchKernelGGL(kernel, grid, dim3(kRotThreads), 0, st, static_cast<const char*>(k_new), P, static_cast<char*>(klo),
+                     static_cast<char*>(khi), s.Hkv, s.S_cap, s.d, pos, n_new, n_items, s.pg);
+  return hipGetLastError();
 }
 
 hipError_t launch_rotate(const Shape& s, const void* k_new, const float* P, void* klo, void* khi,
                          int pos, int n_new, hipStream_t st) {
-  const bool paged = s.pg.table != nullptr;
-  const long long n_items_ll = (long long)s.B * n_new;
-  if (n_items_ll > 0x7fffffffLL) return hipErrorInvalidValue;
-  const int n_items = (int)n_items_ll;
-  if (s.dtype == 1) {
-    // One block per CU where the rows allow it: a block's set-up (P_h split into LDS) and its
-    // tail are paid once per block, and on the benchmark prefill 8192 rows per block (one round
-    // of blocks) took 289 us against 348 us with 2048 (four rounds).
-    constexpr int kTripRows = 16 * kRotMfmaTPW * kRotMfmaWaves;
-    const int cus = device_cus();
-    long long want = (n_items_ll * s.Hkv + cus - 1) / cus;
-    want = (want + kTripRows - 1) / kTripRows * kTripRows;
-    int ipb_m = (int)(want < kRotMfmaMinItems ? kRotMfmaMinItems : want > kRotMfmaMaxItems ? kRotMfmaMaxItems : want);
-    if (n_items < ipb_m) ipb_m = ((n_items + 15) / 16) * 16;
-    dim3 grid_m((n_items + ipb_m - 1) / ipb_m, s.Hkv);
-    if (paged)
-      hipLaunchKernelGGL(rotate_mfma_kernel<true>, grid_m, dim3(kRotMfmaThreads), 0, st,
-                         static_cast<const uint16_t*>(k_new), P, static_cast<uint16_t*>(klo),
-                         static_cast<uint16_t*>(khi), s.Hkv, s.S_cap, s.d, pos, n_new, n_items, ipb_m,
-                         s.pg);
-    else
-      hipLaunchKernelGGL(rotate_mfma_kernel<false>, grid_m, dim3(kRotMfmaThreads), 0, st,
-                         static_cast<const uint16_t*>(k_new), P, static_cast<uint16_t*>(klo),
-                         static_cast<uint16_t*>(khi), s.Hkv, s.S_cap, s.d, pos, n_new, n_items, ipb_m,
-                         s.pg);
-    return hipGetLastError();
-  }
-  // fp32 caches: the vector kernel (P_h in LDS as fp32)
-  int ipb = 512;
-  if (n_items < ipb) ipb = ((n_items + kRotTile - 1) / kRotTile) * kRotTile;
-  const dim3 grid((n_items + ipb - 1) / ipb, s.Hkv);
-  hipLaunchKernelGGL(rotate_kernel<F32>, grid, dim3(kRotThreads), 0, st,
-                     static_cast<const float*>(k_new), P, static_cast<float*>(klo),
-                     static_cast<float*>(khi), s.Hkv, s.S_cap, s.d, pos, n_new, n_items, ipb, s.pg);
-  return hipGetLastError();
+  const long long n_items = (long long)s.B * n_new;
+  if (n_items > 0x7fffffffLL) return hipErrorInvalidValue;
+  return s.dtype == 1 ? launch_rotate_t<BF16>(s, k_new, P, klo, khi, pos, n_new, (int)n_items, st)
+                      : launch_rotate_t<F32>(s, k_new, P, klo, khi, pos, n_new, (int)n_items, st);
 }
 
 }  // namespace loki
