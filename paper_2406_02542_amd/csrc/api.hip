@@ -66,6 +66,38 @@ int score_rows_per_block(const Shape& s) {
   return rows;
 }
 
+// From 90 MB a call on, the bytes it reads of its caches.  The last-level cache holds 256 MiB, so a
+// smaller call finds rows there that it read itself a call or two before, or that the step before it
+// in a model left there, and loads past the caches are slower then; larger ones find none and read
+// 8 to 12 % faster.  us, through / past the caches, each over three copies of its inputs in turn:
+//   one block per head: 602 MB of cache, 80 heads, S = 5230 49.8 / 45.3; 16 x 32 heads, S = 4096,
+//     384 MB read 68.8 / 61.0, on pages 55.4 / 49.5; 96 heads, S = 4853, 82 MB 32.4 / 33.2, 64
+//     heads, S = 4122, 16 MB 16.3 / 18.1
+//   groups, values only: 151 MB 43.6 / 40.5, 125 MB 35.1 / 33.7, 93 MB 39.2 / 36.4; 46 MB 36.7 /
+//     37.9, 24 MB 33.1 / 33.7
+//   dense: 241 MB 48.1 / 42.6, 123 MB 28.7 / 26.0; 83 MB 18.5 / 19.2, 73 MB 19.7 / 19.9, 46 MB 13.8
+//     / 15.1
+// Heads that select for themselves in a group, or tokens of a sequence, find rows that the others
+// have just read: not beyond half of the rows (72 units of 8 heads, k = S / 8 42.1 / 44.4; 2 tokens,
+// k = S / 4, one head 63.8 / 57.8; groups of 4, k = S / 16 91.1 / 86.8).
+bool streams_rows(const Shape& s, int select_mode) {
+  const int tokens = s.rg.queries > 1 ? s.rg.queries : 1;
+  const double unit_rows = (double)(s.B / tokens) * s.Hkv * s.S;
+  double per_row;  // elements of a row that are read
+  if (select_mode == kEveryRow) {
+    per_row = 2 * kD;
+  } else if (select_mode == kLowRankRows) {
+    per_row = kD + s.d;
+  } else {
+    const int lists = tokens * (select_mode == 1 ? 1 : s.G);
+    const double share = (double)lists * s.k / s.S;
+    if (lists > 1 && share > 0.5) return false;
+    per_row = s.d + share * (2 * kD - (select_mode == 1 ? 0 : s.d));
+    if (share > 1.0) per_row = 2 * kD;
+  }
+  return unit_rows * per_row * s.elem_bytes >= 90e6;
+}
+
 int gather_splits(const Shape& s, int select_mode) {
   const int heads = (select_mode == 1) ? s.B * s.Hkv : s.B * s.Hq;
   // about two blocks per CU: a block's set-up and merge cost as much as a few hundred rows, and

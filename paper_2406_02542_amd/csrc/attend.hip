@@ -16,9 +16,9 @@ constexpr int kAttThreads = 256;
 constexpr int kAttWaves = kAttThreads / 64;
 
 // LO_ONLY (with GATHER = false): every row, rotated query, logits from the low-rank slab alone
-// (Appendix E, Algorithm 2).  BALANCED (dense): the blocks of a KV head are dealt out over its sequences by
+// (Appendix E, Algorithm 2).  STREAM: see streams_rows.  BALANCED (dense): the blocks of a KV head are dealt out over its sequences by
 // length (dense_runs).
-template <typename T, int NH, bool GATHER, bool REUSE_LO, bool LO_ONLY = false, bool BALANCED = false>
+template <typename T, int NH, bool GATHER, bool REUSE_LO, bool STREAM, bool LO_ONLY = false, bool BALANCED = false>
 __global__ __launch_bounds__(kAttThreads) void attend_kernel(
     const void* __restrict__ k_a,   // GATHER: klo [units, S_cap, d]; dense: K [units, S_cap, 128]
     const void* __restrict__ k_b,   // GATHER: khi [units, S_cap, 128-d]; dense: unused
@@ -128,8 +128,8 @@ __global__ __launch_bounds__(kAttThreads) void attend_kernel(
                                                          (GATHER || LO_ONLY) ? d : kD, c);
   AttendAcc<T, NH> acc;
   acc.init();
-  attend_rows<T, NH, kAttWaves * RPW, GATHER, REUSE_LO>(acc, qr, ra, s_idx, s_a, wave * RPW + rg,
-                                                        r0, r1);
+  attend_rows<T, NH, kAttWaves * RPW, GATHER, REUSE_LO, false, false, STREAM>(
+      acc, qr, ra, s_idx, s_a, wave * RPW + rg, r0, r1);
   attend_publish<T, NH, kAttWaves>(acc, s_merge);
 
   // thread t owns column t % 128 of heads t / 128, t / 128 + 2, ...
@@ -180,7 +180,7 @@ __global__ __launch_bounds__(kD) void combine_kernel(const float* __restrict__ p
 }
 
 // ---- launchers ------------------------------------------------------------------------
-template <typename T, int NH, bool GATHER>
+template <typename T, int NH, bool GATHER, bool STREAM>
 static hipError_t launch_attend_nh(int blocks_y, int nsplit, int rows_per_block, const void* k_a,
                                    const void* k_b, const void* v, const void* qv,
                                    const int32_t* sel_idx, const float* sel_score, float* partial,
@@ -191,26 +191,26 @@ static hipError_t launch_attend_nh(int blocks_y, int nsplit, int rows_per_block,
   // (d = 128, Exact-TopK of Section 5: it is the whole logit and no key is read again)
   constexpr bool kCanReuse = GATHER && NH == 1;
   if (kCanReuse && sel_score != nullptr) {
-    hipLaunchKernelGGL((attend_kernel<T, NH, GATHER, kCanReuse>), dim3(nsplit, blocks_y),
+    hipLaunchKernelGGL((attend_kernel<T, NH, GATHER, kCanReuse, STREAM>), dim3(nsplit, blocks_y),
                        dim3(kAttThreads), 0, st, k_a, k_b, v, qv, sel_idx, sel_score, partial, tickets,
                        out, Hq, Gq, S_cap, d, n, rows_per_block, nsplit, S_max, rg, pg, xcd_group_blocks, xcd_sets);
   } else {
-    hipLaunchKernelGGL((attend_kernel<T, NH, GATHER, false>), dim3(nsplit, blocks_y),
+    hipLaunchKernelGGL((attend_kernel<T, NH, GATHER, false, STREAM>), dim3(nsplit, blocks_y),
                        dim3(kAttThreads), 0, st, k_a, k_b, v, qv, sel_idx, sel_score, partial, tickets,
                        out, Hq, Gq, S_cap, d, n, rows_per_block, nsplit, S_max, rg, pg, xcd_group_blocks, xcd_sets);
   }
   return hipGetLastError();
 }
 
-template <typename T, bool GATHER>
-static hipError_t launch_attend_t(int NH, int blocks_y, int nsplit, int rows_per_block,
+template <typename T, bool GATHER, bool STREAM>
+static hipError_t launch_attend_s(int NH, int blocks_y, int nsplit, int rows_per_block,
                                   const void* k_a, const void* k_b, const void* v, const void* qv,
                                   const int32_t* sel_idx, const float* sel_score, float* partial,
                                   int32_t* tickets, void* out, int Hq, int Gq, int S_cap, int d, int n, int S_max,
                                   const Ragged& rg, const Paging& pg, int xcd_group_blocks,
                                   int xcd_sets, hipStream_t st) {
 #define LOKI_ATT(NHV)                                                                          \
-  return launch_attend_nh<T, NHV, GATHER>(blocks_y, nsplit, rows_per_block, k_a, k_b, v, qv,   \
+  return launch_attend_nh<T, NHV, GATHER, STREAM>(blocks_y, nsplit, rows_per_block, k_a, k_b, v, qv,   \
                                           sel_idx, sel_score, partial, tickets, out, Hq, Gq, S_cap, d, n, S_max, rg, pg, \
                                           xcd_group_blocks, xcd_sets, st)
   switch (NH) {
@@ -221,6 +221,11 @@ static hipError_t launch_attend_t(int NH, int blocks_y, int nsplit, int rows_per
     default: return hipErrorInvalidValue;
   }
 #undef LOKI_ATT
+}
+
+template <typename T, bool GATHER, typename... Args>
+static hipError_t launch_attend_t(bool stream, Args... args) {
+  return stream ? launch_attend_s<T, GATHER, true>(args...) : launch_attend_s<T, GATHER, false>(args...);
 }
 
 static inline int div_up(int a, int b) { return (a + b - 1) / b; }
@@ -245,17 +250,20 @@ hipError_t launch_gather(const Shape& s, int select_mode, int nsplit, const floa
     xcd = sharers * nsplit;
     blocks_y = div_up(sets, 8) * 8 * sharers;
   }
+  const bool stream = streams_rows(s, select_mode);
   if (s.dtype == 0)
-    return launch_attend_t<F32, true>(NH, blocks_y, nsplit, rpb, klo, khi, v, qhat, sel_idx,
+    return launch_attend_t<F32, true>(stream, NH, blocks_y, nsplit, rpb, klo, khi, v, qhat, sel_idx,
                                       sel_score, partial, tickets, out, s.Hq, s.G, s.S_cap, s.d, s.k, s.S, s.rg, s.pg, xcd, sets, st);
-  return launch_attend_t<BF16, true>(NH, blocks_y, nsplit, rpb, klo, khi, v, qhat, sel_idx,
+  return launch_attend_t<BF16, true>(stream, NH, blocks_y, nsplit, rpb, klo, khi, v, qhat, sel_idx,
                                      sel_score, partial, tickets, out, s.Hq, s.G, s.S_cap, s.d, s.k, s.S, s.rg, s.pg, xcd, sets, st);
 }
 
 template <typename T, int NH>
 static hipError_t launch_dense_balanced_nh(const Shape& s, int nsplit, const void* q, const void* k_full, const void* v,
                                            float* partial, void* out, hipStream_t st) {
-  hipLaunchKernelGGL((attend_kernel<T, NH, false, false, false, true>), dim3(nsplit, s.B * s.Hkv), dim3(kAttThreads), 0, st,
+  const auto kernel = streams_rows(s, kEveryRow) ? attend_kernel<T, NH, false, false, true, false, true>
+                                                 : attend_kernel<T, NH, false, false, false, false, true>;
+  hipLaunchKernelGGL(kernel, dim3(nsplit, s.B * s.Hkv), dim3(kAttThreads), 0, st,
                      k_full, nullptr, v, q, nullptr, nullptr, partial, nullptr, out, s.Hq, s.G, s.S_cap, kD, s.S,
                      div_up(s.S, nsplit), nsplit, s.S, s.rg, Paging{}, 0, 0);
   return hipGetLastError();
@@ -281,17 +289,20 @@ hipError_t launch_dense(const Shape& s, int nsplit, const void* q, const void* k
                         : launch_dense_balanced<BF16>(s, nsplit, q, k_full, v, partial, out, st);
   const int blocks_y = s.B * s.Hkv;
   const int rpb = div_up(s.S, nsplit);
+  const bool stream = streams_rows(s, kEveryRow);
   if (s.dtype == 0)
-    return launch_attend_t<F32, false>(s.G, blocks_y, nsplit, rpb, k_full, nullptr, v, q, nullptr,
+    return launch_attend_t<F32, false>(stream, s.G, blocks_y, nsplit, rpb, k_full, nullptr, v, q, nullptr,
                                        nullptr, partial, nullptr, out, s.Hq, s.G, s.S_cap, kD, s.S, s.S, s.rg, Paging{}, 0, 0, st);
-  return launch_attend_t<BF16, false>(s.G, blocks_y, nsplit, rpb, k_full, nullptr, v, q, nullptr,
+  return launch_attend_t<BF16, false>(stream, s.G, blocks_y, nsplit, rpb, k_full, nullptr, v, q, nullptr,
                                       nullptr, partial, nullptr, out, s.Hq, s.G, s.S_cap, kD, s.S, s.S, s.rg, Paging{}, 0, 0, st);
 }
 
 template <typename T, int NH>
 static hipError_t launch_pca_nh(const Shape& s, int nsplit, int rpb, const float* qhat, const void* klo,
                                 const void* v, float* partial, void* out, hipStream_t st) {
-  hipLaunchKernelGGL((attend_kernel<T, NH, false, false, true>), dim3(nsplit, s.B * s.Hkv),
+  const auto kernel = streams_rows(s, kLowRankRows) ? attend_kernel<T, NH, false, false, true, true>
+                                                    : attend_kernel<T, NH, false, false, false, true>;
+  hipLaunchKernelGGL(kernel, dim3(nsplit, s.B * s.Hkv),
                      dim3(kAttThreads), 0, st, klo, nullptr, v, qhat, nullptr, nullptr, partial, nullptr,
                      out, s.Hq, s.G, s.S_cap, s.d, s.S, rpb, nsplit, s.S, s.rg, Paging{}, 0, 0);
   return hipGetLastError();

@@ -122,7 +122,8 @@ __device__ __forceinline__ void attend_trip(AttendAcc<T, NH>& acc, const float (
 // attention over 2 sequences of 990 rows, 32/8 fp32 heads, 20.4 / 18.3, 2 to 7 of 546 to 2310 rows
 // 4 to 13 % more, large ones 0.6 %; but one block per head beyond 8192 rows, 512 heads in groups of
 // 4, S = 12800, k = 400 46.4 / 47.3, S = 13300, k = 831 62.7 / 64.0.
-template <typename T, int NH, int NGROUPS, bool GATHER, bool REUSE_LO, bool SCORE_BY_ROW = false, bool APART = false>
+// STREAM: rows are loaded past the caches (streams_rows).
+template <typename T, int NH, int NGROUPS, bool GATHER, bool REUSE_LO, bool SCORE_BY_ROW = false, bool APART = false, bool STREAM = false>
 __device__ __forceinline__ void attend_rows(AttendAcc<T, NH>& acc, const float (&qr)[NH][T::EPC],
                                             const RowAddr& ra, const int32_t* s_idx,
                                             const float* s_a, int gid, int r0, int r1) {
@@ -147,9 +148,9 @@ __device__ __forceinline__ void attend_rows(AttendAcc<T, NH>& acc, const float (
         else if constexpr (REUSE_LO)
           alo[j] = s_a[r - r0];
       }
-      kraw[j] = (ok[j] && ra.k_load) ? load16(ra.k_base + (size_t)row * ra.k_row_bytes)
+      kraw[j] = (ok[j] && ra.k_load) ? load16_hint<STREAM>(ra.k_base + (size_t)row * ra.k_row_bytes)
                                      : make_uint4(0, 0, 0, 0);
-      vraw[j] = ok[j] ? load16(ra.v_base + (size_t)row * ra.v_row_bytes) : make_uint4(0, 0, 0, 0);
+      vraw[j] = ok[j] ? load16_hint<STREAM>(ra.v_base + (size_t)row * ra.v_row_bytes) : make_uint4(0, 0, 0, 0);
     }
     if constexpr (APART) {
       attend_trip<T, NH, R, REUSE_LO>(acc, qr, kraw, vraw, alo, ok);
@@ -201,7 +202,7 @@ __device__ __forceinline__ void attend_rows(AttendAcc<T, NH>& acc, const float (
 // The same over a list that is still growing: entries below `there` exist when the call begins, and
 // those of the first trip are loaded before complete(), which completes the list (every wave calls
 // it once).
-template <typename T, int NH, int NGROUPS, bool REUSE_LO, typename Complete>
+template <typename T, int NH, int NGROUPS, bool REUSE_LO, bool STREAM = false, typename Complete>
 __device__ __forceinline__ void attend_growing(AttendAcc<T, NH>& acc, const float (&qr)[NH][T::EPC],
                                                const RowAddr& ra, const int32_t* s_idx, const float* s_a, int gid,
                                                int r0, int r1, int there, Complete complete) {
@@ -222,8 +223,8 @@ __device__ __forceinline__ void attend_growing(AttendAcc<T, NH>& acc, const floa
       if (r >= lo && r < hi) {
         const int row = s_idx[r - r0];
         if constexpr (REUSE_LO) alo[j] = s_a[r - r0];
-        if (ra.k_load) kraw[j] = load16(ra.k_base + (size_t)row * ra.k_row_bytes);
-        vraw[j] = load16(ra.v_base + (size_t)row * ra.v_row_bytes);
+        if (ra.k_load) kraw[j] = load16_hint<STREAM>(ra.k_base + (size_t)row * ra.k_row_bytes);
+        vraw[j] = load16_hint<STREAM>(ra.v_base + (size_t)row * ra.v_row_bytes);
       }
     }
   };

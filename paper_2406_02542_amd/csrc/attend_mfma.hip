@@ -32,8 +32,9 @@ constexpr int kAmWaves = kAmThreads / 64;
 // with row pitch d (Appendix E, Algorithm 2): KSTEPS = ceil(d / 32) of the four 32-column
 // steps of the first product are issued, and columns past d (a partial last step) meet a zero
 // in the B operand, so whatever valid chunk their lanes load does not count.
+// STREAM_V: see streams_rows.
 // BALANCED (dense): the blocks of a KV head are dealt out over its sequences by length (dense_runs).
-template <int NH, bool GATHER, int KSTEPS = 4, bool LO_ONLY = false, bool BALANCED = false>
+template <int NH, bool GATHER, bool STREAM_V, int KSTEPS = 4, bool LO_ONLY = false, bool BALANCED = false>
 __global__ __launch_bounds__(kAmThreads, 2) void attend_mfma_kernel(
     const void* __restrict__ k_a,   // GATHER: klo [units, S_cap, d]; dense: K [units, S_cap, 128]
     const void* __restrict__ k_b,   // GATHER: khi [units, S_cap, 128-d]; dense: unused
@@ -116,7 +117,7 @@ __global__ __launch_bounds__(kAmThreads, 2) void attend_mfma_kernel(
   const AmAddr<KSTEPS> ad = am_make_addr<KSTEPS, LO_ONLY>(k_a, k_b, v, addr_unit, S_cap, kRotated ? d : kD);
   AmState st;
   st.init();
-  am_attend_rows<GATHER, KSTEPS, QT>(ad, bq, s_idx, r0, AmRoundRobin<kAmWaves>(r0, r1), st, [] {});
+  am_attend_rows<GATHER, KSTEPS, QT, STREAM_V>(ad, bq, s_idx, r0, AmRoundRobin<kAmWaves>(r0, r1), st, [] {});
   am_publish<NH, kAmWaves>(st, s_merge);
 
   for (int i = tid; i < NH * kD; i += kAmThreads) {
@@ -145,7 +146,7 @@ __global__ __launch_bounds__(kAmThreads, 2) void attend_mfma_kernel(
   }
 }
 
-template <bool GATHER>
+template <bool GATHER, bool STREAM_V>
 static hipError_t launch_attend_mfma_nh(int NH, int blocks_y, int nsplit, int rpb, const void* k_a,
                                         const void* k_b, const void* v, const void* qv,
                                         const int32_t* sel_idx, float* partial, int32_t* tickets,
@@ -155,11 +156,11 @@ static hipError_t launch_attend_mfma_nh(int NH, int blocks_y, int nsplit, int rp
   uint16_t* o16 = static_cast<uint16_t*>(out);
   switch (NH) {
     case 4:
-      hipLaunchKernelGGL((attend_mfma_kernel<4, GATHER>), grid, block, 0, st, k_a, k_b, v, qv, sel_idx,
+      hipLaunchKernelGGL((attend_mfma_kernel<4, GATHER, STREAM_V>), grid, block, 0, st, k_a, k_b, v, qv, sel_idx,
                          partial, tickets, o16, S_cap, d, n, rpb, nsplit, Hkv, S_max, rg, pg);
       break;
     case 8:
-      hipLaunchKernelGGL((attend_mfma_kernel<8, GATHER>), grid, block, 0, st, k_a, k_b, v, qv, sel_idx,
+      hipLaunchKernelGGL((attend_mfma_kernel<8, GATHER, STREAM_V>), grid, block, 0, st, k_a, k_b, v, qv, sel_idx,
                          partial, tickets, o16, S_cap, d, n, rpb, nsplit, Hkv, S_max, rg, pg);
       break;
     default:
@@ -174,8 +175,9 @@ static hipError_t launch_pca_mfma_nh(const Shape& s, int nsplit, int rpb, const 
                                      hipStream_t st) {
   const dim3 grid(nsplit, s.B * s.Hkv), block(kAmThreads);
   uint16_t* o16 = static_cast<uint16_t*>(out);
+  const bool stream = streams_rows(s, kLowRankRows);
 #define LOKI_PCA_MFMA(KS)                                                                          \
-  hipLaunchKernelGGL((attend_mfma_kernel<NH, false, KS, true>), grid, block, 0, st, klo, nullptr, v, \
+  hipLaunchKernelGGL((stream ? attend_mfma_kernel<NH, false, true, KS, true> : attend_mfma_kernel<NH, false, false, KS, true>), grid, block, 0, st, klo, nullptr, v, \
                      qhat, nullptr, partial, nullptr, o16, s.S_cap, s.d, s.S, rpb, nsplit, s.Hkv, s.S, s.rg,  \
                      Paging{});                                                                    \
   break
@@ -205,18 +207,20 @@ bool attend_mfma_applies(const Shape& s, int heads_per_block) {
 hipError_t launch_dense_mfma(const Shape& s, int nsplit, const void* q, const void* k_full,
                              const void* v, float* partial, void* out, hipStream_t st) {
   const int rpb = (s.S + nsplit - 1) / nsplit;
+  const bool stream = streams_rows(s, kEveryRow);
   if (dense_balanced(s, nsplit)) {
     const dim3 grid(nsplit, s.B * s.Hkv), block(kAmThreads);
     uint16_t* o16 = static_cast<uint16_t*>(out);
     if (s.G == 8)
-      hipLaunchKernelGGL((attend_mfma_kernel<8, false, 4, false, true>), grid, block, 0, st, k_full, nullptr, v, q, nullptr,
+      hipLaunchKernelGGL((stream ? attend_mfma_kernel<8, false, true, 4, false, true> : attend_mfma_kernel<8, false, false, 4, false, true>), grid, block, 0, st, k_full, nullptr, v, q, nullptr,
                          partial, nullptr, o16, s.S_cap, kD, s.S, rpb, nsplit, s.Hkv, s.S, s.rg, Paging{});
     else
-      hipLaunchKernelGGL((attend_mfma_kernel<4, false, 4, false, true>), grid, block, 0, st, k_full, nullptr, v, q, nullptr,
+      hipLaunchKernelGGL((stream ? attend_mfma_kernel<4, false, true, 4, false, true> : attend_mfma_kernel<4, false, false, 4, false, true>), grid, block, 0, st, k_full, nullptr, v, q, nullptr,
                          partial, nullptr, o16, s.S_cap, kD, s.S, rpb, nsplit, s.Hkv, s.S, s.rg, Paging{});
     return hipGetLastError();
   }
-  return launch_attend_mfma_nh<false>(s.G, s.B * s.Hkv, nsplit, rpb, k_full, nullptr, v, q, nullptr,
+  const auto launch = stream ? launch_attend_mfma_nh<false, true> : launch_attend_mfma_nh<false, false>;
+  return launch(s.G, s.B * s.Hkv, nsplit, rpb, k_full, nullptr, v, q, nullptr,
                                       partial, nullptr, out, s.S_cap, kD, s.S, s.Hkv, s.S, s.rg, Paging{}, st);
 }
 
@@ -225,7 +229,8 @@ hipError_t launch_gather_mfma(const Shape& s, int nsplit, const float* qhat, con
                               int32_t* tickets, void* out, hipStream_t st) {
   const int rpb = (s.k + nsplit - 1) / nsplit;
   if (rpb > kMaxGatherChunk) return hipErrorInvalidValue;
-  return launch_attend_mfma_nh<true>(s.G, s.B * s.Hkv, nsplit, rpb, klo, khi, v, qhat, sel_idx,
+  const auto launch = streams_rows(s, 1) ? launch_attend_mfma_nh<true, true> : launch_attend_mfma_nh<true, false>;
+  return launch(s.G, s.B * s.Hkv, nsplit, rpb, klo, khi, v, qhat, sel_idx,
                                      partial, tickets, out, s.S_cap, s.d, s.k, s.Hkv, s.S, s.rg, s.pg, st);
 }
 

@@ -34,11 +34,11 @@ __host__ __device__ constexpr int gram_tile(int c1, int c2) { return c1 * kGramS
 // needs no LDS, no barrier and, G being symmetric, 36 of 64 tiles.  Column sums: bf16 by a column
 // of ones on the other side, fp32 by adding the fp32 values themselves.  What bounds it is the read
 // of the keys: one wave per SIMD with 512 registers holds the 36 tiles and two steps' loads (bf16
-// with three 2 us more, with four 18).  32 heads x 65536 keys, us: bf16 (512 MiB) 95 (5.6 TB/s),
-// fp32 190; through a tile transposed in LDS, with two barriers a tile and all 64 tiles, 131 (4.1
+// with three 2 us more, with four 18).  32 heads x 65536 keys, us: bf16 (512 MiB) 95 (5.6 TB/s), 82
+// with STREAM (bf16 only: fp32 asks for half a line at a time), fp32 190; through a tile transposed in LDS, with two barriers a tile and all 64 tiles, 131 (4.1
 // TB/s) and 267.
 // NT = bf16 terms per element: 1 for bf16 storage, 2 for fp32 storage (value, remainder).
-template <int NT>
+template <int NT, bool STREAM>
 __global__ __launch_bounds__(kGramThreads, 1) void gram_kernel(const void* __restrict__ keys,
                                                                float* __restrict__ gram_part,
                                                                float* __restrict__ sum_part,
@@ -72,13 +72,13 @@ __global__ __launch_bounds__(kGramThreads, 1) void gram_kernel(const void* __res
 #pragma unroll
       for (int e = 0; e < 8; ++e)
 #pragma unroll
-        for (int t = 0; t < NT; ++t) x[NT * e + t] = load16(p + e * kRowBytes + 16 * t);
+        for (int t = 0; t < NT; ++t) x[NT * e + t] = load16_hint<STREAM>(p + e * kRowBytes + 16 * t);
     } else {
 #pragma unroll
       for (int e = 0; e < 8; ++e)
 #pragma unroll
         for (int t = 0; t < NT; ++t)
-          x[NT * e + t] = t0 + 8 * kgrp + e < rows ? load16(p + e * kRowBytes + 16 * t) : make_uint4(0, 0, 0, 0);
+          x[NT * e + t] = t0 + 8 * kgrp + e < rows ? load16_hint<STREAM>(p + e * kRowBytes + 16 * t) : make_uint4(0, 0, 0, 0);
     }
   };
   auto word = [](const uint4& x, int i) { return i == 0 ? x.x : i == 1 ? x.y : i == 2 ? x.z : x.w; };
@@ -376,11 +376,11 @@ hipError_t launch_pca_stage(int stage, int Hkv, int dtype, const void* keys, lon
   double* mat = cov + (size_t)Hkv * kD * kD;
   if (stage == 0) {
     if (dtype == 0)
-      hipLaunchKernelGGL(gram_kernel<2>, dim3(chunks, Hkv), dim3(kGramThreads), 0, st, keys, gram_part,
+      hipLaunchKernelGGL((gram_kernel<2, false>), dim3(chunks, Hkv), dim3(kGramThreads), 0, st, keys, gram_part,
                          sum_part, N, rpc);
-    else
-      hipLaunchKernelGGL(gram_kernel<1>, dim3(chunks, Hkv), dim3(kGramThreads), 0, st, keys, gram_part,
-                         sum_part, N, rpc);
+    else  // (keys that fit the last-level cache may be there: 11 MB 285.2 / 286.2 us a fit, 88 MB 302.5 / 296.1)
+      hipLaunchKernelGGL((2ll * Hkv * N * kD >= 80000000 ? gram_kernel<1, true> : gram_kernel<1, false>), dim3(chunks, Hkv),
+                         dim3(kGramThreads), 0, st, keys, gram_part, sum_part, N, rpc);
   } else if (stage == 1) {
     hipLaunchKernelGGL(cov_reduce_kernel, dim3(kGramSets, Hkv), dim3(kCovThreads), 0, st, gram_part, sum_part, cov, N,
                        chunks);

@@ -101,6 +101,18 @@ struct BF16 {
 };
 
 __device__ inline uint4 load16(const void* p) { return *reinterpret_cast<const uint4*>(p); }
+// STREAM: with the non-temporal hint, for rows that will not be found in a cache again: 1 GB read by
+// 256 blocks 6.4 -> 7.0 TB/s, pieces of 128 bytes in any order 5.4 -> 5.9.  Only for loads that take
+// whole 128-byte lines: a line asked for in two halves is fetched more often with it.
+template <bool STREAM>
+__device__ inline uint4 load16_hint(const void* p) {
+  if constexpr (STREAM) {
+    typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
+    return __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(p)));
+  } else {
+    return load16(p);
+  }
+}
 
 // ---- cross-lane movement through DPP (no LDS traffic) ----------------------------------
 template <int CTRL>

@@ -123,7 +123,7 @@ struct GqaSteps {
 // CLUSTER: cl.C blocks work on one unit, block c on rows [c L, (c + 1) L) of it (L =
 // gqa_slice_rows); they find the threshold together (cluster_impl.h), each attends over the
 // selected rows of its slice, and the block that finishes last merges the partial results.
-template <int THREADS, int NCH, int G, int KPT, bool PAGED, bool CLUSTER = false>
+template <int THREADS, int NCH, int G, int KPT, bool PAGED, bool STREAM_V, bool CLUSTER = false>
 __global__ __launch_bounds__(THREADS, THREADS == 256 ? 2 : 1) void fused_gqa_kernel(
     const uint16_t* klo, const uint16_t* khi, const uint16_t* v,
     const uint16_t* __restrict__ q, const float* __restrict__ P, uint16_t* __restrict__ out,
@@ -556,9 +556,9 @@ __global__ __launch_bounds__(THREADS, THREADS == 256 ? 2 : 1) void fused_gqa_ker
     st.init();
     // (with a copy for the caller the rows wait for the merged list)
     if constexpr (CLUSTER)
-      am_attend_rows<true, 4, 2>(ad, bq, s_idx, 0, GqaSteps<kWaves>(&s_list, n_def, gidx == nullptr), st, complete);
+      am_attend_rows<true, 4, 2, STREAM_V>(ad, bq, s_idx, 0, GqaSteps<kWaves>(&s_list, n_def, gidx == nullptr), st, complete);
     else
-      am_attend_rows<true, 4, 2>(ad, bq, s_idx, 0, AmRoundRobin<kWaves>(0, k, gidx == nullptr ? n_def : 0), st, complete);
+      am_attend_rows<true, 4, 2, STREAM_V>(ad, bq, s_idx, 0, AmRoundRobin<kWaves>(0, k, gidx == nullptr ? n_def : 0), st, complete);
     LOKI_STAMP(7);
     if constexpr (!CLUSTER) __syncthreads();  // every wave has ranked the candidates: their place turns into the merge
     am_publish<G, kWaves>(st, s_merge);  // (CLUSTER: no wave is done before the list is)

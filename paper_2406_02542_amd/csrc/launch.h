@@ -73,6 +73,12 @@ constexpr int kDenseMaxRagged = 64;
 int dense_splits(const Shape& s, bool ragged);
 bool dense_balanced(const Shape& s, int nsplit);
 
+// Whether the rows that a call's attention reads, and with one query head per KV head the slab rows
+// it scores, are loaded past the caches.  select_mode: 0, 1 as in the call, or:
+constexpr int kEveryRow = -1;      // dense attention
+constexpr int kLowRankRows = -2;   // Algorithm 2: every value, the slab
+bool streams_rows(const Shape& s, int select_mode);
+
 struct Workspace {
   float* qhat;       // [B*Hq, 128]
   float* scores;     // [B*Hsel, S]
@@ -153,6 +159,8 @@ bool fused_preferred(const Shape& s);
 bool fused_pinnable(const Shape& s);
 hipError_t launch_fused(const Shape& s, const void* q, const float* P, void* klo, void* khi,
                         void* v, void* out, int32_t* out_idx, hipStream_t st);
+hipError_t launch_fused_f32(const Shape& s, const void* q, const float* P, void* klo, void* khi, void* v, void* out,
+                            int32_t* out_idx, hipStream_t st);  // (its fp32 part)
 // Single-launch step for grouped query heads sharing one selection per KV head (fused_gqa.hip;
 // bf16 caches, select_mode = one selection per KV group).
 bool fused_gqa_eligible(const Shape& s, int select_mode);

@@ -41,8 +41,9 @@ struct PagedRows {
 // Scores rows [row0, row_end) of one unit's low-rank slab with the block's WAVES waves.
 // qr is this lane's slice of qhat (zero for lanes past the slab row's last chunk); `rows`
 // maps a row to this lane's 16-byte chunk of it.  emit(row, scores[G]) is called once
-// per row by the lane that ends up owning it.
-template <typename T, int LPR, int G, int WAVES, typename Rows, typename Emit>
+// per row by the lane that ends up owning it.  STREAM, here and below: rows are loaded past the
+// caches (streams_rows).
+template <typename T, int LPR, int G, int WAVES, bool STREAM = false, typename Rows, typename Emit>
 __device__ __forceinline__ void score_rows(const Rows& rows, bool cact,
                                            const float (&qr)[G][T::EPC], int row0, int row_end,
                                            Emit emit) {
@@ -63,7 +64,7 @@ __device__ __forceinline__ void score_rows(const Rows& rows, bool cact,
 #pragma unroll
         for (int u = 0; u < UNR; ++u) {
           const int row = tile0 + tt * WAVES * 64 + (it0 + u) * RPI + rsub;
-          raw[tt][u] = (cact && row < row_end) ? load16(rows(row)) : make_uint4(0, 0, 0, 0);
+          raw[tt][u] = (cact && row < row_end) ? load16_hint<STREAM>(rows(row)) : make_uint4(0, 0, 0, 0);
         }
 #pragma unroll
       for (int tt = 0; tt < TPI; ++tt)
@@ -102,7 +103,7 @@ struct ScoreTrip {
   uint4 raw[TPI][LPR];
 };
 
-template <int LPR, int WAVES, typename Rows>
+template <int LPR, int WAVES, bool STREAM = false, typename Rows>
 __device__ __forceinline__ void score_load_trip(const Rows& rows, int tile0, int row_end,
                                                 ScoreTrip<LPR>& t) {
   constexpr int RPI = 64 / LPR;
@@ -112,7 +113,7 @@ __device__ __forceinline__ void score_load_trip(const Rows& rows, int tile0, int
 #pragma unroll
     for (int u = 0; u < LPR; ++u) {
       const int row = min(tile0 + tt * WAVES * 64 + u * RPI + rsub, row_end - 1);
-      t.raw[tt][u] = load16(rows(row));
+      t.raw[tt][u] = load16_hint<STREAM>(rows(row));
     }
 }
 
@@ -153,7 +154,7 @@ __device__ __forceinline__ void score_trip(const ScoreTrip<LPR>& cur, const floa
 // turns (the loop body handles two trips), so two trips' loads stay in flight while a trip is
 // scored and no buffer is ever copied; the loads past the last trip are clamped re-reads of
 // the last row.
-template <typename T, int LPR, int G, int WAVES, typename Rows, typename Emit>
+template <typename T, int LPR, int G, int WAVES, bool STREAM = false, typename Rows, typename Emit>
 __device__ __forceinline__ void score_rows_pipelined(const Rows& rows,
                                                      const float (&qr)[G][T::EPC], int row0,
                                                      int row_end, ScoreTrip<LPR>& t0,
@@ -162,9 +163,9 @@ __device__ __forceinline__ void score_rows_pipelined(const Rows& rows,
   const int wave = threadIdx.x >> 6;
   for (int tile0 = row0 + wave * 64; tile0 < row_end; tile0 += 2 * kStride) {
     score_trip<T, LPR, G, WAVES>(t0, qr, tile0, row_end, emit);
-    score_load_trip<LPR, WAVES>(rows, tile0 + 2 * kStride, row_end, t0);
+    score_load_trip<LPR, WAVES, STREAM>(rows, tile0 + 2 * kStride, row_end, t0);
     score_trip<T, LPR, G, WAVES>(t1, qr, tile0 + kStride, row_end, emit);
-    score_load_trip<LPR, WAVES>(rows, tile0 + 3 * kStride, row_end, t1);
+    score_load_trip<LPR, WAVES, STREAM>(rows, tile0 + 3 * kStride, row_end, t1);
   }
 }
 
