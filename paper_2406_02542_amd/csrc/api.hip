@@ -463,7 +463,10 @@ static int decode_impl(const loki_layout* layout, const void* q, const float* P,
   int32_t* idx = out_idx ? out_idx : w.sel_idx;
   StageTimer tm(st);
   hipError_t e;
-  if (path == LOKI_PATH_CLUSTER && (s.G == 1 || !fused_gqa_cluster_eligible(s, select_mode)))
+  // (pinned, the single-launch paths take page tables of up to 64 pages per sequence; by themselves they
+  // hold the pages of the rows there are, whatever the table's width)
+  const bool wide_table = pg.table != nullptr && pg.pages_per_seq > 64;
+  if (path == LOKI_PATH_CLUSTER && (s.G == 1 || wide_table || !fused_gqa_cluster_eligible(s, select_mode)))
     return LOKI_ERR_UNSUPPORTED;
   if (s.G == 1 && path == LOKI_PATH_FUSED && !fused_pinnable(s)) return LOKI_ERR_UNSUPPORTED;
   if (select_mode == LOKI_SELECT_PER_QUERY_HEAD &&
@@ -487,7 +490,7 @@ static int decode_impl(const loki_layout* layout, const void* q, const float* P,
       tm.end();
       return e == hipSuccess ? LOKI_OK : LOKI_ERR_HIP;
     }
-    if (path == LOKI_PATH_FUSED && !fused_gqa_eligible(s, select_mode)) return LOKI_ERR_UNSUPPORTED;
+    if (path == LOKI_PATH_FUSED && (wide_table || !fused_gqa_eligible(s, select_mode))) return LOKI_ERR_UNSUPPORTED;
     if (path == LOKI_PATH_FUSED || (path == 0 && fused_gqa_preferred(s, select_mode))) {
       tm.begin("fused_decode");
       e = launch_fused_gqa(s, q, P, klo, khi, v, out, out_idx, st);

@@ -24,7 +24,6 @@ static bool fused_two_per_cu(const Shape& s) {
 bool fused_eligible(const Shape& s) {
   // several new tokens per sequence: a block would read rows appended by other blocks of the launch
   if (s.rg.queries > 1) return false;
-  if (s.pg.table != nullptr && s.pg.pages_per_seq > kFusedMaxPages) return false;  // page list in LDS
   return s.S <= kFusedMaxS && s.k <= kFusedMaxK;
 }
 

@@ -23,9 +23,9 @@ bool fused_gqa_eligible(const Shape& s, int select_mode) {
   if (s.dtype != 1 || select_mode != 1) return false;
   if (s.G != 2 && s.G != 4 && s.G != 8) return false;
   if (s.rg.queries > 1) return false;
-  if (s.pg.table != nullptr && s.pg.pages_per_seq > kGqaMaxPages) return false;  // page list in LDS
   const int nch = s.d / 8;
   if (s.d % 8 != 0 || (nch & (nch - 1)) != 0 || nch < 2 || s.d >= kD) return false;
+  static_assert(16384 / 256 <= kGqaMaxPages, "the pages of every row fit the list in LDS");
   return s.S <= 16384 && s.k <= kGqaMaxK;
 }
 

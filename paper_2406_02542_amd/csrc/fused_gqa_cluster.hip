@@ -12,6 +12,7 @@ constexpr int kClusterThreads = 512;
 constexpr int kClusterKpt = 32;
 constexpr int kClusterMaxSlice = kClusterThreads * kClusterKpt;  // rows whose keys fit the block's LDS
 constexpr int kClusterMaxList = 8192;                            // selected rows one block may end up with
+static_assert(kClusterMax * kClusterMaxSlice / 256 <= kClusterMaxPages, "the pages of every row fit the list in LDS");
 
 #ifdef LOKI_PHASE_TIMING
 extern "C" int loki_debug_read_cluster_ts(unsigned long long* host_dst, size_t count) {
@@ -48,9 +49,11 @@ int fused_gqa_cluster_blocks(const Shape& s, int select_mode) {
   return C;
 }
 
+// (A paged cache's page list fits LDS at any length, 2 KB at 131072 rows; with a limit of 64 pages, lists
+// of more went to the split path's six launches: us, split / here, 32 groups of 4, S = 131072, k = 8192
+// 145.6 / 69.1, 8 of 4, S = 20185, k = 2523 54.5 / 28.4, 64 of 4, S = 20433 of unequal lengths 72.8 / 39.4.)
 bool fused_gqa_cluster_eligible(const Shape& s, int select_mode) {
   if (s.rg.queries > 1) return false;
-  if (s.pg.table != nullptr && s.pg.pages_per_seq > kGqaMaxPages) return false;  // page list in LDS
   return fused_gqa_cluster_blocks(s, select_mode) > 0;
 }
 

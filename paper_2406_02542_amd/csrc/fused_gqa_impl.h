@@ -12,7 +12,8 @@
 namespace loki {
 
 constexpr int kGqaMaxK = kMaxGatherChunk;  // the index list lives in LDS
-constexpr int kGqaMaxPages = 64;           // a paged cache: 16384 rows in pages of at least 256
+constexpr int kGqaMaxPages = 64;           // a paged cache: 16384 rows in pages of at least 256; CLUSTER: 131072
+constexpr int kClusterMaxPages = 512;
 // 16-byte slab loads a lane keeps in flight in the scoring stage (measured on the 64/8-head
 // shapes at S = 8192: 64-byte slab rows gain 6 % from 16 against 8, the other widths nothing)
 #ifndef LOKI_GQA_SCORE_DEPTH
@@ -144,7 +145,9 @@ __global__ __launch_bounds__(THREADS, THREADS == 256 ? 2 : 1) void fused_gqa_ker
   const int L_max = CLUSTER ? gqa_slice_rows(S_max, cl.C) : S_max;
   int32_t* s_idx = reinterpret_cast<int32_t*>(dyn_smem + Lds::region_bytes(L_max));  // [min(k_max, L_max)]
   __shared__ __align__(16) float s_qhat[G][kD];
-  __shared__ int32_t s_pages[PAGED ? kGqaMaxPages : 1];
+  constexpr int kPages = CLUSTER ? kClusterMaxPages : kGqaMaxPages;
+  static_assert(kPages <= THREADS, "a page a thread");
+  __shared__ int32_t s_pages[PAGED ? kPages : 1];
   __shared__ ResidentSelectSmem<THREADS> s_sel;
   __shared__ ClusterSmem s_cl;
   __shared__ GqaList s_list;
@@ -194,8 +197,8 @@ __global__ __launch_bounds__(THREADS, THREADS == 256 ? 2 : 1) void fused_gqa_ker
   using Rows = std::conditional_t<PAGED, PagedRows, ContiguousRows>;
   Rows slab;
   if constexpr (PAGED) {
-    // the sequence's page list, clamped into the pool; readable after the first barrier below
-    if (tid < kGqaMaxPages && tid < pg.pages_per_seq)
+    // the pages of the sequence's rows, clamped into the pool; readable after the first barrier below
+    if (tid <= (S_max - 1) >> pg.lg_rows && tid < kPages && tid < pg.pages_per_seq)
       s_pages[tid] = min(max(pg.table[(size_t)(unit / Hkv) * pg.pages_per_seq + tid], 0), pg.n_pages - 1);
     slab = PagedRows{reinterpret_cast<const char*>(klo) + score_mfma_chunk_bytes<NCH>(), (size_t)(d * 2),
                      s_pages, pg.lg_rows, Hkv, h};

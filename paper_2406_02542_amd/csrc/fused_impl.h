@@ -148,8 +148,8 @@ fused_decode_kernel(
   using Rows = std::conditional_t<PAGED, PagedRows, ContiguousRows>;
   Rows slab;
   if constexpr (PAGED) {
-    // the sequence's page list, clamped into the pool; readable after the first barrier below
-    if (tid < kFusedMaxPages && tid < pg.pages_per_seq)
+    // the pages of the sequence's rows, clamped into the pool; readable after the first barrier below
+    if (tid <= (S_max - 1) >> pg.lg_rows && tid < kFusedMaxPages && tid < pg.pages_per_seq)
       s_pages[tid] = min(max(pg.table[(size_t)(unit / Hkv) * pg.pages_per_seq + tid], 0), pg.n_pages - 1);
     slab = PagedRows{reinterpret_cast<const char*>(klo) + (size_t)(cact ? cs : 0) * 16, slab_row_bytes,
                      s_pages, pg.lg_rows, Hkv, h};
