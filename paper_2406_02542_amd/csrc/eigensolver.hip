@@ -272,6 +272,14 @@ __global__ __launch_bounds__(kEigThreads, PER_CU) void tridiag_kernel(EigBufs bu
   if (tid == kEigThreads - 1) tri[kD - 1] = a[kRows - 1][1];
 }
 
+// v_mfma_f64_16x16x4_f64: lane l gives row (column) l % 16 of A (B) at k = l / 16 and holds column
+// l % 16, rows l / 16 + 4 i of the result.
+typedef double f64x4_t __attribute__((ext_vector_type(4)));
+
+// lane N of each aligned group of 16 lanes, to every lane of it
+template <int N>
+__device__ __forceinline__ double row_bcast_f64(double x) { return dpp_mov_f64<0x150 + N>(x); }
+
 // ---- eigenpairs of the tridiagonal matrix ------------------------------------------------------
 // Block (slice, head): eigenvalues 16 slice .. 16 slice + 15 in increasing order, 16 threads each.
 // Multisection: a pass evaluates the Sturm count at 16 points of the bracket, 13 passes of 1/17 take
@@ -285,17 +293,21 @@ __global__ __launch_bounds__(kEigThreads, PER_CU) void tridiag_kernel(EigBufs bu
 __global__ __launch_bounds__(kEigThreads) void eigvec_kernel(EigBufs bufs) {
   constexpr int kN = kEigSliceRows;
   constexpr int kPasses = 13;
-  constexpr int kReflChunk = 32;
+  constexpr int kReflChunk = 16;  // reflectors applied at a time
+  constexpr int kChunks = kD / kReflChunk, kGramPitch = kReflChunk + 1;
   constexpr double kTiny = 1e-30;
   __shared__ __align__(16) double2 s_de[kD];  // (d_i, e_(i-1)^2) of the scaled matrix
   __shared__ double s_e[kD], s_invh[kD], s_lam[kN], s_sq[2][kN];
   __shared__ int s_r[kN];
-  __shared__ double s_gram[kReflChunk / 4][6];  // products of the reflectors of a group of four
-  __shared__ __align__(16) double s_buf[2 * kD * kN];  // the factors L, U; then the reflectors, a chunk at a time
+  // products of a chunk's reflectors with each other, row > column; the parts and the whole of their
+  // products with the vectors
+  __shared__ double s_gram[kChunks][kReflChunk][kGramPitch];
+  __shared__ double s_w[kEigThreads / 64][kReflChunk][kN + 1], s_c[kReflChunk][kN + 1];
+  __shared__ __align__(16) double s_buf[2 * kD * kN];  // the factors L, U
   __shared__ double s_dp[kD][kN], s_z[kD][kN + 1], s_dd[kD][kN + 1];
   double(*s_l)[kN] = reinterpret_cast<double(*)[kN]>(s_buf);
   double(*s_u)[kN] = reinterpret_cast<double(*)[kN]>(s_buf + kD * kN);
-  static_assert(kReflChunk * kD <= 2 * kD * kN, "a chunk of reflectors fits the factors' space");
+  static_assert(kN == 16 && kReflChunk == 16 && kEigThreads == 256, "a matrix instruction's tile, a thread for each of its entries");
   const int tid = threadIdx.x, lane = tid & 63, slice = blockIdx.x, head = blockIdx.y;
   const int n16 = tid >> 4, sub = tid & 15;
   const double* tri = eig_tri(bufs, head);
@@ -385,13 +397,20 @@ __global__ __launch_bounds__(kEigThreads) void eigvec_kernel(EigBufs bufs) {
     double p0 = 0.0, p = 1.0;
     double(*num)[kN] = up ? s_u : s_l;
     double(*den)[kN + 1] = up ? s_dd : s_z;
-#pragma unroll 1
-    for (int i0 = 0; i0 < kD; i0 += 8) {
+    double da[8], ea[8], db[8], eb[8];  // 8 rows in use, 8 on their way
+    auto fetch = [&](double (&d)[8], double (&e2)[8], int i0) {
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         const int i = up ? kD - 1 - (i0 + e) : i0 + e;
-        const double e2 = up ? s_de[min(i + 1, kD - 1)].y : s_de[i].y;  // (the first step's meets p0 = 0)
-        const double pn = fma(s_de[i].x - lam, p, -(e2 * p0));
+        d[e] = s_de[i].x;
+        e2[e] = s_de[up ? min(i + 1, kD - 1) : i].y;  // (the first step's meets p0 = 0)
+      }
+    };
+    auto advance = [&](const double (&d)[8], const double (&e2)[8], int i0) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const int i = up ? kD - 1 - (i0 + e) : i0 + e;
+        const double pn = fma(d[e] - lam, p, -(e2[e] * p0));
         num[i][n] = pn;
         den[i][n] = p;
         p0 = p;
@@ -400,6 +419,34 @@ __global__ __launch_bounds__(kEigThreads) void eigvec_kernel(EigBufs bufs) {
       const int ex = -__builtin_amdgcn_frexp_exp(fmax(fabs(p), fabs(p0)));
       p = __builtin_amdgcn_ldexp(p, ex);
       p0 = __builtin_amdgcn_ldexp(p0, ex);
+    };
+    fetch(da, ea, 0);
+#pragma unroll 1
+    for (int i0 = 0; i0 < kD; i0 += 16) {
+      fetch(db, eb, i0 + 8);
+      advance(da, ea, i0);
+      fetch(da, ea, min(i0 + 16, kD - 8));
+      advance(db, eb, i0 + 8);
+    }
+  } else if (tid >= 64) {
+    // meanwhile the other waves: the products of a chunk's reflectors with each other (k permuted alike
+    // for both operands, which are then the same registers; reflectors 126 and 127 do not exist)
+    const int r16 = lane & 15, kg = lane >> 4;
+    for (int c = (tid >> 6) - 1; c < kChunks; c += kEigThreads / 64 - 1) {
+      const int row = kReflChunk * c + r16;
+      const double* v = eig_refl(bufs, head) + (size_t)min(row, kD - 3) * kD + 2 * kg;
+      double2 x[kD / 8];
+#pragma unroll
+      for (int t = 0; t < kD / 8; ++t) x[t] = *reinterpret_cast<const double2*>(v + 8 * t);
+      f64x4_t g0{0.0, 0.0, 0.0, 0.0}, g1{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int t = 0; t < kD / 8; ++t) {
+        if (row > kD - 3) x[t] = make_double2(0.0, 0.0);
+        g0 = __builtin_amdgcn_mfma_f64_16x16x4f64(x[t].x, x[t].x, g0, 0, 0, 0);
+        g1 = __builtin_amdgcn_mfma_f64_16x16x4f64(x[t].y, x[t].y, g1, 0, 0, 0);
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) s_gram[c][kg + 4 * i][r16] = kg + 4 * i > r16 ? g0[i] + g1[i] : 0.0;
     }
   }
   __syncthreads();
@@ -475,81 +522,103 @@ __global__ __launch_bounds__(kEigThreads) void eigvec_kernel(EigBufs bufs) {
     s_sq[1][n] = sq;
   }
   __syncthreads();
-  // back through the reflectors: z <- (I - u u^T / h) z, last reflector first
-  double z[kD / 16];
+  // Back through the reflectors, z <- (I - u u^T / h) z, last reflector first, 16 at a time: their
+  // products with the 16 vectors on the matrix cores (every wave's 32 entries for themselves, added
+  // up in LDS), corrected one reflector after the other by their products with each other, and the
+  // vectors less the reflectors times the result, on the matrix cores again.  A wave holds entries
+  // 32 wave + 16 t + 4 (lane / 16) + i of vector lane % 16 as the accumulators lie, which is also how
+  // the first product takes them.
   {
-    const double inv = 1.0 / sqrt(s_sq[0][n16] + s_sq[1][n16]);
+    const int wave = tid >> 6, r16 = lane & 15, kg = lane >> 4;
+    const double* refl = eig_refl(bufs, head);
+    f64x4_t z[2];
+    {
+      const double inv = 1.0 / sqrt(s_sq[0][r16] + s_sq[1][r16]);
 #pragma unroll
-    for (int u = 0; u < kD / 16; ++u) z[u] = s_z[sub + 16 * u][n16] * inv;
-  }
-  // Four reflectors at a time: their products with z are taken side by side and corrected by the
-  // reflectors' products with each other (one chain of sums instead of four).
-  const double* refl = eig_refl(bufs, head);
-  constexpr int kGroups = kReflChunk / 4;
-  for (int c0 = kD - kReflChunk; c0 >= 0; c0 -= kReflChunk) {  // (reflectors 126 and 127 do not exist: zeros)
-    __syncthreads();  // the factors, or the chunk before, have been read
-    for (int i = tid; i < kReflChunk * kD; i += kEigThreads)
-      s_buf[i] = c0 + i / kD < kD - 2 ? refl[(size_t)c0 * kD + i] : 0.0;
-    __syncthreads();
-    if (n16 < kGroups) {  // 16 threads: the six products of group n16
-      double g[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+      for (int t = 0; t < 2; ++t)
 #pragma unroll
-      for (int u = 0; u < kD / 16; ++u) {
-        const double* v = s_buf + 4 * n16 * kD + sub + 16 * u;
-        const double v0 = v[0], v1 = v[kD], v2 = v[2 * kD], v3 = v[3 * kD];
-        g[0] = fma(v3, v2, g[0]);
-        g[1] = fma(v3, v1, g[1]);
-        g[2] = fma(v3, v0, g[2]);
-        g[3] = fma(v2, v1, g[3]);
-        g[4] = fma(v2, v0, g[4]);
-        g[5] = fma(v1, v0, g[5]);
+        for (int i = 0; i < 4; ++i) z[t][i] = s_z[32 * wave + 16 * t + 4 * kg + i][r16] * inv;
+    }
+    double2 aw[2][2];   // this wave's entries of reflector r16
+    double au[2][4];    // entry 4 (r16 % 4) + r16 / 4 of its tiles, reflectors kg, kg + 4, ..
+    auto fetch = [&](int c) {
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        const int e0 = 32 * wave + 16 * t;
+        const double* v = refl + (size_t)min(kReflChunk * c + r16, kD - 3) * kD + e0 + 4 * kg;
+        aw[t][0] = *reinterpret_cast<const double2*>(v);
+        aw[t][1] = *reinterpret_cast<const double2*>(v + 2);
+#pragma unroll
+        for (int s4 = 0; s4 < 4; ++s4)
+          au[t][s4] = refl[(size_t)min(kReflChunk * c + 4 * s4 + kg, kD - 3) * kD + e0 + 4 * (r16 & 3) + (r16 >> 2)];
+      }
+    };
+    fetch(kChunks - 1);
+#pragma unroll 1
+    for (int c = kChunks - 1; c >= 0; --c) {
+      f64x4_t w{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        w = __builtin_amdgcn_mfma_f64_16x16x4f64(aw[t][0].x, z[t][0], w, 0, 0, 0);
+        w = __builtin_amdgcn_mfma_f64_16x16x4f64(aw[t][0].y, z[t][1], w, 0, 0, 0);
+        w = __builtin_amdgcn_mfma_f64_16x16x4f64(aw[t][1].x, z[t][2], w, 0, 0, 0);
+        w = __builtin_amdgcn_mfma_f64_16x16x4f64(aw[t][1].y, z[t][3], w, 0, 0, 0);
       }
 #pragma unroll
-      for (int e = 0; e < 6; ++e) g[e] = row_sum_f64(g[e]);
-      if (sub == 0)
+      for (int i = 0; i < 4; ++i) s_w[wave][kg + 4 * i][r16] = w[i];
+      double u[2][4];
 #pragma unroll
-        for (int e = 0; e < 6; ++e) s_gram[n16][e] = g[e];
-    }
-    __syncthreads();
-#pragma unroll 2
-    for (int grp = kGroups - 1; grp >= 0; --grp) {
-      const double* vb = s_buf + 4 * grp * kD + sub;
-      double v[4][kD / 16], c[4];
+      for (int t = 0; t < 2; ++t)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        double dot0 = 0.0, dot1 = 0.0;
+        for (int s4 = 0; s4 < 4; ++s4) u[t][s4] = au[t][s4];
+      fetch(max(c - 1, 0));
+      // thread (n16, sub): reflector sub of the chunk, vector n16 (a reflector that does not exist: inv_h = 0)
+      double g[kReflChunk];
 #pragma unroll
-        for (int u = 0; u < kD / 16; u += 2) {
-          v[r][u] = vb[r * kD + 16 * u];
-          v[r][u + 1] = vb[r * kD + 16 * u + 16];
-          dot0 = fma(v[r][u], z[u], dot0);
-          dot1 = fma(v[r][u + 1], z[u + 1], dot1);
-        }
-        c[r] = row_sum_f64(dot0 + dot1);
+      for (int n = 1; n < kReflChunk; ++n) g[n] = s_gram[c][n][sub];
+      const bool exists = kReflChunk * c + sub < kD - 2;
+      const double ih = -s_invh[kReflChunk * c + sub];
+      __syncthreads();
+      double x = (s_w[0][sub][n16] + s_w[1][sub][n16]) + (s_w[2][sub][n16] + s_w[3][sub][n16]);
+      if (!exists) x = 0.0;
+      x = fma(row_bcast_f64<15>(ih * x), g[15], x);
+      x = fma(row_bcast_f64<14>(ih * x), g[14], x);
+      x = fma(row_bcast_f64<13>(ih * x), g[13], x);
+      x = fma(row_bcast_f64<12>(ih * x), g[12], x);
+      x = fma(row_bcast_f64<11>(ih * x), g[11], x);
+      x = fma(row_bcast_f64<10>(ih * x), g[10], x);
+      x = fma(row_bcast_f64<9>(ih * x), g[9], x);
+      x = fma(row_bcast_f64<8>(ih * x), g[8], x);
+      x = fma(row_bcast_f64<7>(ih * x), g[7], x);
+      x = fma(row_bcast_f64<6>(ih * x), g[6], x);
+      x = fma(row_bcast_f64<5>(ih * x), g[5], x);
+      x = fma(row_bcast_f64<4>(ih * x), g[4], x);
+      x = fma(row_bcast_f64<3>(ih * x), g[3], x);
+      x = fma(row_bcast_f64<2>(ih * x), g[2], x);
+      x = fma(row_bcast_f64<1>(ih * x), g[1], x);
+      s_c[sub][n16] = ih * x;
+      __syncthreads();
+#pragma unroll
+      for (int s4 = 0; s4 < 4; ++s4) {
+        const double cf = s_c[4 * s4 + kg][r16];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) z[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(u[t][s4], cf, z[t], 0, 0, 0);
       }
-      const double* g = s_gram[grp];
-      const double* ih = s_invh + c0 + 4 * grp;
-      c[3] = -ih[3] * c[3];
-      c[2] = -ih[2] * fma(c[3], g[0], c[2]);
-      c[1] = -ih[1] * fma(c[2], g[3], fma(c[3], g[1], c[1]));
-      c[0] = -ih[0] * fma(c[1], g[5], fma(c[2], g[4], fma(c[3], g[2], c[0])));
+    }
+    double* Z = bufs.mat + (size_t)head * kD * kD + (size_t)(slice * kN + r16) * kD + 32 * wave + 4 * kg;
 #pragma unroll
-      for (int u = 0; u < kD / 16; ++u)
-        z[u] = fma(c[0], v[0][u], fma(c[1], v[1][u], fma(c[2], v[2][u], fma(c[3], v[3][u], z[u]))));
+    for (int t = 0; t < 2; ++t) {
+      *reinterpret_cast<double2*>(Z + 16 * t) = make_double2(z[t][0], z[t][1]);
+      *reinterpret_cast<double2*>(Z + 16 * t + 2) = make_double2(z[t][2], z[t][3]);
     }
   }
-  double* Z = bufs.mat + (size_t)head * kD * kD + (size_t)(slice * kN + n16) * kD;
-#pragma unroll
-  for (int u = 0; u < kD / 16; ++u) Z[sub + 16 * u] = z[u];
 }
 
 // ---- products of whole matrices with a 16-row slice ----------------------------------------------
-// v_mfma_f64_16x16x4_f64: lane l gives row (column) l % 16 of A (B) at k = l / 16 and holds column
-// l % 16, rows l / 16 + 4 i of the result.  Four waves, two 16-row tiles of the whole matrix each;
+// Four waves, two 16-row tiles of the whole matrix each;
 // operands come straight from the matrix in L2 (16 bytes a lane, k permuted alike for both: k =
 // 8 t + 2 (l / 16) + {0, 1}), so all loads of a product can be in flight at once.  Through tiles
 // staged in LDS and the vector units, with a barrier per tile, the two kernels took 28 and 33 us.
-typedef double f64x4_t __attribute__((ext_vector_type(4)));
 constexpr int kSlicePitch = kD + 2;     // doubles per row of a slice in LDS
 constexpr int kTilesPerWave = kD / 16 / (kEigThreads / 64);
 
