@@ -122,14 +122,15 @@ __device__ __forceinline__ void attend_trip(AttendAcc<T, NH>& acc, const float (
 // attention over 2 sequences of 990 rows, 32/8 fp32 heads, 20.4 / 18.3, 2 to 7 of 546 to 2310 rows
 // 4 to 13 % more, large ones 0.6 %; but one block per head beyond 8192 rows, 512 heads in groups of
 // 4, S = 12800, k = 400 46.4 / 47.3, S = 13300, k = 831 62.7 / 64.0.
-// STREAM: rows are loaded past the caches (streams_rows).
-template <typename T, int NH, int NGROUPS, bool GATHER, bool REUSE_LO, bool SCORE_BY_ROW = false, bool APART = false, bool STREAM = false>
+// STREAM: rows are loaded past the caches (streams_rows).  ROWS: rows per lane group and trip.
+template <typename T, int NH, int NGROUPS, bool GATHER, bool REUSE_LO, bool SCORE_BY_ROW = false, bool APART = false, bool STREAM = false,
+          int ROWS = kRowsInFlight>
 __device__ __forceinline__ void attend_rows(AttendAcc<T, NH>& acc, const float (&qr)[NH][T::EPC],
                                             const RowAddr& ra, const int32_t* s_idx,
                                             const float* s_a, int gid, int r0, int r1) {
   constexpr int EPC = T::EPC;
   constexpr int LPRV = kD / EPC;
-  constexpr int R = kRowsInFlight;
+  constexpr int R = ROWS;
   static_assert(!REUSE_LO || NH == 1, "score reuse needs one query head per selection");
   for (int t0 = r0; t0 < r1; t0 += NGROUPS * R) {
     bool ok[R];

@@ -292,7 +292,20 @@ fused_decode_kernel(
   const RowAddr ra = make_row_addr<T, REUSE_LO>(klo, khi, v, PAGED ? (size_t)0 : (size_t)unit, S_cap, d, c);
   AttendAcc<T, 1> acc;
   acc.init();
-  attend_rows<T, 1, kFusedWaves * RPW, true, REUSE_LO, kScoreByRow, kKeysInLds, STREAM>(acc, qr, ra, s_idx, s_a, wave * RPW + rg, 0, k);
+  auto attend = [&](auto rows) {
+    attend_rows<T, 1, kFusedWaves * RPW, true, REUSE_LO, kScoreByRow, kKeysInLds, STREAM, decltype(rows)::value>(
+        acc, qr, ra, s_idx, s_a, wave * RPW + rg, 0, k);
+  };
+  // fp32, whose rows take twice the lanes: a trip of 8 rows a lane group is as many rows as a bf16 trip of
+  // 4.  us, 4 / 8: 8 heads, S = 1024, k = 256 11.9 / 11.5, 128, S = 4096, k = 1024 43.6 / 40.8, on pages
+  // S = 8000, k = 2000 79.0 / 75.1; but with two blocks on a CU and short lists 512 heads, k = 175 24.6 /
+  // 25.6, k = 256 26.1 / 27.2, in groups of 4, k = 375 41.7 / 42.4; bf16, 512 heads, S = 4096 60.8 / 63.3.
+  if constexpr (T::kBytes == 4 && !kKeysInLds) {
+    if (gridDim.x <= 256 || (!GROUPED && k_max >= 320)) attend(std::integral_constant<int, 2 * kRowsInFlight>{});
+    else attend(std::integral_constant<int, kRowsInFlight>{});
+  } else {
+    attend(std::integral_constant<int, kRowsInFlight>{});
+  }
   LOKI_STAMP(7);
   attend_publish<T, 1, kFusedWaves>(acc, s_merge);
   if (tid < kD) {
