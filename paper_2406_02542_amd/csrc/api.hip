@@ -98,6 +98,28 @@ bool streams_rows(const Shape& s, int select_mode) {
   return unit_rows * per_row * s.elem_bytes >= 90e6;
 }
 
+// The attention of a group reads the slab again, for the selected rows, a line of 128 bytes for each; a
+// slab that was loaded past the caches is not there then.  So it pays while the lines read again are few
+// beside the slab, and from 80 MB of slab on.  Time through / past the caches by the slab's size and by
+// `again`, the lines' bytes over the slab's (2, 4 and 8 heads, 64 to 512 units, d = 16 and 32, contiguous
+// and paged, 150 shapes):
+//   again   50-60 MB     90 MB        110-134 MB   160 MB       200 MB       260 MB
+//   0.12    0.98-1.00    1.03-1.06    1.05-1.10    1.10-1.11    1.09-1.12    1.06-1.09
+//   0.17                 1.04-1.05    1.05-1.08                 1.07-1.09    1.03
+//   0.25    0.97-1.00    1.03-1.05    1.04-1.08    1.03-1.04    0.99-1.01    0.99
+//   0.4     1.01         1.02         0.97-1.01    0.97-0.98    0.97         0.98-0.99
+//   0.5     1.01-1.02    0.97-0.98    0.96-0.97
+// (lengths that may differ: two thirds of the slab that the longest would make.)  Slab rows of more than 64
+// bytes take two loads of half a line: never (d = 64: 0.87 to 0.94).
+int group_streams(const Shape& s) {
+  if (!streams_rows(s, 1)) return 0;
+  if (s.d > 8 * kStreamSlabChunks) return kStreamValues;
+  const double slab = (double)s.B * s.Hkv * s.S * s.d * s.elem_bytes * (s.rg.seq_lens != nullptr ? 0.65 : 1.0);
+  const double again = 128.0 * s.k / ((double)s.S * s.d * s.elem_bytes);
+  const bool pays = slab >= 80e6 && (again <= 0.18 || (again <= 0.26 && slab <= 180e6));
+  return pays ? kStreamValuesAndSlab : kStreamValues;
+}
+
 int gather_splits(const Shape& s, int select_mode) {
   const int heads = (select_mode == 1) ? s.B * s.Hkv : s.B * s.Hq;
   // about two blocks per CU: a block's set-up and merge cost as much as a few hundred rows, and

@@ -71,11 +71,11 @@ bool fused_gqa_preferred(const Shape& s, int select_mode) {
   return bytes < (limit < 140 ? limit : 140) * s.S;
 }
 
-template <int THREADS, int NCH, int G, int KPT, bool PAGED, bool STREAM_V>
+template <int THREADS, int NCH, int G, int KPT, bool PAGED, int STREAM>
 static hipError_t launch_fused_gqa_k(const Shape& s, const void* q, const float* P, const void* klo,
                                      const void* khi, const void* v, void* out, int32_t* out_idx,
                                      hipStream_t st) {
-  auto kern = fused_gqa_kernel<THREADS, NCH, G, KPT, PAGED, STREAM_V>;
+  auto kern = fused_gqa_kernel<THREADS, NCH, G, KPT, PAGED, STREAM>;
   const size_t lds = GqaLds<THREADS, G>::total_bytes(s.S, s.k);
   static std::atomic<unsigned long long> lds_allowed{0};  // per instantiation: devices already set up
   const hipError_t e = allow_dynamic_lds(
@@ -90,7 +90,7 @@ static hipError_t launch_fused_gqa_k(const Shape& s, const void* q, const float*
   return hipGetLastError();
 }
 
-template <int NCH, int G, bool STREAM_V>
+template <int NCH, int G, int STREAM>
 static hipError_t launch_fused_gqa_g(const Shape& s, const void* q, const float* P, const void* klo,
                                      const void* khi, const void* v, void* out, int32_t* out_idx,
                                      hipStream_t st) {
@@ -100,29 +100,29 @@ static hipError_t launch_fused_gqa_g(const Shape& s, const void* q, const float*
   const bool alone = s.B * s.Hkv <= device_cus();
   if (s.pg.table != nullptr) {  // (a paged cache: two block shapes)
     if (s.S > 256 * 32 || alone)
-      return launch_fused_gqa_k<512, NCH, G, 32, true, STREAM_V>(s, q, P, klo, khi, v, out, out_idx, st);
-    return launch_fused_gqa_k<256, NCH, G, 32, true, STREAM_V>(s, q, P, klo, khi, v, out, out_idx, st);
+      return launch_fused_gqa_k<512, NCH, G, 32, true, STREAM>(s, q, P, klo, khi, v, out, out_idx, st);
+    return launch_fused_gqa_k<256, NCH, G, 32, true, STREAM>(s, q, P, klo, khi, v, out, out_idx, st);
   }
-  if (s.S > 256 * 32 || alone) return launch_fused_gqa_k<512, NCH, G, 32, false, STREAM_V>(s, q, P, klo, khi, v, out, out_idx, st);
-  if (s.S <= 256 * 16) return launch_fused_gqa_k<256, NCH, G, 16, false, STREAM_V>(s, q, P, klo, khi, v, out, out_idx, st);
-  return launch_fused_gqa_k<256, NCH, G, 32, false, STREAM_V>(s, q, P, klo, khi, v, out, out_idx, st);
+  if (s.S > 256 * 32 || alone) return launch_fused_gqa_k<512, NCH, G, 32, false, STREAM>(s, q, P, klo, khi, v, out, out_idx, st);
+  if (s.S <= 256 * 16) return launch_fused_gqa_k<256, NCH, G, 16, false, STREAM>(s, q, P, klo, khi, v, out, out_idx, st);
+  return launch_fused_gqa_k<256, NCH, G, 32, false, STREAM>(s, q, P, klo, khi, v, out, out_idx, st);
 }
 
 template <int NCH>
 static hipError_t launch_fused_gqa_n(const Shape& s, const void* q, const float* P, const void* klo,
                                      const void* khi, const void* v, void* out, int32_t* out_idx,
                                      hipStream_t st) {
-  const bool stream = streams_rows(s, 1);
+  const int stream = group_streams(s);
+  auto pick = [&](auto g) {
+    constexpr int G = decltype(g)::value;
+    if constexpr (NCH <= kStreamSlabChunks)
+      if (stream == kStreamValuesAndSlab) return launch_fused_gqa_g<NCH, G, kStreamValuesAndSlab>;
+    return stream ? launch_fused_gqa_g<NCH, G, kStreamValues> : launch_fused_gqa_g<NCH, G, 0>;
+  };
   switch (s.G) {
-    case 2:
-      return stream ? launch_fused_gqa_g<NCH, 2, true>(s, q, P, klo, khi, v, out, out_idx, st)
-                    : launch_fused_gqa_g<NCH, 2, false>(s, q, P, klo, khi, v, out, out_idx, st);
-    case 4:
-      return stream ? launch_fused_gqa_g<NCH, 4, true>(s, q, P, klo, khi, v, out, out_idx, st)
-                    : launch_fused_gqa_g<NCH, 4, false>(s, q, P, klo, khi, v, out, out_idx, st);
-    case 8:
-      return stream ? launch_fused_gqa_g<NCH, 8, true>(s, q, P, klo, khi, v, out, out_idx, st)
-                    : launch_fused_gqa_g<NCH, 8, false>(s, q, P, klo, khi, v, out, out_idx, st);
+    case 2: return pick(std::integral_constant<int, 2>{})(s, q, P, klo, khi, v, out, out_idx, st);
+    case 4: return pick(std::integral_constant<int, 4>{})(s, q, P, klo, khi, v, out, out_idx, st);
+    case 8: return pick(std::integral_constant<int, 8>{})(s, q, P, klo, khi, v, out, out_idx, st);
     default: return hipErrorInvalidValue;
   }
 }

@@ -118,13 +118,14 @@ struct GqaSteps {
 
 // THREADS = 256: two blocks share a CU (S <= 8192); 512: one block per CU (S <= 16384).
 // NCH = 16-byte chunks per slab row (d = 8 NCH); KPT = keys a thread holds in the select stage.
+// STREAM: see group_streams.
 // PAGED: the three slabs are pools addressed through the sequence's page list (see Paging): the
 // list sits in LDS, every slab load looks its page up, and the selected positions are translated
 // to pool rows before the attention stage.
 // CLUSTER: cl.C blocks work on one unit, block c on rows [c L, (c + 1) L) of it (L =
 // gqa_slice_rows); they find the threshold together (cluster_impl.h), each attends over the
 // selected rows of its slice, and the block that finishes last merges the partial results.
-template <int THREADS, int NCH, int G, int KPT, bool PAGED, bool STREAM_V, bool CLUSTER = false>
+template <int THREADS, int NCH, int G, int KPT, bool PAGED, int STREAM, bool CLUSTER = false>
 __global__ __launch_bounds__(THREADS, THREADS == 256 ? 2 : 1) void fused_gqa_kernel(
     const uint16_t* klo, const uint16_t* khi, const uint16_t* v,
     const uint16_t* __restrict__ q, const float* __restrict__ P, uint16_t* __restrict__ out,
@@ -134,6 +135,7 @@ __global__ __launch_bounds__(THREADS, THREADS == 256 ? 2 : 1) void fused_gqa_ker
   constexpr int PPW = kRotParts / kWaves;  // parts of the rotation a wave owns
   static_assert(PPW * kWaves == kRotParts, "the rotation's 8 parts divide over the waves");
   constexpr int d = 8 * NCH;
+  constexpr bool kStreamV = STREAM >= kStreamValues, kStreamSlab = STREAM >= kStreamValuesAndSlab;
   using Lds = GqaLds<THREADS, G, CLUSTER>;
 
   extern __shared__ __align__(16) unsigned char dyn_smem[];
@@ -237,7 +239,7 @@ __global__ __launch_bounds__(THREADS, THREADS == 256 ? 2 : 1) void fused_gqa_ker
       for (int ii = 0; ii < kRotPartLen; ++ii)
         pv[pp][ii] = *reinterpret_cast<const float2*>(Ph + (size_t)((wave * PPW + pp) * kRotPartLen + ii) * kD);
     __builtin_amdgcn_sched_barrier(0);
-    if constexpr (!PAGED) score_mfma_prefetch<NCH, kWaves, kDepth>(slab, row0, row1, sbufs);
+    if constexpr (!PAGED) score_mfma_prefetch<NCH, kWaves, kDepth, kStreamSlab>(slab, row0, row1, sbufs);
 #pragma unroll
     for (int j = 0; j < kQPerThread; ++j) {
       const int i = tid + j * THREADS;
@@ -245,7 +247,7 @@ __global__ __launch_bounds__(THREADS, THREADS == 256 ? 2 : 1) void fused_gqa_ker
     }
     if (tid < kD) s_q[G * kD + tid] = kn_mine;
     __syncthreads();
-    if constexpr (PAGED) score_mfma_prefetch<NCH, kWaves, kDepth>(slab, row0, row1, sbufs);  // the page list is in LDS now
+    if constexpr (PAGED) score_mfma_prefetch<NCH, kWaves, kDepth, kStreamSlab>(slab, row0, row1, sbufs);  // the page list is in LDS now
 #pragma unroll
     for (int g = 0; g < G + 1; ++g)
       if (g < G || app)  // (uniform)
@@ -289,7 +291,7 @@ __global__ __launch_bounds__(THREADS, THREADS == 256 ? 2 : 1) void fused_gqa_ker
     __syncthreads();  // s_qhat complete; the partial sums are dead, the region turns into the scores
     // the loads put in flight before the rotation may have read row S - 1 before it was written
     constexpr int kPrefRows = 2 * kWaves * ScoreMfmaGeom<NCH>::RPS * ScoreMfmaBufs<NCH, kDepth>::UH;
-    if (app && S - 1 - row0 < kPrefRows) score_mfma_prefetch<NCH, kWaves, kDepth>(slab, row0, row1, sbufs);
+    if (app && S - 1 - row0 < kPrefRows) score_mfma_prefetch<NCH, kWaves, kDepth, kStreamSlab>(slab, row0, row1, sbufs);
   }
   LOKI_STAMP(1);
 
@@ -304,7 +306,7 @@ __global__ __launch_bounds__(THREADS, THREADS == 256 ? 2 : 1) void fused_gqa_ker
     const int kgrp = lane >> 4;
     bf16x8_t bq[ScoreMfmaGeom<NCH>::NB][3];
     score_mfma_operands<NCH>(s_qhat[head_ok ? r16 : 0], head_ok, bq);
-    score_mfma_rows<NCH, kWaves, kDepth, true>(
+    score_mfma_rows<NCH, kWaves, kDepth, true, kStreamSlab>(
         slab, row0, row1, bq, sbufs, [&](int rowbase_a, const f32x4_t& acc_a, int rowbase_b, const f32x4_t& acc_b) {
           // lanes 0-15: the group maximum of tile a's rows, lanes 16-31: of tile b's
           const float m = group_max_pair<G>(acc_a, acc_b);
@@ -559,9 +561,9 @@ __global__ __launch_bounds__(THREADS, THREADS == 256 ? 2 : 1) void fused_gqa_ker
     st.init();
     // (with a copy for the caller the rows wait for the merged list)
     if constexpr (CLUSTER)
-      am_attend_rows<true, 4, 2, STREAM_V>(ad, bq, s_idx, 0, GqaSteps<kWaves>(&s_list, n_def, gidx == nullptr), st, complete);
+      am_attend_rows<true, 4, 2, kStreamV>(ad, bq, s_idx, 0, GqaSteps<kWaves>(&s_list, n_def, gidx == nullptr), st, complete);
     else
-      am_attend_rows<true, 4, 2, STREAM_V>(ad, bq, s_idx, 0, AmRoundRobin<kWaves>(0, k, gidx == nullptr ? n_def : 0), st, complete);
+      am_attend_rows<true, 4, 2, kStreamV>(ad, bq, s_idx, 0, AmRoundRobin<kWaves>(0, k, gidx == nullptr ? n_def : 0), st, complete);
     LOKI_STAMP(7);
     if constexpr (!CLUSTER) __syncthreads();  // every wave has ranked the candidates: their place turns into the merge
     am_publish<G, kWaves>(st, s_merge);  // (CLUSTER: no wave is done before the list is)

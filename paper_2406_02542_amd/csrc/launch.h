@@ -78,6 +78,11 @@ bool dense_balanced(const Shape& s, int nsplit);
 constexpr int kEveryRow = -1;      // dense attention
 constexpr int kLowRankRows = -2;   // Algorithm 2: every value, the slab
 bool streams_rows(const Shape& s, int select_mode);
+// The same for the single launches of groups with one selection: 0, or the values of the selected rows,
+// or these and the slab while it is scored (slab rows of up to kStreamSlabChunks 16-byte chunks, of which
+// a load takes whole lines).
+constexpr int kStreamValues = 1, kStreamValuesAndSlab = 2, kStreamSlabChunks = 4;
+int group_streams(const Shape& s);
 
 struct Workspace {
   float* qhat;       // [B*Hq, 128]

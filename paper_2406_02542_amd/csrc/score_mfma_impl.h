@@ -118,17 +118,28 @@ __device__ __forceinline__ ContiguousRows score_mfma_contiguous(const char* slab
   return ContiguousRows{slab + score_mfma_chunk_bytes<NCH>(), (size_t)(NCH * 16)};
 }
 
+// Rows from one step of a wave to its next and from one wave's first to the next wave's.  The waves take
+// steps in turn; with STREAM (see load16_hint) a wave's steps of a buffer follow each other, 64 or more
+// rows in one piece: non-temporal loads of single steps, 8 KB apart, are slower than plain ones (16 x
+// 32 heads, S = 4096, d = 32, scored this way, 66.2 us in steps, 61.9 in pieces; one selection per
+// group, 128 units, S = 16384 64.7, 57.5, plain 60.5).
+template <int NCH, int WAVES, int UH, bool STREAM>
+struct ScoreMfmaOrder {
+  static constexpr int kStep = ScoreMfmaGeom<NCH>::RPS * (STREAM ? 1 : WAVES);
+  static constexpr int kWave = ScoreMfmaGeom<NCH>::RPS * (STREAM ? UH : 1);
+};
+
 // One buffer's loads for the steps starting at row t0; rows past the end re-read the last row
 // (no branch around a load).
-template <int NCH, int WAVES, int UH, typename Rows>
+template <int NCH, int WAVES, int UH, bool STREAM, typename Rows>
 __device__ __forceinline__ void score_mfma_load(const ScoreMfmaLane<NCH, Rows>& ln, int t0, int row_end,
                                                 uint4 (&raw)[UH][ScoreMfmaGeom<NCH>::NL]) {
-  constexpr int RPS = ScoreMfmaGeom<NCH>::RPS, NL = ScoreMfmaGeom<NCH>::NL;
+  constexpr int NL = ScoreMfmaGeom<NCH>::NL;
 #pragma unroll
   for (int u = 0; u < UH; ++u) {
-    const char* p = ln.rows(min(t0 + u * WAVES * RPS + ln.row_in_step, row_end - 1));
+    const char* p = ln.rows(min(t0 + u * ScoreMfmaOrder<NCH, WAVES, UH, STREAM>::kStep + ln.row_in_step, row_end - 1));
 #pragma unroll
-    for (int j = 0; j < NL; ++j) raw[u][j] = load16(p + (size_t)j * 64);
+    for (int j = 0; j < NL; ++j) raw[u][j] = load16_hint<STREAM>(p + (size_t)j * 64);
   }
 }
 
@@ -137,16 +148,16 @@ __device__ __forceinline__ void score_mfma_load(const ScoreMfmaLane<NCH, Rows>& 
 // order (buffer 0 before buffer 1, here as in the loop): loads return in order, and the wait in
 // front of a buffer's first use can only leave the other buffer's loads in flight if they were
 // issued after it on every path into the loop.
-template <int NCH, int WAVES, int DEPTH, typename Rows>
+template <int NCH, int WAVES, int DEPTH, bool STREAM = false, typename Rows>
 __device__ __forceinline__ void score_mfma_prefetch(const Rows& rows, int row0, int row_end,
                                                     ScoreMfmaBufs<NCH, DEPTH>& bufs) {
   constexpr int UH = ScoreMfmaBufs<NCH, DEPTH>::UH;
   constexpr int kTrip = WAVES * ScoreMfmaGeom<NCH>::RPS * UH;
   const ScoreMfmaLane<NCH, Rows> ln(rows);
-  const int t_first = row0 + (int)(threadIdx.x >> 6) * ScoreMfmaGeom<NCH>::RPS;
-  score_mfma_load<NCH, WAVES, UH>(ln, t_first, row_end, bufs.b0);
+  const int t_first = row0 + (int)(threadIdx.x >> 6) * ScoreMfmaOrder<NCH, WAVES, UH, STREAM>::kWave;
+  score_mfma_load<NCH, WAVES, UH, STREAM>(ln, t_first, row_end, bufs.b0);
   __builtin_amdgcn_sched_barrier(0);
-  score_mfma_load<NCH, WAVES, UH>(ln, t_first + kTrip, row_end, bufs.b1);
+  score_mfma_load<NCH, WAVES, UH, STREAM>(ln, t_first + kTrip, row_end, bufs.b1);
   __builtin_amdgcn_sched_barrier(0);
 }
 
@@ -166,7 +177,7 @@ __device__ __forceinline__ void score_mfma_prefetch(const Rows& rows, int row0, 
 // one is missing).  A maximum over the heads of a group is then taken in registers instead of
 // across lanes, and one exchange between 16-lane rows (group_max_pair) leaves the two tiles'
 // results in different lanes, so that what follows — key, store, count — is done once for both.
-template <int NCH, int WAVES, int DEPTH = 8, bool HEADS_IN_REGS = false, typename Rows, typename Emit>
+template <int NCH, int WAVES, int DEPTH = 8, bool HEADS_IN_REGS = false, bool STREAM = false, typename Rows, typename Emit>
 __device__ __forceinline__ void score_mfma_rows(const Rows& rows, int row0, int row_end,
                                                 const bf16x8_t (&bq)[ScoreMfmaGeom<NCH>::NB][3],
                                                 ScoreMfmaBufs<NCH, DEPTH>& bufs, Emit emit) {
@@ -183,7 +194,7 @@ __device__ __forceinline__ void score_mfma_rows(const Rows& rows, int row0, int 
     int pend_row = 0;
 #pragma unroll
     for (int u = 0; u < UH; ++u) {
-      const int trow = t0 + u * WAVES * RPS;
+      const int trow = t0 + u * ScoreMfmaOrder<NCH, WAVES, UH, STREAM>::kStep;
 #pragma unroll
       for (int rb = 0; rb < RB; ++rb) {
         f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
@@ -219,13 +230,13 @@ __device__ __forceinline__ void score_mfma_rows(const Rows& rows, int row0, int 
       }
     }
   };
-  const int t_first = row0 + wave * RPS;
+  const int t_first = row0 + wave * ScoreMfmaOrder<NCH, WAVES, UH, STREAM>::kWave;
   for (int t0 = t_first; t0 < row_end; t0 += 2 * kTrip) {
     score_trip(bufs.b0, t0);
-    score_mfma_load<NCH, WAVES, UH>(ln, t0 + 2 * kTrip, row_end, bufs.b0);
+    score_mfma_load<NCH, WAVES, UH, STREAM>(ln, t0 + 2 * kTrip, row_end, bufs.b0);
     __builtin_amdgcn_sched_barrier(0);
     score_trip(bufs.b1, t0 + kTrip);
-    score_mfma_load<NCH, WAVES, UH>(ln, t0 + 3 * kTrip, row_end, bufs.b1);
+    score_mfma_load<NCH, WAVES, UH, STREAM>(ln, t0 + 3 * kTrip, row_end, bufs.b1);
     __builtin_amdgcn_sched_barrier(0);
   }
 }

@@ -27,6 +27,12 @@ CASES = {
     "group_paged": decode(34, 16, 8, 2000, 32, 700, mode="group", append=True, ragged=True, paged=True),
     "cluster": decode(4, 64, 8, 12000, 64, 3000, mode="group", append=True),
     "cluster_paged": decode(6, 32, 8, 11000, 16, 2750, mode="group", append=True, paged=True),
+    # the same with the slab past the caches while it is scored (few rows kept beside 80 MB of slab and more)
+    "group_alone_slab": decode(24, 32, 8, 9001, 32, 600, mode="group", append=True),
+    "group_two_per_cu_slab": decode(64, 64, 8, 2801, 32, 170, mode="group", append=True),
+    "group_paged_slab": decode(64, 16, 8, 4000, 32, 250, mode="group", append=True, ragged=True, paged=True),
+    "cluster_slab": decode(8, 32, 8, 22001, 32, 1300, mode="group", append=True),
+    "cluster_paged_slab": decode(4, 32, 8, 90001, 16, 2800, mode="group", append=True, paged=True),
     # selection and attention of the split path: one launch on the vector units and the matrix cores, two launches
     "tokens": decode(3, 32, 32, 5001, 32, 1250, append=True, tokens=2),
     "tokens_group": decode(8, 32, 8, 5001, 32, 1250, mode="group", append=True, tokens=2),
