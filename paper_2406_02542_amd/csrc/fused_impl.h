@@ -292,19 +292,23 @@ fused_decode_kernel(
   const RowAddr ra = make_row_addr<T, REUSE_LO>(klo, khi, v, PAGED ? (size_t)0 : (size_t)unit, S_cap, d, c);
   AttendAcc<T, 1> acc;
   acc.init();
-  auto attend = [&](auto rows) {
+  auto attend = [&](auto rows, int r0, int r1) {
     attend_rows<T, 1, kFusedWaves * RPW, true, REUSE_LO, kScoreByRow, kKeysInLds, STREAM, decltype(rows)::value>(
-        acc, qr, ra, s_idx, s_a, wave * RPW + rg, 0, k);
+        acc, qr, ra, s_idx + r0, kScoreByRow ? s_a : s_a + r0, wave * RPW + rg, r0, r1);
   };
   // fp32, whose rows take twice the lanes: a trip of 8 rows a lane group is as many rows as a bf16 trip of
   // 4.  us, 4 / 8: 8 heads, S = 1024, k = 256 11.9 / 11.5, 128, S = 4096, k = 1024 43.6 / 40.8, on pages
   // S = 8000, k = 2000 79.0 / 75.1; but with two blocks on a CU and short lists 512 heads, k = 175 24.6 /
   // 25.6, k = 256 26.1 / 27.2, in groups of 4, k = 375 41.7 / 42.4; bf16, 512 heads, S = 4096 60.8 / 63.3.
+  // What a trip of 4 can hold at the list's end is left to one (us, all in trips of 8 / so: 16
+  // heads, S = 700, k = 42 10.1 / 9.5, k = 129 11.4 / 11.0; 64, S = 1500, k = 129 13.3 / 12.9).
   if constexpr (T::kBytes == 4 && !kKeysInLds) {
-    if (gridDim.x <= 256 || (!GROUPED && k_max >= 320)) attend(std::integral_constant<int, 2 * kRowsInFlight>{});
-    else attend(std::integral_constant<int, kRowsInFlight>{});
+    constexpr int kTrip = kFusedWaves * RPW * kRowsInFlight;  // rows of a trip of 4
+    const int long_rows = gridDim.x <= 256 || (!GROUPED && k_max >= 320) ? (k + kTrip - 1) / (2 * kTrip) * (2 * kTrip) : 0;
+    attend(std::integral_constant<int, 2 * kRowsInFlight>{}, 0, min(long_rows, k));
+    attend(std::integral_constant<int, kRowsInFlight>{}, long_rows, k);
   } else {
-    attend(std::integral_constant<int, kRowsInFlight>{});
+    attend(std::integral_constant<int, kRowsInFlight>{}, 0, k);
   }
   LOKI_STAMP(7);
   attend_publish<T, 1, kFusedWaves>(acc, s_merge);
