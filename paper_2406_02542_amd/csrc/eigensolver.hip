@@ -22,6 +22,7 @@
 // behind it is spread over 8 blocks per head.
 #include "eigensolver.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace loki {
@@ -35,7 +36,7 @@ constexpr int kJacMaxSweeps = 30;
 constexpr int kJacRounds = kD - 1;
 constexpr int kJacSliceCols = 32;               // columns of V an accumulating block owns
 constexpr int kJacSlices = kD / kJacSliceCols;
-constexpr int kJacMaxPerLaunch = 8;             // sweeps per launch at most
+constexpr int kJacMaxPolls = 1 << 22;           // of about a microsecond
 constexpr size_t kMatBytes = (size_t)kD * kD * sizeof(double);
 constexpr size_t kHalfBytes = kMatBytes / 2;
 constexpr size_t kLogBytes = (size_t)kJacRounds * (kD / 2) * sizeof(double);  // one sweep's tangents
@@ -49,12 +50,13 @@ struct EigBufs {
   double* cov;          // [heads][128][128]; dead after project_kernel: the first two sweep logs of a head
   double* mat;          // [heads][128][128]  Z, the vectors before orthonormalisation; then B
   char* vec_lo;         // [heads] 64 KiB: d, e of the tridiagonal matrix; then rows 0..63 of V
-  char* refl;           // [heads][kEigReflBytes]: the reflectors; then rows 64..127 of V and n_logged
+  char* refl;           // [heads][kEigReflBytes]: the reflectors; then rows 64..127 of V and the progress words
   char* more_logs;      // [heads][n_logs - 2] 64 KiB each
-  int* state;           // [heads] kStateMarked, kStateSolved
+  int* state;           // [heads] kStateMarked, and kStateSolvedIn (1 + the Jacobi launch that solved the head)
   int n_logs;           // sweep logs a head has room for (2 or more)
+  int defer;            // of a launch's sweeps, how many are replayed in the next (0 or 1)
 };
-constexpr int kStateMarked = 1, kStateSolved = 2;
+constexpr int kStateMarked = 1, kStateSolvedIn = 2;
 
 __device__ __forceinline__ double* eig_tri(const EigBufs& b, int head) {  // d[128], e[128], tau[128]
   return reinterpret_cast<double*>(b.vec_lo + (size_t)head * kHalfBytes);
@@ -66,9 +68,12 @@ __device__ __forceinline__ double* eig_vec_row(const EigBufs& b, int head, int r
   char* base = row < kD / 2 ? b.vec_lo + (size_t)head * kHalfBytes : b.refl + (size_t)head * kEigReflBytes;
   return reinterpret_cast<double*>(base) + (size_t)(row & (kD / 2 - 1)) * kD;
 }
-__device__ __forceinline__ int* eig_n_logged(const EigBufs& b, int head) {  // [2], behind the rows of V
+// [2], behind the rows of V: sweeps logged so far + kJacLaunchEnded for each launch whose sweeps have
+// ended, and the blocks that have come to the head's launches
+__device__ __forceinline__ int* eig_progress(const EigBufs& b, int head) {
   return reinterpret_cast<int*>(b.refl + (size_t)head * kEigReflBytes + kHalfBytes);
 }
+constexpr int kJacLaunchEnded = 1 << 16;
 __device__ __forceinline__ double* eig_mass(const EigBufs& b, int head) {  // [slices][2]: off-diagonal, diagonal squares
   return reinterpret_cast<double*>(b.refl + (size_t)head * kEigReflBytes + kHalfBytes) + 2;
 }
@@ -691,7 +696,7 @@ __global__ __launch_bounds__(kEigThreads) void project_kernel(EigBufs bufs) {
   const int slice = blockIdx.x, head = blockIdx.y, r0 = slice * kEigSliceRows;
   const double* C = bufs.cov + (size_t)head * kD * kD;
   double* B = bufs.mat + (size_t)head * kD * kD;
-  if (slice == 0 && tid < 2) eig_n_logged(bufs, head)[tid] = 0;
+  if (slice == 0 && tid < 2) eig_progress(bufs, head)[tid] = 0;
   if (bufs.state[head] & kStateMarked) {  // (uniform; set by the launch before)
     for (int e = tid; e < kEigSliceRows * kD; e += kEigThreads) {
       const int r = r0 + e / kD, i = e % kD;
@@ -751,36 +756,22 @@ __device__ __forceinline__ void jacobi_rotation(double t, double& cs, double& sn
   sn = t * cs;
 }
 
-// One launch: block (0, head) runs up to `per_launch` sweeps on B, resident in LDS (129 KiB), and
-// logs every rotation's tangent; blocks (1.., head) replay the log of the launch before on
-// V, whose columns never mix, 32 columns each in LDS.  So the accumulation of one launch runs beside
-// the sweeps of the next, and the host, which cannot know how many sweeps a head will need, enqueues
-// kJacMaxSweeps / per_launch launches whose blocks leave at once when the head is solved.  A sweep
-// is 127 rounds of 64 disjoint rotations; rows and columns of a round are rotated in one pass over
-// 2 x 2 blocks of the upper triangle.  The two log sets take turns.
-__device__ void jacobi_sweeps(const EigBufs& bufs, int head, int launch, int per_launch, double* A) {
+// One launch takes a head through as many sweeps as it has logs.  Of its five blocks the first to come
+// runs the sweeps on B, resident in LDS (129 KiB), and logs every rotation's tangent; the others replay the
+// logs on V, whose columns never mix, 32 columns each in LDS, a sweep as soon as it is logged.  So they
+// wait for a block that runs already and itself waits for nobody, however many of the launch's blocks the
+// device holds.  The host, which cannot know how many sweeps a head will need, enqueues kJacMaxSweeps / n_logs
+// launches whose blocks leave at once when the head is solved; with the sweeps of one launch replayed in the
+// next, which takes two sets of logs, it was over twice as many, 2 to 4 us each: fit of 32 x 65536 keys
+// 321 -> 315 us, 8 x 7000 (9 launches -> 4) 253 -> 242.  A sweep is 127 rounds of 64 disjoint rotations; rows and
+// columns of a round are rotated in one pass over 2 x 2 blocks of the upper triangle.
+__device__ void jacobi_sweeps(const EigBufs& bufs, int head, int launch, double* A) {
   __shared__ double s_c[kD / 2], s_s[kD / 2];
   __shared__ int s_p[kD / 2], s_q[kD / 2];
   __shared__ double s_red[kJacThreads / 64];
-  const int tid = threadIdx.x;
-  int* n_logged = eig_n_logged(bufs, head) + (launch & 1);
-  const int state = bufs.state[head];
-  bool solved = (state & kStateSolved) != 0;  // (uniform; set by an earlier launch)
-  if (launch == 0 && !(state & kStateMarked)) {
-    double off = 0.0, dg = 0.0;
-    for (int s = 0; s < kEigSlices; ++s) {
-      off += eig_mass(bufs, head)[2 * s];
-      dg += eig_mass(bufs, head)[2 * s + 1];
-    }
-    solved = off <= kOffTolerance * dg || dg == 0.0;
-  }
-  if (solved) {
-    if (tid == 0) {
-      *n_logged = 0;
-      bufs.state[head] = state | kStateSolved;
-    }
-    return;
-  }
+  const int tid = threadIdx.x, per_launch = bufs.n_logs - bufs.defer;
+  int* progress = eig_progress(bufs, head);
+  bool solved = false;
   double* Ag = bufs.mat + (size_t)head * kD * kD;
   for (int e = tid; e < kD * kD; e += kJacThreads) A[(e / kD) * kJacPitch + e % kD] = Ag[e];
   __syncthreads();
@@ -813,7 +804,7 @@ __device__ void jacobi_sweeps(const EigBufs& bufs, int head, int launch, int per
     dg = block_sum(dg);
     solved = off <= kOffTolerance * dg || dg == 0.0;  // uniform: every thread holds the same sums
     if (solved) break;
-    double* log = eig_log(bufs, head, (launch & 1) * per_launch + sweep);
+    double* log = eig_log(bufs, head, (launch * per_launch + sweep) % bufs.n_logs);
     for (int round = 0; round < kJacRounds; ++round) {
       if (tid < kD / 2) {
         int p, q;
@@ -856,58 +847,99 @@ __device__ void jacobi_sweeps(const EigBufs& bufs, int head, int launch, int per
       }
       __syncthreads();
     }
+    if (tid == 0)  // (behind a barrier: the block's stores of the log have left its waves)
+      __hip_atomic_fetch_add(progress, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  if (tid == 0) {
+    if (solved) bufs.state[head] |= kStateSolvedIn * (launch + 1);
+    __hip_atomic_fetch_add(progress, kJacLaunchEnded, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
   }
   if (sweep > 0)
     for (int e = tid; e < kD * kD; e += kJacThreads) Ag[e] = A[(e / kD) * kJacPitch + e % kD];
-  if (tid == 0) {
-    *n_logged = sweep;
-    if (solved) bufs.state[head] |= kStateSolved;
-  }
 }
 
-__device__ void jacobi_accumulate(const EigBufs& bufs, int head, int slice, int set, int per_launch, double* s_v) {
+// A wave owns two columns and a lane one pair of a round, so rounds need no barrier.
+__device__ void jacobi_accumulate(const EigBufs& bufs, int head, int slice, int launch, double* s_v) {
   constexpr int kPitch = kJacSliceCols + 1;
-  const int tid = threadIdx.x;
-  const int n_sweeps = eig_n_logged(bufs, head)[set];
-  if (n_sweeps == 0) return;  // (uniform)
-  const int i0 = slice * kJacSliceCols;
+  __shared__ int s_seen;
+  const int tid = threadIdx.x, lane = tid & 63, i0 = slice * kJacSliceCols;
+  // every launch before went to its last log
+  const int per_launch = bufs.n_logs - bufs.defer, end = (launch + 1) * per_launch;
+  const int first = launch * per_launch - (launch > 0 ? bufs.defer : 0);
+  const int last = end < kJacMaxSweeps ? end - bufs.defer : end;
   for (int e = tid; e < kD * kJacSliceCols; e += kJacThreads)
     s_v[(e / kJacSliceCols) * kPitch + e % kJacSliceCols] = eig_vec_row(bufs, head, e / kJacSliceCols)[i0 + e % kJacSliceCols];
-  __syncthreads();
-  // thread: pair slot tid / 16, columns 2 (tid % 16), + 1 of the slice
-  const int slot = tid >> 4, c0 = 2 * (tid & 15);
-  for (int sweep = 0; sweep < n_sweeps; ++sweep) {
-    const double* log = eig_log(bufs, head, set * per_launch + sweep) + slot;
-    double t = log[0];
+  double* column = s_v + 2 * (tid >> 6);
+  for (int sweep = first;; ++sweep) {
+    __syncthreads();
+    if (tid == 0) {
+      int seen = 0;
+      for (int polls = 0; polls < kJacMaxPolls; ++polls) {
+        seen = __hip_atomic_load(eig_progress(bufs, head), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (seen % kJacLaunchEnded > sweep || seen / kJacLaunchEnded > launch || sweep >= last) break;
+        __builtin_amdgcn_s_sleep(8);
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+      s_seen = seen;
+    }
+    __syncthreads();
+    const bool logged = s_seen % kJacLaunchEnded > sweep, ended = s_seen / kJacLaunchEnded > launch;
+    // (a launch that ended before its last sweep solved the head: nothing is left to the next)
+    if (!logged && !ended && sweep < last) {
+      // the wait was given up: no result rather than a wrong one (no sweep takes a thousandth of that time)
+      for (int e = tid; e < kD * kJacSliceCols; e += kJacThreads)
+        eig_vec_row(bufs, head, e / kJacSliceCols)[i0 + e % kJacSliceCols] = __builtin_nan("");
+      return;
+    }
+    if (!logged || sweep >= last) break;
+    const double* log = eig_log(bufs, head, sweep % bufs.n_logs) + lane;
+    double t = log[0], t1 = log[kD / 2];
     for (int round = 0; round < kJacRounds; ++round) {
-      const double next = log[(size_t)min(round + 1, kJacRounds - 1) * (kD / 2)];
+      const double t2 = log[(size_t)min(round + 2, kJacRounds - 1) * (kD / 2)];
       int p, q;
-      jacobi_pair(round, slot, p, q);
+      jacobi_pair(round, lane, p, q);
       double cs, sn;
       jacobi_rotation(t, cs, sn);
-#pragma unroll
-      for (int c = c0; c < c0 + 2; ++c) {
-        const double vx = s_v[p * kPitch + c], vy = s_v[q * kPitch + c];
-        s_v[p * kPitch + c] = cs * vx - sn * vy;
-        s_v[q * kPitch + c] = sn * vx + cs * vy;
-      }
-      t = next;
-      __syncthreads();
+      double* vp = column + p * kPitch;
+      double* vq = column + q * kPitch;
+      const double x0 = vp[0], x1 = vp[1], y0 = vq[0], y1 = vq[1];
+      vp[0] = cs * x0 - sn * y0;
+      vp[1] = cs * x1 - sn * y1;
+      vq[0] = sn * x0 + cs * y0;
+      vq[1] = sn * x1 + cs * y1;
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // the lanes' pairs of the next round
+      t = t1;
+      t1 = t2;
     }
   }
   for (int e = tid; e < kD * kJacSliceCols; e += kJacThreads)
     eig_vec_row(bufs, head, e / kJacSliceCols)[i0 + e % kJacSliceCols] = s_v[(e / kJacSliceCols) * kPitch + e % kJacSliceCols];
 }
 
-__global__ __launch_bounds__(kJacThreads) void jacobi_kernel(EigBufs bufs, int launch, int n_launches, int per_launch) {
+__global__ __launch_bounds__(kJacThreads) void jacobi_kernel(EigBufs bufs, int launch) {
   extern __shared__ __align__(16) unsigned char jac_smem[];
+  __shared__ int s_turn;
   double* mem = reinterpret_cast<double*>(jac_smem);
   const int head = blockIdx.x;
-  if (blockIdx.y == 0) {
-    if (launch < n_launches) jacobi_sweeps(bufs, head, launch, per_launch, mem);
-  } else if (launch > 0) {
-    jacobi_accumulate(bufs, head, blockIdx.y - 1, (launch - 1) & 1, per_launch, mem);
+  // Solved before this launch?  (uniform, and the same for all blocks of the head: what the sweeping block
+  // writes meanwhile names this launch)
+  const int state = bufs.state[head], solved_in = state / kStateSolvedIn;
+  if (solved_in != 0 && solved_in <= launch) return;
+  if (launch == 0 && !(state & kStateMarked)) {
+    double off = 0.0, dg = 0.0;
+    for (int s = 0; s < kEigSlices; ++s) {
+      off += eig_mass(bufs, head)[2 * s];
+      dg += eig_mass(bufs, head)[2 * s + 1];
+    }
+    if (off <= kOffTolerance * dg || dg == 0.0) {
+      if (blockIdx.y == 0 && threadIdx.x == 0) bufs.state[head] = state | kStateSolvedIn;
+      return;
+    }
   }
+  if (threadIdx.x == 0) s_turn = atomicAdd(eig_progress(bufs, head) + 1, 1) - launch * (1 + kJacSlices);
+  __syncthreads();
+  if (s_turn == 0) jacobi_sweeps(bufs, head, launch, mem);
+  else jacobi_accumulate(bufs, head, s_turn - 1, launch, mem);
 }
 
 // ---- results ---------------------------------------------------------------------------------------
@@ -973,7 +1005,7 @@ hipError_t launch_eigensolver(int Hkv, const EigRegions& r, float* P, float* eig
   b.refl = r.refl;
   b.more_logs = r.spare + (size_t)Hkv * kHalfBytes;
   b.state = r.state;
-  b.n_logs = 2 + (r.spare_halves - 1);
+  b.n_logs = std::min(2 + (r.spare_halves - 1), kJacMaxSweeps);
   static std::atomic<unsigned long long> lds_allowed{0};  // devices already set up
   const size_t lds = (size_t)kD * kJacPitch * sizeof(double);
   const hipError_t ea = allow_dynamic_lds(reinterpret_cast<const void*>(jacobi_kernel), (int)lds, lds_allowed);
@@ -986,11 +1018,13 @@ hipError_t launch_eigensolver(int Hkv, const EigRegions& r, float* P, float* eig
   hipLaunchKernelGGL(eigvec_kernel, slices, dim3(kEigThreads), 0, st, b);
   hipLaunchKernelGGL(orthonormalise_kernel, slices, dim3(kEigThreads), 0, st, b);
   hipLaunchKernelGGL(project_kernel, slices, dim3(kEigThreads), 0, st, b);
-  // sweeps per launch: what two log sets leave room for
-  const int per_launch = b.n_logs / 2 < kJacMaxPerLaunch ? b.n_logs / 2 : kJacMaxPerLaunch;
-  const int n_launches = (kJacMaxSweeps + per_launch - 1) / per_launch;
-  for (int l = 0; l <= n_launches; ++l)
-    hipLaunchKernelGGL(jacobi_kernel, dim3(Hkv, 1 + kJacSlices), dim3(kJacThreads), lds, st, b, l, n_launches, per_launch);
+  // The replay of a launch's last sweep is all that runs when it has been logged.  With few logs, so few
+  // rows that the keys may well be rank-deficient, it is left to the next launch, beside whose sweeps it runs
+  // (us, left / not, and with a barrier in every round of the replay: 32 heads of 100 keys 3596 / 4118, 130 of 3000
+  // with dead columns 4541 / 5034).
+  b.defer = b.n_logs <= 4 ? 1 : 0;
+  for (int l = 0; l * (b.n_logs - b.defer) < kJacMaxSweeps; ++l)
+    hipLaunchKernelGGL(jacobi_kernel, dim3(Hkv, 1 + kJacSlices), dim3(kJacThreads), lds, st, b, l);
   hipLaunchKernelGGL(finish_kernel, slices, dim3(kEigThreads), 0, st, b, P, eigenvalues);
   return hipGetLastError();
 }
