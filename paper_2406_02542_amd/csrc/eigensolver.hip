@@ -53,6 +53,7 @@ struct EigBufs {
   char* refl;           // [heads][kEigReflBytes]: the reflectors; then rows 64..127 of V and the progress words
   char* more_logs;      // [heads][n_logs - 2] 64 KiB each
   int* state;           // [heads] kStateMarked, and kStateSolvedIn (1 + the Jacobi launch that solved the head)
+  int n_heads;
   int n_logs;           // sweep logs a head has room for (2 or more)
   int defer;            // of a launch's sweeps, how many are replayed in the next (0 or 1)
 };
@@ -313,7 +314,8 @@ __global__ __launch_bounds__(kEigThreads) void eigvec_kernel(EigBufs bufs) {
   double(*s_l)[kN] = reinterpret_cast<double(*)[kN]>(s_buf);
   double(*s_u)[kN] = reinterpret_cast<double(*)[kN]>(s_buf + kD * kN);
   static_assert(kN == 16 && kReflChunk == 16 && kEigThreads == 256, "a matrix instruction's tile, a thread for each of its entries");
-  const int tid = threadIdx.x, lane = tid & 63, slice = blockIdx.x, head = blockIdx.y;
+  const int tid = threadIdx.x, lane = tid & 63, slice = blockIdx.y, head = blockIdx.x;
+  if (head >= bufs.n_heads) return;
   const int n16 = tid >> 4, sub = tid & 15;
   const double* tri = eig_tri(bufs, head);
   // the Gershgorin interval (every wave for itself)
@@ -655,7 +657,8 @@ __device__ __forceinline__ void slice_product(RowX x, const double* y, f64x4_t (
 __global__ __launch_bounds__(kEigThreads) void orthonormalise_kernel(EigBufs bufs) {
   __shared__ __align__(16) double s_m[kEigSliceRows * kSlicePitch];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r16 = lane & 15, kg = lane >> 4;
-  const int slice = blockIdx.x, head = blockIdx.y, r0 = slice * kEigSliceRows;
+  const int slice = blockIdx.y, head = blockIdx.x, r0 = slice * kEigSliceRows;
+  if (head >= bufs.n_heads) return;
   const double* Z = bufs.mat + (size_t)head * kD * kD;
   f64x4_t acc[kTilesPerWave];
   slice_product([&](int k) { return Z + (size_t)k * kD; }, Z + (size_t)(r0 + r16) * kD, acc);
@@ -693,7 +696,8 @@ __global__ __launch_bounds__(kEigThreads) void project_kernel(EigBufs bufs) {
   __shared__ __align__(16) double s_t[kEigSliceRows * kSlicePitch];
   __shared__ double s_mass[kEigThreads / 64][2];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r16 = lane & 15, kg = lane >> 4;
-  const int slice = blockIdx.x, head = blockIdx.y, r0 = slice * kEigSliceRows;
+  const int slice = blockIdx.y, head = blockIdx.x, r0 = slice * kEigSliceRows;
+  if (head >= bufs.n_heads) return;
   const double* C = bufs.cov + (size_t)head * kD * kD;
   double* B = bufs.mat + (size_t)head * kD * kD;
   if (slice == 0 && tid < 2) eig_progress(bufs, head)[tid] = 0;
@@ -950,7 +954,8 @@ __global__ __launch_bounds__(kEigThreads) void finish_kernel(EigBufs bufs, float
   __shared__ double s_diag[kD];
   __shared__ int s_comp[kEigSliceRows];
   __shared__ float s_out[kD][kEigSliceRows + 1];
-  const int tid = threadIdx.x, slice = blockIdx.x, head = blockIdx.y;
+  const int tid = threadIdx.x, slice = blockIdx.y, head = blockIdx.x;
+  if (head >= bufs.n_heads) return;
   const int n16 = tid >> 4, sub = tid & 15;
   if (tid < kD) s_diag[tid] = bufs.mat[(size_t)head * kD * kD + (size_t)tid * kD + tid];
   if (tid < kEigSliceRows) s_comp[tid] = slice * kEigSliceRows + tid;  // (stands only where values are not numbers)
@@ -1005,12 +1010,16 @@ hipError_t launch_eigensolver(int Hkv, const EigRegions& r, float* P, float* eig
   b.refl = r.refl;
   b.more_logs = r.spare + (size_t)Hkv * kHalfBytes;
   b.state = r.state;
+  b.n_heads = Hkv;
   b.n_logs = std::min(2 + (r.spare_halves - 1), kJacMaxSweeps);
   static std::atomic<unsigned long long> lds_allowed{0};  // devices already set up
   const size_t lds = (size_t)kD * kJacPitch * sizeof(double);
   const hipError_t ea = allow_dynamic_lds(reinterpret_cast<const void*>(jacobi_kernel), (int)lds, lds_allowed);
   if (ea != hipSuccess) return ea;
-  const dim3 slices(kEigSlices, Hkv);
+  // Blocks go to the 8 dies in turn, so with heads counted first, up to a multiple of 8, the slices of a head
+  // share a die and find the head's matrices in its L2.  us per fit, slices first / so: 32 x 65536
+  // keys 315 / 308, 8 x 7000 242 / 237.
+  const dim3 slices((Hkv + 7) / 8 * 8, kEigSlices);
   if (Hkv > device_cus())
     hipLaunchKernelGGL(tridiag_kernel<2>, dim3(Hkv), dim3(kEigThreads), 0, st, b);
   else
