@@ -43,26 +43,38 @@ __host__ __device__ inline size_t fused_region_bytes(int S) {
   return scores > rot ? scores : rot;
 }
 
-// Which (sequence, head) unit a block works on.  Uniform batches: unit = block.  Ragged batches
-// (up to 64 sequences): the sequences are ranked by length and handed out so that the two
-// blocks that share a CU (block i and block i + half the grid, when the whole grid is resident)
-// get a long and a short sequence: the first half of the grid takes the longest sequences in
-// descending order, the second half the rest in ascending order.  Every wave computes the same
-// answer from the length array (lane l ranks sequence l), so no barrier is needed.
-__device__ __forceinline__ int fused_unit_of_block(const Ragged& rag, int B, int Hkv, int block) {
-  if (rag.seq_lens == nullptr || B > 64 || B < 2) return block;
-  const int lane = threadIdx.x & 63;
-  const int mine = lane < B ? rag.seq_lens[lane] : 0;
-  int rank = 0;
-  for (int j = 0; j < B; ++j) {
-    const int other = rag.seq_lens[j];
-    rank += (other > mine || (other == mine && j < lane)) ? 1 : 0;
+// Which (sequence, head) unit a block works on, with the sequence's rows and the rows it keeps.  Uniform
+// batches: unit = block.  Ragged batches (up to 64 sequences): the sequences are ranked by length and
+// handed out so that the two blocks that share a CU (block i and block i + half the grid, when the whole
+// grid is resident) get a long and a short sequence: the first half of the grid takes the longest
+// sequences in descending order, the second half the rest in ascending order.  Every wave computes the
+// same answer from the length array (lane l holds and ranks sequence l), so no barrier is needed; all of
+// the chain behind it waits for this, so each length is loaded once.  (us, the other
+// lengths of the ranking and the block's own length and k from memory again / so: 4 sequences of 32
+// heads, S = 700 13.3 / 12.9, 60 of 16, S = 1000 47.4 / 46.7, 16 of 8 on pages, S = 2000 17.5 / 17.3.)
+struct FusedWork {
+  int unit, S, k;
+};
+__device__ __forceinline__ FusedWork fused_work_of_block(const Ragged& rag, int B, int Hkv, int block, int S_max, int k_max) {
+  if (rag.seq_lens != nullptr && B <= 64 && B >= 2) {
+    const int lane = threadIdx.x & 63;
+    const int mine = lane < B ? rag.seq_lens[lane] : 0;
+    const int keep = lane < B && rag.ks != nullptr ? rag.ks[lane] : k_max;
+    int rank = 0;
+    for (int j = 0; j < B; ++j) {
+      const int other = __builtin_amdgcn_readlane(mine, j);
+      rank += (other > mine || (other == mine && j < lane)) ? 1 : 0;
+    }
+    const int want = paired_rank(block / Hkv, B);
+    const unsigned long long hit = __ballot(lane < B && rank == want);
+    if (hit != 0ull) {  // (always: the ranks are a permutation of 0..B-1, exactly one lane holds each)
+      const int b = __ffsll((long long)hit) - 1;
+      const int S = min(max(__builtin_amdgcn_readlane(mine, b), 1), S_max);  // as seq_rows and seq_keep
+      return {b * Hkv + block % Hkv, S, max(1, min(__builtin_amdgcn_readlane(keep, b), min(k_max, S)))};
+    }
   }
-  const int want = paired_rank(block / Hkv, B);
-  const unsigned long long hit = __ballot(lane < B && rank == want);
-  if (hit == 0ull) return block;              // cannot happen: the ranks are a permutation of 0..B-1
-  const int b = __ffsll((long long)hit) - 1;  // exactly one lane holds each rank
-  return b * Hkv + block % Hkv;
+  const int S = seq_rows(rag, block / Hkv, S_max);
+  return {block, S, seq_keep(rag, block / Hkv, k_max, S)};
 }
 
 // APPEND: the block also rotates the unit's new key with the P_h entries it already holds and
@@ -117,20 +129,19 @@ fused_decode_kernel(
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   // head = b * Hq + query head; unit = b * Hkv + KV head, whose cache it reads
-  int head, unit;
+  FusedWork work;
   if constexpr (!GROUPED) {
-    head = unit = fused_unit_of_block(rag, (int)gridDim.x / Hkv, Hkv, (int)blockIdx.x);
+    work = fused_work_of_block(rag, (int)gridDim.x / Hkv, Hkv, (int)blockIdx.x, S_max, k_max);
   } else {
     // The G heads of a unit read the same slab and largely the same rows: blocks go to the 8 XCDs in
     // turn, so a unit's heads are blocks 8 apart, on one XCD and next to each other in time.
     const int slot = grouped_slot((int)blockIdx.x, G, n_seq * Hkv);
     if (slot < 0) return;  // (padding of the launch; uniform for the block)
-    unit = fused_unit_of_block(rag, n_seq, Hkv, slot);
-    head = unit * G + grouped_head((int)blockIdx.x, G);
+    work = fused_work_of_block(rag, n_seq, Hkv, slot, S_max, k_max);
   }
+  const int unit = work.unit, S = work.S, k = work.k;
+  const int head = GROUPED ? unit * G + grouped_head((int)blockIdx.x, G) : unit;
   const int h = unit % Hkv;
-  const int S = seq_rows(rag, unit / Hkv, S_max);
-  const int k = seq_keep(rag, unit / Hkv, k_max, S);
 
   LOKI_STAMP(0);
 #ifdef LOKI_PHASE_TIMING
