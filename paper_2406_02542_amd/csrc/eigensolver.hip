@@ -17,9 +17,9 @@
 // What bounds it: chains of dependent fp64 steps, not throughput (4 M multiply-adds per head and
 // product).  Jacobi alone, one block per head, needed 12 sweeps of 127 rounds at 2.1 us a round and
 // 74 us a sweep more for the vectors: 4.1 of the 4.23 ms of a fit of 32 heads x 65536 keys, now
-// 0.36 ms (tridiag 125 us, eigvec 89, orthonormalise 14, project 15, the five Jacobi launches 23,
-// finish 7; the Gram pass 96).  Tridiagonalisation is 126 steps of one barrier, and everything
-// behind it is spread over 8 blocks per head.
+// 0.31 ms (tridiag 125 us, eigvec 64, orthonormalise 13, project 13, the two Jacobi launches 9,
+// finish 6; the Gram pass 83, the covariance 8).  Tridiagonalisation is 126 steps of one barrier, and
+// everything behind it is spread over 8 blocks per head.
 #include "eigensolver.h"
 
 #include <algorithm>
