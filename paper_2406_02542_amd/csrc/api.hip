@@ -80,9 +80,12 @@ int score_rows_per_block(const Shape& s) {
 // Heads that select for themselves in a group, or tokens of a sequence, find rows that the others
 // have just read: not beyond half of the rows (72 units of 8 heads, k = S / 8 42.1 / 44.4; 2 tokens,
 // k = S / 4, one head 63.8 / 57.8; groups of 4, k = S / 16 91.1 / 86.8).
+// Lengths that differ are not known here: 0.55 of what the longest would make (a quarter of it to all of it, 62 % on
+// average; MB by the longest, through / past: fp32 94 29.7 / 35.8, 131 34.7 / 38.4, 188 39.6 / 37.9, 301 47.9 /
+// 43.4; bf16 94 24.3 / 27.5, 150 29.9 / 30.7, 301 43.7 / 39.6).
 bool streams_rows(const Shape& s, int select_mode) {
   const int tokens = s.rg.queries > 1 ? s.rg.queries : 1;
-  const double unit_rows = (double)(s.B / tokens) * s.Hkv * s.S;
+  const double unit_rows = (double)(s.B / tokens) * s.Hkv * s.S * (s.rg.seq_lens != nullptr && tokens == 1 ? 0.55 : 1.0);
   double per_row;  // elements of a row that are read
   if (select_mode == kEveryRow) {
     per_row = 2 * kD;

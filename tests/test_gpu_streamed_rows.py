@@ -16,7 +16,7 @@ def decode(*a, **kw):
 CASES = {
     # one block per head: both types, row widths on both forms of the scoring, the append, pages, long rows
     "fused": decode(8, 32, 32, 1900, 32, 475, append=True),
-    "fused_paged": decode(7, 32, 32, 2100, 64, 525, append=True, ragged=True, paged=True),
+    "fused_paged": decode(12, 32, 32, 2100, 64, 525, append=True, ragged=True, paged=True),
     "fused_f32": decode(3, 64, 64, 1100, 32, 333, dtype="f32"),
     "fused_wide_f32": decode(3, 64, 64, 1000, 96, 333, dtype="f32", append=True),
     "fused_long": decode(6, 32, 32, 8300, 16, 1001),
@@ -24,7 +24,7 @@ CASES = {
     # one block per group, 512 and 256 threads, and several blocks per group
     "group_alone": decode(10, 32, 8, 5000, 32, 1250, mode="group", append=True),
     "group_two_per_cu": decode(34, 32, 8, 1900, 64, 475, mode="group", append=True),
-    "group_paged": decode(34, 16, 8, 2000, 32, 700, mode="group", append=True, ragged=True, paged=True),
+    "group_paged": decode(46, 16, 8, 2000, 32, 700, mode="group", append=True, ragged=True, paged=True),
     "cluster": decode(4, 64, 8, 12000, 64, 3000, mode="group", append=True),
     "cluster_paged": decode(6, 32, 8, 11000, 16, 2750, mode="group", append=True, paged=True),
     # the same with the slab past the caches while it is scored (few rows kept beside 80 MB of slab and more)
@@ -43,9 +43,9 @@ CASES = {
     "many_groups": decode(8, 128, 32, 3000, 8, 800, mode="group"),
     # dense attention: matrix cores and vector units, equal and unequal lengths
     "dense_mfma": {"kind": "dense", "B": 5, "Hq": 32, "Hkv": 8, "S": 5003, "dtype": "bf16", "ragged": False},
-    "dense_mfma_ragged": {"kind": "dense", "B": 5, "Hq": 64, "Hkv": 8, "S": 5003, "dtype": "bf16", "ragged": True},
+    "dense_mfma_ragged": {"kind": "dense", "B": 10, "Hq": 64, "Hkv": 8, "S": 5003, "dtype": "bf16", "ragged": True},
     "dense_f32": {"kind": "dense", "B": 3, "Hq": 32, "Hkv": 8, "S": 4001, "dtype": "f32", "ragged": False},
-    "dense_ragged": {"kind": "dense", "B": 6, "Hq": 32, "Hkv": 32, "S": 1303, "dtype": "bf16", "ragged": True},
+    "dense_ragged": {"kind": "dense", "B": 9, "Hq": 32, "Hkv": 32, "S": 1303, "dtype": "bf16", "ragged": True},
     # the Gram pass
     "fit": {"kind": "fit", "Hkv": 16, "N": 20001, "dtype": "bf16", "tau": 20.0},
 }
@@ -55,7 +55,7 @@ CASES = {
 def test_streamed(name):
     c = CASES[name]
     print(f"case {name} {c}", flush=True)
-    assert C.work(c)["bytes"] > 5e7  # (unequal lengths: the rule counts the longest)
+    assert C.work(c)["bytes"] > 5e7  # (unequal lengths: the rule counts 0.55 of what the longest makes)
     s = C.prepare(c, 5)
     got = {k: v.clone() for k, v in C.run(s).items()}
     torch.cuda.synchronize()
