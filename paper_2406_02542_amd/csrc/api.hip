@@ -80,6 +80,8 @@ int score_rows_per_block(const Shape& s) {
 // Heads that select for themselves in a group, or tokens of a sequence, find rows that the others
 // have just read: not beyond half of the rows (72 units of 8 heads, k = S / 8 42.1 / 44.4; 2 tokens,
 // k = S / 4, one head 63.8 / 57.8; groups of 4, k = S / 16 91.1 / 86.8).
+// And not in groups beyond 16384 rows, where it turns on how much the heads' lists have in common (4 x 32/8
+// heads, S = 131072, k = 8192 207 / 203, 169 / 173 with attention peaked on the same rows).
 // Lengths that differ are not known here: 0.55 of what the longest would make (a quarter of it to all of it, 62 % on
 // average; MB by the longest, through / past: fp32 94 29.7 / 35.8, 131 34.7 / 38.4, 188 39.6 / 37.9, 301 47.9 /
 // 43.4; bf16 94 24.3 / 27.5, 150 29.9 / 30.7, 301 43.7 / 39.6).
@@ -95,6 +97,7 @@ bool streams_rows(const Shape& s, int select_mode) {
     const int lists = tokens * (select_mode == 1 ? 1 : s.G);
     const double share = (double)lists * s.k / s.S;
     if (lists > 1 && share > 0.5) return false;
+    if (select_mode != 1 && s.G > 1 && s.S > 16384) return false;
     per_row = s.d + share * (2 * kD - (select_mode == 1 ? 0 : s.d));
     if (share > 1.0) per_row = 2 * kD;
   }
