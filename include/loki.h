@@ -377,6 +377,17 @@ int loki_debug_cluster_spin_limit(unsigned polls);
 int loki_debug_cluster_give_up_at_list(int on);
 
 /*
+ * Test aid: how a call loads the rows of its caches, which does not change its results.  `select_mode` as
+ * in the call, or -1 for dense attention, -2 for loki_pca_attn; of `args` (may be null) only which pointers
+ * are set, and queries_per_seq, count.  `rows`, `kept`: the sums of seq_lens and of the rows kept over the
+ * batch, which a call with lengths of its own decides by.  *form = 0: through the caches; 1: past them, where one
+ * selection per KV head is made and attended over in a single launch the values only; 2: there the slab
+ * too, while it is scored.  Nothing is launched.
+ */
+int loki_debug_row_loads(const loki_layout* layout, int S_max, int d, int k_max, int select_mode,
+                         const loki_step_args* args, double rows, double kept, int* form);
+
+/*
  * Whether a LOKI_PATH_CLUSTER launch on this workspace gave up waiting since its control words
  * were last cleared (by the clearing kernel in front of every launch without
  * LOKI_WORKSPACE_ZEROED, else by the caller's zero fill): *gave_up = 1 or 0 (host pointer).

@@ -95,6 +95,8 @@ def lib() -> ctypes.CDLL:
     L.loki_debug_cluster_spin_limit.argtypes = [ctypes.c_uint]
     L.loki_debug_cluster_give_up_at_list.restype = i32
     L.loki_debug_cluster_give_up_at_list.argtypes = [i32]
+    L.loki_debug_row_loads.restype = i32
+    L.loki_debug_row_loads.argtypes = [LP, i32, i32, i32, i32, vp, ctypes.c_double, ctypes.c_double, ctypes.POINTER(i32)]
     L.loki_cluster_gave_up.restype = i32
     L.loki_cluster_gave_up.argtypes = [vp, ctypes.POINTER(i32), vp]
     L.loki_stream_read.restype = i32
@@ -427,6 +429,16 @@ def loki_debug_cluster_spin_limit(polls: int) -> None:
 def loki_debug_cluster_give_up_at_list(on: bool) -> None:
     """Makes the blocks of PATH_CLUSTER launches give up at the list of candidates (until switched off)."""
     _check(lib().loki_debug_cluster_give_up_at_list(int(on)), "loki_debug_cluster_give_up_at_list")
+
+
+def loki_debug_row_loads(layout: Layout, S_max: int, d: int, k_max: int, select_mode: int, args: Optional[StepArgs] = None,
+                         rows: float = 0.0, kept: float = 0.0) -> int:
+    """How a call loads its rows: 0 through the caches, 1 past them, 2 a group's slab too (see the header)."""
+    form = ctypes.c_int32(0)
+    _check(lib().loki_debug_row_loads(ctypes.byref(layout), S_max, d, k_max, select_mode,
+                                      None if args is None else ctypes.byref(args), float(rows), float(kept),
+                                      ctypes.byref(form)), "loki_debug_row_loads")
+    return form.value
 
 
 def loki_cluster_gave_up(workspace: torch.Tensor, stream=None) -> bool:

@@ -82,31 +82,16 @@ int score_rows_per_block(const Shape& s) {
 // k = S / 4, one head 63.8 / 57.8; groups of 4, k = S / 16 91.1 / 86.8).
 // And not in groups beyond 16384 rows, where it turns on how much the heads' lists have in common (4 x 32/8
 // heads, S = 131072, k = 8192 207 / 203, 169 / 173 with attention peaked on the same rows).
-// Lengths that differ are not known here: 0.55 of what the longest would make (a quarter of it to all of it, 62 % on
-// average; MB by the longest, through / past: fp32 94 29.7 / 35.8, 131 34.7 / 38.4, 188 39.6 / 37.9, 301 47.9 /
-// 43.4; bf16 94 24.3 / 27.5, 150 29.9 / 30.7, 301 43.7 / 39.6).
-bool streams_rows(const Shape& s, int select_mode) {
-  const int tokens = s.rg.queries > 1 ? s.rg.queries : 1;
-  const double unit_rows = (double)(s.B / tokens) * s.Hkv * s.S * (s.rg.seq_lens != nullptr && tokens == 1 ? 0.55 : 1.0);
-  double per_row;  // elements of a row that are read
-  if (select_mode == kEveryRow) {
-    per_row = 2 * kD;
-  } else if (select_mode == kLowRankRows) {
-    per_row = kD + s.d;
-  } else {
-    const int lists = tokens * (select_mode == 1 ? 1 : s.G);
-    const double share = (double)lists * s.k / s.S;
-    if (lists > 1 && share > 0.5) return false;
-    if (select_mode != 1 && s.G > 1 && s.S > 16384) return false;
-    per_row = s.d + share * (2 * kD - (select_mode == 1 ? 0 : s.d));
-    if (share > 1.0) per_row = 2 * kD;
-  }
-  return unit_rows * per_row * s.elem_bytes >= 90e6;
-}
-
-// The attention of a group reads the slab again, for the selected rows, a line of 128 bytes for each; a
-// slab that was loaded past the caches is not there then.  So it pays while the lines read again are few
-// beside the slab, and from 80 MB of slab on.  Time through / past the caches by the slab's size and by
+// Lengths of their own are not known here, so the blocks add them up and decide.  us, through / past / as the
+// blocks decide, batches laid out for S rows of which every sequence holds an eighth, a quarter, half and all:
+//   16 x 32 heads, S = 4096      46 MB 19.8 / 21.6 / 19.9   92 26.6 / 27.8 / 27.9   185 39.5 / 35.0 / 35.2   369 71.0 / 63.0 / 63.0
+//   8 x 32 fp32 heads, S = 3000  34 MB 15.3 / 16.5 / 15.5   67 18.3 / 19.3 / 18.4   135 32.5 / 29.3 / 29.4   270 54.4 / 48.9 / 48.9
+//   dense, 10 x 32, S = 2000     41 MB 14.2 / 16.8 / 14.9   82 20.8 / 22.6 / 20.9   164 37.3 / 33.6 / 34.0   328 60.8 / 54.3 / 54.5
+// (Adding up costs 0 to 0.5 us of a launch, in those of groups up to 1.4, whose first loads wait for it.)
+//
+// The attention of a group with one selection reads the slab again, for the selected rows, a line of 128 bytes
+// for each; a slab that was loaded past the caches is not there then.  So it pays while the lines read again are
+// few beside the slab, and from 80 MB of slab on.  Time through / past the caches by the slab's size and by
 // `again`, the lines' bytes over the slab's (2, 4 and 8 heads, 64 to 512 units, d = 16 and 32, contiguous
 // and paged, 150 shapes):
 //   again   50-60 MB     90 MB        110-134 MB   160 MB       200 MB       260 MB
@@ -115,15 +100,31 @@ bool streams_rows(const Shape& s, int select_mode) {
 //   0.25    0.97-1.00    1.03-1.05    1.04-1.08    1.03-1.04    0.99-1.01    0.99
 //   0.4     1.01         1.02         0.97-1.01    0.97-0.98    0.97         0.98-0.99
 //   0.5     1.01-1.02    0.97-0.98    0.96-0.97
-// (lengths that may differ: two thirds of the slab that the longest would make.)  Slab rows of more than 64
-// bytes take two loads of half a line: never (d = 64: 0.87 to 0.94).
-int group_streams(const Shape& s) {
-  if (!streams_rows(s, 1)) return 0;
-  if (s.d > 8 * kStreamSlabChunks) return kStreamValues;
-  const double slab = (double)s.B * s.Hkv * s.S * s.d * s.elem_bytes * (s.rg.seq_lens != nullptr ? 0.65 : 1.0);
-  const double again = 128.0 * s.k / ((double)s.S * s.d * s.elem_bytes);
-  const bool pays = slab >= 80e6 && (again <= 0.18 || (again <= 0.26 && slab <= 180e6));
-  return pays ? kStreamValuesAndSlab : kStreamValues;
+// Slab rows of more than 64 bytes take two loads of half a line: never (d = 64: 0.87 to 0.94).
+RowLoads row_loads(const Shape& s, int select_mode) {
+  const int tokens = s.rg.queries > 1 ? s.rg.queries : 1;
+  const bool known = s.rg.seq_lens == nullptr && s.rg.ks == nullptr;
+  const float head_bytes = (float)s.Hkv * (float)s.elem_bytes, rows = (float)s.B * (float)s.S, kept = (float)s.B * (float)s.k;
+  RowLoads l;
+  if (select_mode == 0 && s.G > 1 && s.S > 16384) return l;
+  l.entries = s.B;
+  l.max_share = 1e30f;
+  if (select_mode == kEveryRow) {
+    l.row_bytes = head_bytes * 2 * kD;
+  } else if (select_mode == kLowRankRows) {
+    l.row_bytes = head_bytes * (float)(kD + s.d);
+  } else {
+    const int lists = select_mode == 0 ? s.G : 1;  // of a KV head and batch entry
+    l.row_bytes = head_bytes * (float)s.d / (float)tokens;
+    l.kept_bytes = head_bytes * (float)(lists * (2 * kD - (select_mode == 0 ? s.d : 0)));
+    if (tokens * lists > 1) l.max_share = 0.5f / (float)(tokens * lists);
+    if (select_mode == kGroupLaunch && s.d <= 8 * kSlabChunksPast) l.again_bytes = 128.0f * (float)s.Hkv;
+  }
+  if (known)
+    l.form = loads_form(l, rows, kept);
+  else if (rows * l.row_bytes + kept * l.kept_bytes >= kPastBytes)  // (else no lengths up to S reach it)
+    l.form = kByLengths;
+  return l;
 }
 
 int gather_splits(const Shape& s, int select_mode) {
@@ -815,6 +816,38 @@ int loki_debug_cluster_spin_limit(unsigned polls) {
 
 int loki_debug_cluster_give_up_at_list(int on) {
   set_cluster_give_up_at_list(on != 0);
+  return LOKI_OK;
+}
+
+int loki_debug_row_loads(const loki_layout* layout, int S_max, int d, int k_max, int select_mode,
+                         const loki_step_args* args, double rows, double kept, int* form) {
+  Shape s;
+  const int rc = check_layout(layout, &s);
+  if (rc != LOKI_OK) return rc;
+  select_mode = select_mode < 0 ? select_mode : select_mode & ~(LOKI_PATH_MASK | LOKI_WORKSPACE_ZEROED);
+  if (!form || select_mode < kLowRankRows || select_mode > 1 || S_max < 1) return LOKI_ERR_INVALID_ARG;
+  if (args) {
+    s.rg.seq_lens = args->seq_lens;
+    s.rg.ks = args->ks;
+    s.rg.queries = args->queries_per_seq > 1 ? args->queries_per_seq : 1;
+    s.ap.k_new = args->k_new;
+    s.pg.table = args->page_table;
+    s.pg.pages_per_seq = args->pages_per_seq;
+    while (s.pg.lg_rows < 24 && (1 << s.pg.lg_rows) < args->page_rows) ++s.pg.lg_rows;
+  }
+  s.B *= s.rg.queries;
+  s.S = S_max;
+  s.k = k_max;
+  if (select_mode >= 0) {
+    if (d != s.d) return LOKI_ERR_UNSUPPORTED;
+    if (k_max < 1 || k_max > S_max) return LOKI_ERR_INVALID_ARG;
+  }
+  if (s.G == 1 && select_mode == 1) select_mode = 0;
+  int loads = select_mode;
+  if (select_mode == 1 && (fused_gqa_cluster_preferred(s, 1) || fused_gqa_preferred(s, 1))) loads = kGroupLaunch;
+  const RowLoads l = row_loads(s, loads);
+  *form = l.form == kByLengths ? loads_form(l, (float)rows, (float)kept) : l.form;
+  if (select_mode == 0 && s.G > 1 && fused_preferred(s)) *form = kThroughCaches;  // (the one block per head of a group: always)
   return LOKI_OK;
 }
 

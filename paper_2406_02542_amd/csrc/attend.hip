@@ -16,10 +16,11 @@ constexpr int kAttThreads = 256;
 constexpr int kAttWaves = kAttThreads / 64;
 
 // LO_ONLY (with GATHER = false): every row, rotated query, logits from the low-rank slab alone
-// (Appendix E, Algorithm 2).  STREAM: see streams_rows.  BALANCED (dense): the blocks of a KV head are dealt out over its sequences by
-// length (dense_runs).
-template <typename T, int NH, bool GATHER, bool REUSE_LO, bool STREAM, bool LO_ONLY = false, bool BALANCED = false>
-__global__ __launch_bounds__(kAttThreads) void attend_kernel(
+// (Appendix E, Algorithm 2).  STREAM: the rows are loaded past the caches (row_loads).  BALANCED (dense): the
+// blocks of a KV head are dealt out over its sequences by length (dense_runs).
+template <typename T, int NH, bool GATHER, bool REUSE_LO, bool STREAM, bool LO_ONLY, bool BALANCED, int LIST, int SAVED>
+__device__ __forceinline__ void attend_body(
+    int32_t (&s_idx)[LIST], float (&s_a)[SAVED], MergeSmem<kAttWaves, NH>& s_merge, int len /* BALANCED: dense_len */,
     const void* __restrict__ k_a,   // GATHER: klo [units, S_cap, d]; dense: K [units, S_cap, 128]
     const void* __restrict__ k_b,   // GATHER: khi [units, S_cap, 128-d]; dense: unused
     const void* __restrict__ v,     // [units, S_cap, 128]
@@ -35,10 +36,6 @@ __global__ __launch_bounds__(kAttThreads) void attend_kernel(
   constexpr int EPC = T::EPC;
   constexpr int LPRV = kD / EPC;           // lanes per row: 16 (bf16) or 32 (fp32)
   constexpr int RPW = 64 / LPRV;           // rows a wave covers per load instruction
-
-  __shared__ int32_t s_idx[GATHER ? kMaxGatherChunk : 1];
-  __shared__ float s_a[REUSE_LO ? kMaxGatherChunk : 1];
-  __shared__ MergeSmem<kAttWaves, NH> s_merge;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int c = lane % LPRV, rg = lane / LPRV;
@@ -67,14 +64,14 @@ __global__ __launch_bounds__(kAttThreads) void attend_kernel(
     const int Hkv = Hq / Gq, B = (int)gridDim.y / Hkv;
     const int X = nsplit * B, id = by * nsplit + bx, x = id % X;
     int runs, incl;
-    dense_runs(rag, B, S_max, nsplit, runs, incl);
+    dense_runs(len, B, nsplit, runs, incl);
     const unsigned long long behind = __ballot(incl > x);
     if (behind == 0ull) return;  // uniform for the block: no run is left for it
     const int b = __ffsll((long long)behind) - 1;
     const int n_b = __builtin_amdgcn_readlane(runs, b), base = __builtin_amdgcn_readlane(incl, b) - n_b;
     by = b * Hkv + id / X;
     bx = x - base;
-    run_rows = (seq_rows(rag, b, S_max) + n_b - 1) / n_b;
+    run_rows = (__builtin_amdgcn_readlane(len, b) + n_b - 1) / n_b;
     part_stride = (size_t)X;
     part0 = (size_t)(id / X) * Gq * X + x;
   }
@@ -159,6 +156,24 @@ __global__ __launch_bounds__(kAttThreads) void attend_kernel(
   }
 }
 
+template <typename T, int NH, bool GATHER, bool REUSE_LO, bool LO_ONLY = false, bool BALANCED = false>
+__global__ __launch_bounds__(kAttThreads) void attend_kernel(
+    const void* __restrict__ k_a, const void* __restrict__ k_b, const void* __restrict__ v, const void* __restrict__ qv,
+    const int32_t* __restrict__ sel_idx, const float* __restrict__ sel_score, float* partial, int32_t* tickets,
+    void* __restrict__ out, int Hq, int Gq, int S_cap, int d, int n_max, int rows_per_block, int nsplit, int S_max, Ragged rag,
+    Paging pg, int xcd_group_blocks, int xcd_sets) {
+  __shared__ int32_t s_idx[GATHER ? kMaxGatherChunk : 1];
+  __shared__ float s_a[REUSE_LO ? kMaxGatherChunk : 1];
+  __shared__ MergeSmem<kAttWaves, NH> s_merge;
+  const int len = BALANCED ? dense_len(rag, (int)gridDim.y / (Hq / Gq), S_max) : 0;
+  const int form_now = BALANCED ? dense_form(rag.loads, len) : form_of_launch(rag, S_max, n_max);
+  with_form<kPastCaches>(form_now, [&](auto form) __attribute__((always_inline)) {
+    attend_body<T, NH, GATHER, REUSE_LO, decltype(form)::value != kThroughCaches, LO_ONLY, BALANCED>(
+        s_idx, s_a, s_merge, len, k_a, k_b, v, qv, sel_idx, sel_score, partial, tickets, out, Hq, Gq, S_cap, d, n_max, rows_per_block,
+        nsplit, S_max, rag, pg, xcd_group_blocks, xcd_sets);
+  });
+}
+
 // Merges the nsplit partial results of each query head (launches that have no ticket array:
 // the dense baseline and Algorithm 2 of Appendix E).
 template <typename T, bool BALANCED>
@@ -171,7 +186,7 @@ __global__ __launch_bounds__(kD) void combine_kernel(const float* __restrict__ p
   int n = nsplit;
   if constexpr (BALANCED) {
     int runs, incl;
-    dense_runs(rg, B, S_max, nsplit, runs, incl);
+    dense_runs(dense_len(rg, B, S_max), B, nsplit, runs, incl);
     const int b = (int)(head / Hq);
     n = __builtin_amdgcn_readlane(runs, b);
     first = (head % Hq) * (size_t)nsplit * B + (__builtin_amdgcn_readlane(incl, b) - n);
@@ -180,7 +195,7 @@ __global__ __launch_bounds__(kD) void combine_kernel(const float* __restrict__ p
 }
 
 // ---- launchers ------------------------------------------------------------------------
-template <typename T, int NH, bool GATHER, bool STREAM>
+template <typename T, int NH, bool GATHER>
 static hipError_t launch_attend_nh(int blocks_y, int nsplit, int rows_per_block, const void* k_a,
                                    const void* k_b, const void* v, const void* qv,
                                    const int32_t* sel_idx, const float* sel_score, float* partial,
@@ -191,26 +206,26 @@ static hipError_t launch_attend_nh(int blocks_y, int nsplit, int rows_per_block,
   // (d = 128, Exact-TopK of Section 5: it is the whole logit and no key is read again)
   constexpr bool kCanReuse = GATHER && NH == 1;
   if (kCanReuse && sel_score != nullptr) {
-    hipLaunchKernelGGL((attend_kernel<T, NH, GATHER, kCanReuse, STREAM>), dim3(nsplit, blocks_y),
+    hipLaunchKernelGGL((attend_kernel<T, NH, GATHER, kCanReuse>), dim3(nsplit, blocks_y),
                        dim3(kAttThreads), 0, st, k_a, k_b, v, qv, sel_idx, sel_score, partial, tickets,
                        out, Hq, Gq, S_cap, d, n, rows_per_block, nsplit, S_max, rg, pg, xcd_group_blocks, xcd_sets);
   } else {
-    hipLaunchKernelGGL((attend_kernel<T, NH, GATHER, false, STREAM>), dim3(nsplit, blocks_y),
+    hipLaunchKernelGGL((attend_kernel<T, NH, GATHER, false>), dim3(nsplit, blocks_y),
                        dim3(kAttThreads), 0, st, k_a, k_b, v, qv, sel_idx, sel_score, partial, tickets,
                        out, Hq, Gq, S_cap, d, n, rows_per_block, nsplit, S_max, rg, pg, xcd_group_blocks, xcd_sets);
   }
   return hipGetLastError();
 }
 
-template <typename T, bool GATHER, bool STREAM>
-static hipError_t launch_attend_s(int NH, int blocks_y, int nsplit, int rows_per_block,
+template <typename T, bool GATHER>
+static hipError_t launch_attend_t(int NH, int blocks_y, int nsplit, int rows_per_block,
                                   const void* k_a, const void* k_b, const void* v, const void* qv,
                                   const int32_t* sel_idx, const float* sel_score, float* partial,
                                   int32_t* tickets, void* out, int Hq, int Gq, int S_cap, int d, int n, int S_max,
                                   const Ragged& rg, const Paging& pg, int xcd_group_blocks,
                                   int xcd_sets, hipStream_t st) {
 #define LOKI_ATT(NHV)                                                                          \
-  return launch_attend_nh<T, NHV, GATHER, STREAM>(blocks_y, nsplit, rows_per_block, k_a, k_b, v, qv,   \
+  return launch_attend_nh<T, NHV, GATHER>(blocks_y, nsplit, rows_per_block, k_a, k_b, v, qv,   \
                                           sel_idx, sel_score, partial, tickets, out, Hq, Gq, S_cap, d, n, S_max, rg, pg, \
                                           xcd_group_blocks, xcd_sets, st)
   switch (NH) {
@@ -221,11 +236,6 @@ static hipError_t launch_attend_s(int NH, int blocks_y, int nsplit, int rows_per
     default: return hipErrorInvalidValue;
   }
 #undef LOKI_ATT
-}
-
-template <typename T, bool GATHER, typename... Args>
-static hipError_t launch_attend_t(bool stream, Args... args) {
-  return stream ? launch_attend_s<T, GATHER, true>(args...) : launch_attend_s<T, GATHER, false>(args...);
 }
 
 static inline int div_up(int a, int b) { return (a + b - 1) / b; }
@@ -250,22 +260,20 @@ hipError_t launch_gather(const Shape& s, int select_mode, int nsplit, const floa
     xcd = sharers * nsplit;
     blocks_y = div_up(sets, 8) * 8 * sharers;
   }
-  const bool stream = streams_rows(s, select_mode);
+  const Ragged rg = with_loads(s, select_mode);
   if (s.dtype == 0)
-    return launch_attend_t<F32, true>(stream, NH, blocks_y, nsplit, rpb, klo, khi, v, qhat, sel_idx,
-                                      sel_score, partial, tickets, out, s.Hq, s.G, s.S_cap, s.d, s.k, s.S, s.rg, s.pg, xcd, sets, st);
-  return launch_attend_t<BF16, true>(stream, NH, blocks_y, nsplit, rpb, klo, khi, v, qhat, sel_idx,
-                                     sel_score, partial, tickets, out, s.Hq, s.G, s.S_cap, s.d, s.k, s.S, s.rg, s.pg, xcd, sets, st);
+    return launch_attend_t<F32, true>(NH, blocks_y, nsplit, rpb, klo, khi, v, qhat, sel_idx,
+                                      sel_score, partial, tickets, out, s.Hq, s.G, s.S_cap, s.d, s.k, s.S, rg, s.pg, xcd, sets, st);
+  return launch_attend_t<BF16, true>(NH, blocks_y, nsplit, rpb, klo, khi, v, qhat, sel_idx,
+                                     sel_score, partial, tickets, out, s.Hq, s.G, s.S_cap, s.d, s.k, s.S, rg, s.pg, xcd, sets, st);
 }
 
 template <typename T, int NH>
 static hipError_t launch_dense_balanced_nh(const Shape& s, int nsplit, const void* q, const void* k_full, const void* v,
                                            float* partial, void* out, hipStream_t st) {
-  const auto kernel = streams_rows(s, kEveryRow) ? attend_kernel<T, NH, false, false, true, false, true>
-                                                 : attend_kernel<T, NH, false, false, false, false, true>;
-  hipLaunchKernelGGL(kernel, dim3(nsplit, s.B * s.Hkv), dim3(kAttThreads), 0, st,
+  hipLaunchKernelGGL((attend_kernel<T, NH, false, false, false, true>), dim3(nsplit, s.B * s.Hkv), dim3(kAttThreads), 0, st,
                      k_full, nullptr, v, q, nullptr, nullptr, partial, nullptr, out, s.Hq, s.G, s.S_cap, kD, s.S,
-                     div_up(s.S, nsplit), nsplit, s.S, s.rg, Paging{}, 0, 0);
+                     div_up(s.S, nsplit), nsplit, s.S, with_loads(s, kEveryRow), Paging{}, 0, 0);
   return hipGetLastError();
 }
 
@@ -289,22 +297,20 @@ hipError_t launch_dense(const Shape& s, int nsplit, const void* q, const void* k
                         : launch_dense_balanced<BF16>(s, nsplit, q, k_full, v, partial, out, st);
   const int blocks_y = s.B * s.Hkv;
   const int rpb = div_up(s.S, nsplit);
-  const bool stream = streams_rows(s, kEveryRow);
+  const Ragged rg = with_loads(s, kEveryRow);
   if (s.dtype == 0)
-    return launch_attend_t<F32, false>(stream, s.G, blocks_y, nsplit, rpb, k_full, nullptr, v, q, nullptr,
-                                       nullptr, partial, nullptr, out, s.Hq, s.G, s.S_cap, kD, s.S, s.S, s.rg, Paging{}, 0, 0, st);
-  return launch_attend_t<BF16, false>(stream, s.G, blocks_y, nsplit, rpb, k_full, nullptr, v, q, nullptr,
-                                      nullptr, partial, nullptr, out, s.Hq, s.G, s.S_cap, kD, s.S, s.S, s.rg, Paging{}, 0, 0, st);
+    return launch_attend_t<F32, false>(s.G, blocks_y, nsplit, rpb, k_full, nullptr, v, q, nullptr,
+                                       nullptr, partial, nullptr, out, s.Hq, s.G, s.S_cap, kD, s.S, s.S, rg, Paging{}, 0, 0, st);
+  return launch_attend_t<BF16, false>(s.G, blocks_y, nsplit, rpb, k_full, nullptr, v, q, nullptr,
+                                      nullptr, partial, nullptr, out, s.Hq, s.G, s.S_cap, kD, s.S, s.S, rg, Paging{}, 0, 0, st);
 }
 
 template <typename T, int NH>
 static hipError_t launch_pca_nh(const Shape& s, int nsplit, int rpb, const float* qhat, const void* klo,
                                 const void* v, float* partial, void* out, hipStream_t st) {
-  const auto kernel = streams_rows(s, kLowRankRows) ? attend_kernel<T, NH, false, false, true, true>
-                                                    : attend_kernel<T, NH, false, false, false, true>;
-  hipLaunchKernelGGL(kernel, dim3(nsplit, s.B * s.Hkv),
+  hipLaunchKernelGGL((attend_kernel<T, NH, false, false, true>), dim3(nsplit, s.B * s.Hkv),
                      dim3(kAttThreads), 0, st, klo, nullptr, v, qhat, nullptr, nullptr, partial, nullptr,
-                     out, s.Hq, s.G, s.S_cap, s.d, s.S, rpb, nsplit, s.S, s.rg, Paging{}, 0, 0);
+                     out, s.Hq, s.G, s.S_cap, s.d, s.S, rpb, nsplit, s.S, with_loads(s, kLowRankRows), Paging{}, 0, 0);
   return hipGetLastError();
 }
 

@@ -122,7 +122,7 @@ __device__ __forceinline__ void attend_trip(AttendAcc<T, NH>& acc, const float (
 // attention over 2 sequences of 990 rows, 32/8 fp32 heads, 20.4 / 18.3, 2 to 7 of 546 to 2310 rows
 // 4 to 13 % more, large ones 0.6 %; but one block per head beyond 8192 rows, 512 heads in groups of
 // 4, S = 12800, k = 400 46.4 / 47.3, S = 13300, k = 831 62.7 / 64.0.
-// STREAM: rows are loaded past the caches (streams_rows).  ROWS: rows per lane group and trip.
+// STREAM: rows are loaded past the caches (row_loads).  ROWS: rows per lane group and trip.
 template <typename T, int NH, int NGROUPS, bool GATHER, bool REUSE_LO, bool SCORE_BY_ROW = false, bool APART = false, bool STREAM = false,
           int ROWS = kRowsInFlight>
 __device__ __forceinline__ void attend_rows(AttendAcc<T, NH>& acc, const float (&qr)[NH][T::EPC],
@@ -254,10 +254,14 @@ __device__ __forceinline__ void attend_growing(AttendAcc<T, NH>& acc, const floa
 // S = 16384, 144 us with two blocks per CU, 134 dealt out.)  Every wave works it out for itself, lane b
 // for sequence b; the parts of the result lie at [query head][base_b + run].
 constexpr int kDenseMinRun = 128;
-// This lane's sequence: its runs, and the runs of it and the sequences before it.
-__device__ __forceinline__ void dense_runs(const Ragged& rg, int B, int S_max, int nsplit, int& runs, int& incl) {
+// The rows of this lane's sequence.
+__device__ __forceinline__ int dense_len(const Ragged& rg, int B, int S_max) {
   const int lane = threadIdx.x & 63;
-  const int len = lane < B ? seq_rows(rg, lane, S_max) : 0;
+  return lane < B ? seq_rows(rg, lane, S_max) : 0;
+}
+// Its runs, and the runs of it and the sequences before it.
+__device__ __forceinline__ void dense_runs(int len, int B, int nsplit, int& runs, int& incl) {
+  const int lane = threadIdx.x & 63;
   const int total = __builtin_amdgcn_readlane((int)wave_inclusive_scan_u32((uint32_t)len), 63);
   const int X = nsplit * B;
   // equal lengths: nothing to deal out (440 units of 8 heads, S = 3440, eight blocks per CU: 161 us
@@ -282,6 +286,10 @@ __device__ __forceinline__ void dense_runs(const Ragged& rg, int B, int S_max, i
   }
   if (lane >= B) runs = 0;
   incl = (int)wave_inclusive_scan_u32((uint32_t)runs);
+}
+
+__device__ __forceinline__ int dense_form(const RowLoads& l, int len) {
+  return l.form != kByLengths ? l.form : form_of(l, {wave_sum_f32((float)len), 0.f});
 }
 
 template <int WAVES, int NH>

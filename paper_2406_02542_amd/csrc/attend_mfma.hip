@@ -32,10 +32,11 @@ constexpr int kAmWaves = kAmThreads / 64;
 // with row pitch d (Appendix E, Algorithm 2): KSTEPS = ceil(d / 32) of the four 32-column
 // steps of the first product are issued, and columns past d (a partial last step) meet a zero
 // in the B operand, so whatever valid chunk their lanes load does not count.
-// STREAM_V: see streams_rows.
+// STREAM_V: the values are loaded past the caches (row_loads).
 // BALANCED (dense): the blocks of a KV head are dealt out over its sequences by length (dense_runs).
-template <int NH, bool GATHER, bool STREAM_V, int KSTEPS = 4, bool LO_ONLY = false, bool BALANCED = false>
-__global__ __launch_bounds__(kAmThreads, 2) void attend_mfma_kernel(
+template <int NH, bool GATHER, bool STREAM_V, int KSTEPS, bool LO_ONLY, bool BALANCED, int LIST>
+__device__ __forceinline__ void attend_mfma_body(
+    int32_t (&s_idx)[LIST], MergeSmem<kAmWaves, NH>& s_merge, int len /* BALANCED: dense_len */,
     const void* __restrict__ k_a,   // GATHER: klo [units, S_cap, d]; dense: K [units, S_cap, 128]
     const void* __restrict__ k_b,   // GATHER: khi [units, S_cap, 128-d]; dense: unused
     const void* __restrict__ v,     // [units, S_cap, 128]
@@ -48,9 +49,6 @@ __global__ __launch_bounds__(kAmThreads, 2) void attend_mfma_kernel(
     Paging pg) {
   constexpr bool kRotated = GATHER || LO_ONLY;  // the query is the fp32 rotated one
   constexpr int QT = kRotated ? 2 : 1;
-  __shared__ __align__(16) int32_t s_idx[GATHER ? kMaxGatherChunk : 1];
-  __shared__ __align__(16) MergeSmem<kAmWaves, NH> s_merge;
-
   const int tid = threadIdx.x, lane = tid & 63;
   const int r16 = lane & 15, kgrp = lane >> 4;
   int kv_unit = blockIdx.y, split = blockIdx.x;  // one block row per KV unit: its NH heads share the rows
@@ -61,14 +59,14 @@ __global__ __launch_bounds__(kAmThreads, 2) void attend_mfma_kernel(
     const int B = (int)gridDim.y / Hkv;
     const int X = nsplit * B, id = kv_unit * nsplit + split, x = id % X;
     int runs, incl;
-    dense_runs(rg, B, S_max, nsplit, runs, incl);
+    dense_runs(len, B, nsplit, runs, incl);
     const unsigned long long behind = __ballot(incl > x);
     if (behind == 0ull) return;  // uniform for the block: no run is left for it
     const int b = __ffsll((long long)behind) - 1;
     const int n_b = __builtin_amdgcn_readlane(runs, b), base = __builtin_amdgcn_readlane(incl, b) - n_b;
     kv_unit = b * Hkv + id / X;
     split = x - base;
-    run_rows = (seq_rows(rg, b, S_max) + n_b - 1) / n_b;
+    run_rows = (__builtin_amdgcn_readlane(len, b) + n_b - 1) / n_b;
     part_stride = (size_t)X;
     part0 = (size_t)(id / X) * NH * X + x;
   } else {
@@ -146,7 +144,22 @@ __global__ __launch_bounds__(kAmThreads, 2) void attend_mfma_kernel(
   }
 }
 
-template <bool GATHER, bool STREAM_V>
+template <int NH, bool GATHER, int KSTEPS = 4, bool LO_ONLY = false, bool BALANCED = false>
+__global__ __launch_bounds__(kAmThreads, 2) void attend_mfma_kernel(
+    const void* __restrict__ k_a, const void* __restrict__ k_b, const void* __restrict__ v, const void* __restrict__ qv,
+    const int32_t* __restrict__ sel_idx, float* partial, int32_t* tickets, uint16_t* __restrict__ out, int S_cap, int d, int n_max,
+    int rows_per_block, int nsplit, int Hkv, int S_max, Ragged rg, Paging pg) {
+  __shared__ __align__(16) int32_t s_idx[GATHER ? kMaxGatherChunk : 1];
+  __shared__ __align__(16) MergeSmem<kAmWaves, NH> s_merge;
+  const int len = BALANCED ? dense_len(rg, (int)gridDim.y / Hkv, S_max) : 0;
+  const int form_now = BALANCED ? dense_form(rg.loads, len) : form_of_launch(rg, S_max, n_max);
+  with_form<kPastCaches>(form_now, [&](auto form) __attribute__((always_inline)) {
+    attend_mfma_body<NH, GATHER, decltype(form)::value != kThroughCaches, KSTEPS, LO_ONLY, BALANCED>(
+        s_idx, s_merge, len, k_a, k_b, v, qv, sel_idx, partial, tickets, out, S_cap, d, n_max, rows_per_block, nsplit, Hkv, S_max, rg, pg);
+  });
+}
+
+template <bool GATHER>
 static hipError_t launch_attend_mfma_nh(int NH, int blocks_y, int nsplit, int rpb, const void* k_a,
                                         const void* k_b, const void* v, const void* qv,
                                         const int32_t* sel_idx, float* partial, int32_t* tickets,
@@ -156,11 +169,11 @@ static hipError_t launch_attend_mfma_nh(int NH, int blocks_y, int nsplit, int rp
   uint16_t* o16 = static_cast<uint16_t*>(out);
   switch (NH) {
     case 4:
-      hipLaunchKernelGGL((attend_mfma_kernel<4, GATHER, STREAM_V>), grid, block, 0, st, k_a, k_b, v, qv, sel_idx,
+      hipLaunchKernelGGL((attend_mfma_kernel<4, GATHER>), grid, block, 0, st, k_a, k_b, v, qv, sel_idx,
                          partial, tickets, o16, S_cap, d, n, rpb, nsplit, Hkv, S_max, rg, pg);
       break;
     case 8:
-      hipLaunchKernelGGL((attend_mfma_kernel<8, GATHER, STREAM_V>), grid, block, 0, st, k_a, k_b, v, qv, sel_idx,
+      hipLaunchKernelGGL((attend_mfma_kernel<8, GATHER>), grid, block, 0, st, k_a, k_b, v, qv, sel_idx,
                          partial, tickets, o16, S_cap, d, n, rpb, nsplit, Hkv, S_max, rg, pg);
       break;
     default:
@@ -175,10 +188,10 @@ static hipError_t launch_pca_mfma_nh(const Shape& s, int nsplit, int rpb, const 
                                      hipStream_t st) {
   const dim3 grid(nsplit, s.B * s.Hkv), block(kAmThreads);
   uint16_t* o16 = static_cast<uint16_t*>(out);
-  const bool stream = streams_rows(s, kLowRankRows);
+  const Ragged rg = with_loads(s, kLowRankRows);
 #define LOKI_PCA_MFMA(KS)                                                                          \
-  hipLaunchKernelGGL((stream ? attend_mfma_kernel<NH, false, true, KS, true> : attend_mfma_kernel<NH, false, false, KS, true>), grid, block, 0, st, klo, nullptr, v, \
-                     qhat, nullptr, partial, nullptr, o16, s.S_cap, s.d, s.S, rpb, nsplit, s.Hkv, s.S, s.rg,  \
+  hipLaunchKernelGGL((attend_mfma_kernel<NH, false, KS, true>), grid, block, 0, st, klo, nullptr, v, \
+                     qhat, nullptr, partial, nullptr, o16, s.S_cap, s.d, s.S, rpb, nsplit, s.Hkv, s.S, rg,  \
                      Paging{});                                                                    \
   break
   switch ((s.d + 31) / 32) {
@@ -207,21 +220,20 @@ bool attend_mfma_applies(const Shape& s, int heads_per_block) {
 hipError_t launch_dense_mfma(const Shape& s, int nsplit, const void* q, const void* k_full,
                              const void* v, float* partial, void* out, hipStream_t st) {
   const int rpb = (s.S + nsplit - 1) / nsplit;
-  const bool stream = streams_rows(s, kEveryRow);
+  const Ragged rg = with_loads(s, kEveryRow);
   if (dense_balanced(s, nsplit)) {
     const dim3 grid(nsplit, s.B * s.Hkv), block(kAmThreads);
     uint16_t* o16 = static_cast<uint16_t*>(out);
     if (s.G == 8)
-      hipLaunchKernelGGL((stream ? attend_mfma_kernel<8, false, true, 4, false, true> : attend_mfma_kernel<8, false, false, 4, false, true>), grid, block, 0, st, k_full, nullptr, v, q, nullptr,
-                         partial, nullptr, o16, s.S_cap, kD, s.S, rpb, nsplit, s.Hkv, s.S, s.rg, Paging{});
+      hipLaunchKernelGGL((attend_mfma_kernel<8, false, 4, false, true>), grid, block, 0, st, k_full, nullptr, v, q, nullptr,
+                         partial, nullptr, o16, s.S_cap, kD, s.S, rpb, nsplit, s.Hkv, s.S, rg, Paging{});
     else
-      hipLaunchKernelGGL((stream ? attend_mfma_kernel<4, false, true, 4, false, true> : attend_mfma_kernel<4, false, false, 4, false, true>), grid, block, 0, st, k_full, nullptr, v, q, nullptr,
-                         partial, nullptr, o16, s.S_cap, kD, s.S, rpb, nsplit, s.Hkv, s.S, s.rg, Paging{});
+      hipLaunchKernelGGL((attend_mfma_kernel<4, false, 4, false, true>), grid, block, 0, st, k_full, nullptr, v, q, nullptr,
+                         partial, nullptr, o16, s.S_cap, kD, s.S, rpb, nsplit, s.Hkv, s.S, rg, Paging{});
     return hipGetLastError();
   }
-  const auto launch = stream ? launch_attend_mfma_nh<false, true> : launch_attend_mfma_nh<false, false>;
-  return launch(s.G, s.B * s.Hkv, nsplit, rpb, k_full, nullptr, v, q, nullptr,
-                                      partial, nullptr, out, s.S_cap, kD, s.S, s.Hkv, s.S, s.rg, Paging{}, st);
+  return launch_attend_mfma_nh<false>(s.G, s.B * s.Hkv, nsplit, rpb, k_full, nullptr, v, q, nullptr,
+                                      partial, nullptr, out, s.S_cap, kD, s.S, s.Hkv, s.S, rg, Paging{}, st);
 }
 
 hipError_t launch_gather_mfma(const Shape& s, int nsplit, const float* qhat, const void* klo,
@@ -229,9 +241,8 @@ hipError_t launch_gather_mfma(const Shape& s, int nsplit, const float* qhat, con
                               int32_t* tickets, void* out, hipStream_t st) {
   const int rpb = (s.k + nsplit - 1) / nsplit;
   if (rpb > kMaxGatherChunk) return hipErrorInvalidValue;
-  const auto launch = streams_rows(s, 1) ? launch_attend_mfma_nh<true, true> : launch_attend_mfma_nh<true, false>;
-  return launch(s.G, s.B * s.Hkv, nsplit, rpb, klo, khi, v, qhat, sel_idx,
-                                     partial, tickets, out, s.S_cap, s.d, s.k, s.Hkv, s.S, s.rg, s.pg, st);
+  return launch_attend_mfma_nh<true>(s.G, s.B * s.Hkv, nsplit, rpb, klo, khi, v, qhat, sel_idx,
+                                     partial, tickets, out, s.S_cap, s.d, s.k, s.Hkv, s.S, with_loads(s, 1), s.pg, st);
 }
 
 }  // namespace loki

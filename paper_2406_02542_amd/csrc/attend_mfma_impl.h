@@ -131,7 +131,7 @@ struct AmRoundRobin {
 
 // Cache row of list entry r = GATHER ? s_idx[r - r0] : r.  s_idx: 16-byte aligned.  complete():
 // called once by every wave, completes the list; the loads of a first step that may be asked for
-// early are in flight meanwhile.  STREAM_V: values are loaded past the caches (streams_rows); keys are
+// early are in flight meanwhile.  STREAM_V: values are loaded past the caches (row_loads); keys are
 // not, of which an instruction takes 64 bytes of 16 rows, half lines: 16 sequences of 32/8 heads, S =
 // 16384, dense, neither 129.6 us, values 116.7, both 118.3; one selection per group, 96 units, S =
 // 6073, d = 16 39.2, 36.4, 44.6.

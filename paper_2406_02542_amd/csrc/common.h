@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "launch.h"
 
 namespace loki {
@@ -114,6 +116,29 @@ __device__ inline uint4 load16_hint(const void* p) {
   }
 }
 
+// f(form) for the form (see RowLoads) that a launch takes, up to MAX.  The hint is part of the instruction, so
+// a kernel holds what it does behind the choice once for each: the single launches their whole body (two loops in
+// one body, of which the block takes one, cost them 23 to 108 registers that do not fit), and no kernel exists
+// twice.  Loads through the caches come first: the way to the others is a jump past their instructions,
+// 0.4 us that small launches would notice (8 fp32 heads, S = 1024, last 12.0 us, first 11.6; as kernels of their
+// own 11.6), large ones 0 to 0.6 (16 x 32 heads, S = 4096 60.9, kernels of their own 60.8; 64 x 64/8 heads 98.3, 97.7).
+// The empty statements keep the compiler from taking equal instructions out of the branches, which would drop
+// the hint.
+template <int MAX, typename F>
+__device__ __forceinline__ void with_form(int form, F f) {
+  if (MAX == kThroughCaches || __builtin_expect(form == kThroughCaches, 1)) {
+    f(std::integral_constant<int, kThroughCaches>{});
+  } else if (MAX == kPastCaches || form == kPastCaches) {
+    asm volatile("" ::: "memory");
+    f(std::integral_constant<int, MAX < kPastCaches ? MAX : kPastCaches>{});
+    asm volatile("" ::: "memory");
+  } else {
+    asm volatile("" ::: "memory");
+    f(std::integral_constant<int, MAX>{});
+    asm volatile("" ::: "memory");
+  }
+}
+
 // ---- cross-lane movement through DPP (no LDS traffic) ----------------------------------
 template <int CTRL>
 __device__ inline float dpp_mov(float x) {
@@ -137,6 +162,37 @@ __device__ inline float group_allreduce_sum(float x) {
   if constexpr (LANES >= 32) x += __shfl_xor(x, 16);
   if constexpr (LANES >= 64) x += __shfl_xor(x, 32);
   return x;
+}
+
+// The sum over the wave, the same in every lane, without LDS.
+__device__ __forceinline__ float wave_sum_f32(float x) {
+  const int r = __float_as_int(group_allreduce_sum<16>(x));
+  auto row = [&](int lane) { return __int_as_float(__builtin_amdgcn_readlane(r, lane)); };
+  return (row(0) + row(16)) + (row(32) + row(48));
+}
+
+// The rows of a batch's entries and the rows they keep, added up; every wave for itself, lane l entries l, l + 64, ..
+struct RowSums {
+  float rows, kept;
+};
+__device__ __forceinline__ RowSums row_sums(const Ragged& rg, int S_max, int k_max) {
+  const int n = rg.loads.entries, lane = (int)(threadIdx.x & 63);
+  float rows = 0.f, kept = 0.f;
+  for (int b0 = 0; b0 < n; b0 += 64) {  // (uniform; no branch around the loads)
+    const int b = min(b0 + lane, n - 1);
+    const int S = seq_rows(rg, b, S_max), k = seq_keep(rg, b, k_max, S);
+    rows += b0 + lane < n ? (float)S : 0.f;
+    kept += b0 + lane < n ? (float)k : 0.f;
+  }
+  return {wave_sum_f32(rows), wave_sum_f32(kept)};
+}
+// The form of this launch's loads, the same for all its blocks.
+__device__ __forceinline__ int form_of(const RowLoads& l, const RowSums& sums) {
+  return __builtin_amdgcn_readfirstlane(loads_form(l, sums.rows, sums.kept));
+}
+__device__ __forceinline__ int form_of_launch(const Ragged& rg, int S_max, int k_max) {
+  if (rg.loads.form != kByLengths) return rg.loads.form;
+  return form_of(rg.loads, row_sums(rg, S_max, k_max));
 }
 
 // Maximum over each aligned group of LANES consecutive lanes (LANES <= 16), to every lane.

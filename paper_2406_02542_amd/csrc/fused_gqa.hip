@@ -71,11 +71,11 @@ bool fused_gqa_preferred(const Shape& s, int select_mode) {
   return bytes < (limit < 140 ? limit : 140) * s.S;
 }
 
-template <int THREADS, int NCH, int G, int KPT, bool PAGED, int STREAM>
+template <int THREADS, int NCH, int G, int KPT, bool PAGED>
 static hipError_t launch_fused_gqa_k(const Shape& s, const void* q, const float* P, const void* klo,
                                      const void* khi, const void* v, void* out, int32_t* out_idx,
                                      hipStream_t st) {
-  auto kern = fused_gqa_kernel<THREADS, NCH, G, KPT, PAGED, STREAM>;
+  auto kern = fused_gqa_kernel<THREADS, NCH, G, KPT, PAGED>;
   const size_t lds = GqaLds<THREADS, G>::total_bytes(s.S, s.k);
   static std::atomic<unsigned long long> lds_allowed{0};  // per instantiation: devices already set up
   const hipError_t e = allow_dynamic_lds(
@@ -85,12 +85,12 @@ static hipError_t launch_fused_gqa_k(const Shape& s, const void* q, const float*
   hipLaunchKernelGGL(kern, dim3(s.B * s.Hkv), dim3(THREADS), lds, st,
                      static_cast<const uint16_t*>(klo), static_cast<const uint16_t*>(khi),
                      static_cast<const uint16_t*>(v), static_cast<const uint16_t*>(q), P,
-                     static_cast<uint16_t*>(out), out_idx, s.Hkv, s.S, s.S_cap, s.k, s.rg, s.ap, s.pg,
+                     static_cast<uint16_t*>(out), out_idx, s.Hkv, s.S, s.S_cap, s.k, with_loads(s, kGroupLaunch), s.ap, s.pg,
                      ClusterArgs{});
   return hipGetLastError();
 }
 
-template <int NCH, int G, int STREAM>
+template <int NCH, int G>
 static hipError_t launch_fused_gqa_g(const Shape& s, const void* q, const float* P, const void* klo,
                                      const void* khi, const void* v, void* out, int32_t* out_idx,
                                      hipStream_t st) {
@@ -100,29 +100,22 @@ static hipError_t launch_fused_gqa_g(const Shape& s, const void* q, const float*
   const bool alone = s.B * s.Hkv <= device_cus();
   if (s.pg.table != nullptr) {  // (a paged cache: two block shapes)
     if (s.S > 256 * 32 || alone)
-      return launch_fused_gqa_k<512, NCH, G, 32, true, STREAM>(s, q, P, klo, khi, v, out, out_idx, st);
-    return launch_fused_gqa_k<256, NCH, G, 32, true, STREAM>(s, q, P, klo, khi, v, out, out_idx, st);
+      return launch_fused_gqa_k<512, NCH, G, 32, true>(s, q, P, klo, khi, v, out, out_idx, st);
+    return launch_fused_gqa_k<256, NCH, G, 32, true>(s, q, P, klo, khi, v, out, out_idx, st);
   }
-  if (s.S > 256 * 32 || alone) return launch_fused_gqa_k<512, NCH, G, 32, false, STREAM>(s, q, P, klo, khi, v, out, out_idx, st);
-  if (s.S <= 256 * 16) return launch_fused_gqa_k<256, NCH, G, 16, false, STREAM>(s, q, P, klo, khi, v, out, out_idx, st);
-  return launch_fused_gqa_k<256, NCH, G, 32, false, STREAM>(s, q, P, klo, khi, v, out, out_idx, st);
+  if (s.S > 256 * 32 || alone) return launch_fused_gqa_k<512, NCH, G, 32, false>(s, q, P, klo, khi, v, out, out_idx, st);
+  if (s.S <= 256 * 16) return launch_fused_gqa_k<256, NCH, G, 16, false>(s, q, P, klo, khi, v, out, out_idx, st);
+  return launch_fused_gqa_k<256, NCH, G, 32, false>(s, q, P, klo, khi, v, out, out_idx, st);
 }
 
 template <int NCH>
 static hipError_t launch_fused_gqa_n(const Shape& s, const void* q, const float* P, const void* klo,
                                      const void* khi, const void* v, void* out, int32_t* out_idx,
                                      hipStream_t st) {
-  const int stream = group_streams(s);
-  auto pick = [&](auto g) {
-    constexpr int G = decltype(g)::value;
-    if constexpr (NCH <= kStreamSlabChunks)
-      if (stream == kStreamValuesAndSlab) return launch_fused_gqa_g<NCH, G, kStreamValuesAndSlab>;
-    return stream ? launch_fused_gqa_g<NCH, G, kStreamValues> : launch_fused_gqa_g<NCH, G, 0>;
-  };
   switch (s.G) {
-    case 2: return pick(std::integral_constant<int, 2>{})(s, q, P, klo, khi, v, out, out_idx, st);
-    case 4: return pick(std::integral_constant<int, 4>{})(s, q, P, klo, khi, v, out, out_idx, st);
-    case 8: return pick(std::integral_constant<int, 8>{})(s, q, P, klo, khi, v, out, out_idx, st);
+    case 2: return launch_fused_gqa_g<NCH, 2>(s, q, P, klo, khi, v, out, out_idx, st);
+    case 4: return launch_fused_gqa_g<NCH, 4>(s, q, P, klo, khi, v, out, out_idx, st);
+    case 8: return launch_fused_gqa_g<NCH, 8>(s, q, P, klo, khi, v, out, out_idx, st);
     default: return hipErrorInvalidValue;
   }
 }

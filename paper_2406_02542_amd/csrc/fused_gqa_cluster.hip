@@ -131,13 +131,13 @@ size_t fused_gqa_cluster_bytes(const Shape& s, int select_mode) {
   return C ? cluster_plan(s, C).total : 0;
 }
 
-template <int NCH, int G, bool PAGED, int STREAM>
+template <int NCH, int G, bool PAGED>
 static hipError_t launch_cluster_k(const Shape& s, int C, const void* q, const float* P, const void* klo,
                                    const void* khi, const void* v, void* out, int32_t* out_idx,
                                    uint32_t* ctl, bool ctl_clean, void* region, uint32_t spin_limit,
                                    hipStream_t st) {
   using Lds = GqaLds<kClusterThreads, G, true>;
-  auto kern = fused_gqa_kernel<kClusterThreads, NCH, G, kClusterKpt, PAGED, STREAM, true>;
+  auto kern = fused_gqa_kernel<kClusterThreads, NCH, G, kClusterKpt, PAGED, true>;
   const int L = gqa_slice_rows(s.S, C);
   const size_t lds = Lds::total_bytes(L, s.k < L ? s.k : L);
   static std::atomic<unsigned long long> lds_allowed{0};  // per instantiation: devices already set up
@@ -168,7 +168,7 @@ static hipError_t launch_cluster_k(const Shape& s, int C, const void* q, const f
   hipLaunchKernelGGL(kern, dim3(cluster_padded_units(s) * C), dim3(kClusterThreads), lds, st,
                      static_cast<const uint16_t*>(klo), static_cast<const uint16_t*>(khi),
                      static_cast<const uint16_t*>(v), static_cast<const uint16_t*>(q), P,
-                     static_cast<uint16_t*>(out), out_idx, s.Hkv, s.S, s.S_cap, s.k, s.rg, s.ap, s.pg, cl);
+                     static_cast<uint16_t*>(out), out_idx, s.Hkv, s.S, s.S_cap, s.k, with_loads(s, kGroupLaunch), s.ap, s.pg, cl);
   return hipGetLastError();
 }
 
@@ -177,19 +177,13 @@ static hipError_t launch_cluster_n(const Shape& s, int C, const void* q, const f
                                    const void* khi, const void* v, void* out, int32_t* out_idx,
                                    uint32_t* ctl, bool ctl_clean, void* region, uint32_t spin_limit,
                                    hipStream_t st) {
-  const bool paged = s.pg.table != nullptr;
-  const int stream = group_streams(s);
-  auto pick = [&](auto g) {
-    constexpr int G = decltype(g)::value;
-    if constexpr (NCH <= kStreamSlabChunks)
-      if (stream == kStreamValuesAndSlab)
-        return paged ? launch_cluster_k<NCH, G, true, kStreamValuesAndSlab> : launch_cluster_k<NCH, G, false, kStreamValuesAndSlab>;
-    if (stream) return paged ? launch_cluster_k<NCH, G, true, kStreamValues> : launch_cluster_k<NCH, G, false, kStreamValues>;
-    return paged ? launch_cluster_k<NCH, G, true, 0> : launch_cluster_k<NCH, G, false, 0>;
-  };
-#define LOKI_CLUSTER_G(Gn)                                                                                             \
-  case Gn:                                                                                                             \
-    return pick(std::integral_constant<int, Gn>{})(s, C, q, P, klo, khi, v, out, out_idx, ctl, ctl_clean, region, spin_limit, st)
+#define LOKI_CLUSTER_G(Gn)                                                                              \
+  case Gn:                                                                                              \
+    return s.pg.table != nullptr                                                                        \
+               ? launch_cluster_k<NCH, Gn, true>(s, C, q, P, klo, khi, v, out, out_idx, ctl, ctl_clean, region, \
+                                                 spin_limit, st)                                        \
+               : launch_cluster_k<NCH, Gn, false>(s, C, q, P, klo, khi, v, out, out_idx, ctl, ctl_clean, region, \
+                                                  spin_limit, st)
   switch (s.G) {
     LOKI_CLUSTER_G(2);
     LOKI_CLUSTER_G(4);

@@ -118,16 +118,17 @@ struct GqaSteps {
 
 // THREADS = 256: two blocks share a CU (S <= 8192); 512: one block per CU (S <= 16384).
 // NCH = 16-byte chunks per slab row (d = 8 NCH); KPT = keys a thread holds in the select stage.
-// STREAM: see group_streams.
+// FORM: how the rows are loaded, see row_loads.
 // PAGED: the three slabs are pools addressed through the sequence's page list (see Paging): the
 // list sits in LDS, every slab load looks its page up, and the selected positions are translated
 // to pool rows before the attention stage.
 // CLUSTER: cl.C blocks work on one unit, block c on rows [c L, (c + 1) L) of it (L =
 // gqa_slice_rows); they find the threshold together (cluster_impl.h), each attends over the
 // selected rows of its slice, and the block that finishes last merges the partial results.
-template <int THREADS, int NCH, int G, int KPT, bool PAGED, int STREAM, bool CLUSTER = false>
-__global__ __launch_bounds__(THREADS, THREADS == 256 ? 2 : 1) void fused_gqa_kernel(
-    const uint16_t* klo, const uint16_t* khi, const uint16_t* v,
+template <int THREADS, int NCH, int G, int KPT, bool PAGED, int FORM, bool CLUSTER, int PAGES>
+__device__ __forceinline__ void fused_gqa_body(
+    float (&s_qhat)[G][kD], int32_t (&s_pages)[PAGES], ResidentSelectSmem<THREADS>& s_sel, ClusterSmem& s_cl, GqaList& s_list,
+    int& s_gidx_base, const uint16_t* klo, const uint16_t* khi, const uint16_t* v,
     const uint16_t* __restrict__ q, const float* __restrict__ P, uint16_t* __restrict__ out,
     int32_t* __restrict__ out_idx, int Hkv, int S_max, int S_cap, int k_max, Ragged rag, Append ap,
     Paging pg, ClusterArgs cl) {
@@ -135,7 +136,7 @@ __global__ __launch_bounds__(THREADS, THREADS == 256 ? 2 : 1) void fused_gqa_ker
   constexpr int PPW = kRotParts / kWaves;  // parts of the rotation a wave owns
   static_assert(PPW * kWaves == kRotParts, "the rotation's 8 parts divide over the waves");
   constexpr int d = 8 * NCH;
-  constexpr bool kStreamV = STREAM >= kStreamValues, kStreamSlab = STREAM >= kStreamValuesAndSlab;
+  constexpr bool kStreamV = FORM >= kPastCaches, kStreamSlab = FORM >= kPastCachesSlab;
   using Lds = GqaLds<THREADS, G, CLUSTER>;
 
   extern __shared__ __align__(16) unsigned char dyn_smem[];
@@ -146,13 +147,8 @@ __global__ __launch_bounds__(THREADS, THREADS == 256 ? 2 : 1) void fused_gqa_ker
   // rows of the longest slice (CLUSTER) / of the longest sequence: what the score region is laid out for
   const int L_max = CLUSTER ? gqa_slice_rows(S_max, cl.C) : S_max;
   int32_t* s_idx = reinterpret_cast<int32_t*>(dyn_smem + Lds::region_bytes(L_max));  // [min(k_max, L_max)]
-  __shared__ __align__(16) float s_qhat[G][kD];
   constexpr int kPages = CLUSTER ? kClusterMaxPages : kGqaMaxPages;
   static_assert(kPages <= THREADS, "a page a thread");
-  __shared__ int32_t s_pages[PAGED ? kPages : 1];
-  __shared__ ResidentSelectSmem<THREADS> s_sel;
-  __shared__ ClusterSmem s_cl;
-  __shared__ GqaList s_list;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r16 = lane & 15;
@@ -526,7 +522,6 @@ __global__ __launch_bounds__(THREADS, THREADS == 256 ? 2 : 1) void fused_gqa_ker
     if (gidx) {
       // the list holds the certain rows (ascending) followed by the chosen candidates (ascending);
       // the caller's copy is the merge of the two (CLUSTER: behind the rows of the blocks before)
-      __shared__ int s_gidx_base;
       if (tid == 0) s_gidx_base = gidx_base;
       __syncthreads();  // the list is complete
       const int n_list = !CLUSTER ? k : s_list.state == 1 ? s_list.n : 0, n_chosen = n_list - n_def;
@@ -604,6 +599,25 @@ __global__ __launch_bounds__(THREADS, THREADS == 256 ? 2 : 1) void fused_gqa_ker
     }
   }
   LOKI_STAMP(8);
+}
+
+template <int THREADS, int NCH, int G, int KPT, bool PAGED, bool CLUSTER = false>
+__global__ __launch_bounds__(THREADS, THREADS == 256 ? 2 : 1) void fused_gqa_kernel(
+    const uint16_t* klo, const uint16_t* khi, const uint16_t* v, const uint16_t* __restrict__ q, const float* __restrict__ P,
+    uint16_t* __restrict__ out, int32_t* __restrict__ out_idx, int Hkv, int S_max, int S_cap, int k_max, Ragged rag, Append ap,
+    Paging pg, ClusterArgs cl) {
+  __shared__ __align__(16) float s_qhat[G][kD];
+  __shared__ int32_t s_pages[PAGED ? (CLUSTER ? kClusterMaxPages : kGqaMaxPages) : 1];
+  __shared__ ResidentSelectSmem<THREADS> s_sel;
+  __shared__ ClusterSmem s_cl;
+  __shared__ GqaList s_list;
+  __shared__ int s_gidx_base;
+  constexpr int kMaxForm = NCH <= kSlabChunksPast ? kPastCachesSlab : kPastCaches;
+  with_form<kMaxForm>(form_of_launch(rag, S_max, k_max), [&](auto form) __attribute__((always_inline)) {
+    fused_gqa_body<THREADS, NCH, G, KPT, PAGED, decltype(form)::value, CLUSTER>(s_qhat, s_pages, s_sel, s_cl, s_list, s_gidx_base, klo,
+                                                                              khi, v, q, P, out, out_idx, Hkv, S_max, S_cap, k_max,
+                                                                              rag, ap, pg, cl);
+  });
 }
 
 }  // namespace loki

@@ -53,7 +53,7 @@ __host__ __device__ inline size_t fused_region_bytes(int S) {
 // lengths of the ranking and the block's own length and k from memory again / so: 4 sequences of 32
 // heads, S = 700 13.3 / 12.9, 60 of 16, S = 1000 47.4 / 46.7, 16 of 8 on pages, S = 2000 17.5 / 17.3.)
 struct FusedWork {
-  int unit, S, k;
+  int unit, S, k, form;  // form: see RowLoads
 };
 __device__ __forceinline__ FusedWork fused_work_of_block(const Ragged& rag, int B, int Hkv, int block, int S_max, int k_max) {
   if (rag.seq_lens != nullptr && B <= 64 && B >= 2) {
@@ -70,11 +70,16 @@ __device__ __forceinline__ FusedWork fused_work_of_block(const Ragged& rag, int 
     if (hit != 0ull) {  // (always: the ranks are a permutation of 0..B-1, exactly one lane holds each)
       const int b = __ffsll((long long)hit) - 1;
       const int S = min(max(__builtin_amdgcn_readlane(mine, b), 1), S_max);  // as seq_rows and seq_keep
-      return {b * Hkv + block % Hkv, S, max(1, min(__builtin_amdgcn_readlane(keep, b), min(k_max, S)))};
+      int form = rag.loads.form;
+      if (form == kByLengths) {
+        const int S_l = min(max(mine, 1), S_max), k_l = max(1, min(keep, min(k_max, S_l)));
+        form = form_of(rag.loads, {wave_sum_f32(lane < B ? (float)S_l : 0.f), wave_sum_f32(lane < B ? (float)k_l : 0.f)});
+      }
+      return {b * Hkv + block % Hkv, S, max(1, min(__builtin_amdgcn_readlane(keep, b), min(k_max, S))), form};
     }
   }
   const int S = seq_rows(rag, block / Hkv, S_max);
-  return {block, S, seq_keep(rag, block / Hkv, k_max, S)};
+  return {block, S, seq_keep(rag, block / Hkv, k_max, S), form_of_launch(rag, S_max, k_max)};
 }
 
 // APPEND: the block also rotates the unit's new key with the P_h entries it already holds and
@@ -91,12 +96,13 @@ constexpr int kFusedMaxPages = kFusedMaxS / 256;  // pages are at least 256 rows
 // 160 KB: S = 13800, k = 1725 fits, S = 16384 does not, and a block has its CU to itself at the
 // same budget.
 // KPT = keys a thread holds in the select stage (8 for S <= 4096, 16 for S <= 8192, else 32).
-// GROUPED: G query heads to a KV head, every one selecting for itself.  STREAM: see streams_rows (not
-// with groups, whose heads read the same slab and largely the same rows: 90.5 us either way, with the
-// slab's loads streamed too 96.7).
-template <typename T, int LPR, bool REUSE_LO, int KPT, bool APPEND, bool PAGED, bool GROUPED, bool STREAM>
-__global__ __launch_bounds__(kFusedThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) void
-fused_decode_kernel(
+// GROUPED: G query heads to a KV head, every one selecting for itself.  STREAM: the rows are loaded past the
+// caches, see row_loads (not with groups, whose heads read the same slab and largely the same rows: 90.5 us
+// either way, with the slab's loads streamed too 96.7).
+template <typename T, int LPR, bool REUSE_LO, int KPT, bool APPEND, bool PAGED, bool GROUPED, bool STREAM, int NEW, int PAGES>
+__device__ __forceinline__ void fused_decode_body(
+    const FusedWork& work, float (&s_q)[kD], float (&s_qhat)[1][kD], float (&s_kn)[NEW] /* the new key */,
+    ResidentSelectSmem<kFusedThreads>& s_sel, int32_t (&s_pages)[PAGES],
     const typename T::store_t* klo, const typename T::store_t* khi, const typename T::store_t* v,
     const typename T::store_t* __restrict__ q, const float* __restrict__ P,
     typename T::store_t* __restrict__ out, int32_t* __restrict__ out_idx, int n_seq, int Hkv, int G, int S_max,
@@ -118,27 +124,12 @@ fused_decode_kernel(
   int32_t* s_idx = reinterpret_cast<int32_t*>(dyn_smem + fused_region_bytes(S_max));  // [k_max]
   float* s_a = kScoreByRow ? reinterpret_cast<float*>(s_key) : reinterpret_cast<float*>(s_idx + k_max);
 
-  __shared__ __align__(16) float s_q[kD];
-  __shared__ float s_qhat[1][kD];
-  __shared__ __align__(16) float s_kn[APPEND ? kD : 4];                       // the new key
   static_assert(kFusedWaves == kRotParts, "one wave per part of the rotation");
-  __shared__ __align__(16) ResidentSelectSmem<kFusedThreads> s_sel;
   MergeSmem<kFusedWaves, 1>& s_merge = *reinterpret_cast<MergeSmem<kFusedWaves, 1>*>(&s_sel);  // behind the selection
   static_assert(sizeof(s_merge) <= sizeof(s_sel), "the merge fits the histograms");
-  __shared__ int32_t s_pages[PAGED ? kFusedMaxPages : 1];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   // head = b * Hq + query head; unit = b * Hkv + KV head, whose cache it reads
-  FusedWork work;
-  if constexpr (!GROUPED) {
-    work = fused_work_of_block(rag, (int)gridDim.x / Hkv, Hkv, (int)blockIdx.x, S_max, k_max);
-  } else {
-    // The G heads of a unit read the same slab and largely the same rows: blocks go to the 8 XCDs in
-    // turn, so a unit's heads are blocks 8 apart, on one XCD and next to each other in time.
-    const int slot = grouped_slot((int)blockIdx.x, G, n_seq * Hkv);
-    if (slot < 0) return;  // (padding of the launch; uniform for the block)
-    work = fused_work_of_block(rag, n_seq, Hkv, slot, S_max, k_max);
-  }
   const int unit = work.unit, S = work.S, k = work.k;
   const int head = GROUPED ? unit * G + grouped_head((int)blockIdx.x, G) : unit;
   const int h = unit % Hkv;
@@ -331,16 +322,44 @@ fused_decode_kernel(
   LOKI_STAMP(8);
 }
 
+template <typename T, int LPR, bool REUSE_LO, int KPT, bool APPEND, bool PAGED, bool GROUPED>
+__global__ __launch_bounds__(kFusedThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) void
+fused_decode_kernel(
+    const typename T::store_t* klo, const typename T::store_t* khi, const typename T::store_t* v,
+    const typename T::store_t* __restrict__ q, const float* __restrict__ P,
+    typename T::store_t* __restrict__ out, int32_t* __restrict__ out_idx, int n_seq, int Hkv, int G, int S_max,
+    int S_cap, int d, int k_max, Ragged rag, Append ap, Paging pg) {
+  __shared__ __align__(16) float s_q[kD];
+  __shared__ float s_qhat[1][kD];
+  __shared__ __align__(16) float s_kn[APPEND ? kD : 4];
+  __shared__ __align__(16) ResidentSelectSmem<kFusedThreads> s_sel;
+  __shared__ int32_t s_pages[PAGED ? kFusedMaxPages : 1];
+  FusedWork work;
+  if constexpr (!GROUPED) {
+    work = fused_work_of_block(rag, (int)gridDim.x / Hkv, Hkv, (int)blockIdx.x, S_max, k_max);
+  } else {
+    // The G heads of a unit read the same slab and largely the same rows: blocks go to the 8 XCDs in
+    // turn, so a unit's heads are blocks 8 apart, on one XCD and next to each other in time.
+    const int slot = grouped_slot((int)blockIdx.x, G, n_seq * Hkv);
+    if (slot < 0) return;  // (padding of the launch; uniform for the block)
+    work = fused_work_of_block(rag, n_seq, Hkv, slot, S_max, k_max);
+  }
+  with_form<GROUPED ? kThroughCaches : kPastCaches>(work.form, [&](auto form) __attribute__((always_inline)) {
+    fused_decode_body<T, LPR, REUSE_LO, KPT, APPEND, PAGED, GROUPED, decltype(form)::value != kThroughCaches>(
+        work, s_q, s_qhat, s_kn, s_sel, s_pages, klo, khi, v, q, P, out, out_idx, n_seq, Hkv, G, S_max, S_cap, d, k_max, rag, ap, pg);
+  });
+}
+
 inline size_t fused_dynamic_lds(const Shape& s) {
   const bool score_by_row = fused_keys_in_lds(s.S) && s.pg.table == nullptr;
   return fused_region_bytes(s.S) + (size_t)s.k * (score_by_row ? 4 : 8);
 }
 
-template <typename T, int LPR, bool REUSE_LO, int KPT, bool APPEND, bool PAGED, bool GROUPED, bool STREAM>
+template <typename T, int LPR, bool REUSE_LO, int KPT, bool APPEND, bool PAGED, bool GROUPED>
 static hipError_t launch_fused_k(const Shape& s, const void* q, const float* P, void* klo, void* khi,
                                  void* v, void* out, int32_t* out_idx, hipStream_t st) {
   using ST = typename T::store_t;
-  auto kern = fused_decode_kernel<T, LPR, REUSE_LO, KPT, APPEND, PAGED, GROUPED, STREAM>;
+  auto kern = fused_decode_kernel<T, LPR, REUSE_LO, KPT, APPEND, PAGED, GROUPED>;
   const size_t lds = fused_dynamic_lds(s);
   static std::atomic<unsigned long long> lds_allowed{0};  // per instantiation: devices already set up
   const hipError_t ea = allow_dynamic_lds(reinterpret_cast<const void*>(kern),
@@ -349,7 +368,7 @@ static hipError_t launch_fused_k(const Shape& s, const void* q, const float* P, 
   hipLaunchKernelGGL(kern, dim3(GROUPED ? (s.B * s.Hkv + 7) / 8 * 8 * s.G : s.B * s.Hkv), dim3(kFusedThreads), lds, st,
                      static_cast<const ST*>(klo), static_cast<const ST*>(khi),
                      static_cast<const ST*>(v), static_cast<const ST*>(q), P, static_cast<ST*>(out),
-                     out_idx, s.B, s.Hkv, s.G, s.S, s.S_cap, s.d, s.k, s.rg, s.ap, s.pg);
+                     out_idx, s.B, s.Hkv, s.G, s.S, s.S_cap, s.d, s.k, GROUPED ? s.rg : with_loads(s, 0), s.ap, s.pg);
   return hipGetLastError();
 }
 
@@ -359,19 +378,14 @@ static hipError_t launch_fused_a(const Shape& s, const void* q, const float* P, 
   const bool paged = s.pg.table != nullptr, append = s.ap.k_new != nullptr;
   if (s.G > 1) {
     if (append) return hipErrorInvalidValue;  // (G blocks read the row: it is appended by a launch before)
-    const auto launch = paged ? launch_fused_k<T, LPR, REUSE_LO, KPT, false, true, true, false>
-                              : launch_fused_k<T, LPR, REUSE_LO, KPT, false, false, true, false>;
+    const auto launch = paged ? launch_fused_k<T, LPR, REUSE_LO, KPT, false, true, true>
+                              : launch_fused_k<T, LPR, REUSE_LO, KPT, false, false, true>;
     return launch(s, q, P, klo, khi, v, out, out_idx, st);
   }
-  auto pick = [&](auto stream) {
-    constexpr bool STREAM = decltype(stream)::value;
-    if (append)
-      return paged ? launch_fused_k<T, LPR, REUSE_LO, KPT, true, true, false, STREAM>
-                   : launch_fused_k<T, LPR, REUSE_LO, KPT, true, false, false, STREAM>;
-    return paged ? launch_fused_k<T, LPR, REUSE_LO, KPT, false, true, false, STREAM>
-                 : launch_fused_k<T, LPR, REUSE_LO, KPT, false, false, false, STREAM>;
-  };
-  const auto launch = streams_rows(s, 0) ? pick(std::true_type{}) : pick(std::false_type{});
+  const auto launch = append ? (paged ? launch_fused_k<T, LPR, REUSE_LO, KPT, true, true, false>
+                                      : launch_fused_k<T, LPR, REUSE_LO, KPT, true, false, false>)
+                             : (paged ? launch_fused_k<T, LPR, REUSE_LO, KPT, false, true, false>
+                                      : launch_fused_k<T, LPR, REUSE_LO, KPT, false, false, false>);
   return launch(s, q, P, klo, khi, v, out, out_idx, st);
 }
 

@@ -11,12 +11,36 @@ namespace loki {
 
 constexpr int kD = 128;  // head dimension the kernels are written for
 
+// How a launch loads the rows of its caches: through the caches, past them, or past them with the slab of a
+// group while it is scored as well (single launches of groups with one selection; of the others' rows the
+// second is all).
+constexpr int kThroughCaches = 0, kPastCaches = 1, kPastCachesSlab = 2;
+constexpr int kByLengths = -1;  // the kernel decides, by the lengths of the batch
+struct RowLoads {
+  int form = kThroughCaches;
+  int entries = 0;          // of the batch
+  float row_bytes = 0.f;    // of the slab (dense attention: of keys and values), per row of a batch entry
+  float kept_bytes = 0.f;   // per row that a batch entry keeps
+  float max_share = 0.f;    // rows kept over rows, at most
+  float again_bytes = 0.f;  // slab lines that the attention reads again, per row kept; 0: never kPastCachesSlab
+};
+constexpr float kPastBytes = 90e6f, kPastSlabBytes = 80e6f, kPastSlabManyBytes = 180e6f;
+// The one rule, for the host, where it knows the sizes, and for the kernels (row_loads in api.hip has the
+// reasons).  rows, kept: sums over the batch.
+__host__ __device__ inline int loads_form(const RowLoads& l, float rows, float kept) {
+  if (rows * l.row_bytes + kept * l.kept_bytes < kPastBytes || kept > l.max_share * rows) return kThroughCaches;
+  const float slab = rows * l.row_bytes, again = kept * l.again_bytes;
+  if (l.again_bytes == 0.f || slab < kPastSlabBytes) return kPastCaches;
+  return again <= 0.18f * slab || (again <= 0.26f * slab && slab <= kPastSlabManyBytes) ? kPastCachesSlab : kPastCaches;
+}
+
 // Per-sequence sizes of a ragged batch, in device memory (a null pointer: the batch-wide value).
 struct Ragged {
   const int32_t* seq_lens = nullptr;  // [B] cached rows of each sequence, 1..S
   const int32_t* ks = nullptr;        // [B] rows each sequence keeps, 1..min(k, its seq_len)
   int queries = 1;  // consecutive batch entries that share one cached sequence (several new
                     // tokens per sequence: entry b reads and appends to the cache of b / queries)
+  RowLoads loads;   // of the launch at hand
 };
 
 // The current token's key and value when the step also appends them to the cache (Algorithm 1
@@ -73,16 +97,18 @@ constexpr int kDenseMaxRagged = 64;
 int dense_splits(const Shape& s, bool ragged);
 bool dense_balanced(const Shape& s, int nsplit);
 
-// Whether the rows that a call's attention reads, and with one query head per KV head the slab rows
-// it scores, are loaded past the caches.  select_mode: 0, 1 as in the call, or:
+// How a call's rows are loaded, those its attention reads and, with one query head per KV head, the slab rows
+// it scores.  select_mode: 0, 1 as in the call, or:
 constexpr int kEveryRow = -1;      // dense attention
 constexpr int kLowRankRows = -2;   // Algorithm 2: every value, the slab
-bool streams_rows(const Shape& s, int select_mode);
-// The same for the single launches of groups with one selection: 0, or the values of the selected rows,
-// or these and the slab while it is scored (slab rows of up to kStreamSlabChunks 16-byte chunks, of which
-// a load takes whole lines).
-constexpr int kStreamValues = 1, kStreamValuesAndSlab = 2, kStreamSlabChunks = 4;
-int group_streams(const Shape& s);
+constexpr int kGroupLaunch = 2;    // one selection per group, in a single launch
+RowLoads row_loads(const Shape& s, int select_mode);
+inline Ragged with_loads(const Shape& s, int select_mode) {
+  Ragged rg = s.rg;
+  rg.loads = row_loads(s, select_mode);
+  return rg;
+}
+constexpr int kSlabChunksPast = 4;  // 16-byte chunks of a slab row that may be scored past the caches: a load takes whole lines
 
 struct Workspace {
   float* qhat;       // [B*Hq, 128]

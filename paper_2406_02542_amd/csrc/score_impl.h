@@ -42,7 +42,7 @@ struct PagedRows {
 // qr is this lane's slice of qhat (zero for lanes past the slab row's last chunk); `rows`
 // maps a row to this lane's 16-byte chunk of it.  emit(row, scores[G]) is called once
 // per row by the lane that ends up owning it.  STREAM, here and below: rows are loaded past the
-// caches (streams_rows).
+// caches (row_loads).
 template <typename T, int LPR, int G, int WAVES, bool STREAM = false, typename Rows, typename Emit>
 __device__ __forceinline__ void score_rows(const Rows& rows, bool cact,
                                            const float (&qr)[G][T::EPC], int row0, int row_end,

@@ -171,7 +171,8 @@ __device__ __forceinline__ void share_of(int k, int nsplit, int split, int& r0, 
 
 // Vector form.  NH = query heads that share a selection; with one, the ranking score is the
 // low-rank part of the logit and the slab is not read again (REUSE_LO).
-template <typename T, int NH, int KPT, bool GROWING, bool STREAM>
+// (Whether the rows are loaded past the caches, see row_loads, is known when the list is.)
+template <typename T, int NH, int KPT, bool GROWING>
 __global__ __launch_bounds__(kSaThreads, NH == 1 ? 4 : 2) void select_attend_kernel(
     const void* __restrict__ klo, const void* __restrict__ khi, const void* __restrict__ v,
     const float* __restrict__ qhat, typename T::store_t* __restrict__ out, SelectAttendArgs a) {
@@ -203,6 +204,7 @@ __global__ __launch_bounds__(kSaThreads, NH == 1 ? 4 : 2) void select_attend_ker
   const int S = seq_rows(a.rg, b, a.S_max), k = seq_keep(a.rg, b, a.k_max, S);
   int r0, r1;
   share_of(k, a.nsplit, split, r0, r1);
+  const int form_now = form_of_launch(a.rg, a.S_max, a.k_max);
 
   float qr[NH][EPC];  // this lane's slice of the query vectors, on its way during the selection
 #pragma unroll
@@ -220,17 +222,22 @@ __global__ __launch_bounds__(kSaThreads, NH == 1 ? 4 : 2) void select_attend_ker
   const RowAddr ra = make_row_addr<T, REUSE_LO>(klo, khi, v, unit, a.S_cap, a.d, c);
   AttendAcc<T, NH> acc;
   acc.init();
-  if constexpr (GROWING)
-    attend_growing<T, NH, kSaWaves * RPW, REUSE_LO, STREAM>(
-        acc, qr, ra, s_idx, s_a, wave * RPW + rg, r0, r1, there, [&] { share.complete(a, hkv, r0, r1, s_sel, s_pages, s_idx, score); });
-  else
-    attend_rows<T, NH, kSaWaves * RPW, true, REUSE_LO, false, false, STREAM>(acc, qr, ra, s_idx, s_a, wave * RPW + rg, r0, r1);
+  with_form<kPastCaches>(form_now, [&](auto form) __attribute__((always_inline)) {
+    constexpr bool kPast = decltype(form)::value != kThroughCaches;
+    if constexpr (GROWING)
+      attend_growing<T, NH, kSaWaves * RPW, REUSE_LO, kPast>(
+          acc, qr, ra, s_idx, s_a, wave * RPW + rg, r0, r1, there, [&]() __attribute__((always_inline)) {
+            share.complete(a, hkv, r0, r1, s_sel, s_pages, s_idx, score);
+          });
+    else
+      attend_rows<T, NH, kSaWaves * RPW, true, REUSE_LO, false, false, kPast>(acc, qr, ra, s_idx, s_a, wave * RPW + rg, r0, r1);
+  });
   attend_publish<T, NH, kSaWaves>(acc, s_merge);
   finish_share<T, NH>(a, s_merge, head0, sel, split, out);
 }
 
 // Matrix-core form for 4 or 8 query heads that share a selection (bf16 caches, attend_mfma_impl.h).
-template <int NH, int KPT, bool GROWING, bool STREAM_V>
+template <int NH, int KPT, bool GROWING>
 __global__ __launch_bounds__(kSaThreads, 2) void select_attend_mfma_kernel(
     const void* __restrict__ klo, const void* __restrict__ khi, const void* __restrict__ v,
     const float* __restrict__ qhat, uint16_t* __restrict__ out, SelectAttendArgs a) {
@@ -247,6 +254,7 @@ __global__ __launch_bounds__(kSaThreads, 2) void select_attend_mfma_kernel(
   const int S = seq_rows(a.rg, b, a.S_max), k = seq_keep(a.rg, b, a.k_max, S);
   int r0, r1;
   share_of(k, a.nsplit, split, r0, r1);
+  const int form_now = form_of_launch(a.rg, a.S_max, a.k_max);
 
   __shared__ int32_t s_pages[GROWING ? kSaThreads * KPT / 256 : 1];
   SelectShare<KPT> share;
@@ -260,8 +268,11 @@ __global__ __launch_bounds__(kSaThreads, 2) void select_attend_mfma_kernel(
   const AmAddr<4> ad = am_make_addr<4, false>(klo, khi, v, addr_unit, a.S_cap, a.d);
   AmState st;
   st.init();
-  am_attend_rows<true, 4, 2, STREAM_V>(ad, bq, s_idx, r0, AmRoundRobin<kSaWaves>(r0, r1, there), st, [&] {
-    if constexpr (GROWING) share.complete(a, unit % a.Hkv, r0, r1, s_sel, s_pages, s_idx, nullptr);
+  with_form<kPastCaches>(form_now, [&](auto form) __attribute__((always_inline)) {
+    am_attend_rows<true, 4, 2, decltype(form)::value != kThroughCaches>(
+        ad, bq, s_idx, r0, AmRoundRobin<kSaWaves>(r0, r1, there), st, [&]() __attribute__((always_inline)) {
+          if constexpr (GROWING) share.complete(a, unit % a.Hkv, r0, r1, s_sel, s_pages, s_idx, nullptr);
+        });
   });
   am_publish<NH, kSaWaves>(st, s_merge);
   finish_share<BF16, NH>(a, s_merge, head0, unit, split, out);
@@ -332,44 +343,44 @@ static bool attention_begins_early(const SelectAttendArgs& a, dim3 grid) {
   return a.S_max > 2048 && a.S_max <= 8192 && a.xcd_group_blocks == 0 && (int)(grid.x * grid.y) <= device_cus();
 }
 
-template <typename T, int NH, bool STREAM>
+template <typename T, int NH>
 static hipError_t launch_sa(const SelectAttendArgs& a, dim3 grid, const void* klo, const void* khi, const void* v,
                             const float* qhat, void* out, hipStream_t st) {
   auto* o = static_cast<typename T::store_t*>(out);
   if constexpr (T::kBytes == 2 && NH == 1)
     if (attention_begins_early(a, grid)) {
       if (a.per_thread <= 8)
-        hipLaunchKernelGGL((select_attend_kernel<T, NH, 8, true, STREAM>), grid, dim3(kSaThreads), 0, st, klo, khi, v, qhat, o, a);
+        hipLaunchKernelGGL((select_attend_kernel<T, NH, 8, true>), grid, dim3(kSaThreads), 0, st, klo, khi, v, qhat, o, a);
       else
-        hipLaunchKernelGGL((select_attend_kernel<T, NH, 16, true, STREAM>), grid, dim3(kSaThreads), 0, st, klo, khi, v, qhat, o, a);
+        hipLaunchKernelGGL((select_attend_kernel<T, NH, 16, true>), grid, dim3(kSaThreads), 0, st, klo, khi, v, qhat, o, a);
       return hipGetLastError();
     }
   if (a.per_thread <= 8)
-    hipLaunchKernelGGL((select_attend_kernel<T, NH, 8, false, STREAM>), grid, dim3(kSaThreads), 0, st, klo, khi, v, qhat, o, a);
+    hipLaunchKernelGGL((select_attend_kernel<T, NH, 8, false>), grid, dim3(kSaThreads), 0, st, klo, khi, v, qhat, o, a);
   else if (a.per_thread <= 16)
-    hipLaunchKernelGGL((select_attend_kernel<T, NH, 16, false, STREAM>), grid, dim3(kSaThreads), 0, st, klo, khi, v, qhat, o, a);
+    hipLaunchKernelGGL((select_attend_kernel<T, NH, 16, false>), grid, dim3(kSaThreads), 0, st, klo, khi, v, qhat, o, a);
   else
-    hipLaunchKernelGGL((select_attend_kernel<T, NH, 32, false, STREAM>), grid, dim3(kSaThreads), 0, st, klo, khi, v, qhat, o, a);
+    hipLaunchKernelGGL((select_attend_kernel<T, NH, 32, false>), grid, dim3(kSaThreads), 0, st, klo, khi, v, qhat, o, a);
   return hipGetLastError();
 }
 
-template <int NH, bool STREAM>
+template <int NH>
 static hipError_t launch_sa_mfma(const SelectAttendArgs& a, dim3 grid, const void* klo, const void* khi, const void* v,
                                  const float* qhat, void* out, hipStream_t st) {
   auto* o = static_cast<uint16_t*>(out);
   if (attention_begins_early(a, grid)) {
     if (a.per_thread <= 8)
-      hipLaunchKernelGGL((select_attend_mfma_kernel<NH, 8, true, STREAM>), grid, dim3(kSaThreads), 0, st, klo, khi, v, qhat, o, a);
+      hipLaunchKernelGGL((select_attend_mfma_kernel<NH, 8, true>), grid, dim3(kSaThreads), 0, st, klo, khi, v, qhat, o, a);
     else
-      hipLaunchKernelGGL((select_attend_mfma_kernel<NH, 16, true, STREAM>), grid, dim3(kSaThreads), 0, st, klo, khi, v, qhat, o, a);
+      hipLaunchKernelGGL((select_attend_mfma_kernel<NH, 16, true>), grid, dim3(kSaThreads), 0, st, klo, khi, v, qhat, o, a);
     return hipGetLastError();
   }
   if (a.per_thread <= 8)
-    hipLaunchKernelGGL((select_attend_mfma_kernel<NH, 8, false, STREAM>), grid, dim3(kSaThreads), 0, st, klo, khi, v, qhat, o, a);
+    hipLaunchKernelGGL((select_attend_mfma_kernel<NH, 8, false>), grid, dim3(kSaThreads), 0, st, klo, khi, v, qhat, o, a);
   else if (a.per_thread <= 16)
-    hipLaunchKernelGGL((select_attend_mfma_kernel<NH, 16, false, STREAM>), grid, dim3(kSaThreads), 0, st, klo, khi, v, qhat, o, a);
+    hipLaunchKernelGGL((select_attend_mfma_kernel<NH, 16, false>), grid, dim3(kSaThreads), 0, st, klo, khi, v, qhat, o, a);
   else
-    hipLaunchKernelGGL((select_attend_mfma_kernel<NH, 32, false, STREAM>), grid, dim3(kSaThreads), 0, st, klo, khi, v, qhat, o, a);
+    hipLaunchKernelGGL((select_attend_mfma_kernel<NH, 32, false>), grid, dim3(kSaThreads), 0, st, klo, khi, v, qhat, o, a);
   return hipGetLastError();
 }
 
@@ -379,7 +390,7 @@ hipError_t launch_select_attend(const Shape& s, int select_mode, const float* sc
   if (!select_attend_applies(s, select_mode)) return hipErrorInvalidValue;
   const int NH = select_mode == 1 ? s.G : 1, nsplit = select_attend_splits(s, select_mode);
   if (div_up(s.k, nsplit) > kMaxGatherChunk) return hipErrorInvalidValue;
-  const bool mfma = attend_mfma_applies(s, NH), stream = streams_rows(s, select_mode);
+  const bool mfma = attend_mfma_applies(s, NH);
   SelectAttendArgs a;
   a.scores = scores;
   a.user_idx = user_idx;
@@ -394,14 +405,13 @@ hipError_t launch_select_attend(const Shape& s, int select_mode, const float* sc
   a.nsplit = nsplit;
   a.per_thread = ((s.S + kSaThreads - 1) / kSaThreads + 3) & ~3;
   a.xcd_group_blocks = a.xcd_sets = 0;
-  a.rg = s.rg;
+  a.rg = with_loads(s, select_mode);
   a.pg = s.pg;
   int blocks_y = s.B * s.Hq / NH;
   if (mfma) {
     const dim3 grid(nsplit, blocks_y);
-    const auto launch = NH == 8 ? (stream ? launch_sa_mfma<8, true> : launch_sa_mfma<8, false>)
-                                : (stream ? launch_sa_mfma<4, true> : launch_sa_mfma<4, false>);
-    return launch(a, grid, klo, khi, v, qhat, out, st);
+    return NH == 8 ? launch_sa_mfma<8>(a, grid, klo, khi, v, qhat, out, st)
+                   : launch_sa_mfma<4>(a, grid, klo, khi, v, qhat, out, st);
   }
   const int tokens = s.rg.queries > 1 ? s.rg.queries : 1;
   const int sharers = tokens * s.G, sets = s.B / tokens * s.Hkv, rounds = (sets + 7) / 8;
@@ -411,9 +421,7 @@ hipError_t launch_select_attend(const Shape& s, int select_mode, const float* sc
     blocks_y = rounds * 8 * sharers;
   }
   const dim3 grid(nsplit, blocks_y);
-#define LOKI_SA(T, NHV)                                                            \
-  return stream ? launch_sa<T, NHV, true>(a, grid, klo, khi, v, qhat, out, st)     \
-                : launch_sa<T, NHV, false>(a, grid, klo, khi, v, qhat, out, st)
+#define LOKI_SA(T, NHV) return launch_sa<T, NHV>(a, grid, klo, khi, v, qhat, out, st)
   if (s.dtype == 0) {
     switch (NH) {
       case 1: LOKI_SA(F32, 1);
