@@ -492,8 +492,9 @@ static int decode_impl(const loki_layout* layout, const void* q, const float* P,
   int32_t* idx = out_idx ? out_idx : w.sel_idx;
   StageTimer tm(st);
   hipError_t e;
-  // (pinned, the single-launch paths take page tables of up to 64 pages per sequence; by themselves they
-  // hold the pages of the rows there are, whatever the table's width)
+  // (pinned, the single launches of groups refuse page tables of more than 64 pages per sequence, that of one
+  // query head per KV head of more than 32 (fused_pinnable): a promise to callers who pin a path, no limit of
+  // the kernels, which hold the pages of the rows there are)
   const bool wide_table = pg.table != nullptr && pg.pages_per_seq > 64;
   if (path == LOKI_PATH_CLUSTER && (s.G == 1 || wide_table || !fused_gqa_cluster_eligible(s, select_mode)))
     return LOKI_ERR_UNSUPPORTED;
