@@ -287,15 +287,16 @@ template <int N>
 __device__ __forceinline__ double row_bcast_f64(double x) { return dpp_mov_f64<0x150 + N>(x); }
 
 // ---- eigenpairs of the tridiagonal matrix ------------------------------------------------------
-// Block (slice, head): eigenvalues 16 slice .. 16 slice + 15 in increasing order, 16 threads each.
+// Block (head, slice): eigenvalues 16 slice .. 16 slice + 15 in increasing order, 16 threads each.
 // Multisection: a pass evaluates the Sturm count at 16 points of the bracket, 13 passes of 1/17 take
 // the Gershgorin interval to 2e-16 of its length (a pass is a chain of 128 dependent steps
 // whatever the number of points).  The counts use the determinants' recurrence, one dependent
 // multiply-add a step, and not the quotients', whose reciprocal makes the chain six times as
-// long (the kernel, 32 heads: 89 us against 169); the determinants are scaled by a power of
-// two every 8 steps, and the matrix to norm 1, so that nothing over- or underflows.  The twisted
-// factorisation runs its two directions in two lane groups at once and needs no starting vector;
-// the reflectors are applied with a vector's 128 entries spread over 16 lanes.
+// long (the kernel, 32 heads: 89 us against 169, with the reflectors still on the vector units);
+// the determinants are scaled by a power of two every 8 steps, and the matrix to norm 1, so that
+// nothing over- or underflows.  The twisted factorisation runs its two directions in two lane groups
+// at once and needs no starting vector; the reflectors are applied sixteen at a time on the matrix
+// cores, the vectors lying in the accumulators (64 us).
 __global__ __launch_bounds__(kEigThreads) void eigvec_kernel(EigBufs bufs) {
   constexpr int kN = kEigSliceRows;
   constexpr int kPasses = 13;
