@@ -106,7 +106,7 @@ __device__ __forceinline__ void fused_decode_body(
     const typename T::store_t* klo, const typename T::store_t* khi, const typename T::store_t* v,
     const typename T::store_t* __restrict__ q, const float* __restrict__ P,
     typename T::store_t* __restrict__ out, int32_t* __restrict__ out_idx, int n_seq, int Hkv, int G, int S_max,
-    int S_cap, int d, int k_max, Ragged rag, Append ap, Paging pg) {
+    int S_cap, int d, int k_max, bool long_trips, Ragged rag, Append ap, Paging pg) {
   using ST = typename T::store_t;
   constexpr int EPC = T::EPC;
   constexpr int LPRV = kD / EPC;
@@ -302,11 +302,12 @@ __device__ __forceinline__ void fused_decode_body(
   // 4.  us, 4 / 8: 8 heads, S = 1024, k = 256 11.9 / 11.5, 128, S = 4096, k = 1024 43.6 / 40.8, on pages
   // S = 8000, k = 2000 79.0 / 75.1; but with two blocks on a CU and short lists 512 heads, k = 175 24.6 /
   // 25.6, k = 256 26.1 / 27.2, in groups of 4, k = 375 41.7 / 42.4; bf16, 512 heads, S = 4096 60.8 / 63.3.
+  // So: where every block has a CU, or the list is long (launch_fused_k).
   // What a trip of 4 can hold at the list's end is left to one (us, all in trips of 8 / so: 16
   // heads, S = 700, k = 42 10.1 / 9.5, k = 129 11.4 / 11.0; 64, S = 1500, k = 129 13.3 / 12.9).
   if constexpr (T::kBytes == 4 && !kKeysInLds) {
     constexpr int kTrip = kFusedWaves * RPW * kRowsInFlight;  // rows of a trip of 4
-    const int long_rows = gridDim.x <= 256 || (!GROUPED && k_max >= 320) ? (k + kTrip - 1) / (2 * kTrip) * (2 * kTrip) : 0;
+    const int long_rows = long_trips ? (k + kTrip - 1) / (2 * kTrip) * (2 * kTrip) : 0;
     attend(std::integral_constant<int, 2 * kRowsInFlight>{}, 0, min(long_rows, k));
     attend(std::integral_constant<int, kRowsInFlight>{}, long_rows, k);
   } else {
@@ -328,7 +329,7 @@ fused_decode_kernel(
     const typename T::store_t* klo, const typename T::store_t* khi, const typename T::store_t* v,
     const typename T::store_t* __restrict__ q, const float* __restrict__ P,
     typename T::store_t* __restrict__ out, int32_t* __restrict__ out_idx, int n_seq, int Hkv, int G, int S_max,
-    int S_cap, int d, int k_max, Ragged rag, Append ap, Paging pg) {
+    int S_cap, int d, int k_max, bool long_trips, Ragged rag, Append ap, Paging pg) {
   __shared__ __align__(16) float s_q[kD];
   __shared__ float s_qhat[1][kD];
   __shared__ __align__(16) float s_kn[APPEND ? kD : 4];
@@ -346,7 +347,8 @@ fused_decode_kernel(
   }
   with_form<GROUPED ? kThroughCaches : kPastCaches>(work.form, [&](auto form) __attribute__((always_inline)) {
     fused_decode_body<T, LPR, REUSE_LO, KPT, APPEND, PAGED, GROUPED, decltype(form)::value != kThroughCaches>(
-        work, s_q, s_qhat, s_kn, s_sel, s_pages, klo, khi, v, q, P, out, out_idx, n_seq, Hkv, G, S_max, S_cap, d, k_max, rag, ap, pg);
+        work, s_q, s_qhat, s_kn, s_sel, s_pages, klo, khi, v, q, P, out, out_idx, n_seq, Hkv, G, S_max, S_cap, d, k_max, long_trips,
+        rag, ap, pg);
   });
 }
 
@@ -365,10 +367,12 @@ static hipError_t launch_fused_k(const Shape& s, const void* q, const float* P, 
   const hipError_t ea = allow_dynamic_lds(reinterpret_cast<const void*>(kern),
                                           (int)(fused_region_bytes(kFusedMaxS) + kFusedMaxK * 8), lds_allowed);
   if (ea != hipSuccess) return ea;
-  hipLaunchKernelGGL(kern, dim3(GROUPED ? (s.B * s.Hkv + 7) / 8 * 8 * s.G : s.B * s.Hkv), dim3(kFusedThreads), lds, st,
+  const int blocks = GROUPED ? (s.B * s.Hkv + 7) / 8 * 8 * s.G : s.B * s.Hkv;
+  const bool long_trips = blocks <= device_cus() || (!GROUPED && s.k >= 320);  // fp32: see the attention's trips
+  hipLaunchKernelGGL(kern, dim3(blocks), dim3(kFusedThreads), lds, st,
                      static_cast<const ST*>(klo), static_cast<const ST*>(khi),
                      static_cast<const ST*>(v), static_cast<const ST*>(q), P, static_cast<ST*>(out),
-                     out_idx, s.B, s.Hkv, s.G, s.S, s.S_cap, s.d, s.k, GROUPED ? s.rg : with_loads(s, 0), s.ap, s.pg);
+                     out_idx, s.B, s.Hkv, s.G, s.S, s.S_cap, s.d, s.k, long_trips, GROUPED ? s.rg : with_loads(s, 0), s.ap, s.pg);
   return hipGetLastError();
 }
 
