@@ -122,3 +122,33 @@ def test_streamed_pca_attn(G, d):
             ref = torch.softmax(a, -1) @ v[b, h].double()
             err = float((out[b, h * G:(h + 1) * G].double() - ref).norm() / ref.norm())
             assert err < 6e-3, (b, h, err)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("ragged", [False, True])
+def test_the_form_does_not_change_results(dtype, ragged):
+    """One block per head: a large batch past the caches, and its first sequences as a batch of their own through them,
+    are the same bit for bit."""
+    c = decode(16, 32, 32, 2701, 32, 500, dtype=dtype, ragged=ragged)
+    s = C.prepare(c, 7)
+    x, n, dt = s["x"], 3, C._dtype(c)
+    if ragged:
+        x["lens"].sort()  # the first sequences are the short ones
+        x["ks"][:] = [max(1, int(r) * c["k"] // c["S"]) for r in x["lens"]]
+        s["step"] = {k: torch.from_numpy(x[v]).cuda() for k, v in [("seq_lens", "lens"), ("ks", "ks")]}
+
+    def loaded_and_out(B):
+        lay = api.make_layout(B, 32, 32, 128, c["d"], x["cap"], dt)
+        rows, kept = float(x["lens"][:B].sum()), float(x["ks"][:B].sum())
+        step = {k: v[:B] for k, v in s["step"].items()}
+        args = api.StepArgs(**{k: v.data_ptr() for k, v in step.items()}) if step else None
+        form = api.loki_debug_row_loads(lay, c["S"], c["d"], c["k"], 0, args, rows, kept)
+        ws = api.alloc_workspace(lay, c["S"], c["d"], c["k"], 0)
+        out = torch.empty((B, 32, 128), dtype=dt, device="cuda")
+        api.loki_decode_step(lay, x["q"][:B], x["P"], x["klo"][:B], x["khi"][:B], x["v"][:B], c["S"], c["d"], c["k"], 0, ws, out, **step)
+        return form, out
+
+    (form_all, all_), (form_few, few) = loaded_and_out(16), loaded_and_out(n)
+    torch.cuda.synchronize()
+    assert (form_all, form_few) == (1, 0)
+    assert torch.equal(all_[:n], few)
