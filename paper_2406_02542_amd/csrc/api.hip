@@ -79,7 +79,9 @@ int score_rows_per_block(const Shape& s) {
 //     / 15.1
 // Heads that select for themselves in a group, or tokens of a sequence, find rows that the others
 // have just read: not beyond half of the rows (72 units of 8 heads, k = S / 8 42.1 / 44.4; 2 tokens,
-// k = S / 4, one head 63.8 / 57.8; groups of 4, k = S / 16 91.1 / 86.8).
+// k = S / 4, one head 63.8 / 57.8; groups of 4, k = S / 16 91.1 / 86.8).  At the line, lists of one row more and
+// of half together: 16 x 32/8 heads, S = 16384 142.9 / 131.9, 8 x 32/16, S = 16000 132.6 / 129.1, 32 x 64/8,
+// S = 8192, d = 64 171.6 / 163.1; 2 tokens of 4 x 32 heads, S = 6000 58.4 / 54.4.
 // And not in groups beyond 16384 rows, where it turns on how much the heads' lists have in common (4 x 32/8
 // heads, S = 131072, k = 8192 207 / 203, 169 / 173 with attention peaked on the same rows).
 // Lengths of their own are not known here, so the blocks add them up and decide.  us, through / past / as the
