@@ -164,37 +164,6 @@ __device__ inline float group_allreduce_sum(float x) {
   return x;
 }
 
-// The sum over the wave, the same in every lane, without LDS.
-__device__ __forceinline__ float wave_sum_f32(float x) {
-  const int r = __float_as_int(group_allreduce_sum<16>(x));
-  auto row = [&](int lane) { return __int_as_float(__builtin_amdgcn_readlane(r, lane)); };
-  return (row(0) + row(16)) + (row(32) + row(48));
-}
-
-// The rows of a batch's entries and the rows they keep, added up; every wave for itself, lane l entries l, l + 64, ..
-struct RowSums {
-  float rows, kept;
-};
-__device__ __forceinline__ RowSums row_sums(const Ragged& rg, int S_max, int k_max) {
-  const int n = rg.loads.entries, lane = (int)(threadIdx.x & 63);
-  float rows = 0.f, kept = 0.f;
-  for (int b0 = 0; b0 < n; b0 += 64) {  // (uniform; no branch around the loads)
-    const int b = min(b0 + lane, n - 1);
-    const int S = seq_rows(rg, b, S_max), k = seq_keep(rg, b, k_max, S);
-    rows += b0 + lane < n ? (float)S : 0.f;
-    kept += b0 + lane < n ? (float)k : 0.f;
-  }
-  return {wave_sum_f32(rows), wave_sum_f32(kept)};
-}
-// The form of this launch's loads, the same for all its blocks.
-__device__ __forceinline__ int form_of(const RowLoads& l, const RowSums& sums) {
-  return __builtin_amdgcn_readfirstlane(loads_form(l, sums.rows, sums.kept));
-}
-__device__ __forceinline__ int form_of_launch(const Ragged& rg, int S_max, int k_max) {
-  if (rg.loads.form != kByLengths) return rg.loads.form;
-  return form_of(rg.loads, row_sums(rg, S_max, k_max));
-}
-
 // Maximum over each aligned group of LANES consecutive lanes (LANES <= 16), to every lane.
 template <int LANES>
 __device__ inline float group_allreduce_max(float x) {
@@ -220,6 +189,38 @@ __device__ __forceinline__ uint32_t wave_inclusive_scan_u32(uint32_t x) {
   x += dpp_u32<0x142, 0xa, false>(x);  // row_bcast:15 into rows 1 and 3
   x += dpp_u32<0x143, 0xc, false>(x);  // row_bcast:31 into rows 2 and 3
   return x;
+}
+
+// The sum over the wave, the same in every lane, without LDS.
+__device__ __forceinline__ float wave_sum_f32(float x) {
+  x = group_allreduce_sum<16>(x);
+  x += __uint_as_float(dpp_u32<0x142, 0xa, false>(__float_as_uint(x)));  // row_bcast:15 into rows 1 and 3
+  x += __uint_as_float(dpp_u32<0x143, 0xc, false>(__float_as_uint(x)));  // row_bcast:31 into rows 2 and 3
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 63));
+}
+
+// The rows of a batch's entries and the rows they keep, added up; every wave for itself, lane l entries l, l + 64, ..
+struct RowSums {
+  float rows, kept;
+};
+__device__ __forceinline__ RowSums row_sums(const Ragged& rg, int S_max, int k_max) {
+  const int n = rg.loads.entries, lane = (int)(threadIdx.x & 63);
+  float rows = 0.f, kept = 0.f;
+  for (int b0 = 0; b0 < n; b0 += 64) {  // (uniform; no branch around the loads)
+    const int b = min(b0 + lane, n - 1);
+    const int S = seq_rows(rg, b, S_max), k = seq_keep(rg, b, k_max, S);
+    rows += b0 + lane < n ? (float)S : 0.f;
+    kept += b0 + lane < n ? (float)k : 0.f;
+  }
+  return {wave_sum_f32(rows), wave_sum_f32(kept)};
+}
+// The form of this launch's loads, the same for all its blocks.
+__device__ __forceinline__ int form_of(const RowLoads& l, const RowSums& sums) {
+  return __builtin_amdgcn_readfirstlane(loads_form(l, sums.rows, sums.kept));
+}
+__device__ __forceinline__ int form_of_launch(const Ragged& rg, int S_max, int k_max) {
+  if (rg.loads.form != kByLengths) return rg.loads.form;
+  return form_of(rg.loads, row_sums(rg, S_max, k_max));
 }
 
 __device__ inline float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
