@@ -20,7 +20,7 @@ constexpr int kAttWaves = kAttThreads / 64;
 // blocks of a KV head are dealt out over its sequences by length (dense_runs).
 template <typename T, int NH, bool GATHER, bool REUSE_LO, bool STREAM, bool LO_ONLY, bool BALANCED, int LIST, int SAVED>
 __device__ __forceinline__ void attend_body(
-    int32_t (&s_idx)[LIST], float (&s_a)[SAVED], MergeSmem<kAttWaves, NH>& s_merge, int len /* BALANCED: dense_len */,
+    int32_t (&s_idx)[LIST], float (&s_a)[SAVED], MergeSmem<kAttWaves, NH>& s_merge, const DenseRuns& deal /* BALANCED */,
     const void* __restrict__ k_a,   // GATHER: klo [units, S_cap, d]; dense: K [units, S_cap, 128]
     const void* __restrict__ k_b,   // GATHER: khi [units, S_cap, 128-d]; dense: unused
     const void* __restrict__ v,     // [units, S_cap, 128]
@@ -63,15 +63,13 @@ __device__ __forceinline__ void attend_body(
   if constexpr (BALANCED) {
     const int Hkv = Hq / Gq, B = (int)gridDim.y / Hkv;
     const int X = nsplit * B, id = by * nsplit + bx, x = id % X;
-    int runs, incl;
-    dense_runs(len, B, nsplit, runs, incl);
-    const unsigned long long behind = __ballot(incl > x);
+    const unsigned long long behind = __ballot(deal.incl > x);
     if (behind == 0ull) return;  // uniform for the block: no run is left for it
     const int b = __ffsll((long long)behind) - 1;
-    const int n_b = __builtin_amdgcn_readlane(runs, b), base = __builtin_amdgcn_readlane(incl, b) - n_b;
+    const int n_b = __builtin_amdgcn_readlane(deal.runs, b), base = __builtin_amdgcn_readlane(deal.incl, b) - n_b;
     by = b * Hkv + id / X;
     bx = x - base;
-    run_rows = (__builtin_amdgcn_readlane(len, b) + n_b - 1) / n_b;
+    run_rows = (__builtin_amdgcn_readlane(deal.len, b) + n_b - 1) / n_b;
     part_stride = (size_t)X;
     part0 = (size_t)(id / X) * Gq * X + x;
   }
@@ -165,11 +163,12 @@ __global__ __launch_bounds__(kAttThreads) void attend_kernel(
   __shared__ int32_t s_idx[GATHER ? kMaxGatherChunk : 1];
   __shared__ float s_a[REUSE_LO ? kMaxGatherChunk : 1];
   __shared__ MergeSmem<kAttWaves, NH> s_merge;
-  const int len = BALANCED ? dense_len(rag, (int)gridDim.y / (Hq / Gq), S_max) : 0;
-  const int form_now = BALANCED ? dense_form(rag.loads, len) : form_of_launch(rag, S_max, n_max);
+  DenseRuns deal;
+  if constexpr (BALANCED) deal = dense_runs(rag, (int)gridDim.y / (Hq / Gq), S_max, nsplit);
+  const int form_now = BALANCED ? dense_form(rag.loads, deal) : form_of_launch(rag, S_max, n_max);
   with_form<kPastCaches>(form_now, [&](auto form) __attribute__((always_inline)) {
     attend_body<T, NH, GATHER, REUSE_LO, decltype(form)::value != kThroughCaches, LO_ONLY, BALANCED>(
-        s_idx, s_a, s_merge, len, k_a, k_b, v, qv, sel_idx, sel_score, partial, tickets, out, Hq, Gq, S_cap, d, n_max, rows_per_block,
+        s_idx, s_a, s_merge, deal, k_a, k_b, v, qv, sel_idx, sel_score, partial, tickets, out, Hq, Gq, S_cap, d, n_max, rows_per_block,
         nsplit, S_max, rag, pg, xcd_group_blocks, xcd_sets);
   });
 }
@@ -185,11 +184,10 @@ __global__ __launch_bounds__(kD) void combine_kernel(const float* __restrict__ p
   size_t first = head * nsplit;
   int n = nsplit;
   if constexpr (BALANCED) {
-    int runs, incl;
-    dense_runs(dense_len(rg, B, S_max), B, nsplit, runs, incl);
+    const DenseRuns deal = dense_runs(rg, B, S_max, nsplit);
     const int b = (int)(head / Hq);
-    n = __builtin_amdgcn_readlane(runs, b);
-    first = (head % Hq) * (size_t)nsplit * B + (__builtin_amdgcn_readlane(incl, b) - n);
+    n = __builtin_amdgcn_readlane(deal.runs, b);
+    first = (head % Hq) * (size_t)nsplit * B + (__builtin_amdgcn_readlane(deal.incl, b) - n);
   }
   T::store1(out + head * kD + col, combine_splits<false>(partial + first * kPartialStride, n, col));
 }

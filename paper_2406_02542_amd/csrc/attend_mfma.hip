@@ -36,7 +36,7 @@ constexpr int kAmWaves = kAmThreads / 64;
 // BALANCED (dense): the blocks of a KV head are dealt out over its sequences by length (dense_runs).
 template <int NH, bool GATHER, bool STREAM_V, int KSTEPS, bool LO_ONLY, bool BALANCED, int LIST>
 __device__ __forceinline__ void attend_mfma_body(
-    int32_t (&s_idx)[LIST], MergeSmem<kAmWaves, NH>& s_merge, int len /* BALANCED: dense_len */,
+    int32_t (&s_idx)[LIST], MergeSmem<kAmWaves, NH>& s_merge, const DenseRuns& deal /* BALANCED */,
     const void* __restrict__ k_a,   // GATHER: klo [units, S_cap, d]; dense: K [units, S_cap, 128]
     const void* __restrict__ k_b,   // GATHER: khi [units, S_cap, 128-d]; dense: unused
     const void* __restrict__ v,     // [units, S_cap, 128]
@@ -58,15 +58,13 @@ __device__ __forceinline__ void attend_mfma_body(
   if constexpr (BALANCED) {
     const int B = (int)gridDim.y / Hkv;
     const int X = nsplit * B, id = kv_unit * nsplit + split, x = id % X;
-    int runs, incl;
-    dense_runs(len, B, nsplit, runs, incl);
-    const unsigned long long behind = __ballot(incl > x);
+    const unsigned long long behind = __ballot(deal.incl > x);
     if (behind == 0ull) return;  // uniform for the block: no run is left for it
     const int b = __ffsll((long long)behind) - 1;
-    const int n_b = __builtin_amdgcn_readlane(runs, b), base = __builtin_amdgcn_readlane(incl, b) - n_b;
+    const int n_b = __builtin_amdgcn_readlane(deal.runs, b), base = __builtin_amdgcn_readlane(deal.incl, b) - n_b;
     kv_unit = b * Hkv + id / X;
     split = x - base;
-    run_rows = (__builtin_amdgcn_readlane(len, b) + n_b - 1) / n_b;
+    run_rows = (__builtin_amdgcn_readlane(deal.len, b) + n_b - 1) / n_b;
     part_stride = (size_t)X;
     part0 = (size_t)(id / X) * NH * X + x;
   } else {
@@ -151,11 +149,12 @@ __global__ __launch_bounds__(kAmThreads, 2) void attend_mfma_kernel(
     int rows_per_block, int nsplit, int Hkv, int S_max, Ragged rg, Paging pg) {
   __shared__ __align__(16) int32_t s_idx[GATHER ? kMaxGatherChunk : 1];
   __shared__ __align__(16) MergeSmem<kAmWaves, NH> s_merge;
-  const int len = BALANCED ? dense_len(rg, (int)gridDim.y / Hkv, S_max) : 0;
-  const int form_now = BALANCED ? dense_form(rg.loads, len) : form_of_launch(rg, S_max, n_max);
+  DenseRuns deal;
+  if constexpr (BALANCED) deal = dense_runs(rg, (int)gridDim.y / Hkv, S_max, nsplit);
+  const int form_now = BALANCED ? dense_form(rg.loads, deal) : form_of_launch(rg, S_max, n_max);
   with_form<kPastCaches>(form_now, [&](auto form) __attribute__((always_inline)) {
     attend_mfma_body<NH, GATHER, decltype(form)::value != kThroughCaches, KSTEPS, LO_ONLY, BALANCED>(
-        s_idx, s_merge, len, k_a, k_b, v, qv, sel_idx, partial, tickets, out, S_cap, d, n_max, rows_per_block, nsplit, Hkv, S_max, rg, pg);
+        s_idx, s_merge, deal, k_a, k_b, v, qv, sel_idx, partial, tickets, out, S_cap, d, n_max, rows_per_block, nsplit, Hkv, S_max, rg, pg);
   });
 }
 
