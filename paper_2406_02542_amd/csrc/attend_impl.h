@@ -202,11 +202,12 @@ __device__ __forceinline__ void attend_rows(AttendAcc<T, NH>& acc, const float (
 
 // The same over a list that is still growing: entries below `there` exist when the call begins, and
 // those of the first trip are loaded before complete(), which completes the list (every wave calls
-// it once).
-template <typename T, int NH, int NGROUPS, bool REUSE_LO, bool STREAM = false, typename Complete>
+// it once).  The form of the loads is chosen around each trip's: around the whole, complete() would be there twice
+// (64 heads, S = 8192, k = 2048 34.1 us, 32.7 so).
+template <typename T, int NH, int NGROUPS, bool REUSE_LO, typename Complete>
 __device__ __forceinline__ void attend_growing(AttendAcc<T, NH>& acc, const float (&qr)[NH][T::EPC],
                                                const RowAddr& ra, const int32_t* s_idx, const float* s_a, int gid,
-                                               int r0, int r1, int there, Complete complete) {
+                                               int r0, int r1, int there, int form_now, Complete complete) {
   constexpr int R = kRowsInFlight;
   uint4 kraw[R], vraw[R];
   float alo[R];
@@ -217,17 +218,20 @@ __device__ __forceinline__ void attend_growing(AttendAcc<T, NH>& acc, const floa
       alo[j] = 0.f;
     }
   };
-  auto load = [&](int t0, int lo, int hi) {  // the trip's entries in [lo, hi)
+  auto load = [&](int t0, int lo, int hi) __attribute__((always_inline)) {  // the trip's entries in [lo, hi)
+    with_form<kPastCaches>(form_now, [&](auto form) __attribute__((always_inline)) {
+      constexpr bool kPast = decltype(form)::value != kThroughCaches;
 #pragma unroll
-    for (int j = 0; j < R; ++j) {
-      const int r = t0 + j * NGROUPS + gid;
-      if (r >= lo && r < hi) {
-        const int row = s_idx[r - r0];
-        if constexpr (REUSE_LO) alo[j] = s_a[r - r0];
-        if (ra.k_load) kraw[j] = load16_hint<STREAM>(ra.k_base + (size_t)row * ra.k_row_bytes);
-        vraw[j] = load16_hint<STREAM>(ra.v_base + (size_t)row * ra.v_row_bytes);
+      for (int j = 0; j < R; ++j) {
+        const int r = t0 + j * NGROUPS + gid;
+        if (r >= lo && r < hi) {
+          const int row = s_idx[r - r0];
+          if constexpr (REUSE_LO) alo[j] = s_a[r - r0];
+          if (ra.k_load) kraw[j] = load16_hint<kPast>(ra.k_base + (size_t)row * ra.k_row_bytes);
+          vraw[j] = load16_hint<kPast>(ra.v_base + (size_t)row * ra.v_row_bytes);
+        }
       }
-    }
+    });
   };
   clear();
   if (there > r0) load(r0, r0, min(r1, there));

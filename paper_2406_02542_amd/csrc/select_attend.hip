@@ -222,16 +222,17 @@ __global__ __launch_bounds__(kSaThreads, NH == 1 ? 4 : 2) void select_attend_ker
   const RowAddr ra = make_row_addr<T, REUSE_LO>(klo, khi, v, unit, a.S_cap, a.d, c);
   AttendAcc<T, NH> acc;
   acc.init();
-  with_form<kPastCaches>(form_now, [&](auto form) __attribute__((always_inline)) {
-    constexpr bool kPast = decltype(form)::value != kThroughCaches;
-    if constexpr (GROWING)
-      attend_growing<T, NH, kSaWaves * RPW, REUSE_LO, kPast>(
-          acc, qr, ra, s_idx, s_a, wave * RPW + rg, r0, r1, there, [&]() __attribute__((always_inline)) {
-            share.complete(a, hkv, r0, r1, s_sel, s_pages, s_idx, score);
-          });
-    else
-      attend_rows<T, NH, kSaWaves * RPW, true, REUSE_LO, false, false, kPast>(acc, qr, ra, s_idx, s_a, wave * RPW + rg, r0, r1);
-  });
+  if constexpr (GROWING) {
+    attend_growing<T, NH, kSaWaves * RPW, REUSE_LO>(
+        acc, qr, ra, s_idx, s_a, wave * RPW + rg, r0, r1, there, form_now, [&]() __attribute__((always_inline)) {
+          share.complete(a, hkv, r0, r1, s_sel, s_pages, s_idx, score);
+        });
+  } else {
+    with_form<kPastCaches>(form_now, [&](auto form) __attribute__((always_inline)) {
+      attend_rows<T, NH, kSaWaves * RPW, true, REUSE_LO, false, false, decltype(form)::value != kThroughCaches>(
+          acc, qr, ra, s_idx, s_a, wave * RPW + rg, r0, r1);
+    });
+  }
   attend_publish<T, NH, kSaWaves>(acc, s_merge);
   finish_share<T, NH>(a, s_merge, head0, sel, split, out);
 }

@@ -44,3 +44,14 @@ def test_tridiagonalisation_of_more_heads_than_cus_shares_a_cu(kernels):
     """Two blocks of 4 waves on the 4 SIMDs of a CU: at most 256 of a SIMD's 512 registers each, nothing in scratch."""
     (regs, scratch), = [v for k, v in kernels.items() if "tridiag_kernelILi2E" in k]
     assert regs <= 256 and scratch == 0
+
+
+def test_selection_and_attention_in_one_launch_keep_their_registers(kernels):
+    """A list that grows is completed in one place, whatever the form of the loads around it: nothing in scratch, and with
+    one head per block room for four waves a SIMD."""
+    found = {k: v for k, v in kernels.items() if "select_attend_kernel" in k}
+    assert found
+    for name, (regs, scratch) in found.items():
+        assert scratch == 0, name
+        if "BF16ELi1E" in name or "F32ELi1E" in name:
+            assert regs <= 128, name
